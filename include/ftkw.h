@@ -82,7 +82,8 @@ ftk_status ftk_ctx_peak_memory(ftk_ctx *ctx, size_t *peak, int reset);
  * stream bracket every ftk_apply_h launch ("apply_h"), the Green's-function
  * loops and the filter runs.  A Green's-function batch whose n-step loop is
  * replayed from a graph is timed as a whole ("lanczos_block": n steps of its
- * rhs_block sequences); without graphs, steps 1, 9, 17, ... of every batch are
+ * rhs_block sequences), and so is a launch of whole sequences of a small cluster
+ * ("lanczos_block": all of the launch's sequences); without graphs, steps 1, 9, 17, ... of every batch are
  * timed ("lanczos_step": all launches of one step, i.e. u = H v_k - beta_k
  * v_{k-1} with <v_k|u>, w_k = u - alpha_k v_k with ||w_k||, and the scalar and
  * multi-shift updates; with the multi-pass H v the second half of a step runs
@@ -351,7 +352,10 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * Galerkin residual ||chi|| |p_n| kept per sequence (maximum over shifts).
  * rhs_block (1, 2, 4, 8, 16 or 32) sets how many sequences share one launch; 0
  * takes the value ftk_autotune picks for this Hamiltonian and n_omega.  32 runs
- * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").
+ * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").  Clusters
+ * of 6 to 12 sites run every sequence of the call in one launch, one workgroup
+ * each, whatever rhs_block says (unless a tuning key forces another form); the
+ * start vectors of such a launch take up to 32 MiB of device memory.
  * resid_tol > 0 truncates each sequence at the first step k <= n_steps after
  * which the largest Galerkin residual over the shifts, per unit right-hand side
  * (|p_k| beta_{k+1} / |d_k|), is <= resid_tol (Sec. V, truncation of the CG

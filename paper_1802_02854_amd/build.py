@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libftkw.so")
-SOURCES = ["kernels.hip", "cocg.hip", "capi.cpp", "host_math.cpp", "server.cpp"]
+SOURCES = ["kernels.hip", "resident.hip", "cocg.hip", "capi.cpp", "host_math.cpp", "server.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950",

@@ -20,6 +20,7 @@
 #include "cocg.h"
 #include "ftkw_internal.h"
 #include "kernels.h"
+#include "resident.h"
 
 using namespace ftk;
 
@@ -1399,13 +1400,26 @@ struct GreenOut {
     std::vector<SeqState> states;     // [nseq]
 };
 
+// Sequences of op run one per workgroup, whole (resident.h), unless a tuning key
+// asks for another form
+bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
+
+// What run_green makes start vectors from: spin operators sq[tag], or pairs a, b
+// with tag = 4 pair + polarization.
+struct StartOps {
+    const std::vector<SqParams> *sq = nullptr;
+    const std::vector<SpinOpParams> *a = nullptr, *b = nullptr;
+};
+
 // rhs_block and layout of a run: the autotuner's pick for rhs_block 0.  32
 // sequences exist only as a stack.
 void resolve_layout(const ftk_hamiltonian *h, int rhs_block, int n_omega, int &B, int &stack)
 {
     B = rhs_block;
     stack = -1;
-    if (B == 0) {
+    if (B == 0 && resident_run(h->op)) {
+        B = 1;  // every sequence of the call shares the launch: nothing to tune
+    } else if (B == 0) {
         const TuneResult t = autotune(h, n_omega);
         B = t.rhs_block;
         stack = t.stacked;
@@ -1417,13 +1431,153 @@ void resolve_layout(const ftk_hamiltonian *h, int rhs_block, int n_omega, int &B
              "rhs_block 32 runs only as a stack of multi-pass sequences (N >= 16, stack_batch not 0, no plain loop)");
 }
 
+// Several buffers of one call in one device allocation.
+struct Arena {
+    std::vector<std::pair<void **, size_t>> parts;
+    DevBuf mem;
+    template <class T>
+    void part(T **p, size_t n)
+    {
+        parts.push_back({(void **)p, (n * sizeof(T) + 255) / 256 * 256});
+    }
+    void allocate(ftk_ctx *ctx)
+    {
+        size_t total = 0;
+        for (auto &q : parts) total += q.second;
+        mem = DevBuf(ctx, total);
+        char *at = (char *)mem.p;
+        for (auto &q : parts) {
+            *q.first = at;
+            at += q.second;
+        }
+    }
+};
+
+// Device bytes of the start vectors and shift states that one launch of resident
+// sequences may take: 512 sequences at 12 sites, well over one per compute unit
+// (and inside what a served request reserves beyond its counted buffers).
+constexpr size_t kResidentBytes = size_t(32) << 20;
+// Steps between two residual tests of a truncated resident run.
+constexpr int kResidentCheck = 16;
+
+// run_green for small clusters: every item is one workgroup that runs all n steps.
+// Device rows are the items' order; the outputs' rows their index.
+GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega, int nw, double eta, double rtol,
+                            int nseq, const std::vector<GreenItem> &work, const StartOps &ops)
+{
+    ftk_ctx *ctx = h->ctx;
+    hipStream_t s = ctx->stream;
+    const size_t dim = h->dim, rows = work.size();
+    GreenOut out;
+    out.g.resize((size_t)nseq * nw * 2);
+    out.alpha.resize((size_t)nseq * n);
+    out.beta.resize((size_t)nseq * n);
+    out.states.resize(nseq);
+    if (rows == 0) return out;
+    const bool stop = rtol > 0.0;
+    const size_t per = 16 * dim * (stop ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
+    const size_t slab = std::min(rows, std::max<size_t>(1, kResidentBytes / per));
+
+    Arena m;
+    ResidentSeq *seq;
+    SqParams *sq;
+    SpinOpParams *pa, *pb;
+    SeqState *st;
+    ShiftState *sh;
+    double *al, *be, *g, *om, *chi, *carry;
+    m.part(&seq, rows);
+    m.part(&sq, ops.sq ? ops.sq->size() : 0);
+    m.part(&pa, ops.a ? ops.a->size() : 0);
+    m.part(&pb, ops.b ? ops.b->size() : 0);
+    m.part(&om, nw);
+    m.part(&st, rows);
+    m.part(&al, rows * n);
+    m.part(&be, rows * n);
+    m.part(&g, rows * nw * 2);
+    m.part(&chi, slab * dim * 2);
+    m.part(&carry, stop ? slab * dim * 4 : 0);
+    m.part(&sh, stop ? slab * nw : 0);
+    m.allocate(ctx);
+
+    std::vector<ResidentSeq> hseq(rows);
+    for (size_t i = 0; i < rows; ++i)
+        hseq[i] = ResidentSeq{(const double2 *)work[i].phi, work[i].tag, (int)i, work[i].Em};
+    auto up = [&](void *dst, const void *src, size_t bytes) {
+        HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
+    };
+    up(seq, hseq.data(), rows * sizeof(ResidentSeq));
+    up(om, omega, sizeof(double) * nw);
+    if (ops.sq) up(sq, ops.sq->data(), ops.sq->size() * sizeof(SqParams));
+    if (ops.a) up(pa, ops.a->data(), ops.a->size() * sizeof(SpinOpParams));
+    if (ops.b) up(pb, ops.b->data(), ops.b->size() * sizeof(SpinOpParams));
+
+    for (size_t r0 = 0; r0 < rows; r0 += slab) {
+        const int cnt = (int)std::min(slab, rows - r0);
+        ResidentRun run{};
+        run.seq = seq + r0;
+        run.sq = sq;
+        run.a = pa;
+        run.b = pb;
+        run.chi = chi;
+        run.st = st;
+        run.alpha = al;
+        run.beta = be;
+        run.stride = n;
+        run.tol = 1e-12 * h->table.norm_bound;
+        run.carry = stop ? carry : nullptr;
+        ShiftRun shifts{st + r0, al + r0 * n, be + r0 * n, n, om, nw, eta, g + r0 * 2 * nw};
+        launch_start_vectors(h->n_sites, ops.sq ? kLoadSpin : kLoadPair, run, cnt, s);
+        ctx->timed("lanczos_block", true, [&] {
+            for (int k = 0; k < n; k = run.k1) {
+                run.k0 = k;
+                run.k1 = stop ? std::min(n, k + kResidentCheck) : n;
+                launch_resident(h->op, run, cnt, s);
+                if (stop) launch_shifts_until(shifts, run.k0, run.k1, rtol, sh, cnt, s);
+            }
+            if (!stop) launch_shifts(shifts, cnt, s);
+        });
+    }
+    HIP_CHECK(hipGetLastError());
+    // every row to its index (the rows' order is the indices')
+    const bool all = (int)rows == nseq;
+    std::vector<double> hg(all ? 0 : rows * nw * 2), ha(all ? 0 : rows * n), hb(all ? 0 : rows * n);
+    std::vector<SeqState> hs(all ? 0 : rows);
+    auto down = [&](void *dst, const void *src, size_t bytes) {
+        HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+    };
+    down(all ? out.states.data() : hs.data(), st, sizeof(SeqState) * rows);
+    down(all ? out.g.data() : hg.data(), g, sizeof(double) * rows * nw * 2);
+    down(all ? out.alpha.data() : ha.data(), al, sizeof(double) * rows * n);
+    down(all ? out.beta.data() : hb.data(), be, sizeof(double) * rows * n);
+    HIP_CHECK(hipStreamSynchronize(s));
+    for (size_t i = 0; !all && i < rows; ++i) {
+        const size_t r = (size_t)work[i].index;
+        out.states[r] = hs[i];
+        std::copy(hg.begin() + i * nw * 2, hg.begin() + (i + 1) * nw * 2, out.g.begin() + r * nw * 2);
+        std::copy(ha.begin() + i * n, ha.begin() + (i + 1) * n, out.alpha.begin() + r * n);
+        std::copy(hb.begin() + i * n, hb.begin() + (i + 1) * n, out.beta.begin() + r * n);
+    }
+    return out;
+}
+
+void check_green(const GreenOut &out)
+{
+    for (const SeqState &q : out.states)
+        if (q.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in Green's-function Lanczos coefficients");
+}
+
 // Runs the items in batches of B through one graph-captured BatchRunner; load(run, r,
 // item) writes the item's right-hand side into slot r.  Slots of sequences not listed
-// stay zero.
+// stay zero.  Small clusters run resident instead, from ops.
 template <class Load>
 GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const double *omega, int nw, double eta,
-                   double rtol, int nseq, const std::vector<GreenItem> &work, Load &&load)
+                   double rtol, int nseq, const std::vector<GreenItem> &work, const StartOps &ops, Load &&load)
 {
+    if (resident_run(h->op)) {
+        GreenOut out = run_green_resident(h, n, omega, nw, eta, rtol, nseq, work, ops);
+        check_green(out);
+        return out;
+    }
     ftk_ctx *ctx = h->ctx;
     hipStream_t s = ctx->stream;
     DevBuf gdev(ctx, sizeof(double) * 2 * (size_t)std::max(1, nseq) * nw);
@@ -1471,8 +1625,7 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     HIP_CHECK(hipMemcpyAsync(out.alpha.data(), adev.p, sizeof(double) * out.alpha.size(), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipMemcpyAsync(out.beta.data(), bdev.p, sizeof(double) * out.beta.size(), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
-    for (int i = 0; i < nseq; ++i)
-        if (out.states[i].numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in Green's-function Lanczos coefficients");
+    check_green(out);
     return out;
 }
 
@@ -1673,7 +1826,7 @@ ftk_status ftk_shifted_krylov_spectrum(const ftk_hamiltonian *h, const ftk_state
             *out = sp.release();
             return;
         }
-        GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work,
+        GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work, StartOps{&sq},
                                  [&](BatchRunner &run, int r, const GreenItem &q) { run.load_rhs(sq[q.tag], q.phi, r); });
         sp->g = std::move(res.g);
         sp->alpha = std::move(res.alpha);
@@ -1878,11 +2031,12 @@ ftk_status ftk_pair_green(const ftk_hamiltonian *h, const ftk_states *st, const 
                 }
             }
         // lam = A phi^m and rho = B phi^m of the pair being loaded
-        DevBuf lam(ctx, sizeof(double) * 2 * (size_t)dim), rho(ctx, sizeof(double) * 2 * (size_t)dim);
+        const size_t vb = resident_run(h->op) ? 0 : sizeof(double) * 2 * (size_t)dim;
+        DevBuf lam(ctx, vb), rho(ctx, vb);
         const double *cur_phi = nullptr;
         int cur_pair = -1;
         GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work,
-                                 [&](BatchRunner &run, int r, const GreenItem &q) {
+                                 StartOps{nullptr, &opa, &opb}, [&](BatchRunner &run, int r, const GreenItem &q) {
                                      const int pair = q.tag / 4;
                                      if (q.phi != cur_phi || pair != cur_pair) {
                                          launch_apply_spin_op(opa[pair], q.phi, lam.d(), ctx->stream);

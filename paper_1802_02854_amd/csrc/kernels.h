@@ -19,6 +19,8 @@ struct HvParams {
     uint8_t isz[kMaxBonds];    // 1 for z bonds
     double ap[kMaxBonds];      // flip amplitude, parallel spins
     double aa[kMaxBonds];      // flip amplitude, antiparallel spins
+    uint32_t code[kMaxBonds];  // mask | bond type << 30
+    double ap3[3], aa3[3];     // the amplitudes by bond type
     double jq, kq;             // J/4, K/4
     // bond-parity vectors: bit b of par(x) = bit i_b(x) ^ bit j_b(x) is the XOR of
     // smask[l] over the set bits l of x
@@ -101,6 +103,7 @@ int hv_mode(const HvOp &op);
 int hv_grid(const HvOp &op);         // grid of the H-applying kernels (= number of partial sums)
 int hv_grid(const HvOp &op, int B);  // per-sequence grid of a stack of B sequences (multi-pass form)
 void set_hv_mode(int mode);          // force a mode if available (-1: by size), for tuning
+int forced_hv_mode();                // the forced mode, -1 when none
 void set_pass_grid(int grid);        // workgroups per reducing multi-pass launch (0: two per compute unit)
 int pass_grid_cap(const HvOp &op);   // the workgroups a reducing multi-pass launch of op may use
 void set_full_grid(int on);          // 1: passes without partial sums run one workgroup per tile

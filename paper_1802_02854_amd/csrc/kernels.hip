@@ -25,6 +25,7 @@
 
 #include "exact_sum.h"
 #include "kernels.h"
+#include "shift_update.h"
 
 namespace ftk {
 
@@ -41,6 +42,9 @@ HvParams make_hv_params(const BondTable &t)
         P.isz[b] = t.gamma[b] == 2 ? 1 : 0;
         P.ap[b] = t.ap[b];
         P.aa[b] = t.aa[b];
+        P.code[b] = P.mask[b] | (uint32_t)t.gamma[b] << 30;
+        P.ap3[t.gamma[b]] = t.ap[b];
+        P.aa3[t.gamma[b]] = t.aa[b];
         P.smask[t.bi[b]] |= 1ull << b;
         P.smask[t.bj[b]] |= 1ull << b;
         if (t.gamma[b] == 2) P.zmask |= 1ull << b;
@@ -185,6 +189,10 @@ void device_checks_selftest(uint32_t *, hipStream_t) {}
 void device_checks_read(unsigned int out[3], bool) { out[0] = out[1] = out[2] = 0u; }
 #endif
 
+}  // namespace ftk
+#include "spin_ops.h"  // its gathers carry the bounds checks above
+namespace ftk {
+
 static int g_hv_mode = -1;  // -1: chosen by size
 static int g_pass_grid = 0;  // workgroups of a multi-pass launch (0: two per compute unit)
 static bool g_full_grid = true;  // passes without partial sums: one workgroup per tile
@@ -192,6 +200,7 @@ static bool g_fuse_fin = true;   // beta finalisation inside the middle pass of 
 static int g_cus = 256;      // compute units of the device (set with the kernel attributes)
 
 void set_hv_mode(int mode) { g_hv_mode = mode; }
+int forced_hv_mode() { return g_hv_mode; }
 void set_pass_grid(int grid) { g_pass_grid = grid; }
 void set_full_grid(int on) { g_full_grid = on != 0; }
 static int g_hints = -1;  // forced hint set of the multi-pass form (-1: per op)
@@ -1049,55 +1058,6 @@ __global__ void __launch_bounds__(kBlock) k_finalize_alpha(SeqState *st, const d
     }
 }
 
-// One step of the forward LDL^T recurrence of (z - T)^{-1}_{00} for the shift z = zr + i zi
-// (App. A.3): d_k, the running product p_k and the accumulated G; alpha = alpha_k,
-// bk = beta_k.
-__device__ __forceinline__ void shift_update(ShiftState &q, double zr, double zi, double alpha, double bk, int k)
-{
-    if (k == 0) {
-        q.dr = zr - alpha;
-        q.di = zi;
-        q.pr = 1.0;
-        q.pi = 0.0;
-        const double den = q.dr * q.dr + q.di * q.di;
-        q.gr = q.dr / den;
-        q.gi = -q.di / den;
-    } else {
-        const double den = q.dr * q.dr + q.di * q.di;
-        const double rr = q.dr / den, ri = -q.di / den;  // 1/d_{k-1}
-        const double fr = bk * rr, fi = bk * ri;         // beta_k / d_{k-1}
-        const double pr = q.pr * fr - q.pi * fi;
-        const double pi = q.pr * fi + q.pi * fr;
-        const double b2 = bk * bk;
-        q.dr = (zr - alpha) - b2 * rr;
-        q.di = zi - b2 * ri;
-        q.pr = pr;
-        q.pi = pi;
-        const double p2r = pr * pr - pi * pi, p2i = 2.0 * pr * pi;
-        const double dn = q.dr * q.dr + q.di * q.di;
-        q.gr = q.gr + (p2r * q.dr + p2i * q.di) / dn;
-        q.gi = q.gi + (p2i * q.dr - p2r * q.di) / dn;
-    }
-}
-
-// maximum over a block of BLOCK threads; valid in thread 0
-template <int BLOCK>
-__device__ __forceinline__ double block_max(double v)
-{
-    __shared__ double sh[BLOCK / 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double m = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < BLOCK / 64; ++i) m = sh[i] > m ? sh[i] : m;
-    return m;
-}
-
 // beta_{k+1} = ||w_k|| from the partial sums, the forward LDL^T recurrence of
 // (z - T)^{-1}_{00} per shift z = omega + shift_re + i eta, and the stopping test,
 // for sequence r, by one block of BLOCK threads.
@@ -1122,8 +1082,7 @@ __device__ void finalize_beta_seq(const FinBeta &f, int r)
         ShiftState q = sh[j];
         shift_update(q, zr, zi, alpha, bk, k);
         sh[j] = q;
-        // residual after k+1 steps: |p_k| beta_{k+1} / |d_k|
-        const double rs = sqrt((q.pr * q.pr + q.pi * q.pi) / (q.dr * q.dr + q.di * q.di)) * bn;
+        const double rs = shift_residual(q, bn);
         rmax = rs > rmax ? rs : rmax;
     }
     const double m = block_max<BLOCK>(rmax);
@@ -1256,52 +1215,6 @@ void launch_sum_partials(const double *partials, int nparts, double *result, hip
 }
 
 // ---------------------------------------------------------------------------
-// chi = S^alpha_{+Q} phi (Sec. V): x and y flip one spin, z is diagonal.
-// <down|S^y|up> = +i/2 and <up|S^y|down> = -i/2 (bit 1 = spin down).  h holds
-// the per-site factors (interleaved), the 1/2 of S = sigma/2 included.
-template <class Coef>
-__device__ __forceinline__ double2 sq_part(int n_sites, int alpha, const Coef &h, const double2 *__restrict__ phi,
-                                           uint32_t x)
-{
-    double re = 0.0, im = 0.0;
-    if (alpha == 2) {
-        double cr = 0.0, ci = 0.0;
-        for (int l = 0; l < n_sites; ++l) {
-            if ((x >> l) & 1u) {
-                cr = cr - h[2 * l];
-                ci = ci - h[2 * l + 1];
-            } else {
-                cr = cr + h[2 * l];
-                ci = ci + h[2 * l + 1];
-            }
-        }
-        const double2 p = phi[x];
-        re = cr * p.x - ci * p.y;
-        im = cr * p.y + ci * p.x;
-    } else {
-        for (int l = 0; l < n_sites; ++l) {
-            double cr = h[2 * l], ci = h[2 * l + 1];
-            if (alpha == 1) {
-                if ((x >> l) & 1u) {
-                    const double t = cr;
-                    cr = -ci;
-                    ci = t;
-                } else {
-                    const double t = cr;
-                    cr = ci;
-                    ci = -t;
-                }
-            }
-            const double2 p = phi[FTK_IDX(x ^ (1u << l), 0, 1u << n_sites, 12)];
-            const double tr = cr * p.x - ci * p.y;
-            const double ti = cr * p.y + ci * p.x;
-            re = re + tr;
-            im = im + ti;
-        }
-    }
-    return make_double2(re, im);
-}
-
 __global__ void __launch_bounds__(kBlock) k_apply_sq(SqParams P, const double2 *__restrict__ phi,
                                                      double2 *__restrict__ chi, int stride, int offset)
 {
@@ -1317,17 +1230,13 @@ void launch_apply_sq(const SqParams &P, const double *phi, double *chi, hipStrea
                        (double2 *)chi, stride, offset);
 }
 
-// chi = A phi for a linear spin operator (operators A, B of Sec. III.B): the three
-// components formed as above, added per element in the order (x + y) + z.
+// chi = A phi for a linear spin operator
 __global__ void __launch_bounds__(kBlock) k_apply_spin_op(SpinOpParams P, const double2 *__restrict__ phi,
                                                           double2 *__restrict__ chi)
 {
     const uint32_t dim = 1u << P.n_sites;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
-        const double2 a = sq_part(P.n_sites, 0, P.h[0], phi, x);
-        const double2 b = sq_part(P.n_sites, 1, P.h[1], phi, x);
-        const double2 c = sq_part(P.n_sites, 2, P.h[2], phi, x);
-        chi[x] = make_double2((a.x + b.x) + c.x, (a.y + b.y) + c.y);
+        chi[x] = spin_op_part(P.n_sites, P.h, phi, x);
     }
 }
 
@@ -1338,24 +1247,13 @@ void launch_apply_spin_op(const SpinOpParams &P, const double *phi, double *chi,
                        (double2 *)chi);
 }
 
-// the start vectors of the polarization identity: lam + rho, lam - rho, lam + i rho,
-// lam - i rho for k = 0..3
+// the start vectors of the polarization identity
 __global__ void __launch_bounds__(kBlock) k_polarize(uint32_t dim, int k, const double2 *__restrict__ lam,
                                                      const double2 *__restrict__ rho, double2 *__restrict__ chi,
                                                      int stride, int offset)
 {
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
-        const double2 a = lam[x], b = rho[x];
-        double2 o;
-        if (k == 0)
-            o = make_double2(a.x + b.x, a.y + b.y);
-        else if (k == 1)
-            o = make_double2(a.x - b.x, a.y - b.y);
-        else if (k == 2)
-            o = make_double2(a.x - b.y, a.y + b.x);
-        else
-            o = make_double2(a.x + b.y, a.y - b.x);
-        chi[(size_t)x * stride + offset] = o;
+        chi[(size_t)x * stride + offset] = polarize_part(k, lam[x], rho[x]);
     }
 }
 
@@ -1772,7 +1670,7 @@ __global__ void __launch_bounds__(kBlock) k_finalize_beta_batch(SeqState *st, co
         ShiftState q = sh[j];
         shift_update(q, zr, zi, alpha, bk, k);
         sh[j] = q;
-        const double res = sqrt((q.pr * q.pr + q.pi * q.pi) / (q.dr * q.dr + q.di * q.di)) * bn;
+        const double res = shift_residual(q, bn);
         rmax = res > rmax ? res : rmax;
     }
     const double m = block_max<kBlock>(rmax);

@@ -1,0 +1,94 @@
+"""Whole-sequence kernels of small clusters against the per-step kernels, bit for bit.
+
+The per-step kernels are pinned to the oracle (test_gpu_parity.py); forcing a form of H v
+selects them.  Inner products are the double nearest the exact sum in both, so every
+coefficient and every output must agree exactly.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import paper_1802_02854_amd as ftk
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return ftk, ftk.Context(0), torch
+
+
+def _ring(ftk, N):
+    """A ring of N sites (any N) with chords to the second and third neighbours (36 bonds at
+    N = 12, past the 32 of one parity word), bond types in turn."""
+    ij = sorted({(min(i, (i + d) % N), max(i, (i + d) % N)) for d in (1, 2, 3) for i in range(N)})
+    xy = np.stack([np.cos(np.arange(N)), np.sin(1.7 * np.arange(N))], axis=1)
+    return ftk.Cluster(N, np.array([b[0] for b in ij], np.int32), np.array([b[1] for b in ij], np.int32),
+                       (np.arange(len(ij)) % 3).astype(np.int8), xy)
+
+
+def _both(ftk, fn):
+    """fn() on the resident path and on the per-step kernels."""
+    out = [fn()]
+    ftk.set_tuning("hv_variant", 0)
+    try:
+        out.append(fn())
+    finally:
+        ftk.set_tuning("hv_variant", -1)
+    return out
+
+
+@pytest.mark.parametrize("N", [6, 7, 8, 9, 10, 11, 12])
+def test_resident_sequences_match_per_step(env, N):
+    """Spectra (fixed length, one step, truncated) and operator pairs at every resident size."""
+    ftk, ctx, torch = env
+    print(f"resident N={N}", flush=True)
+    cl = _ring(ftk, N)
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.13)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    draws = torch.view_as_complex(torch.randn(1, 1 << N, 2, dtype=torch.float64, device="cuda", generator=g))
+    st = ftk.TypicalStates(h, seed=0, n_vectors=1, betas=[0.5], E_b=None, eps=None, L=3, M=4, n_steps=12, gaussians=draws)
+    qs = [(0.0, 0.0), (0.7, -0.4)]
+    n = min(40, (1 << N) // 2)  # no breakdown
+    for omega, eta, steps, tol, shells in ((np.linspace(-3, 3, 130), 0.3, n, 0.0, (0, 3)),
+                                           (np.linspace(-2, 2, 5), 0.3, 1, 0.0, (1, 2)),
+                                           (np.linspace(-3, 3, 600), 1.0, n, 1e-2, (0, 3))):
+        def spectrum():
+            sp = ftk.Spectrum(h, st, q_xy=qs, omega=omega, eta=eta, n_steps=steps, rhs_block=1, resid_tol=tol,
+                              shells=shells)
+            return [sp.raw(), sp.norms(), [sp.lanczos(0, 0, m, a, q) for m in range(3) for a in range(3) for q in range(2)]]
+        a, b = _both(ftk, spectrum)
+        assert np.array_equal(a[0][0], b[0][0]) and np.array_equal(a[0][1], b[0][1]) and np.array_equal(a[1], b[1])
+        for (al, be), (al2, be2) in zip(a[2], b[2]):
+            assert np.array_equal(al, al2) and np.array_equal(be, be2)
+        assert np.abs(a[0][0]).max() > 0
+    assert any(len(al) < n for al, _ in a[2]), "the truncated run never stopped early"
+
+    op_a = np.stack([ftk.momentum_operator(cl, 0, qs[1]), ftk.momentum_operator(cl, 2, qs[0])])
+    op_b = np.stack([ftk.momentum_operator(cl, 1, qs[1]), ftk.momentum_operator(cl, 0, qs[0])])
+    a, b = _both(ftk, lambda: ftk.PairSpectrum(h, st, op_a=op_a, op_b=op_b, omega=np.linspace(-3, 3, 33), eta=0.2,
+                                               n_steps=n, rhs_block=1).raw())
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+
+
+def test_resident_breakdown_and_many_shifts(env):
+    """Sequences that exhaust their Krylov space (three separate bonds have four
+    energies) end at the same step, and more sequences and shifts than one workgroup's share
+    give the per-step results."""
+    ftk, ctx, torch = env
+    print("resident breakdown", flush=True)
+    cl = ftk.Cluster(6, np.array([0, 2, 4], np.int32), np.array([1, 3, 5], np.int32), np.zeros(3, np.int8),
+                     np.arange(12.0).reshape(6, 2))
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.0)
+    st = ftk.TypicalStates(h, seed=3, n_vectors=2, betas=[0.0, 1.0], E_b=None, eps=None, L=40, M=4, n_steps=30)
+    a, b = _both(ftk, lambda: (lambda sp: [sp.raw(), [sp.lanczos(1, 1, m, 2, 0) for m in range(40)]])(
+        ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-3, 3, 1100), eta=0.4, n_steps=90, rhs_block=1)))
+    steps = [len(al) for al, _ in a[1]]
+    assert min(steps) < 90
+    assert steps == [len(al) for al, _ in b[1]]
+    for (al, be), (al2, be2) in zip(a[1], b[1]):
+        assert np.array_equal(al, al2) and np.array_equal(be, be2)
+    assert np.array_equal(a[0][0], b[0][0]) and np.array_equal(a[0][1], b[0][1])
