@@ -353,9 +353,9 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * rhs_block (1, 2, 4, 8, 16 or 32) sets how many sequences share one launch; 0
  * takes the value ftk_autotune picks for this Hamiltonian and n_omega.  32 runs
  * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").  Clusters
- * of 6 to 12 sites run every sequence of the call in one launch, one workgroup
+ * of 6 to 14 sites run every sequence of the call in one launch, one workgroup
  * each, whatever rhs_block says (unless a tuning key forces another form); the
- * start vectors of such a launch take up to 32 MiB of device memory.
+ * vectors of such a launch take up to 192 MiB of device memory.
  * resid_tol > 0 truncates each sequence at the first step k <= n_steps after
  * which the largest Galerkin residual over the shifts, per unit right-hand side
  * (|p_k| beta_{k+1} / |d_k|), is <= resid_tol (Sec. V, truncation of the CG

@@ -75,6 +75,9 @@ struct ftk_ctx {
     ftk_alloc_fn alloc_fn = nullptr;  // caller's allocator (both or neither)
     ftk_free_fn free_fn = nullptr;
     void *alloc_user = nullptr;
+    // device bytes of the start vectors, carried vectors and shift states that one launch
+    // of resident sequences may take: one sequence per compute unit at 14 sites, more below
+    size_t resident_bytes = size_t(192) << 20;
     size_t bytes = 0;
     size_t peak = 0;  // high-water mark of bytes since the last reset
     bool timing = false;
@@ -1265,6 +1268,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega);
 }  // namespace
 
 void ftk::set_last_error(const std::string &msg) { g_error = msg; }
+void ftk::limit_resident_bytes(ftk_ctx *ctx, size_t bytes) { ctx->resident_bytes = bytes; }
 
 int ftk::tuned_rhs_block(int device, int n_sites, int n_omega)
 {
@@ -1453,10 +1457,6 @@ struct Arena {
     }
 };
 
-// Device bytes of the start vectors and shift states that one launch of resident
-// sequences may take: 512 sequences at 12 sites, well over one per compute unit
-// (and inside what a served request reserves beyond its counted buffers).
-constexpr size_t kResidentBytes = size_t(32) << 20;
 // Steps between two residual tests of a truncated resident run.
 constexpr int kResidentCheck = 16;
 
@@ -1475,8 +1475,9 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     out.states.resize(nseq);
     if (rows == 0) return out;
     const bool stop = rtol > 0.0;
-    const size_t per = 16 * dim * (stop ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
-    const size_t slab = std::min(rows, std::max<size_t>(1, kResidentBytes / per));
+    const bool carried = stop || h->n_sites >= kResidentPlanes;
+    const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
+    const size_t slab = std::min(rows, std::max<size_t>(1, ctx->resident_bytes / per));
 
     Arena m;
     ResidentSeq *seq;
@@ -1495,7 +1496,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     m.part(&be, rows * n);
     m.part(&g, rows * nw * 2);
     m.part(&chi, slab * dim * 2);
-    m.part(&carry, stop ? slab * dim * 4 : 0);
+    m.part(&carry, carried ? slab * dim * 4 : 0);
     m.part(&sh, stop ? slab * nw : 0);
     m.allocate(ctx);
 
@@ -1524,7 +1525,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
         run.beta = be;
         run.stride = n;
         run.tol = 1e-12 * h->table.norm_bound;
-        run.carry = stop ? carry : nullptr;
+        run.carry = carried ? carry : nullptr;
         ShiftRun shifts{st + r0, al + r0 * n, be + r0 * n, n, om, nw, eta, g + r0 * 2 * nw};
         launch_start_vectors(h->n_sites, ops.sq ? kLoadSpin : kLoadPair, run, cnt, s);
         ctx->timed("lanczos_block", true, [&] {

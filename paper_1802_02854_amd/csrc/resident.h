@@ -6,9 +6,10 @@
 
 namespace ftk {
 
-// clusters whose vector a workgroup keeps in its registers and LDS
+// clusters whose vector, or one plane of it, a workgroup keeps in its registers and LDS
 constexpr int kResidentMinSites = 6;
-constexpr int kResidentMaxSites = 12;
+constexpr int kResidentMaxSites = 14;
+constexpr int kResidentPlanes = 13;  // from here on a plane at a time, with a carry buffer
 // whether sequences of op run resident (by size, unless a form of H v is forced)
 bool resident(const HvOp &op);
 
@@ -35,6 +36,7 @@ struct ResidentRun {
     double tol;              // breakdown threshold
     int k0, k1;              // steps [k0, k1); k0 > 0 resumes from carry
     double *carry;           // per sequence w_{k-1}, w_{k-2} (4 * 2^N doubles); NULL for a whole run
+                             // below kResidentPlanes sites
     double *vout;            // NULL, or per sequence the vectors w_{k-1} of these steps...
     size_t vstride;          // ... this many doubles apart
 };

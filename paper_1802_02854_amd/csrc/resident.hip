@@ -1,4 +1,4 @@
-// Krylov sequences of small clusters (2^6 .. 2^12 states): one workgroup runs one
+// Krylov sequences of small clusters (2^6 .. 2^14 states): one workgroup runs one
 // sequence from its start vector to its last step.  Compiled with
 // -ffp-contract=off; the operations per element are those of the per-step kernels
 // (kernels.hip), and every inner product is the double nearest the exact sum, so
@@ -96,6 +96,19 @@ __device__ __forceinline__ void lds_barrier()
 
 constexpr int log2c(int x) { return x <= 1 ? 0 : 1 + log2c(x / 2); }
 
+// a value that every lane holds, in scalar registers
+__device__ __forceinline__ double uniform(double x)
+{
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = x;
+    u.i[0] = __builtin_amdgcn_readfirstlane(u.i[0]);
+    u.i[1] = __builtin_amdgcn_readfirstlane(u.i[1]);
+    return u.d;
+}
+
 // Sum over the workgroup, rounded, in every thread; sh holds one pair per wave.
 // One barrier, which also ends the phase before it.
 template <int T>
@@ -112,7 +125,7 @@ __device__ __forceinline__ double block_sum(double hi, double lo, double2 *sh)
     } else {
         lds_barrier();
     }
-    return hi + lo;
+    return uniform(hi + lo);
 }
 
 // the start vectors of the sequences, 2^N entries each
@@ -131,44 +144,161 @@ __global__ void __launch_bounds__(kBlock) k_start_vectors(int n_sites, int load,
     }
 }
 
-// A bond for one thread: its amplitudes for the elements whose register bits it
-// flips with even and odd parity, and the register bits it flips.
+// The sequence's state after its start vector and after the steps of a launch; pad
+// keeps 1 + the first step after which a scalar was not finite (1: the start).
+__device__ __forceinline__ void start_state(SeqState *st, double norm2, double norm, double inv, double shift_re, int bad)
+{
+    st->norm2 = norm2;
+    st->norm = norm;
+    st->inv_cur = inv;
+    st->inv_prev = 0.0;
+    st->beta_cur = 0.0;
+    st->alpha_cur = 0.0;
+    st->shift_re = shift_re;
+    st->max_resid = 0.0;
+    st->done = norm > 0.0 ? 0 : 1;
+    st->steps = 0;
+    st->numeric_error = bad;
+    st->pad = bad;
+}
+__device__ __forceinline__ void end_state(SeqState *st, double inv, double inv_prev, double bcur, double a, int done,
+                                          int steps, int bad)
+{
+    st->inv_cur = inv;
+    st->inv_prev = inv_prev;
+    st->beta_cur = bcur;
+    st->alpha_cur = a;
+    st->done = done;
+    st->steps = steps;
+    st->numeric_error = bad != 0;
+    st->pad = bad;
+}
+
+// The bond constants of a thread: one bond's code per lane, the amplitudes by bond
+// type (scalar), the bond parities of the thread's element 0.
 struct BondAt {
-    double even, odd;
-    uint32_t mr;
+    double even, odd;  // amplitudes of elements whose register bits the bond flips with even, odd parity
+    uint32_t m;        // flip mask
+};
+struct Bonds {
+    int code;
+    double ap0, ap1, ap2, aa0, aa1, aa2;
+    uint32_t par_lo, par_hi;
+    __device__ Bonds(const HvParams &P, uint64_t par)
+        : ap0(P.ap3[0]), ap1(P.ap3[1]), ap2(P.ap3[2]), aa0(P.aa3[0]), aa1(P.aa3[1]), aa2(P.aa3[2]),
+          par_lo((uint32_t)par), par_hi((uint32_t)(par >> 32))
+    {
+        const int l = (int)(threadIdx.x & 63);
+        code = (int)P.code[l < P.n_bonds ? l : 0];
+    }
+    __device__ __forceinline__ BondAt at(int b) const
+    {
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane(code, b);
+        const uint32_t type = c >> 30;
+        const double p0 = ap0, p1 = ap1, p2 = ap2, q0 = aa0, q1 = aa1, q2 = aa2;
+        const double ap = type == 0 ? p0 : type == 1 ? p1 : p2;
+        const double aa = type == 0 ? q0 : type == 1 ? q1 : q2;
+        const bool anti = ((b < 32 ? par_lo : par_hi) & (1u << (b & 31))) != 0;
+        return BondAt{anti ? aa : ap, anti ? ap : aa, c & 0x3fffffffu};
+    }
 };
 
-// One fma per element; a bond that flips no register bit takes one amplitude for all.
-template <int E>
-__device__ __forceinline__ void accumulate(double (&re)[E], double (&im)[E], const double2 (&v)[E], BondAt at)
+// Bit e: element e of a thread takes a bond's odd amplitude.  One code path for every
+// bond: a branch on the register bits costs more in copies of the sums, which the two
+// sides keep in different registers, than the selects it saves.
+__device__ __forceinline__ uint32_t odd_elements(uint32_t mr)
 {
-    const double even = at.even, odd = at.odd;
-    if (at.mr == 0) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            re[e] = fma(even, v[e].x, re[e]);
-            im[e] = fma(even, v[e].y, im[e]);
-        }
-    } else {
-        uint32_t sel = 0;  // bit e: element e takes the odd amplitude
-        if (at.mr & 1u) sel ^= 0xAAu;
-        if (at.mr & 2u) sel ^= 0xCCu;
-        if (at.mr & 4u) sel ^= 0xF0u;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const double a = ((sel >> e) & 1u) ? odd : even;
-            re[e] = fma(a, v[e].x, re[e]);
-            im[e] = fma(a, v[e].y, im[e]);
-        }
-    }
+    uint32_t sel = 0;
+    if (mr & 1u) sel ^= 0xAAAAu;
+    if (mr & 2u) sel ^= 0xCCCCu;
+    if (mr & 4u) sel ^= 0xF0F0u;
+    if (mr & 8u) sel ^= 0xFF00u;
+    return sel;
+}
+
+// One bond on 16 sums of a thread.  Sum e takes entry e ^ mr of the 16 entries STRIDE
+// bytes apart at LDS address t0 (entries 8..15 at t8 = t0 + 8 STRIDE, so that every
+// offset fits the instruction) with the amplitude of the parity of e & mr; mr, the
+// register bits the bond flips, has at most two bits set.  Each value of mr has its
+// own offsets and amplitude registers, so a sum costs one fma; written as one asm
+// block because the compiler keeps the sums of different cases in different
+// registers and copies all of them for every bond, and without the cases each sum
+// takes two selects and an address (14 sites, 200 steps of 64 sequences: 12.2 ms
+// with selects).  Eight reads are in flight; they return in order, and every one is
+// waited for in the block.
+#define FTK_RD(r, base, k) "ds_read_b64 %[v" #r "], %[" #base "] offset:" #k "*%[st]\n\t"
+#define FTK_RD_0(r) FTK_RD(r, t0, 0)
+#define FTK_RD_1(r) FTK_RD(r, t0, 1)
+#define FTK_RD_2(r) FTK_RD(r, t0, 2)
+#define FTK_RD_3(r) FTK_RD(r, t0, 3)
+#define FTK_RD_4(r) FTK_RD(r, t0, 4)
+#define FTK_RD_5(r) FTK_RD(r, t0, 5)
+#define FTK_RD_6(r) FTK_RD(r, t0, 6)
+#define FTK_RD_7(r) FTK_RD(r, t0, 7)
+#define FTK_RD_8(r) FTK_RD(r, t8, 0)
+#define FTK_RD_9(r) FTK_RD(r, t8, 1)
+#define FTK_RD_10(r) FTK_RD(r, t8, 2)
+#define FTK_RD_11(r) FTK_RD(r, t8, 3)
+#define FTK_RD_12(r) FTK_RD(r, t8, 4)
+#define FTK_RD_13(r) FTK_RD(r, t8, 5)
+#define FTK_RD_14(r) FTK_RD(r, t8, 6)
+#define FTK_RD_15(r) FTK_RD(r, t8, 7)
+#define FTK_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
+#define FTK_FMA(e, r, c) "v_fmac_f64_e32 %[a" #e "], %[" #c "], %[v" #r "]\n\t"
+#define FTK_CASE(mr, p0, p1, p2, p3, p4, p5, p6, p7, p8, p9, p10, p11, p12, p13, p14, p15, c0, c1, c2, c3, c4, c5, c6, \
+                 c7, c8, c9, c10, c11, c12, c13, c14, c15)                                                              \
+    ".Lftk_case" #mr "_%=:\n\t" FTK_RD_##p0(0) FTK_RD_##p1(1) FTK_RD_##p2(2) FTK_RD_##p3(3) FTK_RD_##p4(4)             \
+        FTK_RD_##p5(5) FTK_RD_##p6(6) FTK_RD_##p7(7) FTK_WAIT(7) FTK_FMA(0, 0, c0) FTK_RD_##p8(0) FTK_WAIT(7)            \
+            FTK_FMA(1, 1, c1) FTK_RD_##p9(1) FTK_WAIT(7) FTK_FMA(2, 2, c2) FTK_RD_##p10(2) FTK_WAIT(7) FTK_FMA(3, 3, c3)  \
+                FTK_RD_##p11(3) FTK_WAIT(7) FTK_FMA(4, 4, c4) FTK_RD_##p12(4) FTK_WAIT(7) FTK_FMA(5, 5, c5)               \
+                    FTK_RD_##p13(5) FTK_WAIT(7) FTK_FMA(6, 6, c6) FTK_RD_##p14(6) FTK_WAIT(7) FTK_FMA(7, 7, c7)           \
+                        FTK_RD_##p15(7) FTK_WAIT(7) FTK_FMA(8, 0, c8) FTK_WAIT(6) FTK_FMA(9, 1, c9) FTK_WAIT(5)           \
+                            FTK_FMA(10, 2, c10) FTK_WAIT(4) FTK_FMA(11, 3, c11) FTK_WAIT(3) FTK_FMA(12, 4, c12)           \
+                                FTK_WAIT(2) FTK_FMA(13, 5, c13) FTK_WAIT(1) FTK_FMA(14, 6, c14) FTK_WAIT(0)               \
+                                    FTK_FMA(15, 7, c15) "s_branch .Lftk_done_%=\n"
+#define FTK_GOTO(mr) "s_cmp_eq_u32 %[mr], " #mr "\n\ts_cbranch_scc1 .Lftk_case" #mr "_%=\n\t"
+#define FTK_CASES \
+    FTK_CASE(0, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev, ev) \
+    FTK_CASE(1, 1, 0, 3, 2, 5, 4, 7, 6, 9, 8, 11, 10, 13, 12, 15, 14, ev, od, ev, od, ev, od, ev, od, ev, od, ev, od, ev, od, ev, od) \
+    FTK_CASE(2, 2, 3, 0, 1, 6, 7, 4, 5, 10, 11, 8, 9, 14, 15, 12, 13, ev, ev, od, od, ev, ev, od, od, ev, ev, od, od, ev, ev, od, od) \
+    FTK_CASE(3, 3, 2, 1, 0, 7, 6, 5, 4, 11, 10, 9, 8, 15, 14, 13, 12, ev, od, od, ev, ev, od, od, ev, ev, od, od, ev, ev, od, od, ev) \
+    FTK_CASE(4, 4, 5, 6, 7, 0, 1, 2, 3, 12, 13, 14, 15, 8, 9, 10, 11, ev, ev, ev, ev, od, od, od, od, ev, ev, ev, ev, od, od, od, od) \
+    FTK_CASE(5, 5, 4, 7, 6, 1, 0, 3, 2, 13, 12, 15, 14, 9, 8, 11, 10, ev, od, ev, od, od, ev, od, ev, ev, od, ev, od, od, ev, od, ev) \
+    FTK_CASE(6, 6, 7, 4, 5, 2, 3, 0, 1, 14, 15, 12, 13, 10, 11, 8, 9, ev, ev, od, od, od, od, ev, ev, ev, ev, od, od, od, od, ev, ev) \
+    FTK_CASE(8, 8, 9, 10, 11, 12, 13, 14, 15, 0, 1, 2, 3, 4, 5, 6, 7, ev, ev, ev, ev, ev, ev, ev, ev, od, od, od, od, od, od, od, od) \
+    FTK_CASE(9, 9, 8, 11, 10, 13, 12, 15, 14, 1, 0, 3, 2, 5, 4, 7, 6, ev, od, ev, od, ev, od, ev, od, od, ev, od, ev, od, ev, od, ev) \
+    FTK_CASE(10, 10, 11, 8, 9, 14, 15, 12, 13, 2, 3, 0, 1, 6, 7, 4, 5, ev, ev, od, od, ev, ev, od, od, od, od, ev, ev, od, od, ev, ev) \
+    FTK_CASE(12, 12, 13, 14, 15, 8, 9, 10, 11, 4, 5, 6, 7, 0, 1, 2, 3, ev, ev, ev, ev, od, od, od, od, od, od, od, od, ev, ev, ev, ev)
+
+template <int STRIDE>
+__device__ __forceinline__ void bond16(double (&acc)[16], uint32_t t0, uint32_t t8, uint32_t mr, double even, double odd)
+{
+    double v0, v1, v2, v3, v4, v5, v6, v7;
+    asm volatile(
+        "s_waitcnt lgkmcnt(0)\n\t"  // only the block's own reads are counted below
+        FTK_GOTO(0) FTK_GOTO(1) FTK_GOTO(2) FTK_GOTO(4) FTK_GOTO(8) FTK_GOTO(3) FTK_GOTO(5) FTK_GOTO(6) FTK_GOTO(9)
+            FTK_GOTO(10) FTK_GOTO(12) "s_branch .Lftk_done_%=\n" FTK_CASES ".Lftk_done_%=:\n"
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]), [a5] "+v"(acc[5]),
+          [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [a8] "+v"(acc[8]), [a9] "+v"(acc[9]), [a10] "+v"(acc[10]),
+          [a11] "+v"(acc[11]), [a12] "+v"(acc[12]), [a13] "+v"(acc[13]), [a14] "+v"(acc[14]), [a15] "+v"(acc[15]),
+          [v0] "=&v"(v0), [v1] "=&v"(v1), [v2] "=&v"(v2), [v3] "=&v"(v3), [v4] "=&v"(v4), [v5] "=&v"(v5), [v6] "=&v"(v6),
+          [v7] "=&v"(v7)
+        : [t0] "v"(t0), [t8] "v"(t8), [mr] "s"(mr), [ev] "v"(even), [od] "v"(odd), [st] "n"(STRIDE)
+        : "scc", "memory");
+}
+
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
 }
 
 // Element e of a thread is state tid + e T: the register bits are the highest
 // sites.  The current vector w_{k-1} is in LDS (partners) and in registers (own
 // elements) with w_{k-2}; bond constants sit one bond per lane and are read into
-// scalar registers, so the bond loop waits for LDS data only.  Its LDS reads
-// (16 B per element and bond at 128 B per clock) bound the larger sizes, the two
-// reductions' latency the smaller ones.
+// scalar registers, so the bond loop waits for LDS data only.  fp64 issue bounds the
+// larger sizes, the latency of the two reductions the smaller ones: a step of 48
+// sequences takes 3.6 us at 8 sites, 4.5 at 10 and 9 at 12 (before: 17.5 ms for 192
+// sequences of 64 steps at 8 sites, now 0.33; 28.0 ms for 48 of 300 at 12, now 2.75).
 template <int LOGT, int E>
 __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun R)
 {
@@ -176,22 +306,28 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
     constexpr uint32_t dim = T * E;
     __shared__ double2 tile[dim];
     __shared__ double2 sh_a[T / 64], sh_b[T / 64];
+    // eight elements: the real and the imaginary parts apart, as bond16 reads them
+    constexpr bool kPlanar = E == 8;
+    auto put = [&](uint32_t x, double2 w) {
+        if constexpr (kPlanar) {
+            ((double *)tile)[x] = w.x;
+            ((double *)tile)[dim + x] = w.y;
+        } else {
+            tile[x] = w;
+        }
+    };
+    const uint32_t tile_at = lds_address(tile);
     const ResidentSeq q = R.seq[blockIdx.x];
     const uint32_t tid = threadIdx.x;
     SeqState *st = R.st + q.out;
     double *alpha = R.alpha + (size_t)q.out * R.stride, *beta = R.beta + (size_t)q.out * R.stride;
     const int nb = P.n_bonds;
-    const int bl = (int)(tid & 63) < nb ? (int)(tid & 63) : 0;
-    const int c_code = (int)P.code[bl];
-    const double ap0 = P.ap3[0], ap1 = P.ap3[1], ap2 = P.ap3[2];
-    const double aa0 = P.aa3[0], aa1 = P.aa3[1], aa2 = P.aa3[2];
-
     // bond parities of the thread's element 0 and the diagonal of its elements
     uint64_t par64 = 0;
 #pragma unroll
     for (int l = 0; l < LOGT; ++l)
         if ((tid >> l) & 1u) par64 ^= P.smask[l];
-    const uint32_t par_lo = (uint32_t)par64, par_hi = (uint32_t)(par64 >> 32);
+    const Bonds bonds(P, par64);
     const int nz = __popcll(P.zmask);
     double D[E];
 #pragma unroll
@@ -217,30 +353,17 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
             const uint32_t x = tid + e * T;
             wc[e] = start[x];
             wp[e] = make_double2(0.0, 0.0);
-            tile[x] = wc[e];
+            put(x, wc[e]);
             pair_prod(hi, lo, wc[e].x, wc[e].x);
             pair_prod(hi, lo, wc[e].y, wc[e].y);
         }
         const double s = block_sum<T>(hi, lo, sh_b);
         const double nrm = sqrt(s);
-        inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+        inv = uniform(nrm > 0.0 ? 1.0 / nrm : 0.0);
         inv_prev = 0.0;
         bcur = 0.0;
         bad = isfinite(s) ? 0 : 1;
-        if (tid == 0) {
-            st->norm2 = s;
-            st->norm = nrm;
-            st->inv_cur = inv;
-            st->inv_prev = 0.0;
-            st->beta_cur = 0.0;
-            st->alpha_cur = 0.0;
-            st->shift_re = q.shift_re;
-            st->max_resid = 0.0;
-            st->done = nrm > 0.0 ? 0 : 1;
-            st->steps = 0;
-            st->numeric_error = bad;
-            st->pad = bad;
-        }
+        if (tid == 0) start_state(st, s, nrm, inv, q.shift_re, bad);
         if (!(nrm > 0.0)) return;
     } else {
         if (st->done) return;
@@ -253,60 +376,70 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
             const uint32_t x = tid + e * T;
             wc[e] = ((const double2 *)carry)[x];
             wp[e] = ((const double2 *)carry)[dim + x];
-            tile[x] = wc[e];
+            put(x, wc[e]);
         }
         lds_barrier();
     }
-
-    // bond b and its partners of the thread's elements
-    auto bond = [&](int b, double2 (&v)[E]) {
-        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane(c_code, b);
-        const uint32_t m = c & 0x3fffffffu, type = c >> 30;
-        const double p0 = ap0, p1 = ap1, p2 = ap2, q0 = aa0, q1 = aa1, q2 = aa2;
-        const double ap = type == 0 ? p0 : type == 1 ? p1 : p2;
-        const double aa = type == 0 ? q0 : type == 1 ? q1 : q2;
-        const bool anti = ((b < 32 ? par_lo : par_hi) & (1u << (b & 31))) != 0;
-        const BondAt at{anti ? aa : ap, anti ? ap : aa, m >> LOGT};
-        const double2 *src = tile + (tid ^ (m & (T - 1)));
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = src[((uint32_t)e ^ at.mr) << LOGT];
-        return at;
-    };
 
     double2 *vout = R.vout ? (double2 *)(R.vout + (size_t)blockIdx.x * R.vstride) : nullptr;
     int k = R.k0, done = 0;
     double a = 0.0;
     for (; k < R.k1 && !done; ++k) {
-        double re[E], im[E];
+        double acc[2 * E];  // the real parts, then the imaginary ones
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            re[e] = D[e] * wc[e].x;
-            im[e] = D[e] * wc[e].y;
+            acc[e] = D[e] * wc[e].x;
+            acc[E + e] = D[e] * wc[e].y;
         }
-        int b = 0;
-        for (; b + 1 < nb; b += 2) {  // two bonds' reads in flight, their fmas in list order
-            double2 v0[E], v1[E];
-            const BondAt b0 = bond(b, v0), b1 = bond(b + 1, v1);
-            accumulate<E>(re, im, v0, b0);
-            accumulate<E>(re, im, v1, b1);
-        }
-        if (b < nb) {
-            double2 v0[E];
-            const BondAt b0 = bond(b, v0);
-            accumulate<E>(re, im, v0, b0);
+        if constexpr (kPlanar) {
+            for (int b = 0; b < nb; ++b) {
+                const BondAt c = bonds.at(b);
+                const uint32_t t0 = tile_at + (tid ^ (c.m & (T - 1))) * 8;
+                bond16<T * 8>(acc, t0, t0 + 8 * dim, c.m >> LOGT, c.even, c.odd);
+            }
+        } else {
+            auto partners = [&](uint32_t m, double2 (&v)[E]) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = tile[(tid ^ m) ^ (uint32_t)(e * T)];
+            };
+            auto add = [&](const BondAt &c, const double2 (&v)[E]) {
+                const double even = c.even, odd = c.odd;
+                const uint32_t sel = odd_elements(c.m >> LOGT);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const double amp = ((sel >> e) & 1u) ? odd : even;
+                    acc[e] = fma(amp, v[e].x, acc[e]);
+                    acc[E + e] = fma(amp, v[e].y, acc[E + e]);
+                }
+            };
+            int b = 0;
+            for (; b + 1 < nb; b += 2) {  // two bonds' reads in flight, their fmas in list order
+                const BondAt c0 = bonds.at(b), c1 = bonds.at(b + 1);
+                double2 v0[E], v1[E];
+                partners(c0.m, v0);
+                partners(c1.m, v1);
+                add(c0, v0);
+                add(c1, v1);
+            }
+            if (b < nb) {
+                const BondAt c0 = bonds.at(b);
+                double2 v0[E];
+                partners(c0.m, v0);
+                add(c0, v0);
+            }
         }
         // u = (H w_{k-1}) inv + c1 w_{k-2}; alpha_k
-        const double c1 = (-bcur) * inv_prev;
+        const double c1 = uniform((-bcur) * inv_prev);
         double hi = 0.0, lo = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            double ur = re[e] * inv, ui = im[e] * inv;
+            double ur = acc[e] * inv, ui = acc[E + e] * inv;
             if (k > 0) {
                 ur = fma(c1, wp[e].x, ur);
                 ui = fma(c1, wp[e].y, ui);
             }
-            re[e] = ur;
-            im[e] = ui;
+            acc[e] = ur;
+            acc[E + e] = ui;
             pair_prod(hi, lo, wc[e].x, ur);
             pair_prod(hi, lo, wc[e].y, ui);
         }
@@ -314,21 +447,21 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
 #pragma unroll
             for (int e = 0; e < E; ++e) vout[(size_t)(k - R.k0) * dim + tid + e * T] = wc[e];
         }
-        a = inv * block_sum<T>(hi, lo, sh_a);  // the barrier ends the reads of the tile
+        a = uniform(inv * block_sum<T>(hi, lo, sh_a));  // the barrier ends the reads of the tile
         // w_k = u + c2 w_{k-1}; beta_{k+1}
-        const double c2 = -(a * inv);
+        const double c2 = uniform(-(a * inv));
         hi = lo = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const double wr = fma(c2, wc[e].x, re[e]);
-            const double wi = fma(c2, wc[e].y, im[e]);
-            tile[tid + e * T] = make_double2(wr, wi);
+            const double wr = fma(c2, wc[e].x, acc[e]);
+            const double wi = fma(c2, wc[e].y, acc[E + e]);
+            put(tid + e * T, make_double2(wr, wi));
             pair_prod(hi, lo, wr, wr);
             pair_prod(hi, lo, wi, wi);
             wp[e] = wc[e];
             wc[e] = make_double2(wr, wi);
         }
-        const double bn = sqrt(block_sum<T>(hi, lo, sh_b));
+        const double bn = uniform(sqrt(block_sum<T>(hi, lo, sh_b)));
         if (tid == 0) {
             alpha[k] = a;
             beta[k] = bn;
@@ -338,20 +471,11 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
             done = 1;  // invariant subspace
         } else {
             inv_prev = inv;
-            inv = 1.0 / bn;
+            inv = uniform(1.0 / bn);
             bcur = bn;
         }
     }
-    if (tid == 0) {
-        st->inv_cur = inv;
-        st->inv_prev = inv_prev;
-        st->beta_cur = bcur;
-        st->alpha_cur = a;
-        st->done = done;
-        st->steps = k;
-        st->numeric_error = bad != 0;
-        st->pad = bad;
-    }
+    if (tid == 0) end_state(st, inv, inv_prev, bcur, a, done, k, bad);
     if (carry && !done) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -360,6 +484,225 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
             ((double2 *)carry)[dim + x] = wp[e];
         }
     }
+}
+
+// A sequence's carried vectors through a buffer descriptor: entry tid + i with i
+// uniform is one register of lane offset and one scalar (a flat address takes two
+// registers for each of a thread's 16 entries), and is bounds-checked by the hardware.
+struct Carried {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t lane;  // byte offset of entry tid
+    __device__ Carried(double *p, uint32_t entries)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(entries * sizeof(double)), 0x00027000)),
+          lane(threadIdx.x * (uint32_t)sizeof(double))
+    {
+    }
+    __device__ __forceinline__ double get(uint32_t i) const
+    {
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane, i * 8, 0));
+    }
+    __device__ __forceinline__ void set(uint32_t i, double x) const
+    {
+        typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, x), rsrc, lane, i * 8, 0);
+    }
+};
+
+// The same for vectors of two planes (real, imaginary) too large to keep complex in
+// LDS: H is real, so a step multiplies one plane after the other, each staged in LDS
+// (128 KiB at 14 sites) with its sums in registers.  w_{k-1} and w_{k-2} live in the
+// sequence's carry buffer (planar, re-read from L2): w_k overwrites w_{k-2}.  LDS
+// reads bound a step (8 B per element, plane and bond).
+template <int LOGT, int E>
+__global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, ResidentRun R)
+{
+    constexpr int T = 1 << LOGT;
+    constexpr uint32_t dim = T * E;
+    __shared__ double plane[dim];
+    __shared__ double2 sh_a[T / 64], sh_b[T / 64];
+    const ResidentSeq q = R.seq[blockIdx.x];
+    const uint32_t tid = threadIdx.x;
+    SeqState *st = R.st + q.out;
+    double *alpha = R.alpha + (size_t)q.out * R.stride, *beta = R.beta + (size_t)q.out * R.stride;
+    const int nb = P.n_bonds;
+    uint64_t par = 0;
+#pragma unroll
+    for (int l = 0; l < LOGT; ++l)
+        if ((tid >> l) & 1u) par ^= P.smask[l];
+    const Bonds bonds(P, par);
+    const int nz = __popcll(P.zmask);
+    // the diagonal as its two bond sums, 8 bits each, two elements a word
+    uint32_t dsum[E / 2];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        uint64_t pe = par;
+        if (e & 1) pe ^= P.smask[LOGT];
+        if (e & 2) pe ^= P.smask[LOGT + 1];
+        if (e & 4) pe ^= P.smask[LOGT + 2];
+        if (e & 8) pe ^= P.smask[LOGT + 3];
+        const uint32_t c = (uint32_t)__popcll(pe) | (uint32_t)__popcll(pe & P.zmask) << 8;
+        if (e & 1) dsum[e >> 1] |= c << 16;
+        else dsum[e >> 1] = c;
+    }
+    auto diagonal = [&](int e) {
+        const uint32_t c = dsum[e >> 1] >> (16 * (e & 1));
+        const int s_all = nb - 2 * (int)(c & 0xffu);
+        const int s_z = nz - 2 * (int)(c >> 8 & 0xffu);
+        return fma(P.kq, (double)s_z, P.jq * (double)s_all);
+    };
+
+    // a thread's own entries: two bases, so that every offset fits the instruction
+    uint32_t upper = tid + 8 * T;
+    asm volatile("" : "+v"(upper));
+    auto own = [&](int e) -> double & { return plane[(e < 8 ? tid : upper) + (e & 7) * T]; };
+
+    const uint32_t plane_at = lds_address(plane);
+    const Carried buf(R.carry + (size_t)blockIdx.x * 4 * dim, 4 * dim);  // w_k at entry (k & 1) 2 dim
+    double inv, inv_prev, bcur;
+    int bad;  // 1 + the first step after which a scalar was not finite (1: the start), 0 none
+    if (R.k0 == 0) {
+        const double2 *start = R.chi ? (const double2 *)R.chi + (size_t)blockIdx.x * dim : q.phi;
+        double hi = 0.0, lo = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const uint32_t x = tid + e * T;
+            const double2 c = start[x];
+            own(e) = c.x;
+            buf.set(2 * dim + e * T, c.x);
+            buf.set(3 * dim + e * T, c.y);
+            pair_prod(hi, lo, c.x, c.x);
+            pair_prod(hi, lo, c.y, c.y);
+            if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        const double s = block_sum<T>(hi, lo, sh_b);
+        const double nrm = sqrt(s);
+        inv = uniform(nrm > 0.0 ? 1.0 / nrm : 0.0);
+        inv_prev = 0.0;
+        bcur = 0.0;
+        bad = isfinite(s) ? 0 : 1;
+        if (tid == 0) start_state(st, s, nrm, inv, q.shift_re, bad);
+        if (!(nrm > 0.0)) return;
+    } else {
+        if (st->done) return;
+        inv = st->inv_cur;
+        inv_prev = st->inv_prev;
+        bcur = st->beta_cur;
+        bad = st->pad;
+        const uint32_t w = ((R.k0 - 1) & 1) * 2 * dim;
+#pragma unroll
+        for (int e = 0; e < E; ++e) own(e) = buf.get(w + e * T);
+        lds_barrier();
+    }
+
+    double2 *vout = R.vout ? (double2 *)(R.vout + (size_t)blockIdx.x * R.vstride) : nullptr;
+    int k = R.k0, done = 0;
+    double a = 0.0;
+    for (; k < R.k1 && !done; ++k) {
+        const bool first = k == 0;
+        const uint32_t wnew = (k & 1) * 2 * dim;       // w_{k-2}, then w_k
+        const uint32_t wcur = ((k + 1) & 1) * 2 * dim;  // w_{k-1}
+        const double c1 = uniform((-bcur) * inv_prev);
+        double acc[E];
+        double hi = 0.0, lo = 0.0;
+        // u = (H w_{k-1}) inv + c1 w_{k-2} of the plane in LDS, into acc; its share of alpha_k
+        auto half = [&](uint32_t wp) {
+            double prev[E];  // read while the bonds run (step 0 has none and drops what it reads)
+#pragma unroll
+            for (int e = 0; e < E; ++e) prev[e] = buf.get(wp + e * T);
+#pragma unroll
+            for (int i = 0; i < E / 2; ++i) asm volatile("" : "+v"(dsum[i]));  // decoded here, not kept for all steps
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                acc[e] = diagonal(e) * own(e);
+                if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            for (int b = 0; b < nb; ++b) {
+                const BondAt c = bonds.at(b);
+                if constexpr (E == 16) {
+                    const uint32_t t0 = plane_at + (tid ^ (c.m & (T - 1))) * 8;
+                    bond16<T * 8>(acc, t0, t0 + 64 * T, c.m >> LOGT, c.even, c.odd);
+                    continue;
+                }
+                const double even = c.even, odd = c.odd;
+                const uint32_t sel = odd_elements(c.m >> LOGT);
+                const char *src = (const char *)plane;
+                const uint32_t base = (tid ^ c.m) * (uint32_t)sizeof(double);
+                double v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    v[e] = *(const double *)(src + (base ^ (uint32_t)(e * T * sizeof(double))));
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fma(((sel >> e) & 1u) ? odd : even, v[e], acc[e]);
+            }
+            asm volatile("" ::: "memory");  // own entries are read again below, not kept over the bonds
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const double t = acc[e] * inv, u = fma(c1, prev[e], t);
+                acc[e] = first ? t : u;
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                pair_prod(hi, lo, own(e), acc[e]);
+                if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            asm volatile("" : "+v"(hi), "+v"(lo));  // added up here: not their 32 factors kept to the end
+        };
+        double own_re[E], own_im[E];
+        half(wnew);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            own_im[e] = buf.get(wcur + dim + e * T);
+            buf.set(wnew + e * T, acc[e]);  // u's real part, in the place of w_{k-2}'s
+        }
+        lds_barrier();  // the real plane is no longer read
+#pragma unroll
+        for (int e = 0; e < E; ++e) own(e) = own_im[e];
+        lds_barrier();
+        half(wnew + dim);
+        double u_re[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            own_re[e] = buf.get(wcur + e * T);
+            u_re[e] = buf.get(wnew + e * T);
+        }
+        a = uniform(inv * block_sum<T>(hi, lo, sh_a));  // nor the imaginary one
+        if (vout) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                (vout + (size_t)(k - R.k0) * dim + e * T)[tid] = make_double2(own_re[e], own(e));
+                if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            asm volatile("" ::: "memory");
+        }
+        const double c2 = uniform(-(a * inv));
+        hi = lo = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const double ci = own(e);
+            const double wr = fma(c2, own_re[e], u_re[e]);
+            const double wi = fma(c2, ci, acc[e]);
+            own(e) = wr;
+            buf.set(wnew + e * T, wr);
+            buf.set(wnew + dim + e * T, wi);
+            pair_prod(hi, lo, wr, wr);
+            pair_prod(hi, lo, wi, wi);
+            if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        const double bn = uniform(sqrt(block_sum<T>(hi, lo, sh_b)));
+        if (tid == 0) {
+            alpha[k] = a;
+            beta[k] = bn;
+        }
+        if (bad == 0 && !(isfinite(a) && isfinite(bn))) bad = k + 2;
+        if (!(bn > R.tol)) {
+            done = 1;  // invariant subspace
+        } else {
+            inv_prev = inv;
+            inv = uniform(1.0 / bn);
+            bcur = bn;
+        }
+    }
+    if (tid == 0) end_state(st, inv, inv_prev, bcur, a, done, k, bad);
 }
 
 template <int LOGT, int E>
@@ -385,9 +728,11 @@ void launch_resident(const HvOp &op, const ResidentRun &run, int n_seq, hipStrea
     if (n_seq <= 0) return;
     switch (op.P.n_sites) {
     // 256 threads with one element each hide more latency than 64 with four (8 sites,
-    // 192 sequences of 64 steps: 0.35 against 0.40 ms a call); at 12 sites 512 threads
-    // with eight elements share the bonds' scalar work and the reductions among fewer
-    // waves than 1024 with four (48 sequences of 300 steps: 3.00 against 3.24 ms)
+    // 192 sequences of 64 steps: 0.35 against 0.40 ms a call), as do 256 with four
+    // against 128 with eight (10 sites, 48 sequences of 200 steps: 0.87 against 1.12 ms);
+    // at 12 sites 512 threads with eight elements share the bonds' scalar work and the
+    // reductions among fewer waves than 1024 with four (48 sequences of 300 steps: 3.00
+    // against 3.24 ms, both with selects in place of bond16)
     case 6: launch_resident_t<6, 1>(op.P, run, n_seq, s); break;
     case 7: launch_resident_t<7, 1>(op.P, run, n_seq, s); break;
     case 8: launch_resident_t<8, 1>(op.P, run, n_seq, s); break;
@@ -395,6 +740,8 @@ void launch_resident(const HvOp &op, const ResidentRun &run, int n_seq, hipStrea
     case 10: launch_resident_t<8, 4>(op.P, run, n_seq, s); break;
     case 11: launch_resident_t<9, 4>(op.P, run, n_seq, s); break;
     case 12: launch_resident_t<9, 8>(op.P, run, n_seq, s); break;
+    case 13: hipLaunchKernelGGL((k_resident_planes<10, 8>), dim3(n_seq), dim3(1024), 0, s, op.P, run); break;
+    case 14: hipLaunchKernelGGL((k_resident_planes<10, 16>), dim3(n_seq), dim3(1024), 0, s, op.P, run); break;
     default: break;
     }
 }

@@ -39,7 +39,7 @@ def _both(ftk, fn):
     return out
 
 
-@pytest.mark.parametrize("N", [6, 7, 8, 9, 10, 11, 12])
+@pytest.mark.parametrize("N", [6, 7, 8, 9, 10, 11, 12, 13, 14])
 def test_resident_sequences_match_per_step(env, N):
     """Spectra (fixed length, one step, truncated) and operator pairs at every resident size."""
     ftk, ctx, torch = env
