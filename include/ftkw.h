@@ -88,7 +88,8 @@ ftk_status ftk_ctx_peak_memory(ftk_ctx *ctx, size_t *peak, int reset);
  * v_{k-1} with <v_k|u>, w_k = u - alpha_k v_k with ||w_k||, and the scalar and
  * multi-shift updates; with the multi-pass H v the second half of a step runs
  * inside the next step, so a timed step is the second half of step k-1 and the
- * first half of step k), and the filter runs' steps likewise ("filter_step").
+ * first half of step k), and the filter runs' steps likewise ("filter_step";
+ * "filter_run" for a launch of whole filter sequences of a small cluster).
  * ftk_ctx_kernel_time synchronises the stream and returns the number of timed
  * launches and their mean duration in milliseconds, then forgets them. */
 ftk_status ftk_ctx_set_timing(ftk_ctx *ctx, int enable);

@@ -172,6 +172,32 @@ struct DevBuf {
     double *d() const { return (double *)p; }
 };
 
+// Several buffers of one call in one device allocation.
+struct Arena {
+    std::vector<std::pair<void **, size_t>> parts;
+    DevBuf mem;
+    template <class T>
+    void part(T **p, size_t n)
+    {
+        parts.push_back({(void **)p, (n * sizeof(T) + 255) / 256 * 256});
+    }
+    void allocate(ftk_ctx *ctx)
+    {
+        size_t total = 0;
+        for (auto &q : parts) total += q.second;
+        mem = DevBuf(ctx, total);
+        char *at = (char *)mem.p;
+        for (auto &q : parts) {
+            *q.first = at;
+            at += q.second;
+        }
+    }
+};
+
+// Sequences of op run one per workgroup, whole (resident.h), unless a tuning key
+// asks for another form
+bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
+
 }  // namespace
 
 struct ftk_hamiltonian {
@@ -218,6 +244,23 @@ struct Krylov {
         HIP_CHECK(hipMemcpyAsync(&r, scalar.p, sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_CHECK(hipStreamSynchronize(s));
         return r;
+    }
+
+    // rounded Re<a|b> to device memory
+    void dot_to(const double *a, const double *b, double *out)
+    {
+        launch_dot(dim, a, b, partials.d(), s);
+        launch_sum_partials(partials.d(), nparts, out, s);
+    }
+    // rounded ||v_m||^2 of m < count vectors vs doubles apart to out[m]
+    void dots(const double *v, int count, size_t vs, double *out)
+    {
+        const int most = std::min(1024, kMaxGrid * 16 / nparts);  // vectors the partial sums have room for
+        for (int m = 0; m < count; m += most) {
+            const int B = std::min(most, count - m);
+            launch_dot(dim, v + m * vs, v + m * vs, partials.d(), s, B, vs);
+            launch_sum_partials(partials.d(), nparts, out + m, s, B);
+        }
     }
 
     // n Lanczos steps of sequence i started from `start` (w_{-1}); buffers W0, W1
@@ -812,130 +855,237 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
         for (int a = 0; a < st->na; ++a) any_beta = any_beta || st->betas[a] > 0;
         // Taylor workspace only when some anchor has beta > 0
         const size_t tbytes = any_beta ? vbytes : 0;
-        DevBuf phi0(ctx, vbytes), phib(ctx, vbytes), t(ctx, tbytes), tn(ctx, tbytes), acc(ctx, tbytes);
-        DevBuf W0(ctx, vbytes), W1(ctx, vbytes), Vbuf(ctx, vbytes * nb);
-        DevBuf coef(ctx, sizeof(double) * 2 * (size_t)st->L * n);
-        std::vector<double> hcoef((size_t)2 * st->L * n);
+        DevBuf phi0(ctx, vbytes), t(ctx, tbytes), tn(ctx, tbytes), acc(ctx, tbytes);
+        DevBuf sums(ctx, sizeof(double) * 3 * (size_t)st->L);
+        std::vector<double> hsums((size_t)3 * st->L);
         const double N = (double)h->n_sites;
 
-        for (int sv = 0; sv < st->nv; ++sv) {
-            // phi_0 = g / ||g||
+        // phi_0 = g / ||g|| of vector sv
+        auto start_vector = [&](int sv) {
             if (p->gaussian_dev)
                 launch_copy(dim, p->gaussian_dev + (size_t)sv * 2 * dim, phi0.d(), s);
             else
                 launch_gaussian(dim, p->seed, (uint64_t)p->first_vector + sv, phi0.d(), s);
-            {
-                const double nrm = std::sqrt(kr.dot(phi0.d(), phi0.d()));
-                if (!(nrm > 0) || !std::isfinite(nrm)) fail(FTK_ENUMERIC, "start vector has zero or non-finite norm");
-                launch_scale(dim, phi0.d(), 1.0 / nrm, s);
+            const double nrm = std::sqrt(kr.dot(phi0.d(), phi0.d()));
+            if (!(nrm > 0) || !std::isfinite(nrm)) fail(FTK_ENUMERIC, "start vector has zero or non-finite norm");
+            launch_scale(dim, phi0.d(), 1.0 / nrm, s);
+        };
+        // phi_beta = e^{-beta H / 2} phi_0 of anchor a (Appendix A); returns its log norm
+        auto imaginary_time = [&](int a, double *phib) {
+            launch_copy(dim, phi0.d(), phib, s);
+            const TaylorPlan plan = taylor_plan(h->n_sites, st->betas[a], h->table.norm_bound, lambda);
+            double log_norm = 0.0;
+            for (int sp = 0; sp < plan.Md; ++sp) {
+                launch_copy(dim, phib, t.d(), s);
+                launch_copy(dim, phib, acc.d(), s);
+                double *tc = t.d(), *tnx = tn.d();
+                for (int k = 1; k <= plan.K; ++k) {
+                    const double sk = plan.c / (double)k;
+                    const double ca = sk * plan.ell;
+                    const double cb = -(sk / N);
+                    launch_taylor_term(h->op, tc, tnx, acc.d(), ca, cb, s);
+                    std::swap(tc, tnx);
+                }
+                const double nrm = std::sqrt(kr.dot(acc.d(), acc.d()));
+                if (!(nrm > 0) || !std::isfinite(nrm)) fail(FTK_ENUMERIC, "imaginary-time state lost its norm");
+                launch_copy(dim, acc.d(), phib, s);
+                launch_scale(dim, phib, 1.0 / nrm, s);
+                log_norm += std::log(nrm);
             }
-            for (int a = 0; a < st->na; ++a) {
-                const size_t sa = (size_t)sv * st->na + a;
-                // phi_beta = e^{-beta H / 2} phi_0 (Appendix A)
-                launch_copy(dim, phi0.d(), phib.d(), s);
-                const TaylorPlan plan = taylor_plan(h->n_sites, st->betas[a], h->table.norm_bound, lambda);
-                double log_norm = 0.0;
-                for (int sp = 0; sp < plan.Md; ++sp) {
-                    launch_copy(dim, phib.d(), t.d(), s);
-                    launch_copy(dim, phib.d(), acc.d(), s);
-                    double *tc = t.d(), *tnx = tn.d();
-                    for (int k = 1; k <= plan.K; ++k) {
-                        const double sk = plan.c / (double)k;
-                        const double ca = sk * plan.ell;
-                        const double cb = -(sk / N);
-                        launch_taylor_term(h->op, tc, tnx, acc.d(), ca, cb, s);
-                        std::swap(tc, tnx);
-                    }
-                    const double nrm = std::sqrt(kr.dot(acc.d(), acc.d()));
-                    if (!(nrm > 0) || !std::isfinite(nrm)) fail(FTK_ENUMERIC, "imaginary-time state lost its norm");
-                    launch_copy(dim, acc.d(), phib.d(), s);
-                    launch_scale(dim, phib.d(), 1.0 / nrm, s);
-                    log_norm += std::log(nrm);
-                }
-                log_norm -= N * st->betas[a] * plan.ell / 2.0;
-                st->log_norm[sa] = log_norm;
-
-                // pass 1: Lanczos coefficients of phi_beta
-                auto noflush = [](int, int) {};
-                kr.run(0, phib.d(), W0.d(), W1.d(), n, 0.0, nullptr, nullptr, 0, 0.0, nullptr, 0, noflush);
-                SeqState q1 = kr.read_state(0);
-                if (q1.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in filter Lanczos coefficients");
-                int steps = q1.steps;
-                std::vector<double> al(steps), be(steps);
-                HIP_CHECK(hipMemcpyAsync(al.data(), kr.al(0), sizeof(double) * steps, hipMemcpyDeviceToHost, s));
-                HIP_CHECK(hipMemcpyAsync(be.data(), kr.be(0), sizeof(double) * steps, hipMemcpyDeviceToHost, s));
-                HIP_CHECK(hipStreamSynchronize(s));
-                if (auto_window && sv == 0) {
-                    shell_window(al.data(), be.data(), steps, st->L, margin, &st->E_b[a], &st->eps[a]);
-                    if (!(std::isfinite(st->eps[a]) && st->eps[a] > 0))
-                        fail(FTK_ENUMERIC, "automatic shell window is empty or not finite");
-                }
-                std::vector<int> k_m;  // per-shell steps under residual truncation
-                if (p->resid_tol > 0) {
-                    // each filter operator on its own (Sec. V): shell m takes T_{k_m} for the
-                    // first k_m at which all of its M contour shifts have converged
-                    std::vector<double> zr(st->M), zi(st->M);
-                    k_m.resize(st->L);
-                    int kmax = 1;
-                    for (int m = 0; m < st->L; ++m) {
-                        for (int j = 1; j <= st->M; ++j) {
-                            const double th = 2.0 * M_PI * ((double)j - 0.5) / (double)st->M;
-                            zr[j - 1] = shell_energy(st->E_b[a], st->eps[a], m) + st->eps[a] * std::cos(th);
-                            zi[j - 1] = st->eps[a] * std::sin(th);
-                        }
-                        k_m[m] = truncation_steps(al.data(), be.data(), steps, zr.data(), zi.data(), st->M,
-                                                  p->resid_tol);
-                        kmax = std::max(kmax, k_m[m]);
-                    }
-                    steps = kmax;
-                    al.resize(steps);
-                    be.resize(steps);
-                }
-                std::copy(al.begin(), al.end(), st->alpha.begin() + sa * n);
-                std::copy(be.begin(), be.end(), st->beta.begin() + sa * n);
-                st->steps[sa] = steps;
-
-                // shell coefficients c^m (host, Sec. III.B); the device accumulates the
-                // unnormalised residuals w_{k-1} = v_k / inv_k, so fold inv_k into c^m_k
-                shell_coefficients(al.data(), be.data(), steps, q1.norm, st->E_b[a], st->eps[a], st->L, st->M,
-                                   hcoef.data(), k_m.empty() ? nullptr : k_m.data());
-                {
-                    std::vector<double> inv(steps);
-                    inv[0] = 1.0 / q1.norm;
-                    for (int k = 1; k < steps; ++k) inv[k] = 1.0 / be[k - 1];
-                    for (int m = 0; m < st->L; ++m)
-                        for (int k = 0; k < steps; ++k) {
-                            double *c = &hcoef[2 * ((size_t)m * steps + k)];
-                            c[0] = c[0] * inv[k];
-                            c[1] = c[1] * inv[k];
-                        }
-                }
-                HIP_CHECK(hipMemcpyAsync(coef.p, hcoef.data(), sizeof(double) * 2 * st->L * steps,
-                                         hipMemcpyHostToDevice, s));
-
-                // pass 2: regenerate v_k and accumulate phi^m = sum_k c^m_k v_k
-                DevBuf shells(ctx, vbytes * st->L);
-                HIP_CHECK(hipMemsetAsync(shells.p, 0, vbytes * st->L, s));
-                auto flush = [&](int k0, int cnt) {
-                    launch_accumulate(dim, Vbuf.d(), cnt, coef.d(), steps, k0, shells.d(), st->L, s);
-                };
-                kr.run(0, phib.d(), W0.d(), W1.d(), steps, 0.0, nullptr, nullptr, 0, 0.0, Vbuf.d(), nb, flush);
-                std::vector<double> al2(steps);
-                HIP_CHECK(hipMemcpyAsync(al2.data(), kr.al(0), sizeof(double) * steps, hipMemcpyDeviceToHost, s));
-                HIP_CHECK(hipStreamSynchronize(s));
-                if (std::memcmp(al2.data(), al.data(), sizeof(double) * steps) != 0)
-                    fail(FTK_EDEVICE, "regenerated Lanczos sequence differs from the first pass");
+            return log_norm - N * st->betas[a] * plan.ell / 2.0;
+        };
+        // After pass 1 of (vector sv, anchor a): T_n kept, the automatic window, the steps pass 2
+        // takes, and the shell coefficients [L][steps] into hcoef.  al, be hold q1.steps entries.
+        auto shell_setup = [&](int sv, int a, const SeqState &q1, std::vector<double> &al, std::vector<double> &be,
+                               double *hcoef) {
+            const size_t sa = (size_t)sv * st->na + a;
+            if (q1.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in filter Lanczos coefficients");
+            int steps = q1.steps;
+            if (auto_window && sv == 0) {
+                shell_window(al.data(), be.data(), steps, st->L, margin, &st->E_b[a], &st->eps[a]);
+                if (!(std::isfinite(st->eps[a]) && st->eps[a] > 0))
+                    fail(FTK_ENUMERIC, "automatic shell window is empty or not finite");
+            }
+            std::vector<int> k_m;  // per-shell steps under residual truncation
+            if (p->resid_tol > 0) {
+                // each filter operator on its own (Sec. V): shell m takes T_{k_m} for the
+                // first k_m at which all of its M contour shifts have converged
+                std::vector<double> zr(st->M), zi(st->M);
+                k_m.resize(st->L);
+                int kmax = 1;
                 for (int m = 0; m < st->L; ++m) {
-                    const double *pm = shells.d() + (size_t)m * 2 * dim;
-                    st->n_m[sa * st->L + m] = kr.dot(pm, pm);
-                    if (p->shell_moments) {
-                        // H phi^m into the (now free) first Lanczos buffer
-                        launch_apply_h(h->op, pm, W0.d(), s);
-                        st->h1[sa * st->L + m] = kr.dot(pm, W0.d());
-                        st->h2[sa * st->L + m] = kr.dot(W0.d(), W0.d());
+                    for (int j = 1; j <= st->M; ++j) {
+                        const double th = 2.0 * M_PI * ((double)j - 0.5) / (double)st->M;
+                        zr[j - 1] = shell_energy(st->E_b[a], st->eps[a], m) + st->eps[a] * std::cos(th);
+                        zi[j - 1] = st->eps[a] * std::sin(th);
                     }
+                    k_m[m] = truncation_steps(al.data(), be.data(), steps, zr.data(), zi.data(), st->M, p->resid_tol);
+                    kmax = std::max(kmax, k_m[m]);
                 }
-                st->phi.push_back(std::move(shells));
+                steps = kmax;
+                al.resize(steps);
+                be.resize(steps);
+            }
+            std::copy(al.begin(), al.end(), st->alpha.begin() + sa * n);
+            std::copy(be.begin(), be.end(), st->beta.begin() + sa * n);
+            st->steps[sa] = steps;
+
+            // shell coefficients c^m (host, Sec. III.B); the device accumulates the
+            // unnormalised residuals w_{k-1} = v_k / inv_k, so fold inv_k into c^m_k
+            shell_coefficients(al.data(), be.data(), steps, q1.norm, st->E_b[a], st->eps[a], st->L, st->M, hcoef,
+                               k_m.empty() ? nullptr : k_m.data());
+            std::vector<double> inv(steps);
+            inv[0] = 1.0 / q1.norm;
+            for (int k = 1; k < steps; ++k) inv[k] = 1.0 / be[k - 1];
+            for (int m = 0; m < st->L; ++m)
+                for (int k = 0; k < steps; ++k) {
+                    double *c = &hcoef[2 * ((size_t)m * steps + k)];
+                    c[0] = c[0] * inv[k];
+                    c[1] = c[1] * inv[k];
+                }
+            return steps;
+        };
+        auto check_regenerated = [&](const double *al2, const std::vector<double> &al) {
+            if (std::memcmp(al2, al.data(), sizeof(double) * al.size()) != 0)
+                fail(FTK_EDEVICE, "regenerated Lanczos sequence differs from the first pass");
+        };
+        // n_m (and the moments) of the finished shells of pair sa; hv: a free vector
+        auto shell_sums = [&](size_t sa, const DevBuf &shells, double *hv) {
+            const int L = st->L, per = p->shell_moments ? 3 : 1;
+            kr.dots(shells.d(), L, 2 * (size_t)dim, sums.d());
+            if (p->shell_moments)
+                for (int m = 0; m < L; ++m) {
+                    const double *pm = shells.d() + (size_t)m * 2 * dim;
+                    launch_apply_h(h->op, pm, hv, s);
+                    kr.dot_to(pm, hv, sums.d() + L + m);
+                    kr.dot_to(hv, hv, sums.d() + 2 * L + m);
+                }
+            HIP_CHECK(hipMemcpyAsync(hsums.data(), sums.p, sizeof(double) * per * L, hipMemcpyDeviceToHost, s));
+            HIP_CHECK(hipStreamSynchronize(s));
+            std::copy(hsums.begin(), hsums.begin() + L, st->n_m.begin() + sa * L);
+            if (p->shell_moments) {
+                std::copy(hsums.begin() + L, hsums.begin() + 2 * L, st->h1.begin() + sa * L);
+                std::copy(hsums.begin() + 2 * L, hsums.begin() + 3 * L, st->h2.begin() + sa * L);
+            }
+        };
+
+        if (resident_run(h->op)) {
+            // Small clusters: the filter sequences of several (vector, anchor) pairs run
+            // side by side, one workgroup each; pass 2 in blocks of nb steps with the
+            // sequences' vectors carried over.
+            const size_t pairs = (size_t)st->nv * st->na, cplx = 2 * (size_t)dim;
+            const size_t group = std::min(pairs, std::max<size_t>(1, ctx->resident_bytes / (vbytes * (nb + 3))));
+            Arena m;
+            ResidentSeq *seq;
+            SeqState *state;
+            double *phib, *carry, *vbuf, *coef, *al_d, *be_d;
+            m.part(&seq, group);
+            m.part(&state, group);
+            m.part(&phib, group * cplx);
+            m.part(&carry, group * 2 * cplx);
+            m.part(&vbuf, group * nb * cplx);
+            m.part(&coef, group * 2 * st->L * n);
+            m.part(&al_d, group * n);
+            m.part(&be_d, group * n);
+            m.allocate(ctx);
+            std::vector<ResidentSeq> hseq(group);
+            std::vector<SeqState> hstate(group);
+            std::vector<double> hcoef(group * 2 * st->L * n), hal(group * n), hbe(group * n);
+            std::vector<std::vector<double>> al(group), be(group);
+            std::vector<int> steps(group);
+            for (size_t i = 0; i < group; ++i)
+                hseq[i] = ResidentSeq{(const double2 *)(phib + i * cplx), 0, (int)i, 0.0};
+            HIP_CHECK(hipMemcpyAsync(seq, hseq.data(), group * sizeof(ResidentSeq), hipMemcpyHostToDevice, s));
+            ResidentRun run{};
+            run.seq = seq;
+            run.st = state;
+            run.alpha = al_d;
+            run.beta = be_d;
+            run.stride = n;
+            run.tol = 1e-12 * h->table.norm_bound;
+            run.carry = carry;
+            int have = -1;  // the vector in phi0
+            for (size_t g0 = 0; g0 < pairs; g0 += group) {
+                const size_t cnt = std::min(group, pairs - g0);
+                for (size_t i = 0; i < cnt; ++i) {
+                    const int sv = (int)((g0 + i) / st->na), a = (int)((g0 + i) % st->na);
+                    if (sv != have) start_vector(sv);
+                    have = sv;
+                    st->log_norm[g0 + i] = imaginary_time(a, phib + i * cplx);
+                }
+                run.k0 = 0;
+                run.k1 = n;
+                run.vout = nullptr;
+                ctx->timed("filter_run", true, [&] { launch_resident(h->op, run, (int)cnt, s); });
+                HIP_CHECK(hipMemcpyAsync(hstate.data(), state, cnt * sizeof(SeqState), hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipMemcpyAsync(hal.data(), al_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipMemcpyAsync(hbe.data(), be_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipStreamSynchronize(s));
+                int most = 0;
+                std::vector<DevBuf> shells;
+                for (size_t i = 0; i < cnt; ++i) {
+                    const int sv = (int)((g0 + i) / st->na), a = (int)((g0 + i) % st->na);
+                    al[i].assign(hal.begin() + i * n, hal.begin() + i * n + hstate[i].steps);
+                    be[i].assign(hbe.begin() + i * n, hbe.begin() + i * n + hstate[i].steps);
+                    steps[i] = shell_setup(sv, a, hstate[i], al[i], be[i], hcoef.data() + i * 2 * st->L * n);
+                    most = std::max(most, steps[i]);
+                    shells.emplace_back(ctx, vbytes * st->L);
+                    HIP_CHECK(hipMemsetAsync(shells[i].p, 0, vbytes * st->L, s));
+                }
+                HIP_CHECK(hipMemcpyAsync(coef, hcoef.data(), sizeof(double) * cnt * 2 * st->L * n, hipMemcpyHostToDevice, s));
+                run.vout = vbuf;
+                run.vstride = nb * cplx;
+                for (int k0 = 0; k0 < most; k0 += nb) {
+                    run.k0 = k0;
+                    run.k1 = std::min(most, k0 + nb);
+                    ctx->timed("filter_run", true, [&] { launch_resident(h->op, run, (int)cnt, s); });
+                    for (size_t i = 0; i < cnt; ++i)
+                        if (steps[i] > k0)
+                            launch_accumulate(dim, vbuf + i * nb * cplx, std::min(nb, steps[i] - k0),
+                                              coef + i * 2 * st->L * n, steps[i], k0, shells[i].d(), st->L, s);
+                }
+                HIP_CHECK(hipMemcpyAsync(hal.data(), al_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
+                for (size_t i = 0; i < cnt; ++i) {
+                    shell_sums(g0 + i, shells[i], carry);
+                    check_regenerated(hal.data() + i * n, al[i]);
+                    st->phi.push_back(std::move(shells[i]));
+                }
+            }
+        } else {
+            DevBuf phib(ctx, vbytes), W0(ctx, vbytes), W1(ctx, vbytes), Vbuf(ctx, vbytes * nb);
+            DevBuf coef(ctx, sizeof(double) * 2 * (size_t)st->L * n);
+            std::vector<double> hcoef((size_t)2 * st->L * n);
+            for (int sv = 0; sv < st->nv; ++sv) {
+                start_vector(sv);
+                for (int a = 0; a < st->na; ++a) {
+                    const size_t sa = (size_t)sv * st->na + a;
+                    st->log_norm[sa] = imaginary_time(a, phib.d());
+
+                    // pass 1: Lanczos coefficients of phi_beta
+                    auto noflush = [](int, int) {};
+                    kr.run(0, phib.d(), W0.d(), W1.d(), n, 0.0, nullptr, nullptr, 0, 0.0, nullptr, 0, noflush);
+                    const SeqState q1 = kr.read_state(0);
+                    std::vector<double> al(q1.steps), be(q1.steps);
+                    HIP_CHECK(hipMemcpyAsync(al.data(), kr.al(0), sizeof(double) * q1.steps, hipMemcpyDeviceToHost, s));
+                    HIP_CHECK(hipMemcpyAsync(be.data(), kr.be(0), sizeof(double) * q1.steps, hipMemcpyDeviceToHost, s));
+                    HIP_CHECK(hipStreamSynchronize(s));
+                    const int steps = shell_setup(sv, a, q1, al, be, hcoef.data());
+                    HIP_CHECK(hipMemcpyAsync(coef.p, hcoef.data(), sizeof(double) * 2 * st->L * steps,
+                                             hipMemcpyHostToDevice, s));
+
+                    // pass 2: regenerate v_k and accumulate phi^m = sum_k c^m_k v_k
+                    DevBuf shells(ctx, vbytes * st->L);
+                    HIP_CHECK(hipMemsetAsync(shells.p, 0, vbytes * st->L, s));
+                    auto flush = [&](int k0, int cnt) {
+                        launch_accumulate(dim, Vbuf.d(), cnt, coef.d(), steps, k0, shells.d(), st->L, s);
+                    };
+                    kr.run(0, phib.d(), W0.d(), W1.d(), steps, 0.0, nullptr, nullptr, 0, 0.0, Vbuf.d(), nb, flush);
+                    std::vector<double> al2(steps);
+                    HIP_CHECK(hipMemcpyAsync(al2.data(), kr.al(0), sizeof(double) * steps, hipMemcpyDeviceToHost, s));
+                    shell_sums(sa, shells, W0.d());  // the first Lanczos buffer is free now
+                    check_regenerated(al2.data(), al);
+                    st->phi.push_back(std::move(shells));
+                }
             }
         }
         HIP_CHECK(hipGetLastError());
@@ -1404,10 +1554,6 @@ struct GreenOut {
     std::vector<SeqState> states;     // [nseq]
 };
 
-// Sequences of op run one per workgroup, whole (resident.h), unless a tuning key
-// asks for another form
-bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
-
 // What run_green makes start vectors from: spin operators sq[tag], or pairs a, b
 // with tag = 4 pair + polarization.
 struct StartOps {
@@ -1434,28 +1580,6 @@ void resolve_layout(const ftk_hamiltonian *h, int rhs_block, int n_omega, int &B
         need(BatchRunner::stack_for(h, B, stack < 0 ? -1 : stack),
              "rhs_block 32 runs only as a stack of multi-pass sequences (N >= 16, stack_batch not 0, no plain loop)");
 }
-
-// Several buffers of one call in one device allocation.
-struct Arena {
-    std::vector<std::pair<void **, size_t>> parts;
-    DevBuf mem;
-    template <class T>
-    void part(T **p, size_t n)
-    {
-        parts.push_back({(void **)p, (n * sizeof(T) + 255) / 256 * 256});
-    }
-    void allocate(ftk_ctx *ctx)
-    {
-        size_t total = 0;
-        for (auto &q : parts) total += q.second;
-        mem = DevBuf(ctx, total);
-        char *at = (char *)mem.p;
-        for (auto &q : parts) {
-            *q.first = at;
-            at += q.second;
-        }
-    }
-};
 
 // Steps between two residual tests of a truncated resident run.
 constexpr int kResidentCheck = 16;

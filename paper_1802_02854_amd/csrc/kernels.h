@@ -215,8 +215,8 @@ void launch_dot(uint32_t dim, const double *a, const double *b, double *partials
 // st->norm2 = sum, norm = sqrt, inv_cur = 1/norm; resets the rest of the state
 void launch_start_sequence(SeqState *st, const double *partials, int nparts, double shift_re,
                            hipStream_t s);
-// result[0] = rounded sum of partials
-void launch_sum_partials(const double *partials, int nparts, double *result, hipStream_t s);
+// result[r] = rounded sum of the partials of r < B (2*nparts apart)
+void launch_sum_partials(const double *partials, int nparts, double *result, hipStream_t s, int B = 1);
 
 // chi = S^alpha_{+Q} phi; h = e^{iQ.R_l}/(2 sqrt N) per site (interleaved, n_sites entries)
 struct SqParams {

@@ -1184,8 +1184,8 @@ __global__ void __launch_bounds__(kBlock) k_start_sequence(SeqState *st, const d
 
 __global__ void __launch_bounds__(kBlock) k_sum_partials(const double *partials, int nparts, double *result)
 {
-    const double s = reduce_partials(partials, nparts);
-    if (threadIdx.x == 0) result[0] = s;
+    const double s = reduce_partials(partials + (size_t)blockIdx.x * 2 * nparts, nparts);
+    if (threadIdx.x == 0) result[blockIdx.x] = s;
 }
 
 void launch_dot(uint32_t dim, const double *a, const double *b, double *partials, hipStream_t s, int B, size_t vs)
@@ -1209,9 +1209,9 @@ void launch_start_stacked(int B, uint32_t dim, const double *chi, double *partia
     hipLaunchKernelGGL(k_start_sequence, dim3(B), dim3(kBlock), 0, s, st, partials, vec_grid(dim), shifts);
 }
 
-void launch_sum_partials(const double *partials, int nparts, double *result, hipStream_t s)
+void launch_sum_partials(const double *partials, int nparts, double *result, hipStream_t s, int B)
 {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, s, partials, nparts, result);
+    hipLaunchKernelGGL(k_sum_partials, dim3(B), dim3(kBlock), 0, s, partials, nparts, result);
 }
 
 // ---------------------------------------------------------------------------

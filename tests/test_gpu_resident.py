@@ -92,3 +92,22 @@ def test_resident_breakdown_and_many_shifts(env):
     for (al, be), (al2, be2) in zip(a[1], b[1]):
         assert np.array_equal(al, al2) and np.array_equal(be, be2)
     assert np.array_equal(a[0][0], b[0][0]) and np.array_equal(a[0][1], b[0][1])
+
+
+@pytest.mark.parametrize("N,nb", [(6, 0), (9, 5), (12, 1), (13, 7), (14, 64)])
+def test_resident_filter_runs_match_per_step(env, N, nb):
+    """Filtered states of several vectors and anchors (blocks of pass 2 of every size, shell
+    moments, per-shell truncation) from the resident filter runs and the per-step ones."""
+    ftk, ctx, torch = env
+    print(f"resident filter N={N} nb={nb}", flush=True)
+    h = ftk.Hamiltonian(ctx, _ring(ftk, N), -1.0, 0.07)
+    n = 23
+    for tol in (0.0, 0.5):
+        def states():
+            st = ftk.TypicalStates(h, seed=5, n_vectors=2, betas=[0.0, 0.4, 1.5], E_b=None, eps=None, L=11, M=4, n_steps=n,
+                                   block_steps=nb, shell_moments=True, resid_tol=tol)
+            return [*st.scalars(), *st.moments(), *st.window(),
+                    *[x for s in range(2) for a in range(3) for x in st.lanczos(s, a)],
+                    *[st.shell(s, a, m).cpu().numpy() for s in range(2) for a in range(3) for m in (0, 5, 10)]]
+        for x, y in zip(*_both(ftk, states)):
+            assert np.array_equal(x, y)
