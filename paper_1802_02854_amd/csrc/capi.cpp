@@ -220,18 +220,20 @@ struct Krylov {
     uint32_t dim;
     int nparts;
     int nparts_hv;
-    DevBuf partials, partials_b, state, alpha, beta, scalar;  // partials_b: norms of fused steps
+    DevBuf partials, partials_b, state;  // partials_b: norms of fused steps
+    int n_st, slot = 0;                  // sequences; which of their two states is current
+    DevBuf alpha, beta, scalar;
     int n_max;
     Krylov(const ftk_hamiltonian *H, int n_steps_max, int n_states)
         : h(H), ctx(H->ctx), s(H->ctx->stream), dim(H->dim), nparts(vec_grid(H->dim)), nparts_hv(hv_grid(H->op)),
           partials(H->ctx, sizeof(double) * 2 * kMaxGrid * 16), partials_b(H->ctx, sizeof(double) * 2 * kMaxGrid * 16),
-          state(H->ctx, sizeof(SeqState) * (size_t)std::max(1, n_states)),
+          state(H->ctx, sizeof(SeqState) * 2 * (size_t)std::max(1, n_states)), n_st(std::max(1, n_states)),
           alpha(H->ctx, sizeof(double) * (size_t)std::max(1, n_steps_max) * std::max(1, n_states)),
           beta(H->ctx, sizeof(double) * (size_t)std::max(1, n_steps_max) * std::max(1, n_states)),
           scalar(H->ctx, sizeof(double) * 8), n_max(n_steps_max)
     {
     }
-    SeqState *st(int i) const { return (SeqState *)state.p + i; }
+    SeqState *st(int i) const { return (SeqState *)state.p + slot * n_st + i; }
     double *al(int i) const { return alpha.d() + (size_t)i * n_max; }
     double *be(int i) const { return beta.d() + (size_t)i * n_max; }
 
@@ -265,14 +267,13 @@ struct Krylov {
 
     // n Lanczos steps of sequence i started from `start` (w_{-1}); buffers W0, W1
     // alternate; Vbuf (optional) receives v_k for k in [k0, k0 + nb) and the
-    // callback flushes it; shifts (optional) get the per-step update.
+    // callback flushes it.
     template <class Flush>
-    void run(int i, const double *start, double *W0, double *W1, int n, double shift_re,
-             ShiftState *shifts, const double *omega, int n_omega, double eta, double *Vbuf,
-             int nb, Flush &&flush)
+    void run(int i, const double *start, double *W0, double *W1, int n, double *Vbuf, int nb, Flush &&flush)
     {
+        slot = 0;
         launch_dot(dim, start, start, partials.d(), s);
-        launch_start_sequence(st(i), partials.d(), nparts, shift_re, s);
+        launch_start_sequence(st(i), partials.d(), nparts, 0.0, s);
         const double tol = 1e-12 * h->table.norm_bound;
         double *W[2] = {W0, W1};
         const bool fuse = lanczos_fusable(h->op) && !g_plain_loop;
@@ -289,23 +290,26 @@ struct Krylov {
                 if (fuse && k > 0) {
                     // second half of step k-1 inside the first pass of step k (which also
                     // finalises alpha_{k-1}); its beta finalisation rides in the middle pass
-                    // when there is one.  alpha partials in pa, norm partials in pb.
+                    // when there is one, else in the last.  alpha partials in pa, norm
+                    // partials in pb.
                     const FinAlpha fa{pa, nparts_hv, al(i), 0, k - 1};
                     launch_lanczos_fused_first(h->op, W[(k - 1) % 2], prv, st(i), pb, s, Stack(),
                                                fa_on ? &fa : nullptr);
-                    const FinBeta fb{st(i), pb, nparts_hv, be(i), k - 1, tol, shifts, omega, n_omega, eta, 0.0, 0};
-                    const bool mid = beta_in_middle_pass(h->op);
-                    if (!mid)
-                        launch_finalize_beta(st(i), pb, nparts_hv, be(i), k - 1, tol, shifts, omega, n_omega, eta, s);
-                    launch_lanczos_a_rest(h->op, cur, prv, out, vout, st(i), pa, s, Stack(), mid ? &fb : nullptr);
+                    const FinBeta fb{st(i), pb, nparts_hv, be(i), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, 0};
+                    const bool mid = beta_in_middle_pass(h->op), last = beta_in_last_pass(h->op);
+                    if (!mid && !last)
+                        launch_finalize_beta(st(i), pb, nparts_hv, be(i), k - 1, tol, nullptr, nullptr, 0, 0.0, s);
+                    SeqState *now = st(i);
+                    if (last) slot ^= 1;
+                    launch_lanczos_a_rest(h->op, cur, prv, out, vout, now, pa, s, Stack(), mid || last ? &fb : nullptr,
+                                          last ? st(i) : nullptr);
                     if (!fa_on) launch_finalize_alpha(st(i), pa, nparts_hv, al(i), k, s);
                 } else {
                     launch_lanczos_a(h->op, cur, prv, out, vout, st(i), partials.d(), k == 0, s);
                     if (!(fuse && fa_on)) launch_finalize_alpha(st(i), partials.d(), nparts_hv, al(i), k, s);
                     if (!fuse) {
                         launch_lanczos_b(dim, cur, out, st(i), partials.d(), s);
-                        launch_finalize_beta(st(i), partials.d(), nparts, be(i), k, tol, shifts, omega, n_omega, eta,
-                                             s);
+                        launch_finalize_beta(st(i), partials.d(), nparts, be(i), k, tol, nullptr, nullptr, 0, 0.0, s);
                     }
                 }
             });
@@ -319,7 +323,7 @@ struct Krylov {
             if (fa_on) launch_finalize_alpha(st(i), pa, nparts_hv, al(i), n - 1, s);
             const double *cur = n == 1 ? start : W[(n - 2) % 2];
             launch_lanczos_b(dim, cur, W[(n - 1) % 2], st(i), partials.d(), s);
-            launch_finalize_beta(st(i), partials.d(), nparts, be(i), n - 1, tol, shifts, omega, n_omega, eta, s);
+            launch_finalize_beta(st(i), partials.d(), nparts, be(i), n - 1, tol, nullptr, nullptr, 0, 0.0, s);
         }
     }
 
@@ -1063,7 +1067,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
 
                     // pass 1: Lanczos coefficients of phi_beta
                     auto noflush = [](int, int) {};
-                    kr.run(0, phib.d(), W0.d(), W1.d(), n, 0.0, nullptr, nullptr, 0, 0.0, nullptr, 0, noflush);
+                    kr.run(0, phib.d(), W0.d(), W1.d(), n, nullptr, 0, noflush);
                     const SeqState q1 = kr.read_state(0);
                     std::vector<double> al(q1.steps), be(q1.steps);
                     HIP_CHECK(hipMemcpyAsync(al.data(), kr.al(0), sizeof(double) * q1.steps, hipMemcpyDeviceToHost, s));
@@ -1079,7 +1083,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     auto flush = [&](int k0, int cnt) {
                         launch_accumulate(dim, Vbuf.d(), cnt, coef.d(), steps, k0, shells.d(), st->L, s);
                     };
-                    kr.run(0, phib.d(), W0.d(), W1.d(), steps, 0.0, nullptr, nullptr, 0, 0.0, Vbuf.d(), nb, flush);
+                    kr.run(0, phib.d(), W0.d(), W1.d(), steps, Vbuf.d(), nb, flush);
                     std::vector<double> al2(steps);
                     HIP_CHECK(hipMemcpyAsync(al2.data(), kr.al(0), sizeof(double) * steps, hipMemcpyDeviceToHost, s));
                     shell_sums(sa, shells, W0.d());  // the first Lanczos buffer is free now
@@ -1175,11 +1179,14 @@ struct BatchRunner {
     bool stacked;           // B > 1 as a stack of multi-pass sequences
     int nparts_a, nparts_b;
     bool fuse;  // multi-pass H v: halves of consecutive steps fused
+    bool late;  // the multi-shift update once per finished sequence, not every step
+    int slot = 0;  // which of the sequences' two states is current
     DevBuf chi, W0, W1, st, al, be, shifts, omega, partials, partials_b, part;  // partials_b: norms of fused steps
     Stack sk;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool capturing = false;
+    int end_slot = 0;  // the current state after the captured steps
 
     static bool stack_for(const ftk_hamiltonian *H, int B_, int stack)
     {
@@ -1201,11 +1208,11 @@ struct BatchRunner {
           eta(eta_), tol(1e-12 * H->table.norm_bound), rtol(rtol_), stacked(stack_for(H, B_, stack)),
           nparts_a(B_ == 1 ? hv_grid(op) : (stacked ? hv_grid(op, B_) : hv_batch_grid(H->dim, B_))),
           nparts_b(B_ == 1 || stacked ? vec_grid(H->dim) : vec_batch_grid(H->dim, B_)),
-          fuse(stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop)),
+          fuse(stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop)), late(rtol_ == 0.0 && !g_plain_loop),
           chi(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), W0(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_),
-          W1(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), st(H->ctx, sizeof(SeqState) * B_),
+          W1(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), st(H->ctx, sizeof(SeqState) * 2 * B_),
           al(H->ctx, sizeof(double) * (size_t)n_ * B_), be(H->ctx, sizeof(double) * (size_t)n_ * B_),
-          shifts(H->ctx, sizeof(ShiftState) * (size_t)nw_ * B_), omega(H->ctx, sizeof(double) * nw_),
+          shifts(H->ctx, late ? sizeof(double) : sizeof(ShiftState) * (size_t)nw_ * B_), omega(H->ctx, sizeof(double) * nw_),
           partials(H->ctx, sizeof(double) * 2 * (size_t)kMaxGrid * B_),
           partials_b(H->ctx, fuse ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
           part(H->ctx, stacked ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
@@ -1224,7 +1231,7 @@ struct BatchRunner {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
-    SeqState *states() const { return (SeqState *)st.p; }
+    SeqState *states() const { return (SeqState *)st.p + slot * B; }
 
     // right-hand side r = S^alpha_Q phi in the runner's layout
     void load_rhs(const SqParams &P, const double *phi, int r)
@@ -1246,6 +1253,7 @@ struct BatchRunner {
 
     void start(const BatchShifts &sh)
     {
+        slot = 0;
         if (B == 1) {
             launch_dot(dim, chi.d(), chi.d(), partials.d(), s);
             launch_start_sequence(states(), partials.d(), nparts_b, sh.re[0], s);
@@ -1263,36 +1271,40 @@ struct BatchRunner {
         const double *prv = k == 1 ? chi.d() : W[k % 2];
         double *out = W[k % 2];
         SeqState *q = states();
-        ShiftState *sh = (ShiftState *)shifts.p;
+        ShiftState *sh = late ? nullptr : (ShiftState *)shifts.p;
+        const int nsh = late ? 0 : nw;
         // per-step events only outside graph capture (a captured graph is timed as a whole)
         ctx->timed("lanczos_step", !capturing && (k & 7) == 1, [&] {
             if (B > 1 && !stacked) {
                 launch_lanczos_a_batch(B, op.P, cur, prv, out, q, partials.d(), k == 0, s);
                 launch_finalize_alpha_batch(B, q, partials.d(), nparts_a, al.d(), n, k, s);
                 launch_lanczos_b_batch(B, dim, cur, out, q, partials.d(), s);
-                launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nw, eta,
+                launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nsh, eta,
                                            s, rtol);
             } else if (fuse && k > 0) {
                 // second half of step k-1 inside the first pass of step k (which also
                 // finalises alpha_{k-1}); its beta finalisation rides in the middle pass
-                // when there is one.  alpha partials in pa, norm partials in pb.
+                // when there is one, else in the last (without a residual test).  alpha
+                // partials in pa, norm partials in pb.
                 const bool fa_on = alpha_in_fused_pass();
                 double *pa = partials.d(), *pb = fa_on ? partials_b.d() : partials.d();
                 const FinAlpha fa{pa, nparts_a, al.d(), n, k - 1};
                 launch_lanczos_fused_first(op, W[(k - 1) % 2], prv, q, pb, s, sk, fa_on ? &fa : nullptr);
-                const FinBeta fb{q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nw, eta, rtol, n};
-                const bool mid = beta_in_middle_pass(op);
-                if (!mid)
-                    launch_finalize_beta(q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nw, eta, s, rtol, B, n);
-                launch_lanczos_a_rest(op, cur, prv, out, nullptr, q, pa, s, sk, mid ? &fb : nullptr);
-                if (!fa_on) launch_finalize_alpha(q, pa, nparts_a, al.d(), k, s, B, n);
+                const FinBeta fb{q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nsh, eta, rtol, n};
+                const bool mid = beta_in_middle_pass(op), last = late && beta_in_last_pass(op);
+                if (!mid && !last)
+                    launch_finalize_beta(q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nsh, eta, s, rtol, B, n);
+                if (last) slot ^= 1;
+                launch_lanczos_a_rest(op, cur, prv, out, nullptr, q, pa, s, sk, mid || last ? &fb : nullptr,
+                                      last ? states() : nullptr);
+                if (!fa_on) launch_finalize_alpha(states(), pa, nparts_a, al.d(), k, s, B, n);
             } else {
                 launch_lanczos_a(op, cur, prv, out, nullptr, q, partials.d(), k == 0, s, sk);
                 if (!(fuse && alpha_in_fused_pass()))
                     launch_finalize_alpha(q, partials.d(), nparts_a, al.d(), k, s, B, n);
                 if (!fuse) {
                     launch_lanczos_b(dim, cur, out, q, partials.d(), s);
-                    launch_finalize_beta(q, partials.d(), nparts_b, be.d(), k, tol, sh, omega.d(), nw, eta, s, rtol);
+                    launch_finalize_beta(q, partials.d(), nparts_b, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol);
                 }
             }
         });
@@ -1306,8 +1318,17 @@ struct BatchRunner {
         double *W[2] = {W0.d(), W1.d()};
         const double *cur = n == 1 ? chi.d() : W[(n - 2) % 2];
         launch_lanczos_b(dim, cur, W[(n - 1) % 2], states(), partials.d(), s, B, sk.vs);
-        launch_finalize_beta(states(), partials.d(), nparts_b, be.d(), n - 1, tol, (ShiftState *)shifts.p, omega.d(),
-                             nw, eta, s, rtol, B, n);
+        launch_finalize_beta(states(), partials.d(), nparts_b, be.d(), n - 1, tol,
+                             late ? nullptr : (ShiftState *)shifts.p, omega.d(), late ? 0 : nw, eta, s, rtol, B, n);
+    }
+
+    // g [cnt][n_omega] of the first cnt sequences, after run()
+    void read_green(int cnt, double *g)
+    {
+        if (late)
+            launch_shifts(ShiftRun{states(), al.d(), be.d(), n, omega.d(), nw, eta, g}, cnt, s);
+        else
+            launch_finish_green(states(), (const ShiftState *)shifts.p, nw, g, s, cnt);
     }
 
     void run()
@@ -1325,6 +1346,7 @@ struct BatchRunner {
         }
         if (g_use_graphs) {
             if (!exec) {
+                slot = 0;
                 capturing = true;
                 HIP_CHECK(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
                 for (int k = 0; k < n; ++k) step(k);
@@ -1332,7 +1354,9 @@ struct BatchRunner {
                 HIP_CHECK(hipStreamEndCapture(s, &graph));
                 capturing = false;
                 HIP_CHECK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+                end_slot = slot;
             }
+            slot = end_slot;
             // the whole n-step loop of the batch: B sequences x n steps
             ctx->timed("lanczos_block", true, [&] { HIP_CHECK(hipGraphLaunch(exec, s)); });
         } else {
@@ -1488,6 +1512,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
     // hint set hn (-1: by working set)
     auto time_it = [&](int B, int stk, int pg, int hn) {
         BatchRunner run(h, B, nt, omega.data(), n_omega, 0.01, 0.0, stk, pg, hn);
+        DevBuf gout(h->ctx, sizeof(double) * 2 * (size_t)n_omega * B);
         for (int r = 0; r < B; ++r) {
             launch_gaussian(h->dim, 7, r, g.d(), s);
             run.load_rhs(P, g.d(), r);
@@ -1500,6 +1525,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
             HIP_CHECK(hipStreamSynchronize(s));
             auto t0 = std::chrono::steady_clock::now();
             run.run();
+            run.read_green(B, gout.d());
             HIP_CHECK(hipStreamSynchronize(s));
             auto t1 = std::chrono::steady_clock::now();
             if (rep > 0) secs = std::min(secs, std::chrono::duration<double>(t1 - t0).count());
@@ -1584,6 +1610,45 @@ void resolve_layout(const ftk_hamiltonian *h, int rhs_block, int n_omega, int &B
 // Steps between two residual tests of a truncated resident run.
 constexpr int kResidentCheck = 16;
 
+GreenOut empty_green(int nseq, int n, int nw)
+{
+    GreenOut out;
+    out.g.resize((size_t)nseq * nw * 2);
+    out.alpha.resize((size_t)nseq * n);
+    out.beta.resize((size_t)nseq * n);
+    out.states.resize(nseq);
+    return out;
+}
+
+// The device rows (one per item, in the items' order) brought to the outputs' rows
+// (the items' index); synchronises.
+GreenOut download_green(hipStream_t s, int nseq, int n, int nw, const std::vector<GreenItem> &work, const SeqState *st,
+                        const double *al, const double *be, const double *g)
+{
+    const size_t rows = work.size();
+    GreenOut out = empty_green(nseq, n, nw);
+    // every row to its index (the rows' order is the indices')
+    const bool all = (int)rows == nseq;
+    std::vector<double> hg(all ? 0 : rows * nw * 2), ha(all ? 0 : rows * n), hb(all ? 0 : rows * n);
+    std::vector<SeqState> hs(all ? 0 : rows);
+    auto down = [&](void *dst, const void *src, size_t bytes) {
+        HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+    };
+    down(all ? out.states.data() : hs.data(), st, sizeof(SeqState) * rows);
+    down(all ? out.g.data() : hg.data(), g, sizeof(double) * rows * nw * 2);
+    down(all ? out.alpha.data() : ha.data(), al, sizeof(double) * rows * n);
+    down(all ? out.beta.data() : hb.data(), be, sizeof(double) * rows * n);
+    HIP_CHECK(hipStreamSynchronize(s));
+    for (size_t i = 0; !all && i < rows; ++i) {
+        const size_t r = (size_t)work[i].index;
+        out.states[r] = hs[i];
+        std::copy(hg.begin() + i * nw * 2, hg.begin() + (i + 1) * nw * 2, out.g.begin() + r * nw * 2);
+        std::copy(ha.begin() + i * n, ha.begin() + (i + 1) * n, out.alpha.begin() + r * n);
+        std::copy(hb.begin() + i * n, hb.begin() + (i + 1) * n, out.beta.begin() + r * n);
+    }
+    return out;
+}
+
 // run_green for small clusters: every item is one workgroup that runs all n steps.
 // Device rows are the items' order; the outputs' rows their index.
 GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega, int nw, double eta, double rtol,
@@ -1592,12 +1657,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     ftk_ctx *ctx = h->ctx;
     hipStream_t s = ctx->stream;
     const size_t dim = h->dim, rows = work.size();
-    GreenOut out;
-    out.g.resize((size_t)nseq * nw * 2);
-    out.alpha.resize((size_t)nseq * n);
-    out.beta.resize((size_t)nseq * n);
-    out.states.resize(nseq);
-    if (rows == 0) return out;
+    if (rows == 0) return empty_green(nseq, n, nw);
     const bool stop = rtol > 0.0;
     const bool carried = stop || h->n_sites >= kResidentPlanes;
     const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
@@ -1663,26 +1723,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
         });
     }
     HIP_CHECK(hipGetLastError());
-    // every row to its index (the rows' order is the indices')
-    const bool all = (int)rows == nseq;
-    std::vector<double> hg(all ? 0 : rows * nw * 2), ha(all ? 0 : rows * n), hb(all ? 0 : rows * n);
-    std::vector<SeqState> hs(all ? 0 : rows);
-    auto down = [&](void *dst, const void *src, size_t bytes) {
-        HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
-    };
-    down(all ? out.states.data() : hs.data(), st, sizeof(SeqState) * rows);
-    down(all ? out.g.data() : hg.data(), g, sizeof(double) * rows * nw * 2);
-    down(all ? out.alpha.data() : ha.data(), al, sizeof(double) * rows * n);
-    down(all ? out.beta.data() : hb.data(), be, sizeof(double) * rows * n);
-    HIP_CHECK(hipStreamSynchronize(s));
-    for (size_t i = 0; !all && i < rows; ++i) {
-        const size_t r = (size_t)work[i].index;
-        out.states[r] = hs[i];
-        std::copy(hg.begin() + i * nw * 2, hg.begin() + (i + 1) * nw * 2, out.g.begin() + r * nw * 2);
-        std::copy(ha.begin() + i * n, ha.begin() + (i + 1) * n, out.alpha.begin() + r * n);
-        std::copy(hb.begin() + i * n, hb.begin() + (i + 1) * n, out.beta.begin() + r * n);
-    }
-    return out;
+    return download_green(s, nseq, n, nw, work, st, al, be, g);
 }
 
 void check_green(const GreenOut &out)
@@ -1705,51 +1746,36 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     }
     ftk_ctx *ctx = h->ctx;
     hipStream_t s = ctx->stream;
-    DevBuf gdev(ctx, sizeof(double) * 2 * (size_t)std::max(1, nseq) * nw);
-    DevBuf adev(ctx, sizeof(double) * (size_t)std::max(1, nseq) * n), bdev(ctx, sizeof(double) * (size_t)std::max(1, nseq) * n);
-    DevBuf sdev(ctx, sizeof(SeqState) * (size_t)std::max(1, nseq));
-    HIP_CHECK(hipMemsetAsync(gdev.p, 0, gdev.n, s));
-    HIP_CHECK(hipMemsetAsync(adev.p, 0, adev.n, s));
-    HIP_CHECK(hipMemsetAsync(bdev.p, 0, bdev.n, s));
-    HIP_CHECK(hipMemsetAsync(sdev.p, 0, sdev.n, s));
-    if (!work.empty()) {
-        const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
-        BatchRunner run(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints);
-        for (size_t w0 = 0; w0 < work.size(); w0 += B) {
-            const int cnt = (int)std::min<size_t>(B, work.size() - w0);
-            if (cnt < B) HIP_CHECK(hipMemsetAsync(run.chi.p, 0, run.chi.n, s));
-            BatchShifts bs;
-            for (int r = 0; r < kMaxBatch; ++r) bs.re[r] = 0.0;
-            for (int r = 0; r < cnt; ++r) {
-                load(run, r, work[w0 + r]);
-                bs.re[r] = work[w0 + r].Em;
-            }
-            run.start(bs);
-            run.run();
-            for (int r = 0; r < cnt; ++r) {
-                const GreenItem &q = work[w0 + r];
-                launch_finish_green(run.states() + r, (ShiftState *)run.shifts.p + (size_t)r * nw, nw,
-                                    gdev.d() + (size_t)q.index * 2 * nw, s);
-                HIP_CHECK(hipMemcpyAsync(adev.d() + (size_t)q.index * n, run.al.d() + (size_t)r * n,
-                                         sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-                HIP_CHECK(hipMemcpyAsync(bdev.d() + (size_t)q.index * n, run.be.d() + (size_t)r * n,
-                                         sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-                HIP_CHECK(hipMemcpyAsync((SeqState *)sdev.p + q.index, run.states() + r, sizeof(SeqState),
-                                         hipMemcpyDeviceToDevice, s));
-            }
+    const size_t rows = work.size();
+    if (rows == 0) return empty_green(nseq, n, nw);
+    Arena m;
+    double *g, *al, *be;
+    SeqState *st;
+    m.part(&st, rows);
+    m.part(&al, rows * n);
+    m.part(&be, rows * n);
+    m.part(&g, rows * nw * 2);
+    m.allocate(ctx);
+    const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
+    BatchRunner run(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints);
+    for (size_t w0 = 0; w0 < rows; w0 += B) {
+        const int cnt = (int)std::min<size_t>(B, rows - w0);
+        if (cnt < B) HIP_CHECK(hipMemsetAsync(run.chi.p, 0, run.chi.n, s));
+        BatchShifts bs;
+        for (int r = 0; r < kMaxBatch; ++r) bs.re[r] = 0.0;
+        for (int r = 0; r < cnt; ++r) {
+            load(run, r, work[w0 + r]);
+            bs.re[r] = work[w0 + r].Em;
         }
+        run.start(bs);
+        run.run();
+        run.read_green(cnt, g + w0 * 2 * nw);
+        HIP_CHECK(hipMemcpyAsync(al + w0 * n, run.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, s));
+        HIP_CHECK(hipMemcpyAsync(be + w0 * n, run.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, s));
+        HIP_CHECK(hipMemcpyAsync(st + w0, run.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, s));
     }
     HIP_CHECK(hipGetLastError());
-    GreenOut out;
-    out.g.resize((size_t)nseq * nw * 2);
-    out.alpha.resize((size_t)nseq * n);
-    out.beta.resize((size_t)nseq * n);
-    out.states.resize(nseq);
-    HIP_CHECK(hipMemcpyAsync(out.states.data(), sdev.p, sizeof(SeqState) * nseq, hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipMemcpyAsync(out.g.data(), gdev.p, sizeof(double) * out.g.size(), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipMemcpyAsync(out.alpha.data(), adev.p, sizeof(double) * out.alpha.size(), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipMemcpyAsync(out.beta.data(), bdev.p, sizeof(double) * out.beta.size(), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
+    GreenOut out = download_green(s, nseq, n, nw, work, st, al, be, g);
     check_green(out);
     return out;
 }

@@ -180,6 +180,9 @@ bool alpha_in_fused_pass();  // the fused first pass finalises the previous alph
 // more workgroup column of its first (middle) pass: plans of three or more passes;
 // the middle pass does not depend on beta, the last pass does
 bool beta_in_middle_pass(const HvOp &op);
+// true when its last pass can do that itself, given a second place for the sequences'
+// states (st_out): plans of two passes
+bool beta_in_last_pass(const HvOp &op);
 // a stack of B > 1 sequences (Stack) runs the multi-pass kernels whatever form
 // single vectors use; it needs a plan of at least two passes and the scratch vector
 bool lanczos_stackable(const HvOp &op);
@@ -187,7 +190,7 @@ void launch_lanczos_fused_first(const HvOp &op, double *W, const double *Wm2, Se
                                 hipStream_t s, const Stack &sk = Stack(), const FinAlpha *fa = nullptr);
 void launch_lanczos_a_rest(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
                            SeqState *st, double *partials, hipStream_t s, const Stack &sk = Stack(),
-                           const FinBeta *fb = nullptr);
+                           const FinBeta *fb = nullptr, SeqState *st_out = nullptr);
 // alpha_k = rounded sum of the partials; alpha[k] recorded.  B > 1: sequences
 // st[0..B), partials 2*nparts apart, alpha rows astride apart.
 void launch_finalize_alpha(SeqState *st, const double *partials, int nparts, double *alpha_out,
@@ -204,9 +207,9 @@ void launch_lanczos_b(uint32_t dim, const double *Wcur, double *U, SeqState *st,
 void launch_finalize_beta(SeqState *st, const double *partials, int nparts, double *beta_out,
                           int k, double tol, ShiftState *shifts, const double *omega, int n_omega,
                           double eta, hipStream_t s, double rtol = 0.0, int B = 1, int bstride = 0);
-// g = norm2 * G for every shift of a finished sequence (complex, interleaved).
+// g = norm2 * G for every shift of B finished sequences (complex, interleaved).
 void launch_finish_green(const SeqState *st, const ShiftState *shifts, int n_omega, double *g,
-                         hipStream_t s);
+                         hipStream_t s, int B = 1);
 
 // partial sums of Re<a|b> (a, b interleaved complex, dim entries); B > 1: B pairs
 // of vectors vs doubles apart, partials 2*vec_grid apart

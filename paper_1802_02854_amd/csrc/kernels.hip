@@ -643,8 +643,17 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeo
     const uint64_t pe6 = FIRST ? P.smask[g.esite[0]] : 0, pe7 = FIRST ? P.smask[g.esite[1]] : 0,
                    pe8 = FIRST ? P.smask[g.esite[2]] : 0;
     const int nz = __popcll(P.zmask);
-    if (!epi.active()) return;
-    if (LAST) epi.init();
+    bool begun = false;
+    if constexpr (LAST && Epi::kReduces) {
+        if (epi.fin == 2) {
+            if (!epi.template begin<kPassThreads>(blockIdx.y)) return;
+            begun = true;
+        }
+    }
+    if (!begun) {
+        if (!epi.active()) return;
+        if (LAST) epi.init();
+    }
     __shared__ SegLds seg;
     stage_segment(seg, P, g);
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gx) {
@@ -850,8 +859,8 @@ static void launch_passes_h(const HvOp &op, int p0, const double *v, Epi epi, hi
         Epi ep = epi;
         if constexpr (Epi::kReduces) {
             // a middle pass can carry the beta finalisation as one more column
-            ep.fin = (p == fin_pass && !first && !last) ? 1 : 0;
-            if (ep.fin) grid.x += 1;
+            ep.fin = (p == fin_pass && !first && !last) ? 1 : (last && ep.st_out) ? 2 : 0;
+            if (ep.fin == 1) grid.x += 1;
         }
         if (first && last)
             hipLaunchKernelGGL((k_hv_pass<Epi, true, true, SH>), grid, dim3(kPassThreads), lds, s, op.P, g,
@@ -923,8 +932,10 @@ struct EpiLanczosADev {
     double *partials;
     const SeqState *st;
     int first;
-    int fin;     // a middle pass also finalises beta of the previous half step (extra column)
+    int fin;     // 1: a middle pass also finalises beta of the previous half step (extra column)
+                 // 2: the last pass does, every workgroup for itself (begin)
     FinBeta fb;
+    SeqState *st_out;  // with fin 2: the state after that half step
     double inv, c1, hi, lo, err;
     __device__ void finalize_block(int r) const { finalize_beta_seq<kPassThreads>(fb, r); }
     // sequence r of a stacked batch: vectors vs entries apart, pstride partial doubles apart
@@ -934,6 +945,7 @@ struct EpiLanczosADev {
         U += r * vs;
         if (vout) vout += r * vs;
         st += r;
+        if (st_out) st_out += r;
         partials += (size_t)r * pstride;
     }
     __device__ bool active() const { return !st->done; }
@@ -942,6 +954,46 @@ struct EpiLanczosADev {
         inv = st->inv_cur;
         c1 = (-st->beta_cur) * st->inv_prev;
         hi = lo = err = 0.0;
+    }
+    // In place of active() and init() with fin 2: beta_k of the previous half step from
+    // its partial sums, in every workgroup of sequence r; workgroup 0 records it and
+    // writes the state to st_out (the others still read st).  A two-pass step is two
+    // launches this way instead of three, and no launch waits for the shift update,
+    // which runs once per finished sequence (16 sites, 72 sequences of 300 steps with
+    // 1000 shifts in stacks of 32: 55.7 -> 49.6 ms).
+    template <int BLOCK>
+    __device__ bool begin(int r)
+    {
+        const SeqState q = *st;
+        const bool record = blockIdx.x == 0 && threadIdx.x == 0;
+        if (q.done) {
+            if (record) *st_out = q;
+            return false;
+        }
+        __shared__ double s_bn;
+        const double ssum = reduce_partials<BLOCK>(fb.partials + (size_t)r * 2 * fb.nparts, fb.nparts);
+        if (threadIdx.x == 0) s_bn = sqrt(ssum);
+        __syncthreads();
+        const double bn = s_bn;
+        const bool ends = !(bn > fb.tol);  // invariant subspace
+        if (record) {
+            SeqState o = q;
+            fb.beta_out[(size_t)r * fb.bstride + fb.k] = bn;
+            o.steps = fb.k + 1;
+            if (!isfinite(bn)) o.numeric_error = 1;
+            if (ends) {
+                o.done = 1;
+            } else {
+                o.inv_prev = q.inv_cur;
+                o.inv_cur = 1.0 / bn;
+                o.beta_cur = bn;
+            }
+            *st_out = o;
+        }
+        inv = 1.0 / bn;
+        c1 = (-bn) * q.inv_cur;
+        hi = lo = err = 0.0;
+        return !ends;
     }
     __device__ double2 load(size_t x) const { return first ? make_double2(0.0, 0.0) : Wprev[x]; }
     __device__ void apply(size_t x, double re, double im, const double2 &wc, const double2 &wp)
@@ -973,6 +1025,7 @@ void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, d
     e.st = st;
     e.first = first_step;
     e.fin = 0;
+    e.st_out = nullptr;
     if (sk.B > 1 || sk.scratch)
         launch_passes(op, 0, Wcur, e, s, sk.B, sk.scratch, sk.vs);
     else
@@ -1002,9 +1055,11 @@ void launch_lanczos_fused_first(const HvOp &op, double *W, const double *Wm2, Se
 bool alpha_in_fused_pass() { return g_fuse_fin; }
 
 bool beta_in_middle_pass(const HvOp &op) { return g_fuse_fin && op.plan.n_passes >= 3; }
+bool beta_in_last_pass(const HvOp &op) { return g_fuse_fin && op.plan.n_passes == 2; }
 
 void launch_lanczos_a_rest(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
-                           SeqState *st, double *partials, hipStream_t s, const Stack &sk, const FinBeta *fb)
+                           SeqState *st, double *partials, hipStream_t s, const Stack &sk, const FinBeta *fb,
+                           SeqState *st_out)
 {
     EpiLanczosADev e;
     e.Wprev = (const double2 *)Wprev;
@@ -1014,8 +1069,9 @@ void launch_lanczos_a_rest(const HvOp &op, const double *Wcur, const double *Wpr
     e.st = st;
     e.first = 0;
     e.fin = 0;
+    e.st_out = st_out;
     if (fb) e.fb = *fb;
-    launch_passes(op, 1, Wcur, e, s, sk.B, sk.scratch, sk.vs, fb ? 1 : -1);
+    launch_passes(op, 1, Wcur, e, s, sk.B, sk.scratch, sk.vs, fb && !st_out ? 1 : -1);
 }
 
 __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double2 *__restrict__ Wcur,
@@ -1105,6 +1161,9 @@ __global__ void __launch_bounds__(kBlock) k_finalize_beta(FinBeta f) { finalize_
 
 __global__ void k_finish_green(const SeqState *st, const ShiftState *sh, int n_omega, double2 *g)
 {
+    st += blockIdx.y;
+    sh += (size_t)blockIdx.y * n_omega;
+    g += (size_t)blockIdx.y * n_omega;
     const double n2 = st->norm2;
     const bool any = st->steps > 0;
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n_omega; j += gridDim.x * blockDim.x) {
@@ -1135,10 +1194,10 @@ void launch_finalize_beta(SeqState *st, const double *partials, int nparts, doub
 }
 
 void launch_finish_green(const SeqState *st, const ShiftState *shifts, int n_omega, double *g,
-                         hipStream_t s)
+                         hipStream_t s, int B)
 {
     int grid = (n_omega + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_finish_green, dim3(grid < 1 ? 1 : grid), dim3(kBlock), 0, s, st, shifts, n_omega,
+    hipLaunchKernelGGL(k_finish_green, dim3(grid < 1 ? 1 : grid, B), dim3(kBlock), 0, s, st, shifts, n_omega,
                        (double2 *)g);
 }
 
