@@ -88,13 +88,11 @@ __device__ __forceinline__ void csqrt_s(double x, double y, double &r, double &i
 
 // up to 5 exact sums per block, (hi, lo) pairs in partials[(block * 5 + j) * 2]
 template <int NS>
-__device__ __forceinline__ void write_partials5(double *partials, double (&hi)[NS], double (&lo)[NS],
-                                                double (&err)[NS])
+__device__ __forceinline__ void write_partials5(double *partials, double (&hi)[NS], double (&lo)[NS])
 {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        dd_add(hi[j], lo[j], err[j]);
-        block_reduce_dd<kBlock>(hi[j], lo[j]);
+        block_pair<kBlock>(hi[j], lo[j]);
         if (threadIdx.x == 0) {
             partials[(blockIdx.x * 5 + j) * 2] = hi[j];
             partials[(blockIdx.x * 5 + j) * 2 + 1] = lo[j];
@@ -104,30 +102,29 @@ __device__ __forceinline__ void write_partials5(double *partials, double (&hi)[N
 }
 
 // sums over w of: Re w^T w = sum (w_r^2 - w_i^2), sum w_r w_i, <lam|w> (re, im), ||w||^2
-__device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &l, double (&hi)[5], double (&lo)[5],
-                                               double (&err)[5])
+__device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &l, double (&hi)[5], double (&lo)[5])
 {
-    acc_prod(hi[0], lo[0], err[0], w.x, w.x);
-    acc_prod(hi[0], lo[0], err[0], -w.y, w.y);
-    acc_prod(hi[1], lo[1], err[1], w.x, w.y);
-    acc_prod(hi[2], lo[2], err[2], l.x, w.x);
-    acc_prod(hi[2], lo[2], err[2], l.y, w.y);
-    acc_prod(hi[3], lo[3], err[3], l.x, w.y);
-    acc_prod(hi[3], lo[3], err[3], -l.y, w.x);
-    acc_prod(hi[4], lo[4], err[4], w.x, w.x);
-    acc_prod(hi[4], lo[4], err[4], w.y, w.y);
+    pair_prod(hi[0], lo[0], w.x, w.x);
+    pair_prod(hi[0], lo[0], -w.y, w.y);
+    pair_prod(hi[1], lo[1], w.x, w.y);
+    pair_prod(hi[2], lo[2], l.x, w.x);
+    pair_prod(hi[2], lo[2], l.y, w.y);
+    pair_prod(hi[3], lo[3], l.x, w.y);
+    pair_prod(hi[3], lo[3], -l.y, w.x);
+    pair_prod(hi[4], lo[4], w.x, w.x);
+    pair_prod(hi[4], lo[4], w.y, w.y);
 }
 
 __global__ void __launch_bounds__(kBlock) k_cocg_start_sums(uint32_t dim, const double2 *__restrict__ w,
                                                             const double2 *__restrict__ lam, double *partials)
 {
-    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0}, err[5] = {0, 0, 0, 0, 0};
+    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 v = w[x];
         const double2 l = lam[x];
-        cocg_norm_sums(v, l, hi, lo, err);
+        cocg_norm_sums(v, l, hi, lo);
     }
-    write_partials5<5>(partials, hi, lo, err);
+    write_partials5<5>(partials, hi, lo);
 }
 
 // u = (H w_{k-1}) inv_k + c1 w_{k-2} into U (U may be Wprev: each element is read
@@ -142,7 +139,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_a(uint32_t dim, const double2 *
     cmul_v(st->bkr, st->bki, st->ipr, st->ipi, c1r, c1i);
     c1r = -c1r;
     c1i = -c1i;
-    double hi[2] = {0, 0}, lo[2] = {0, 0}, err[2] = {0, 0};
+    double hi[2] = {0, 0}, lo[2] = {0, 0};
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 h = Hw[x];
         const double2 wc = Wcur[x];
@@ -155,12 +152,12 @@ __global__ void __launch_bounds__(kBlock) k_cocg_a(uint32_t dim, const double2 *
             ui = fma(c1r, wp.y, fma(c1i, wp.x, ti));
         }
         U[x] = make_double2(ur, ui);
-        acc_prod(hi[0], lo[0], err[0], wc.x, ur);
-        acc_prod(hi[0], lo[0], err[0], -wc.y, ui);
-        acc_prod(hi[1], lo[1], err[1], wc.x, ui);
-        acc_prod(hi[1], lo[1], err[1], wc.y, ur);
+        pair_prod(hi[0], lo[0], wc.x, ur);
+        pair_prod(hi[0], lo[0], -wc.y, ui);
+        pair_prod(hi[1], lo[1], wc.x, ui);
+        pair_prod(hi[1], lo[1], wc.y, ur);
     }
-    write_partials5<2>(partials, hi, lo, err);
+    write_partials5<2>(partials, hi, lo);
 }
 
 // w_k = u + c2 w_{k-1} over U (in place); partial sums of w_k^T w_k, <lam|w_k>, ||w_k||^2
@@ -171,7 +168,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
 {
     if (st->done) return;
     const double c2r = st->c2r, c2i = st->c2i;
-    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0}, err[5] = {0, 0, 0, 0, 0};
+    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = U[x];
         const double2 wc = Wcur[x];
@@ -180,9 +177,9 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
         const double wi = fma(c2r, wc.y, fma(c2i, wc.x, u.y));
         const double2 w = make_double2(wr, wi);
         U[x] = w;
-        cocg_norm_sums(w, l, hi, lo, err);
+        cocg_norm_sums(w, l, hi, lo);
     }
-    write_partials5<5>(partials, hi, lo, err);
+    write_partials5<5>(partials, hi, lo);
 }
 
 // rounded sum j of the 5-sum partials (thread 0)
@@ -190,8 +187,8 @@ __device__ __forceinline__ double reduce_sum5(const double *partials, int nparts
 {
     double hi = 0.0, lo = 0.0;
     for (int i = threadIdx.x; i < nparts; i += kBlock)
-        dd_add_dd(hi, lo, partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
-    block_reduce_dd<kBlock>(hi, lo);
+        pair_add(hi, lo, partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
+    block_pair<kBlock>(hi, lo);
     __syncthreads();
     return hi + lo;
 }

@@ -76,7 +76,7 @@ struct PassGeom {
     uint8_t ysite[9];                   // sites of tile bits 0..5 (lane) and 9..11 (wave)
     uint8_t esite[3];                   // sites of tile bits 6..8 (register element e)
     uint8_t hsite[kMaxSites];           // sites of the tile-index bits
-    uint8_t tbi[kMaxBonds], tbj[kMaxBonds];  // tile bit positions of the segment's bond ends
+    uint32_t code[kMaxBonds];           // of bond b0 + i: its flip mask in tile bits | bond type << 30
     uint8_t rev;                        // tiles in descending order (set per launch)
 };
 struct HvPlan {

@@ -23,6 +23,7 @@
 #include <cstring>
 #include <vector>
 
+#include "bond_ops.h"
 #include "exact_sum.h"
 #include "kernels.h"
 #include "shift_update.h"
@@ -115,8 +116,7 @@ HvPlan make_hv_plan(const BondTable &t)
                 g.ebit[e] = x;
             }
             for (int b = g.b0; b < g.b1; ++b) {
-                g.tbi[b] = (uint8_t)pos[t.bi[b]];
-                g.tbj[b] = (uint8_t)pos[t.bj[b]];
+                g.code[b - g.b0] = 1u << pos[t.bi[b]] | 1u << pos[t.bj[b]] | (uint32_t)t.gamma[b] << 30;
             }
             for (int j = 0; j < 3; ++j) g.esite[j] = (uint8_t)tsite[6 + j];
             // (tile index, lane, wave, e) -> x must be a bijection onto [0, 2^N)
@@ -127,7 +127,7 @@ HvPlan make_hv_plan(const BondTable &t)
             seen |= g.ebit[7];
             for (int j = 0; j < nh; ++j) ok = ok && !(seen >> g.hsite[j] & 1u), seen |= 1u << g.hsite[j];
             ok = ok && seen == (N == 32 ? ~0u : (1u << N) - 1u);
-            for (int b = g.b0; b < g.b1; ++b) ok = ok && g.tbi[b] < kPassBits && g.tbj[b] < kPassBits;
+            for (int b = g.b0; b < g.b1; ++b) ok = ok && pos[t.bi[b]] >= 0 && pos[t.bj[b]] >= 0;
             if (!ok) plan.n_passes = -1;
         }
         if (plan.n_passes < 0) continue;
@@ -343,25 +343,6 @@ __device__ __forceinline__ void hv_at(const HvParams &P, uint32_t x, const doubl
 // Blocked form: the 8 elements xb + 64 e (xb has bits 6..8 clear).
 constexpr int kRegShift = 6;
 
-// The bond constants of a pass segment (tile bit positions of both ends, the two
-// flip amplitudes), staged once per workgroup in LDS: the bond loop then reads LDS
-// only instead of kernel-argument memory behind waits on global memory.  Visible
-// to the loop after the first barrier of the tile loop.
-struct SegLds {
-    uint32_t pq[kMaxBonds];  // tbi | tbj << 8
-    double aa[kMaxBonds], ap[kMaxBonds];
-};
-__device__ __forceinline__ void stage_segment(SegLds &seg, const HvParams &P, const PassGeom &g)
-{
-    const int b = g.b0 + (int)threadIdx.x;
-    if (b < g.b1) {
-        const uint32_t bb = FTK_IDX(b, 0, kMaxBonds, 9);
-        seg.pq[bb] = (uint32_t)g.tbi[bb] | (uint32_t)g.tbj[bb] << 8;
-        seg.aa[bb] = P.aa[bb];
-        seg.ap[bb] = P.ap[bb];
-    }
-}
-
 template <int MR>
 __device__ __forceinline__ void bond_accum(double (&re)[kR], double (&im)[kR], const double2 (&pv)[kR],
                                            double ampA, double ampB)
@@ -371,43 +352,6 @@ __device__ __forceinline__ void bond_accum(double (&re)[kR], double (&im)[kR], c
         const double amp = (__builtin_popcount(e & MR) & 1) ? ampB : ampA;
         re[e] = fma(amp, pv[e ^ MR].x, re[e]);
         im[e] = fma(amp, pv[e ^ MR].y, im[e]);
-    }
-}
-
-// The same with partners read straight from the LDS tile (src = tile + (yb ^ mrest)):
-// the compiler interleaves the LDS reads with the fmas instead of holding all kR
-// partners in registers.
-template <int MR>
-__device__ __forceinline__ void bond_accum_lds(double (&re)[kR], double (&im)[kR], const double2 *src,
-                                               double ampA, double ampB)
-{
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-        const double amp = (__builtin_popcount(e & MR) & 1) ? ampB : ampA;
-        const double2 q = src[(e ^ MR) << kRegShift];
-        re[e] = fma(amp, q.x, re[e]);
-        im[e] = fma(amp, q.y, im[e]);
-    }
-}
-
-// The same for any register mask mr without a switch: the partner of element e is
-// tile[base ^ (e << kRegShift)] with base = yb ^ (the bond's full flip mask), and
-// element e takes ampB when e & mr has odd parity (bit e of sel).  One code path for
-// every bond, so the accumulators stay in their registers across the bond loop
-// (the eight switch cases merged their results through register copies).
-__device__ __forceinline__ void bond_accum_lds_flat(double (&re)[kR], double (&im)[kR], const double2 *tile,
-                                                    uint32_t base, uint32_t mr, double ampA, double ampB)
-{
-    uint32_t sel = 0;
-    if (mr & 1u) sel ^= 0xAAu;
-    if (mr & 2u) sel ^= 0xCCu;
-    if (mr & 4u) sel ^= 0xF0u;
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-        const double2 q = tile[base ^ ((uint32_t)e << kRegShift)];
-        const double amp = ((sel >> e) & 1u) ? ampB : ampA;
-        re[e] = fma(amp, q.x, re[e]);
-        im[e] = fma(amp, q.y, im[e]);
     }
 }
 
@@ -485,6 +429,9 @@ struct EpiApply {
     __device__ void select(int, size_t, int) {}
     __device__ bool active() const { return true; }
     __device__ void init() {}
+    __device__ void prepare(int) {}
+    template <int BLOCK>
+    __device__ bool begin(int) { return true; }
     __device__ double2 load(size_t) const { return make_double2(0.0, 0.0); }
     __device__ void apply(size_t x, double re, double im, const double2 &, const double2 &) { w[x] = make_double2(re, im); }
     __device__ void operator()(size_t x, double re, double im, const double2 &vx) { apply(x, re, im, vx, load(x)); }
@@ -500,6 +447,9 @@ struct EpiTaylor {
     __device__ void select(int, size_t, int) {}
     __device__ bool active() const { return true; }
     __device__ void init() {}
+    __device__ void prepare(int) {}
+    template <int BLOCK>
+    __device__ bool begin(int) { return true; }
     __device__ double2 load(size_t x) const { return acc[x]; }
     __device__ void apply(size_t x, double re, double im, const double2 &tx, const double2 &c)
     {
@@ -603,15 +553,65 @@ __global__ void __launch_bounds__(kTileThreads) k_hv_tiled(HvParams P, const dou
     epi.template finish<kTileThreads>();
 }
 
-// One pass of the multi-pass form over every tile of its site set.  A thread
-// owns the kR elements of tile index yb + 64 e (yb = lane | wave << 9); FIRST
-// starts from D v, otherwise from the partial sums in `part`; LAST hands the
-// finished (H v)[x] to the epilogue, otherwise the partial sums go back to `part`.
+// ---------------------------------------------------------------------------
+// Multi-pass form.  A thread owns the kR elements of tile index yb + 64 e
+// (yb = lane | wave << 9).  The tile is in LDS as two planes, real parts and
+// imaginary parts (8 B entries: bond16's reads), 64 KiB, two workgroups per compute unit.
+struct PassThread {
+    uint32_t yb;   // tile index of element 0
+    uint32_t xy;   // the thread's part of the state index
+    uint64_t par;  // bond parities of that part
+    __device__ PassThread(const HvParams &P, const PassGeom &g) : xy(0), par(0)
+    {
+        const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        yb = FTK_IDX(lane | (wave << 9), 7u << kRegShift, kPassTile, 7);
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+            if ((lane >> j) & 1u) xy |= 1u << g.ysite[j], par ^= P.smask[g.ysite[j]];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if ((wave >> j) & 1u) xy |= 1u << g.ysite[6 + j], par ^= P.smask[g.ysite[6 + j]];
+    }
+};
+
+// D(x) = K/4 s_z + J/4 s_all of a thread's elements, s = (bonds) - 2 (antiparallel bonds),
+// counted on the bond-parity vector: tile-index part, thread part, register-element part
+__device__ __forceinline__ void pass_diagonal(const HvParams &P, const PassGeom &g, uint64_t par, double (&D)[kR])
+{
+    const uint64_t pe6 = P.smask[g.esite[0]], pe7 = P.smask[g.esite[1]], pe8 = P.smask[g.esite[2]];
+    const int nz = __popcll(P.zmask);
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+        uint64_t pe = par;
+        if (e & 1) pe ^= pe6;
+        if (e & 2) pe ^= pe7;
+        if (e & 4) pe ^= pe8;
+        const int s_all = P.n_bonds - 2 * __popcll(pe);
+        const int s_z = nz - 2 * __popcll(pe & P.zmask);
+        D[e] = fma(P.kq, (double)s_z, P.jq * (double)s_all);
+    }
+}
+
+// the segment's bonds in list order on the thread's sums (real parts, imaginary parts)
+__device__ __forceinline__ void pass_bonds(double (&acc)[2 * kR], const Bonds &bonds, int n, uint32_t tile_at, uint32_t yb)
+{
+    for (int b = 0; b < n; ++b) {
+        const BondAt c = bonds.at(b);
+        const uint32_t t0 =
+            tile_at + FTK_IDX(yb ^ (c.m & ~(7u << kRegShift)), 7u << kRegShift, kPassTile, 8) * (uint32_t)sizeof(double);
+        bond16<(int)(sizeof(double) << kRegShift)>(acc, t0, t0 + kPassTile * (uint32_t)sizeof(double),
+                                                   (c.m >> kRegShift) & 7u, c.even, c.odd);
+    }
+}
+
+// One pass over every tile of its site set.  FIRST starts from D v, otherwise from the
+// partial sums in `part`; LAST hands the finished (H v)[x] to the epilogue, whose inputs
+// are read while the bonds run; otherwise the partial sums go back to `part`.
 template <class Epi, bool FIRST, bool LAST, bool SH>
 __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeom g, const double2 *__restrict__ v,
                                                          double2 *part, Epi epi, size_t vs)
 {
-    extern __shared__ double2 tile[];
+    extern __shared__ double planes[];
     // the tile workgroups are gx = gridDim.x columns; a middle pass of a Lanczos step
     // may carry one more column that finalises beta of the previous half step
     uint32_t gx = gridDim.x;
@@ -628,96 +628,70 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeo
     v += blockIdx.y * vs;
     part += blockIdx.y * vs;
     epi.select(blockIdx.y, vs, 2 * gx);
+    if (!epi.active()) return;
     const int hbits = P.n_sites - kPassBits;
     const uint32_t ntiles = 1u << hbits;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t yb = FTK_IDX(lane | (wave << 9), 7u << kRegShift, kPassTile, 7);
-    uint32_t xy = 0;
-    uint64_t pxy = 0;  // bond parities of the thread's base offset
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-        if ((lane >> j) & 1u) xy |= 1u << g.ysite[j], pxy ^= P.smask[g.ysite[j]];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-        if ((wave >> j) & 1u) xy |= 1u << g.ysite[6 + j], pxy ^= P.smask[g.ysite[6 + j]];
-    const uint64_t pe6 = FIRST ? P.smask[g.esite[0]] : 0, pe7 = FIRST ? P.smask[g.esite[1]] : 0,
-                   pe8 = FIRST ? P.smask[g.esite[2]] : 0;
-    const int nz = __popcll(P.zmask);
+    const PassThread t(P, g);
+    const Bonds bonds(P, g.code, g.b1 - g.b0, t.par >> g.b0);
+    const uint32_t tile_at = lds_address(planes);
+    double *re = planes + t.yb, *im = re + kPassTile;
+    if (LAST) epi.prepare(blockIdx.y);
     bool begun = false;
-    if constexpr (LAST && Epi::kReduces) {
-        if (epi.fin == 2) {
-            if (!epi.template begin<kPassThreads>(blockIdx.y)) return;
-            begun = true;
-        }
-    }
-    if (!begun) {
-        if (!epi.active()) return;
-        if (LAST) epi.init();
-    }
-    __shared__ SegLds seg;
-    stage_segment(seg, P, g);
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gx) {
-        const uint32_t t = g.rev ? ntiles - 1u - ti : ti;
+        const uint32_t tt = g.rev ? ntiles - 1u - ti : ti;
         uint32_t xh = 0;
-        for (int j = 0; j < hbits; ++j) xh |= ((t >> j) & 1u) << g.hsite[j];
-        const uint32_t xb = xh | xy;
-        double re[kR], im[kR];
-        __syncthreads();  // the previous tile is no longer read
-#pragma unroll
-        for (int e = 0; e < kR; ++e) {
-            const double2 o = ld_nt(&v[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
-            tile[yb + (e << kRegShift)] = o;
-            if (FIRST) {
-                re[e] = o.x;
-                im[e] = o.y;
-            } else {
-                const double2 q = ld_nt(&part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
-                re[e] = q.x;
-                im[e] = q.y;
+        uint64_t par = t.par;
+        for (int j = 0; j < hbits; ++j)
+            if ((tt >> j) & 1u) {
+                xh |= 1u << g.hsite[j];
+                if (FIRST) par ^= P.smask[g.hsite[j]];
             }
-        }
+        uint32_t xb = xh | t.xy;
+        double acc[2 * kR];
+        double2 o[kR];
+#pragma unroll
+        for (int e = 0; e < kR; ++e) o[e] = ld_nt(&v[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
         if (FIRST) {
-            // D(x) = K/4 s_z + J/4 s_all with s = (bonds) - 2 (antiparallel bonds), from
-            // the bond-parity vector: tile-index part, thread part, register-element part
-            uint64_t par = pxy;
-            for (int j = 0; j < hbits; ++j)
-                if ((t >> j) & 1u) par ^= P.smask[g.hsite[j]];
+            double D[kR];
+            pass_diagonal(P, g, par, D);
 #pragma unroll
             for (int e = 0; e < kR; ++e) {
-                uint64_t pe = par;
-                if (e & 1) pe ^= pe6;
-                if (e & 2) pe ^= pe7;
-                if (e & 4) pe ^= pe8;
-                const int s_all = P.n_bonds - 2 * __popcll(pe);
-                const int s_z = nz - 2 * __popcll(pe & P.zmask);
-                const double D = fma(P.kq, (double)s_z, P.jq * (double)s_all);
-                re[e] = D * re[e];
-                im[e] = D * im[e];
+                acc[e] = D[e] * o[e].x;
+                acc[kR + e] = D[e] * o[e].y;
             }
-        }
-        __syncthreads();
-        for (int b = g.b0; b < g.b1; ++b) {
-            const uint32_t pq = seg.pq[b];
-            const uint32_t pi = pq & 0xffu, pj = pq >> 8;
-            const uint32_t tm = (1u << pi) | (1u << pj);
-            const uint32_t mrest = tm & ~(7u << kRegShift);
-            const int mr = (tm >> kRegShift) & 7;
-            const bool anti = ((yb >> pi) ^ (yb >> pj)) & 1u;
-            const double aa = seg.aa[b], ap = seg.ap[b];
-            const double ampA = anti ? aa : ap;
-            const double ampB = anti ? ap : aa;
-            const uint32_t base = FTK_IDX(yb ^ mrest, 7u << kRegShift, kPassTile, 8) ^ ((uint32_t)mr << kRegShift);
-            bond_accum_lds_flat(re, im, tile, base, (uint32_t)mr, ampA, ampB);
-        }
-        if (LAST) {
-            double2 in[kR];
-#pragma unroll
-            for (int e = 0; e < kR; ++e) in[e] = epi.load(FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6));
-#pragma unroll
-            for (int e = 0; e < kR; ++e) epi.apply(FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6), re[e], im[e], tile[yb + (e << kRegShift)], in[e]);
         } else {
 #pragma unroll
-            for (int e = 0; e < kR; ++e) st_h<!SH>(&part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)], make_double2(re[e], im[e]));
+            for (int e = 0; e < kR; ++e) {
+                const double2 q = ld_nt(&part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
+                acc[e] = q.x;
+                acc[kR + e] = q.y;
+            }
+        }
+        lds_barrier();  // the previous tile is no longer read
+#pragma unroll
+        for (int e = 0; e < kR; ++e) {
+            re[e << kRegShift] = o[e].x;
+            im[e << kRegShift] = o[e].y;
+        }
+        double2 in[kR];
+        if (LAST) {
+#pragma unroll
+            for (int e = 0; e < kR; ++e) in[e] = epi.load(FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6));
+        }
+        lds_barrier();
+        pass_bonds(acc, bonds, g.b1 - g.b0, tile_at, t.yb);
+        asm volatile("" : "+v"(xb));  // addresses formed again, not kept over the bonds
+        if (LAST) {
+            if (!begun && !epi.template begin<kPassThreads>(blockIdx.y)) return;
+            begun = true;
+#pragma unroll
+            for (int e = 0; e < kR; ++e)
+                epi.apply(FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6), acc[e], acc[kR + e],
+                          make_double2(re[e << kRegShift], im[e << kRegShift]), in[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < kR; ++e)
+                st_h<!SH>(&part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)], make_double2(acc[e], acc[kR + e]));
         }
     }
     if (LAST) epi.template finish<kPassThreads>();
@@ -735,105 +709,87 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(HvParams P, P
                                                                   double *partials, size_t vs, FinAlpha fa,
                                                                   int use_fa)
 {
-    extern __shared__ double2 tile[];
+    extern __shared__ double planes[];
     W += blockIdx.y * vs;
     Wm2 += blockIdx.y * vs;
     part += blockIdx.y * vs;
     st += blockIdx.y;
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
     if (st->done) return;
-    double a;
-    if (use_fa) {
-        // alpha_{k-1} = inv_{k-1} <v_{k-1}|u_{k-1}>, as k_finalize_alpha forms it, in every
-        // workgroup; workgroup 0 records it
-        __shared__ double s_a;
-        const double d = reduce_partials<kPassThreads>(fa.partials + (size_t)blockIdx.y * 2 * fa.nparts, fa.nparts);
-        if (threadIdx.x == 0) {
-            s_a = st->inv_cur * d;
-            if (blockIdx.x == 0) {
-                if (!isfinite(s_a)) st->numeric_error = 1;
-                st->alpha_cur = s_a;
-                fa.alpha_out[(size_t)blockIdx.y * fa.astride + fa.k] = s_a;
-            }
-        }
-        __syncthreads();
-        a = s_a;
-    } else {
-        a = st->alpha_cur;
-    }
-    const double c2 = -(a * st->inv_cur);
+    const double inv = st->inv_cur;
+    double c2 = 0.0;
+    if (!use_fa) c2 = -(st->alpha_cur * inv);
+    // the thread's first partial of alpha_{k-1}, read during the setup below
+    const double *pa = fa.partials + (size_t)blockIdx.y * 2 * fa.nparts;
+    double ah = 0.0, al = 0.0;
+    if (use_fa && (int)threadIdx.x < fa.nparts) ah = pa[2 * threadIdx.x], al = pa[2 * threadIdx.x + 1];
     const int hbits = P.n_sites - kPassBits;
     const uint32_t ntiles = 1u << hbits;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t yb = FTK_IDX(lane | (wave << 9), 7u << kRegShift, kPassTile, 7);
-    uint32_t xy = 0;
-    uint64_t pxy = 0;
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-        if ((lane >> j) & 1u) xy |= 1u << g.ysite[j], pxy ^= P.smask[g.ysite[j]];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-        if ((wave >> j) & 1u) xy |= 1u << g.ysite[6 + j], pxy ^= P.smask[g.ysite[6 + j]];
-    const uint64_t pe6 = P.smask[g.esite[0]], pe7 = P.smask[g.esite[1]], pe8 = P.smask[g.esite[2]];
-    const int nz = __popcll(P.zmask);
-    __shared__ SegLds seg;
-    stage_segment(seg, P, g);
-    double hi = 0.0, lo = 0.0, err = 0.0;
+    const PassThread t(P, g);
+    const Bonds bonds(P, g.code, g.b1 - g.b0, t.par >> g.b0);
+    const uint32_t tile_at = lds_address(planes);
+    double *re = planes + t.yb, *im = re + kPassTile;
+    if (use_fa) {
+        // alpha_{k-1} = inv_{k-1} <v_{k-1}|u_{k-1}>, as k_finalize_alpha forms it, in
+        // every workgroup; workgroup 0 records it
+        for (int i = threadIdx.x + kPassThreads; i < fa.nparts; i += kPassThreads)
+            pair_add(ah, al, pa[2 * i], pa[2 * i + 1]);
+        block_pair<kPassThreads>(ah, al);
+        const double a = uniform(inv * (ah + al));
+        if (threadIdx.x == 0 && blockIdx.x == 0) {
+            if (!isfinite(a)) st->numeric_error = 1;
+            st->alpha_cur = a;
+            fa.alpha_out[(size_t)blockIdx.y * fa.astride + fa.k] = a;
+        }
+        c2 = -(a * inv);
+    }
+    double hi = 0.0, lo = 0.0;
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gridDim.x) {
-        const uint32_t t = g.rev ? ntiles - 1u - ti : ti;
+        const uint32_t tt = g.rev ? ntiles - 1u - ti : ti;
         uint32_t xh = 0;
-        uint64_t par = pxy;
+        uint64_t par = t.par;
         for (int j = 0; j < hbits; ++j)
-            if ((t >> j) & 1u) xh |= 1u << g.hsite[j], par ^= P.smask[g.hsite[j]];
-        const uint32_t xb = xh | xy;
-        __syncthreads();
+            if ((tt >> j) & 1u) xh |= 1u << g.hsite[j], par ^= P.smask[g.hsite[j]];
+        uint32_t xb = xh | t.xy;
         // w_{k-1} to the tile (W, Wm2 and part are distinct buffers).  No global store
-        // in this loop: on gfx950 loads and stores share one counter, so a store issued
-        // between two elements' loads would make the second element wait for it.
+        // among these loads: on gfx950 loads and stores share one counter, so a store
+        // issued between two elements' loads would make the second element wait for it.
+        double2 u[kR], wp[kR];
 #pragma unroll
         for (int e = 0; e < kR; ++e) {
-            const double2 u = ld_h<SH>(&W[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
-            const double2 wp = ld_h<SH>(&Wm2[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
-            const double wr = fma(c2, wp.x, u.x);
-            const double wi = fma(c2, wp.y, u.y);
-            tile[yb + (e << kRegShift)] = make_double2(wr, wi);
-            acc_prod(hi, lo, err, wr, wr);
-            acc_prod(hi, lo, err, wi, wi);
+            u[e] = ld_h<SH>(&W[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
+            wp[e] = ld_h<SH>(&Wm2[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)]);
+        }
+        double acc[2 * kR];
+        lds_barrier();  // the previous tile is no longer read
+#pragma unroll
+        for (int e = 0; e < kR; ++e) {
+            const double wr = fma(c2, wp[e].x, u[e].x);
+            const double wi = fma(c2, wp[e].y, u[e].y);
+            re[e << kRegShift] = wr;
+            im[e << kRegShift] = wi;
+            pair_prod(hi, lo, wr, wr);
+            pair_prod(hi, lo, wi, wi);
         }
         // w_{k-1} to global memory and D w, from the thread's own tile entries
-        double re[kR], im[kR];
+        asm volatile("" : "+v"(xb)::"memory");  // addresses formed again where they are used, not kept
+        double D[kR];
+        pass_diagonal(P, g, par, D);
 #pragma unroll
         for (int e = 0; e < kR; ++e) {
-            const double2 o = tile[yb + (e << kRegShift)];
+            const double2 o = make_double2(re[e << kRegShift], im[e << kRegShift]);
             st_h<SH>(&W[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)], o);
-            uint64_t pe = par;
-            if (e & 1) pe ^= pe6;
-            if (e & 2) pe ^= pe7;
-            if (e & 4) pe ^= pe8;
-            const int s_all = P.n_bonds - 2 * __popcll(pe);
-            const int s_z = nz - 2 * __popcll(pe & P.zmask);
-            const double D = fma(P.kq, (double)s_z, P.jq * (double)s_all);
-            re[e] = D * o.x;
-            im[e] = D * o.y;
+            acc[e] = D[e] * o.x;
+            acc[kR + e] = D[e] * o.y;
         }
-        __syncthreads();
-        for (int b = g.b0; b < g.b1; ++b) {
-            const uint32_t pq = seg.pq[b];
-            const uint32_t pi = pq & 0xffu, pj = pq >> 8;
-            const uint32_t tm = (1u << pi) | (1u << pj);
-            const uint32_t mrest = tm & ~(7u << kRegShift);
-            const int mr = (tm >> kRegShift) & 7;
-            const bool anti = ((yb >> pi) ^ (yb >> pj)) & 1u;
-            const double aa = seg.aa[b], ap = seg.ap[b];
-            const double ampA = anti ? aa : ap;
-            const double ampB = anti ? ap : aa;
-            const uint32_t base = FTK_IDX(yb ^ mrest, 7u << kRegShift, kPassTile, 8) ^ ((uint32_t)mr << kRegShift);
-            bond_accum_lds_flat(re, im, tile, base, (uint32_t)mr, ampA, ampB);
-        }
+        lds_barrier();
+        pass_bonds(acc, bonds, g.b1 - g.b0, tile_at, t.yb);
+        asm volatile("" : "+v"(xb));
 #pragma unroll
-        for (int e = 0; e < kR; ++e) part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)] = make_double2(re[e], im[e]);
+        for (int e = 0; e < kR; ++e)
+            part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)] = make_double2(acc[e], acc[kR + e]);
     }
-    write_partial<kPassThreads>(partials, hi, lo, err);
+    write_partial<kPassThreads>(partials, hi, lo);
 }
 
 // passes p0..n_passes-1 of the multi-pass form (the first of them starts from
@@ -936,7 +892,7 @@ struct EpiLanczosADev {
                  // 2: the last pass does, every workgroup for itself (begin)
     FinBeta fb;
     SeqState *st_out;  // with fin 2: the state after that half step
-    double inv, c1, hi, lo, err;
+    double inv, c1, hi, lo;
     __device__ void finalize_block(int r) const { finalize_beta_seq<kPassThreads>(fb, r); }
     // sequence r of a stacked batch: vectors vs entries apart, pstride partial doubles apart
     __device__ void select(int r, size_t vs, int pstride)
@@ -948,51 +904,57 @@ struct EpiLanczosADev {
         if (st_out) st_out += r;
         partials += (size_t)r * pstride;
     }
-    __device__ bool active() const { return !st->done; }
+    __device__ bool active() const
+    {
+        if (!st->done) return true;
+        if (fin == 2 && blockIdx.x == 0 && threadIdx.x == 0) *st_out = *st;  // a finished sequence stays as it is
+        return false;
+    }
     __device__ void init()
     {
         inv = st->inv_cur;
         c1 = (-st->beta_cur) * st->inv_prev;
-        hi = lo = err = 0.0;
+        hi = lo = 0.0;
     }
-    // In place of active() and init() with fin 2: beta_k of the previous half step from
-    // its partial sums, in every workgroup of sequence r; workgroup 0 records it and
-    // writes the state to st_out (the others still read st).  A two-pass step is two
-    // launches this way instead of three, and no launch waits for the shift update,
+    // Before the tiles of the last pass, and before the first epilogue.  With fin 2 beta_k
+    // of the previous half step is summed from its partials here, in every workgroup of
+    // sequence r (the thread's first partial read ahead of the tile); workgroup 0 records
+    // it and writes the state to st_out (the others still read st).  A two-pass step is
+    // two launches this way instead of three, and no launch waits for the shift update,
     // which runs once per finished sequence (16 sites, 72 sequences of 300 steps with
     // 1000 shifts in stacks of 32: 55.7 -> 49.6 ms).
+    double bh, bl;
+    __device__ void prepare(int r)
+    {
+        init();
+        bh = bl = 0.0;
+        const double *pb = fb.partials + (size_t)r * 2 * fb.nparts;
+        if (fin == 2 && (int)threadIdx.x < fb.nparts) bh = pb[2 * threadIdx.x], bl = pb[2 * threadIdx.x + 1];
+    }
     template <int BLOCK>
     __device__ bool begin(int r)
     {
-        const SeqState q = *st;
-        const bool record = blockIdx.x == 0 && threadIdx.x == 0;
-        if (q.done) {
-            if (record) *st_out = q;
-            return false;
-        }
-        __shared__ double s_bn;
-        const double ssum = reduce_partials<BLOCK>(fb.partials + (size_t)r * 2 * fb.nparts, fb.nparts);
-        if (threadIdx.x == 0) s_bn = sqrt(ssum);
-        __syncthreads();
-        const double bn = s_bn;
+        if (fin != 2) return true;
+        const double *pb = fb.partials + (size_t)r * 2 * fb.nparts;
+        for (int i = threadIdx.x + BLOCK; i < fb.nparts; i += BLOCK) pair_add(bh, bl, pb[2 * i], pb[2 * i + 1]);
+        block_pair<BLOCK>(bh, bl);
+        const double bn = uniform(sqrt(bh + bl));
         const bool ends = !(bn > fb.tol);  // invariant subspace
-        if (record) {
-            SeqState o = q;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
             fb.beta_out[(size_t)r * fb.bstride + fb.k] = bn;
-            o.steps = fb.k + 1;
-            if (!isfinite(bn)) o.numeric_error = 1;
+            *st_out = *st;
+            st_out->steps = fb.k + 1;
+            if (!isfinite(bn)) st_out->numeric_error = 1;
             if (ends) {
-                o.done = 1;
+                st_out->done = 1;
             } else {
-                o.inv_prev = q.inv_cur;
-                o.inv_cur = 1.0 / bn;
-                o.beta_cur = bn;
+                st_out->inv_prev = inv;
+                st_out->inv_cur = 1.0 / bn;
+                st_out->beta_cur = bn;
             }
-            *st_out = o;
         }
-        inv = 1.0 / bn;
-        c1 = (-bn) * q.inv_cur;
-        hi = lo = err = 0.0;
+        c1 = uniform((-bn) * inv);  // init() read inv_{k-1}
+        inv = uniform(1.0 / bn);
         return !ends;
     }
     __device__ double2 load(size_t x) const { return first ? make_double2(0.0, 0.0) : Wprev[x]; }
@@ -1005,12 +967,12 @@ struct EpiLanczosADev {
         }
         U[x] = make_double2(ur, ui);
         if (vout) vout[x] = wc;
-        acc_prod(hi, lo, err, wc.x, ur);
-        acc_prod(hi, lo, err, wc.y, ui);
+        pair_prod(hi, lo, wc.x, ur);
+        pair_prod(hi, lo, wc.y, ui);
     }
     __device__ void operator()(size_t x, double re, double im, const double2 &wc) { apply(x, re, im, wc, load(x)); }
     template <int BLOCK>
-    __device__ void finish() { write_partial<BLOCK>(partials, hi, lo, err); }
+    __device__ void finish() { write_partial<BLOCK>(partials, hi, lo); }
 };
 
 void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U,
@@ -1084,17 +1046,17 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
     if (st->done) return;
     const double c2 = -(st->alpha_cur * st->inv_cur);
-    double hi = 0.0, lo = 0.0, err = 0.0;
+    double hi = 0.0, lo = 0.0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 wc = Wcur[x];
         const double2 u = U[x];
         const double wr = fma(c2, wc.x, u.x);
         const double wi = fma(c2, wc.y, u.y);
         U[x] = make_double2(wr, wi);
-        acc_prod(hi, lo, err, wr, wr);
-        acc_prod(hi, lo, err, wi, wi);
+        pair_prod(hi, lo, wr, wr);
+        pair_prod(hi, lo, wi, wi);
     }
-    write_partial<kBlock>(partials, hi, lo, err);
+    write_partial<kBlock>(partials, hi, lo);
 }
 
 __global__ void __launch_bounds__(kBlock) k_finalize_alpha(SeqState *st, const double *partials,
@@ -1208,13 +1170,13 @@ __global__ void __launch_bounds__(kBlock) k_dot(uint32_t dim, const double2 *__r
     a += blockIdx.y * vs;
     b += blockIdx.y * vs;
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
-    double hi = 0.0, lo = 0.0, err = 0.0;
+    double hi = 0.0, lo = 0.0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = a[x], v = b[x];
-        acc_prod(hi, lo, err, u.x, v.x);
-        acc_prod(hi, lo, err, u.y, v.y);
+        pair_prod(hi, lo, u.x, v.x);
+        pair_prod(hi, lo, u.y, v.y);
     }
-    write_partial<kBlock>(partials, hi, lo, err);
+    write_partial<kBlock>(partials, hi, lo);
 }
 
 __global__ void __launch_bounds__(kBlock) k_start_sequence(SeqState *st, const double *partials,
@@ -1495,15 +1457,14 @@ struct BatchGeom {
 // per-sequence (hi, lo) sums of a block: lanes with equal lane % B combine, then
 // waves in order; partials[(block * B + r) * 2 + {0, 1}]
 template <int B, int BLOCK>
-__device__ __forceinline__ void write_partial_batch(double *partials, double hi, double lo, double err)
+__device__ __forceinline__ void write_partial_batch(double *partials, double hi, double lo)
 {
     __shared__ double sh[BLOCK / 64][B][2];
-    dd_add(hi, lo, err);
 #pragma unroll
     for (int off = 32; off >= B; off >>= 1) {
         double oh = __shfl_xor(hi, off, 64);
         double ol = __shfl_xor(lo, off, 64);
-        dd_add_dd(hi, lo, oh, ol);
+        pair_add(hi, lo, oh, ol);
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane < B) {
@@ -1513,7 +1474,7 @@ __device__ __forceinline__ void write_partial_batch(double *partials, double hi,
     __syncthreads();
     if (threadIdx.x < B) {
         double h = sh[0][threadIdx.x][0], l = sh[0][threadIdx.x][1];
-        for (int w = 1; w < BLOCK / 64; ++w) dd_add_dd(h, l, sh[w][threadIdx.x][0], sh[w][threadIdx.x][1]);
+        for (int w = 1; w < BLOCK / 64; ++w) pair_add(h, l, sh[w][threadIdx.x][0], sh[w][threadIdx.x][1]);
         partials[2 * (blockIdx.x * B + threadIdx.x)] = h;
         partials[2 * (blockIdx.x * B + threadIdx.x) + 1] = l;
     }
@@ -1524,8 +1485,8 @@ __device__ __forceinline__ double reduce_partials_strided(const double *partials
 {
     double hi = 0.0, lo = 0.0;
     for (int i = threadIdx.x; i < nparts; i += blockDim.x)
-        dd_add_dd(hi, lo, partials[2 * (i * B + r)], partials[2 * (i * B + r) + 1]);
-    block_reduce_dd<kBlock>(hi, lo);
+        pair_add(hi, lo, partials[2 * (i * B + r)], partials[2 * (i * B + r) + 1]);
+    block_pair<kBlock>(hi, lo);
     return hi + lo;
 }
 
@@ -1536,7 +1497,7 @@ struct EpiLanczosABatch {
     double *partials;
     const SeqState *st;  // [B]
     int first;
-    double inv, c1, hi, lo, err;
+    double inv, c1, hi, lo;
     int done;
     __device__ bool active() const { return true; }
     __device__ void init(int r)
@@ -1544,7 +1505,7 @@ struct EpiLanczosABatch {
         inv = st[r].inv_cur;
         c1 = (-st[r].beta_cur) * st[r].inv_prev;
         done = st[r].done;
-        hi = lo = err = 0.0;
+        hi = lo = 0.0;
     }
     __device__ double2 load(size_t idx) const { return (first || done) ? make_double2(0.0, 0.0) : Wprev[idx]; }
     __device__ void apply(size_t idx, double re, double im, const double2 &wc, const double2 &wp)
@@ -1556,11 +1517,11 @@ struct EpiLanczosABatch {
             ui = fma(c1, wp.y, ui);
         }
         U[idx] = make_double2(ur, ui);
-        acc_prod(hi, lo, err, wc.x, ur);
-        acc_prod(hi, lo, err, wc.y, ui);
+        pair_prod(hi, lo, wc.x, ur);
+        pair_prod(hi, lo, wc.y, ui);
     }
     template <int BLOCK>
-    __device__ void finish() { write_partial_batch<B, BLOCK>(partials, hi, lo, err); }
+    __device__ void finish() { write_partial_batch<B, BLOCK>(partials, hi, lo); }
 };
 
 template <int B, class Epi>
@@ -1657,7 +1618,7 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b_batch(uint32_t dim, const 
     const int r = threadIdx.x % B;  // kBlock and the grid stride are multiples of B
     const int done = st[r].done;
     const double c2 = -(st[r].alpha_cur * st[r].inv_cur);
-    double hi = 0.0, lo = 0.0, err = 0.0;
+    double hi = 0.0, lo = 0.0;
     const size_t n = (size_t)dim * B;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
         if (done) continue;
@@ -1666,10 +1627,10 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b_batch(uint32_t dim, const 
         const double wr = fma(c2, wc.x, u.x);
         const double wi = fma(c2, wc.y, u.y);
         U[idx] = make_double2(wr, wi);
-        acc_prod(hi, lo, err, wr, wr);
-        acc_prod(hi, lo, err, wi, wi);
+        pair_prod(hi, lo, wr, wr);
+        pair_prod(hi, lo, wi, wi);
     }
-    write_partial_batch<B, kBlock>(partials, hi, lo, err);
+    write_partial_batch<B, kBlock>(partials, hi, lo);
 }
 
 void launch_lanczos_b_batch(int B, uint32_t dim, const double *Wcur, double *U, SeqState *st, double *partials,
@@ -1760,14 +1721,14 @@ void launch_finalize_beta_batch(int B, SeqState *st, const double *partials, int
 template <int B>
 __global__ void __launch_bounds__(kBlock) k_dot_batch(uint32_t dim, const double2 *__restrict__ a, double *partials)
 {
-    double hi = 0.0, lo = 0.0, err = 0.0;
+    double hi = 0.0, lo = 0.0;
     const size_t n = (size_t)dim * B;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
         const double2 u = a[idx];
-        acc_prod(hi, lo, err, u.x, u.x);
-        acc_prod(hi, lo, err, u.y, u.y);
+        pair_prod(hi, lo, u.x, u.x);
+        pair_prod(hi, lo, u.y, u.y);
     }
-    write_partial_batch<B, kBlock>(partials, hi, lo, err);
+    write_partial_batch<B, kBlock>(partials, hi, lo);
 }
 
 __global__ void __launch_bounds__(kBlock) k_start_batch(SeqState *st, const double *partials, int nparts, int B,
