@@ -356,7 +356,9 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").  Clusters
  * of 6 to 14 sites run every sequence of the call in one launch, one workgroup
  * each, whatever rhs_block says (unless a tuning key forces another form); the
- * vectors of such a launch take up to 192 MiB of device memory.
+ * vectors of such a launch take up to 256 MiB of device memory.  From 16 sites
+ * on, batches whose vectors (4 per sequence) come to at most 256 MiB run in two
+ * chains on two streams, with the buffers of both (not while kernel timing is on).
  * resid_tol > 0 truncates each sequence at the first step k <= n_steps after
  * which the largest Galerkin residual over the shifts, per unit right-hand side
  * (|p_k| beta_{k+1} / |d_k|), is <= resid_tol (Sec. V, truncation of the CG

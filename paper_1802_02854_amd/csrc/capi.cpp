@@ -75,9 +75,12 @@ struct ftk_ctx {
     ftk_alloc_fn alloc_fn = nullptr;  // caller's allocator (both or neither)
     ftk_free_fn free_fn = nullptr;
     void *alloc_user = nullptr;
-    // device bytes of the start vectors, carried vectors and shift states that one launch
-    // of resident sequences may take: one sequence per compute unit at 14 sites, more below
-    size_t resident_bytes = size_t(192) << 20;
+    // device bytes a call may take to run more sequences at a time than it was asked to
+    // (the vectors of a launch of resident sequences: one sequence per compute unit at 14
+    // sites, more below; a second chain of batches)
+    size_t spare_bytes = size_t(256) << 20;
+    hipStream_t second = nullptr;  // of the second chain, made when first needed
+    std::once_flag second_once;
     size_t bytes = 0;
     size_t peak = 0;  // high-water mark of bytes since the last reset
     bool timing = false;
@@ -111,6 +114,7 @@ struct ftk_ctx {
     ~ftk_ctx()
     {
         clear_events();
+        if (second) (void)hipStreamDestroy(second);
         if (own_stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -978,7 +982,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             // side by side, one workgroup each; pass 2 in blocks of nb steps with the
             // sequences' vectors carried over.
             const size_t pairs = (size_t)st->nv * st->na, cplx = 2 * (size_t)dim;
-            const size_t group = std::min(pairs, std::max<size_t>(1, ctx->resident_bytes / (vbytes * (nb + 3))));
+            const size_t group = std::min(pairs, std::max<size_t>(1, ctx->spare_bytes / (vbytes * (nb + 3))));
             Arena m;
             ResidentSeq *seq;
             SeqState *state;
@@ -1186,6 +1190,7 @@ struct BatchRunner {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool capturing = false;
+    int runs = 0;
     int end_slot = 0;  // the current state after the captured steps
 
     static bool stack_for(const ftk_hamiltonian *H, int B_, int stack)
@@ -1203,7 +1208,7 @@ struct BatchRunner {
     }
 
     BatchRunner(const ftk_hamiltonian *H, int B_, int n_, const double *omega_host, int nw_, double eta_,
-                double rtol_ = 0.0, int stack = -1, int pass_grid = 0, int hints = -1)
+                double rtol_ = 0.0, int stack = -1, int pass_grid = 0, int hints = -1, bool own_partials = false)
         : h(H), op(with_grid(H->op, pass_grid, hints)), ctx(H->ctx), s(H->ctx->stream), dim(H->dim), B(B_), n(n_), nw(nw_),
           eta(eta_), tol(1e-12 * H->table.norm_bound), rtol(rtol_), stacked(stack_for(H, B_, stack)),
           nparts_a(B_ == 1 ? hv_grid(op) : (stacked ? hv_grid(op, B_) : hv_batch_grid(H->dim, B_))),
@@ -1215,10 +1220,10 @@ struct BatchRunner {
           shifts(H->ctx, late ? sizeof(double) : sizeof(ShiftState) * (size_t)nw_ * B_), omega(H->ctx, sizeof(double) * nw_),
           partials(H->ctx, sizeof(double) * 2 * (size_t)kMaxGrid * B_),
           partials_b(H->ctx, fuse ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
-          part(H->ctx, stacked ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
+          part(H->ctx, stacked || own_partials ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
     {
         need(B <= 16 || stacked, "more than 16 sequences per launch need the stacked layout");
-        if (stacked) {
+        if (stacked || own_partials) {  // else the Hamiltonian's scratch vector
             sk.B = B;
             sk.scratch = part.d();
             sk.vs = 2 * (size_t)dim;
@@ -1344,7 +1349,11 @@ struct BatchRunner {
             }
             return;
         }
-        if (g_use_graphs) {
+        // The first batch is launched step by step: the GPU starts at once and the host
+        // stays ahead of it.  The graph for the following ones is captured while it runs
+        // (16 sites, one batch of 32 sequences of 200 steps: 74 us a step with the capture
+        // first, 67 without; replayed and launched steps take the same time).
+        if (g_use_graphs && runs++ > 0) {
             if (!exec) {
                 slot = 0;
                 capturing = true;
@@ -1442,7 +1451,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega);
 }  // namespace
 
 void ftk::set_last_error(const std::string &msg) { g_error = msg; }
-void ftk::limit_resident_bytes(ftk_ctx *ctx, size_t bytes) { ctx->resident_bytes = bytes; }
+void ftk::limit_spare_bytes(ftk_ctx *ctx, size_t bytes) { ctx->spare_bytes = bytes; }
 
 int ftk::tuned_rhs_block(int device, int n_sites, int n_omega)
 {
@@ -1661,7 +1670,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     const bool stop = rtol > 0.0;
     const bool carried = stop || h->n_sites >= kResidentPlanes;
     const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
-    const size_t slab = std::min(rows, std::max<size_t>(1, ctx->resident_bytes / per));
+    const size_t slab = std::min(rows, std::max<size_t>(1, ctx->spare_bytes / per));
 
     Arena m;
     ResidentSeq *seq;
@@ -1735,9 +1744,12 @@ void check_green(const GreenOut &out)
 // Runs the items in batches of B through one graph-captured BatchRunner; load(run, r,
 // item) writes the item's right-hand side into slot r.  Slots of sequences not listed
 // stay zero.  Small clusters run resident instead, from ops.
+// Two chains of batches on two streams, where load_any_stream says that load works
+// on either.
 template <class Load>
 GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const double *omega, int nw, double eta,
-                   double rtol, int nseq, const std::vector<GreenItem> &work, const StartOps &ops, Load &&load)
+                   double rtol, int nseq, const std::vector<GreenItem> &work, const StartOps &ops, bool load_any_stream,
+                   Load &&load)
 {
     if (resident_run(h->op)) {
         GreenOut out = run_green_resident(h, n, omega, nw, eta, rtol, nseq, work, ops);
@@ -1757,10 +1769,46 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     m.part(&g, rows * nw * 2);
     m.allocate(ctx);
     const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
-    BatchRunner run(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints);
-    for (size_t w0 = 0; w0 < rows; w0 += B) {
+    BatchRunner first(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints);
+    // A second chain of batches on its own stream fills the first one's launch gaps and
+    // overlaps its loads with the other's bonds: all workgroups of a small launch are in
+    // the same phase.  Worth it while both chains' vectors stay near the last-level cache:
+    // us per sequence and step, one chain against two, 16 sites, stacks of 32 (256 MiB for
+    // both): 1.89 / 1.52; 18 sites, 16 (512 MiB): 6.4 / 5.4; 20 sites, 4 (512 MiB): 35.1 /
+    // 29.7; but 20 sites, 16 (2 GiB): 31.0 / 35.4 and 24 sites, 1 (2 GiB): 510 / 557.
+    // Kernel timing wants the launches of one stream.
+    const size_t vectors = sizeof(double) * 2 * (size_t)h->dim * B * 4;
+    bool two = load_any_stream && first.fuse && rows > (size_t)B && vectors <= ctx->spare_bytes && !ctx->timing;
+    std::unique_ptr<BatchRunner> other;
+    struct Joined {  // nothing of the second chain runs once its buffers are freed
+        hipStream_t s = nullptr;
+        hipEvent_t e = nullptr;
+        ~Joined()
+        {
+            if (s) (void)hipStreamSynchronize(s);
+            if (e) (void)hipEventDestroy(e);
+        }
+    } joined;
+    if (two) {
+        try {
+            other = std::make_unique<BatchRunner>(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints, true);
+        } catch (const Error &e) {
+            if (e.status != FTK_ENOMEM) throw;
+            two = false;  // no room for it: one chain
+        }
+    }
+    if (two) {
+        std::call_once(ctx->second_once, [&] { HIP_CHECK(hipStreamCreate(&ctx->second)); });
+        other->s = joined.s = ctx->second;
+        // after everything queued so far: the shells, the allocations of this call
+        HIP_CHECK(hipEventCreateWithFlags(&joined.e, hipEventDisableTiming));
+        HIP_CHECK(hipEventRecord(joined.e, s));
+        HIP_CHECK(hipStreamWaitEvent(joined.s, joined.e, 0));
+    }
+    for (size_t w0 = 0, batch = 0; w0 < rows; w0 += B, ++batch) {
+        BatchRunner &run = two && batch % 2 ? *other : first;
         const int cnt = (int)std::min<size_t>(B, rows - w0);
-        if (cnt < B) HIP_CHECK(hipMemsetAsync(run.chi.p, 0, run.chi.n, s));
+        if (cnt < B) HIP_CHECK(hipMemsetAsync(run.chi.p, 0, run.chi.n, run.s));
         BatchShifts bs;
         for (int r = 0; r < kMaxBatch; ++r) bs.re[r] = 0.0;
         for (int r = 0; r < cnt; ++r) {
@@ -1770,9 +1818,13 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
         run.start(bs);
         run.run();
         run.read_green(cnt, g + w0 * 2 * nw);
-        HIP_CHECK(hipMemcpyAsync(al + w0 * n, run.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, s));
-        HIP_CHECK(hipMemcpyAsync(be + w0 * n, run.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, s));
-        HIP_CHECK(hipMemcpyAsync(st + w0, run.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, s));
+        HIP_CHECK(hipMemcpyAsync(al + w0 * n, run.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, run.s));
+        HIP_CHECK(hipMemcpyAsync(be + w0 * n, run.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, run.s));
+        HIP_CHECK(hipMemcpyAsync(st + w0, run.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, run.s));
+    }
+    if (two) {
+        HIP_CHECK(hipEventRecord(joined.e, joined.s));
+        HIP_CHECK(hipStreamWaitEvent(s, joined.e, 0));
     }
     HIP_CHECK(hipGetLastError());
     GreenOut out = download_green(s, nseq, n, nw, work, st, al, be, g);
@@ -1977,7 +2029,7 @@ ftk_status ftk_shifted_krylov_spectrum(const ftk_hamiltonian *h, const ftk_state
             *out = sp.release();
             return;
         }
-        GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work, StartOps{&sq},
+        GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work, StartOps{&sq}, true,
                                  [&](BatchRunner &run, int r, const GreenItem &q) { run.load_rhs(sq[q.tag], q.phi, r); });
         sp->g = std::move(res.g);
         sp->alpha = std::move(res.alpha);
@@ -2187,7 +2239,7 @@ ftk_status ftk_pair_green(const ftk_hamiltonian *h, const ftk_states *st, const 
         const double *cur_phi = nullptr;
         int cur_pair = -1;
         GreenOut res = run_green(h, B, stack, n, p->omega, nw, p->eta, p->resid_tol, nseq, work,
-                                 StartOps{nullptr, &opa, &opb}, [&](BatchRunner &run, int r, const GreenItem &q) {
+                                 StartOps{nullptr, &opa, &opb}, false, [&](BatchRunner &run, int r, const GreenItem &q) {
                                      const int pair = q.tag / 4;
                                      if (q.phi != cur_phi || pair != cur_pair) {
                                          launch_apply_spin_op(opa[pair], q.phi, lam.d(), ctx->stream);

@@ -69,8 +69,8 @@ int plan_layout(int n_sites, int n_bonds, const int32_t *bi, const int32_t *bj, 
                 int32_t *site_perm, int32_t *bond_order);
 // message returned by ftk_last_error on this thread
 void set_last_error(const std::string &msg);
-// device bytes one launch of resident sequences on ctx may take beside its results
-void limit_resident_bytes(ftk_ctx *ctx, size_t bytes);
+// device bytes a call on ctx may take to run more sequences at a time than asked
+void limit_spare_bytes(ftk_ctx *ctx, size_t bytes);
 // rhs_block the autotuner has recorded for (device, n_sites, n_omega) in this
 // process or the tuning cache file; 0 when it has none
 int tuned_rhs_block(int device, int n_sites, int n_omega);

@@ -77,9 +77,10 @@ size_t footprint(int n_sites, const ftk_ts_params *tp, const ftk_spec_params *sp
     return (size_t)std::ceil(1.02 * peak + 64.0 * 1024 * 1024);
 }
 
-// small clusters run their sequences resident: those launches' vectors fit in the 64
-// MiB that a reservation holds beyond the buffers it counts
-constexpr size_t kServedResidentBytes = size_t(48) << 20;
+// what a served request's calls may take to run more sequences at a time (resident
+// launches of small clusters, a second chain of batches): it fits in the 64 MiB that a
+// reservation holds beyond the buffers it counts
+constexpr size_t kServedSpareBytes = size_t(48) << 20;
 
 struct Request {
     uint64_t id = 0;
@@ -416,7 +417,7 @@ ftk_status ftk_server_create(int device, size_t hbm_budget, int n_workers, ftk_s
                 for (ftk_ctx *x : srv->ctxs) ftk_ctx_destroy(x);
                 fail(s, ftk_last_error());
             }
-            limit_resident_bytes(c, kServedResidentBytes);
+            limit_spare_bytes(c, kServedSpareBytes);
             srv->ctxs.push_back(c);
         }
         srv->record_occupancy();

@@ -1,0 +1,37 @@
+"""Two chains of batches on two streams against one chain, bit for bit."""
+import numpy as np
+import pytest
+
+from seeded_inputs import SUPERCELLS
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,B,alloc", [(16, 1, None), (16, 4, "torch"), (18, 16, None), (20, 4, None)])
+def test_two_chains_match_one(N, B, alloc):
+    """An odd number of batches, the last one ragged, every batch's graph replayed at most once
+    more than it was launched step by step; kernel timing keeps the batches in one chain."""
+    import torch
+
+    import paper_1802_02854_amd as ftk
+    print(f"chains N={N} B={B}", flush=True)
+    ctx = ftk.Context(0, allocator=alloc)
+    cl = ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[N]))[0]
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
+    L = {1: 7, 4: 6, 16: 16}[B]
+    st = ftk.TypicalStates(h, seed=2, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=L, M=4, n_steps=8)
+    alpha = 4 if B == 1 else 7
+    res = []
+    for timing in (False, True, False):
+        ctx.set_timing(timing)
+        for _ in range(2):
+            sp = ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-3, 3, 40), eta=0.1, n_steps=9, rhs_block=B,
+                              alpha_mask=alpha)
+            res.append((*sp.raw(), sp.norms()))
+            # the caller's own work between the calls
+            torch.zeros(1 << 20, device="cuda").add_(1.0)
+    ctx.set_timing(False)
+    for r in res[1:]:
+        for x, y in zip(res[0], r):
+            assert np.array_equal(x, y)
+    assert np.abs(res[0][0]).max() > 0
