@@ -280,9 +280,10 @@ struct Krylov {
         launch_start_sequence(st(i), partials.d(), nparts, 0.0, s);
         const double tol = 1e-12 * h->table.norm_bound;
         double *W[2] = {W0, W1};
+        const bool pairs = lanczos_pairs(h->op, 1) && !g_plain_loop;
         const bool fuse = lanczos_fusable(h->op) && !g_plain_loop;
         const bool fa_on = fuse && alpha_in_fused_pass();
-        double *pa = partials.d(), *pb = fa_on ? partials_b.d() : partials.d();
+        double *pa = partials.d(), *pb = fa_on || pairs ? partials_b.d() : partials.d();
         int k0 = 0;
         for (int k = 0; k < n; ++k) {
             // w_k goes to W[k % 2]; v_k comes from w_{k-1}, v_{k-1} from w_{k-2}
@@ -291,7 +292,14 @@ struct Krylov {
             double *out = W[k % 2];
             double *vout = Vbuf ? Vbuf + (size_t)(k - k0) * 2 * dim : nullptr;
             ctx->timed("filter_step", (k & 7) == 1, [&] {
-                if (fuse && k > 0) {
+                if (pairs) {
+                    const FinBeta fb{st(i), pb, nparts, be(i), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, 0};
+                    SeqState *now = st(i);
+                    if (k > 0) slot ^= 1;
+                    launch_lanczos_pair_a(h->op, cur, prv, out, vout, now, pa, k == 0, s, k > 0 ? &fb : nullptr, st(i));
+                    const FinAlpha fa{pa, nparts_hv, al(i), 0, k};
+                    launch_lanczos_b(dim, cur, out, st(i), pb, s, 1, 0, &fa);
+                } else if (fuse && k > 0) {
                     // second half of step k-1 inside the first pass of step k (which also
                     // finalises alpha_{k-1}); its beta finalisation rides in the middle pass
                     // when there is one, else in the last.  alpha partials in pa, norm
@@ -322,7 +330,9 @@ struct Krylov {
                 k0 = k + 1;
             }
         }
-        if (fuse) {
+        if (pairs) {
+            launch_finalize_beta(st(i), pb, nparts, be(i), n - 1, tol, nullptr, nullptr, 0, 0.0, s);
+        } else if (fuse) {
             // alpha and the second half of the last step
             if (fa_on) launch_finalize_alpha(st(i), pa, nparts_hv, al(i), n - 1, s);
             const double *cur = n == 1 ? start : W[(n - 2) % 2];
@@ -631,9 +641,10 @@ ftk_status ftk_apply_h_strided(const ftk_hamiltonian *h, const double *v, double
         const size_t span = n_rhs > 0 ? stride * (size_t)(n_rhs - 1) + 2 * (size_t)h->dim : 0;
         need(v + span <= w || w + span <= v, "v and w overlap");
         HIP_CHECK(hipSetDevice(h->ctx->device));
-        for (int r = 0; r < n_rhs; ++r)
+        if (!h->ctx->timing) launch_apply_h(h->op, v, w, h->ctx->stream, n_rhs, stride);
+        for (int r = 0; r < n_rhs && h->ctx->timing; ++r)
             h->ctx->timed("apply_h", true,
-                          [&] { launch_apply_h(h->op, v + r * stride, w + r * stride, h->ctx->stream); });
+                          [&] { launch_apply_h(h->op, v + r * stride, w + r * stride, h->ctx->stream, 1); });
         HIP_CHECK(hipGetLastError());
     });
 }
@@ -691,8 +702,7 @@ ftk_status ftk_apply_h_noalloc(const ftk_hamiltonian *h, const double *v, double
                                      std::to_string(kNoAllocMaxSites));
             op.scratch = noalloc_scratch(h->ctx->device);
         }
-        for (int r = 0; r < n_rhs; ++r)
-            launch_apply_h(op, v + 2 * (size_t)h->dim * r, w + 2 * (size_t)h->dim * r, h->ctx->stream);
+        launch_apply_h(op, v, w, h->ctx->stream, n_rhs, 2 * (size_t)h->dim);
         HIP_CHECK(hipGetLastError());
     });
 }
@@ -1182,7 +1192,8 @@ struct BatchRunner {
     double eta, tol, rtol;  // breakdown threshold; residual truncation (0: off)
     bool stacked;           // B > 1 as a stack of multi-pass sequences
     int nparts_a, nparts_b;
-    bool fuse;  // multi-pass H v: halves of consecutive steps fused
+    bool pairs;  // small stacks: a step is two launches
+    bool fuse;   // multi-pass H v: halves of consecutive steps fused
     bool late;  // the multi-shift update once per finished sequence, not every step
     int slot = 0;  // which of the sequences' two states is current
     DevBuf chi, W0, W1, st, al, be, shifts, omega, partials, partials_b, part;  // partials_b: norms of fused steps
@@ -1211,16 +1222,18 @@ struct BatchRunner {
                 double rtol_ = 0.0, int stack = -1, int pass_grid = 0, int hints = -1, bool own_partials = false)
         : h(H), op(with_grid(H->op, pass_grid, hints)), ctx(H->ctx), s(H->ctx->stream), dim(H->dim), B(B_), n(n_), nw(nw_),
           eta(eta_), tol(1e-12 * H->table.norm_bound), rtol(rtol_), stacked(stack_for(H, B_, stack)),
-          nparts_a(B_ == 1 ? hv_grid(op) : (stacked ? hv_grid(op, B_) : hv_batch_grid(H->dim, B_))),
+          nparts_a(B_ == 1 || (stacked && lanczos_pairs(op, B_)) ? hv_grid(op)
+                                                                 : (stacked ? hv_grid(op, B_) : hv_batch_grid(H->dim, B_))),
           nparts_b(B_ == 1 || stacked ? vec_grid(H->dim) : vec_batch_grid(H->dim, B_)),
-          fuse(stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop)), late(rtol_ == 0.0 && !g_plain_loop),
+          pairs((B_ == 1 || stacked) && lanczos_pairs(op, B_) && !g_plain_loop),
+          fuse(!pairs && (stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop))), late(rtol_ == 0.0 && !g_plain_loop),
           chi(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), W0(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_),
           W1(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), st(H->ctx, sizeof(SeqState) * 2 * B_),
           al(H->ctx, sizeof(double) * (size_t)n_ * B_), be(H->ctx, sizeof(double) * (size_t)n_ * B_),
           shifts(H->ctx, late ? sizeof(double) : sizeof(ShiftState) * (size_t)nw_ * B_), omega(H->ctx, sizeof(double) * nw_),
           partials(H->ctx, sizeof(double) * 2 * (size_t)kMaxGrid * B_),
-          partials_b(H->ctx, fuse ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
-          part(H->ctx, stacked || own_partials ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
+          partials_b(H->ctx, fuse || pairs ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
+          part(H->ctx, (stacked || own_partials) && !pairs ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
     {
         need(B <= 16 || stacked, "more than 16 sequences per launch need the stacked layout");
         if (stacked || own_partials) {  // else the Hamiltonian's scratch vector
@@ -1286,6 +1299,17 @@ struct BatchRunner {
                 launch_lanczos_b_batch(B, dim, cur, out, q, partials.d(), s);
                 launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nsh, eta,
                                            s, rtol);
+            } else if (pairs) {
+                const FinBeta fb{q, partials_b.d(), nparts_b, be.d(), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, n};
+                const bool in_a = late && k > 0;
+                if (in_a) slot ^= 1;
+                launch_lanczos_pair_a(op, cur, prv, out, nullptr, q, partials.d(), k == 0, s, in_a ? &fb : nullptr,
+                                      states(), B, sk.vs);
+                const FinAlpha fa{partials.d(), nparts_a, al.d(), n, k};
+                launch_lanczos_b(dim, cur, out, states(), partials_b.d(), s, B, sk.vs, &fa);
+                if (!late)
+                    launch_finalize_beta(q, partials_b.d(), nparts_b, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol,
+                                         B, n);
             } else if (fuse && k > 0) {
                 // second half of step k-1 inside the first pass of step k (which also
                 // finalises alpha_{k-1}); its beta finalisation rides in the middle pass
@@ -1318,6 +1342,9 @@ struct BatchRunner {
     // the second half of the last step when the halves are fused across steps
     void finish()
     {
+        if (pairs && late)
+            launch_finalize_beta(states(), partials_b.d(), nparts_b, be.d(), n - 1, tol, nullptr, nullptr, 0, eta, s,
+                                 0.0, B, n);
         if (!fuse) return;
         if (alpha_in_fused_pass()) launch_finalize_alpha(states(), partials.d(), nparts_a, al.d(), n - 1, s, B, n);
         double *W[2] = {W0.d(), W1.d()};
@@ -1551,7 +1578,8 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
     }
     // the winner's persistent workgroups per reducing multi-pass launch: half and twice
     // the default (results do not depend on it: the partial sums are exact)
-    if (hv_mode(h->op) == 3 && (best.rhs_block == 1 || best.stacked)) {
+    if ((hv_mode(h->op) == 3 || h->n_sites >= kGatherSites) && lanczos_stackable(h->op) &&
+        (best.rhs_block == 1 || best.stacked)) {
         const int cap = pass_grid_cap(h->op);
         for (int pg : {cap / 2, 2 * cap}) {
             if (pg < 1 || pg > kMaxGrid) continue;
@@ -1778,7 +1806,7 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     // 29.7; but 20 sites, 16 (2 GiB): 31.0 / 35.4 and 24 sites, 1 (2 GiB): 510 / 557.
     // Kernel timing wants the launches of one stream.
     const size_t vectors = sizeof(double) * 2 * (size_t)h->dim * B * 4;
-    bool two = load_any_stream && first.fuse && rows > (size_t)B && vectors <= ctx->spare_bytes && !ctx->timing;
+    bool two = load_any_stream && (first.fuse || first.pairs) && rows > (size_t)B && vectors <= ctx->spare_bytes && !ctx->timing;
     std::unique_ptr<BatchRunner> other;
     struct Joined {  // nothing of the second chain runs once its buffers are freed
         hipStream_t s = nullptr;

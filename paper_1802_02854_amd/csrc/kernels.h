@@ -53,6 +53,9 @@ struct ShiftState {
 
 constexpr int kR = 8;               // elements per thread in the blocked H v
 constexpr int kBlock = 256;         // threads per block of the vector kernels
+constexpr int kMaxRows = 32768;     // rows of one launch (grid y)
+constexpr int kGatherSites = 18;    // largest N that single vectors run one element per thread
+constexpr int kPairBits = 19;       // largest log2(sequences * 2^N) of the two-launch Lanczos step
 constexpr int kMaxGrid = 4096;      // blocks of the grid-stride vector kernels
 constexpr int kChunk = 512;         // elements per wave in the blocked H v (64 lanes x 8)
 constexpr int kTile = 8192;         // elements per workgroup tile staged in LDS (128 KiB)
@@ -122,8 +125,8 @@ void device_checks_read(unsigned int out[3], bool clear);
 // the index it was given (0) to out_dev[0]; nothing in the release build
 void device_checks_selftest(uint32_t *out_dev, hipStream_t s);
 
-// w = H v (natural order, one vector)
-void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s);
+// w = H v (natural order, n_rhs vectors stride doubles apart)
+void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s, int n_rhs = 1, size_t stride = 0);
 
 // A stack of B independent sequences run through the multi-pass kernels in one
 // grid (sequence r in blockIdx.y): sequence r's vectors start r*vs doubles after
@@ -175,6 +178,16 @@ struct FinAlpha {
     int astride;
     int k;
 };
+// Step k in two launches, for small stacks whose H v runs one element per thread:
+//   launch_lanczos_pair_a: u_k, and before it beta of step k-1 from fb (every workgroup
+//       reduces its partials; the state goes from st to st_out);
+//   launch_lanczos_b with fa: alpha_k from its partials, then w_k.
+// The partials of alpha and of the norm are in two buffers: a launch reads one and
+// writes the other.
+bool lanczos_pairs(const HvOp &op, int B);
+void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
+                           SeqState *st, double *partials, int first_step, hipStream_t s, const FinBeta *fb,
+                           SeqState *st_out, int B = 1, size_t vs = 0);
 bool alpha_in_fused_pass();  // the fused first pass finalises the previous alpha
 // true when launch_lanczos_a_rest can run the beta finalisation of step k-1 as one
 // more workgroup column of its first (middle) pass: plans of three or more passes;
@@ -197,8 +210,9 @@ void launch_finalize_alpha(SeqState *st, const double *partials, int nparts, dou
                            int k, hipStream_t s, int B = 1, int astride = 0);
 // second half: w_k = u - alpha_k v_k in place of u; partial sums of ||w_k||^2
 // (vec_grid of them).  B > 1: vectors vs doubles apart, partials 2*vec_grid apart.
+// fa: alpha_k is summed here first.
 void launch_lanczos_b(uint32_t dim, const double *Wcur, double *U, SeqState *st,
-                      double *partials, hipStream_t s, int B = 1, size_t vs = 0);
+                      double *partials, hipStream_t s, int B = 1, size_t vs = 0, const FinAlpha *fa = nullptr);
 // beta_{k+1}, inv_{k+1}, breakdown test and the multi-shift update of step k.
 // rtol > 0: the sequence also stops (done) once the largest Galerkin residual over
 // the shifts, per unit right-hand side, is <= rtol.

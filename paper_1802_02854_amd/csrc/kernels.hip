@@ -227,10 +227,12 @@ int hv_mode(const HvOp &op)
     int best = dim >= (uint32_t)kTile ? 2 : (dim >= (uint32_t)kChunk ? 1 : 0);
     if (g_hv_mode == 3) return multi ? 3 : best;
     if (g_hv_mode >= 0) return g_hv_mode <= best ? g_hv_mode : best;
-    // by size: the multi-pass form once a vector outgrows the caches (measured: also with
-    // 5 passes it beats the single-kernel tiled form, 11.9 against 16.9 ms at 28 sites,
-    // 48.5 against 81.8 ms at 30)
-    if (multi && op.P.n_sites >= 18) return 3;
+    // by size: one element per thread while a vector fits in an XCD's L2 (4 MiB, 18 sites;
+    // the measurements are at k_hv_simple), the multi-pass form above (also with 5 passes
+    // it beats the single-kernel tiled form, 11.9 against 16.9 ms at 28 sites, 48.5 against
+    // 81.8 ms at 30)
+    if (op.P.n_sites <= kGatherSites) return 0;
+    if (multi) return 3;
     return best;
 }
 
@@ -316,28 +318,43 @@ __device__ __forceinline__ void st_h(double2 *p, double2 a)
 }
 
 // ---------------------------------------------------------------------------
-// (H v)[x] by the contract, one element: D from integer bond-parity sums, then
-// one fma per bond in list order.
+constexpr int kGather = 8;  // partner loads in flight per thread
+
+// C bonds from bond b on of one element, their partner loads all in flight at once.
+template <int C>
+__device__ __forceinline__ void hv_bonds(const HvParams &P, int b, uint32_t x, uint64_t par,
+                                         const double2 *__restrict__ v, double &re, double &im)
+{
+    double2 vy[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) vy[i] = v[FTK_IDX(x ^ P.mask[b + i], 0, 1u << P.n_sites, 1)];
+    const uint32_t anti = (uint32_t)(par >> b);
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        const double amp = (anti >> i) & 1u ? P.aa[b + i] : P.ap[b + i];
+        re = fma(amp, vy[i].x, re);
+        im = fma(amp, vy[i].y, im);
+    }
+}
+
+// (H v)[x] by the contract, one element: D from the bond parities, then one fma per
+// bond in list order.
 __device__ __forceinline__ void hv_at(const HvParams &P, uint32_t x, const double2 *__restrict__ v,
                                       double &re, double &im, double2 &vx)
 {
-    int s_all = 0, s_z = 0;
-    for (int b = 0; b < P.n_bonds; ++b) {
-        const int s = (((x >> P.bi[b]) ^ (x >> P.bj[b])) & 1u) ? -1 : 1;
-        s_all += s;
-        if (P.isz[b]) s_z += s;
-    }
-    const double D = fma(P.kq, (double)s_z, P.jq * (double)s_all);
     vx = v[x];
+    uint64_t par = 0;
+    for (int l = 0; l < P.n_sites; ++l)
+        if ((x >> l) & 1u) par ^= P.smask[l];
+    const int s_all = P.n_bonds - 2 * __popcll(par);
+    const int s_z = __popcll(P.zmask) - 2 * __popcll(par & P.zmask);
+    const double D = fma(P.kq, (double)s_z, P.jq * (double)s_all);
     re = D * vx.x;
     im = D * vx.y;
-    for (int b = 0; b < P.n_bonds; ++b) {
-        const bool anti = ((x >> P.bi[b]) ^ (x >> P.bj[b])) & 1u;
-        const double amp = anti ? P.aa[b] : P.ap[b];
-        const double2 vy = v[FTK_IDX(x ^ P.mask[b], 0, 1u << P.n_sites, 1)];
-        re = fma(amp, vy.x, re);
-        im = fma(amp, vy.y, im);
-    }
+    int b = 0;
+    for (; b + kGather <= P.n_bonds; b += kGather) hv_bonds<kGather>(P, b, x, par, v, re, im);
+    for (; b + 4 <= P.n_bonds; b += 4) hv_bonds<4>(P, b, x, par, v, re, im);
+    for (; b < P.n_bonds; ++b) hv_bonds<1>(P, b, x, par, v, re, im);
 }
 
 // Blocked form: the 8 elements xb + 64 e (xb has bits 6..8 clear).
@@ -426,7 +443,7 @@ __device__ __forceinline__ void offdiag_block(const HvParams &P, uint32_t xb, ui
 struct EpiApply {
     static constexpr bool kReduces = false;  // no per-workgroup partial sums
     double2 *w;
-    __device__ void select(int, size_t, int) {}
+    __device__ void select(int r, size_t vs, int) { w += r * vs; }
     __device__ bool active() const { return true; }
     __device__ void init() {}
     __device__ void prepare(int) {}
@@ -463,18 +480,33 @@ struct EpiTaylor {
     __device__ void finish() {}
 };
 
-// one element per thread (small clusters)
+// One element per thread, partners from global memory, kGather of them in flight: a
+// small cluster's vector is in the L2s, and what an apply takes is the latency of its
+// chain of loads, shortest with one element in each of the most threads (the forms with
+// eight elements per thread have 1/8 of the wavefronts and a chain of loads each).  us
+// per apply at 12 / 14 / 16 / 18 / 20 sites: 10.4 / 18.6 / 24.1 / 28.5 / 39.1 tiled, -  / -
+// / 17.0 / 19.4 / 35.8 multi-pass, 5.7 / 5.7 / 5.7 / 10.5 / 34 here (up to 16 sites the
+// host's launch); workgroups of 512 and 1024 or 16 loads in flight are no faster.  From 20
+// sites the caches' bandwidth bounds it (the gathers of 20 sites come at 15 TB/s).
 template <class Epi>
-__global__ void __launch_bounds__(kBlock) k_hv_simple(HvParams P, const double2 *__restrict__ v, Epi epi)
+__global__ void __launch_bounds__(kBlock) k_hv_simple(HvParams P, const double2 *__restrict__ v, size_t vs, Epi epi)
 {
-    if (!epi.active()) return;
     const uint32_t dim = 1u << P.n_sites;
-    epi.init();
-    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
+    // sequence or row blockIdx.y
+    v += blockIdx.y * vs;
+    epi.select(blockIdx.y, vs, 2 * gridDim.x);
+    if (!epi.active()) return;
+    epi.prepare(blockIdx.y);
+    for (uint32_t x0 = blockIdx.x * kBlock; x0 < dim; x0 += gridDim.x * kBlock) {
+        const uint32_t x = x0 + threadIdx.x;
         double re, im;
-        double2 vx;
-        hv_at(P, x, v, re, im, vx);
-        epi(x, re, im, vx);
+        double2 vx, in;
+        if (x < dim) {
+            in = epi.load(x);
+            hv_at(P, x, v, re, im, vx);
+        }
+        if (x0 == blockIdx.x * kBlock && !epi.template begin<kBlock>(blockIdx.y)) return;
+        if (x < dim) epi.apply(x, re, im, vx, in);
     }
     epi.template finish<kBlock>();
 }
@@ -860,15 +892,26 @@ void launch_hv(const HvOp &op, const double *v, Epi epi, hipStream_t s)
         hipLaunchKernelGGL(k_hv_blocked<Epi>, dim3(grid), dim3(kBlock), 0, s, P, (const double2 *)v, epi);
         break;
     default:
-        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(grid), dim3(kBlock), 0, s, P, (const double2 *)v, epi);
+        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(grid), dim3(kBlock), 0, s, P, (const double2 *)v, (size_t)0, epi);
     }
 }
 
-void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s)
+void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s, int n_rhs, size_t stride)
 {
     EpiApply e;
     e.w = (double2 *)w;
-    launch_hv(op, v, e, s);
+    if (hv_mode(op) == 0) {  // all rows in one launch
+        for (int r = 0; r < n_rhs; r += kMaxRows) {
+            hipLaunchKernelGGL(k_hv_simple<EpiApply>, dim3(hv_grid(op), std::min(kMaxRows, n_rhs - r)), dim3(kBlock), 0,
+                               s, op.P, (const double2 *)(v + r * stride), stride / 2, e);
+            e.w += kMaxRows * (stride / 2);
+        }
+        return;
+    }
+    for (int r = 0; r < n_rhs; ++r) {
+        launch_hv(op, v + r * stride, e, s);
+        e.w += stride / 2;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -994,6 +1037,34 @@ void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, d
         launch_hv(op, Wcur, e, s);
 }
 
+// u = H v_k - beta_k v_{k-1} for the two-launch form
+void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
+                           SeqState *st, double *partials, int first_step, hipStream_t s, const FinBeta *fb,
+                           SeqState *st_out, int B, size_t vs)
+{
+    EpiLanczosADev e;
+    e.Wprev = (const double2 *)Wprev;
+    e.U = (double2 *)U;
+    e.vout = (double2 *)vout;
+    e.partials = partials;
+    e.st = st;
+    e.first = first_step;
+    e.fin = fb ? 2 : 0;
+    e.st_out = st_out;
+    if (fb) e.fb = *fb;
+    hipLaunchKernelGGL(k_hv_simple<EpiLanczosADev>, dim3(hv_grid(op), B), dim3(kBlock), 0, s, op.P,
+                       (const double2 *)Wcur, vs / 2, e);
+}
+
+// us per step and sequence, multi-pass against two launches of one element per thread:
+// 16 sites, 1 sequence: 35 (46 in four launches, tiled) / 13.4, stack of 4: 7.5 / 5.1, of
+// 8: 4.3 / 3.7, of 16: 2.4 / 3.0; 18 sites, 2: 17.9 / 16.7, 4: 10.3 / 13.7.  A larger stack fills
+// the chip with multi-pass tiles, whose bonds read LDS.
+bool lanczos_pairs(const HvOp &op, int B)
+{
+    return g_fuse_fin && hv_mode(op) == 0 && ((size_t)B << op.P.n_sites) <= ((size_t)1 << kPairBits);
+}
+
 bool lanczos_fusable(const HvOp &op) { return hv_mode(op) == 3 && op.plan.n_passes >= 2; }
 bool lanczos_stackable(const HvOp &op) { return op.plan.n_passes >= 2 && op.scratch != nullptr; }
 
@@ -1038,14 +1109,27 @@ void launch_lanczos_a_rest(const HvOp &op, const double *Wcur, const double *Wpr
 
 __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double2 *__restrict__ Wcur,
                                                       double2 *__restrict__ U, SeqState *st,
-                                                      double *partials, size_t vs)
+                                                      double *partials, size_t vs, FinAlpha fa, int use_fa)
 {
     Wcur += blockIdx.y * vs;
     U += blockIdx.y * vs;
     st += blockIdx.y;
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
     if (st->done) return;
-    const double c2 = -(st->alpha_cur * st->inv_cur);
+    double c2;
+    if (use_fa) {
+        // alpha_k as k_finalize_alpha forms it, in every workgroup; workgroup 0 records it
+        const double inv = st->inv_cur;
+        const double a = uniform(inv * reduce_partials(fa.partials + (size_t)blockIdx.y * 2 * fa.nparts, fa.nparts));
+        if (threadIdx.x == 0 && blockIdx.x == 0) {
+            if (!isfinite(a)) st->numeric_error = 1;
+            st->alpha_cur = a;
+            fa.alpha_out[(size_t)blockIdx.y * fa.astride + fa.k] = a;
+        }
+        c2 = -(a * inv);
+    } else {
+        c2 = -(st->alpha_cur * st->inv_cur);
+    }
     double hi = 0.0, lo = 0.0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 wc = Wcur[x];
@@ -1141,10 +1225,10 @@ void launch_finalize_alpha(SeqState *st, const double *partials, int nparts, dou
 }
 
 void launch_lanczos_b(uint32_t dim, const double *Wcur, double *U, SeqState *st,
-                      double *partials, hipStream_t s, int B, size_t vs)
+                      double *partials, hipStream_t s, int B, size_t vs, const FinAlpha *fa)
 {
     hipLaunchKernelGGL(k_lanczos_b, dim3(vec_grid(dim), B), dim3(kBlock), 0, s, dim, (const double2 *)Wcur,
-                       (double2 *)U, st, partials, vs / 2);
+                       (double2 *)U, st, partials, vs / 2, fa ? *fa : FinAlpha{nullptr, 0, nullptr, 0, 0}, fa ? 1 : 0);
 }
 
 void launch_finalize_beta(SeqState *st, const double *partials, int nparts, double *beta_out,

@@ -1,0 +1,67 @@
+"""H v with one element per thread, all rows in one launch, and the two-launch Lanczos step
+built on it, bit for bit against the forms they stand in for."""
+import numpy as np
+import pytest
+
+from seeded_inputs import SUPERCELLS
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import paper_1802_02854_amd as ftk
+    return ftk, ftk.Context(0), torch
+
+
+def _forced(ftk, mode, f):
+    ftk.set_tuning("hv_variant", mode)
+    try:
+        return f()
+    finally:
+        ftk.set_tuning("hv_variant", -1)
+
+
+@pytest.mark.parametrize("N,rows,pad,layout", [(6, 3, 5, False), (8, 1, 0, True), (12, 5, 64, False), (16, 3, 7, False),
+                                               (18, 2, 0, True)])
+def test_rows_in_one_launch(env, N, rows, pad, layout):
+    """Rows a padded stride apart; the padding of the output is left alone."""
+    ftk, ctx, torch = env
+    print(f"gather rows N={N} rows={rows}", flush=True)
+    cl = ftk.honeycomb_cluster(*SUPERCELLS[N])
+    h = ftk.Hamiltonian(ctx, ftk.plan_layout(cl)[0] if layout else cl, -1.0, 0.1)
+    v = torch.randn(rows, (1 << N) + pad, dtype=torch.complex128, generator=torch.Generator().manual_seed(N)).cuda()
+    v = v[:, :1 << N]
+
+    def apply():
+        base = torch.full((rows, (1 << N) + pad), 7.0 + 0j, dtype=torch.complex128, device="cuda")
+        h.apply(v, out=base[:, :1 << N])
+        torch.cuda.synchronize()
+        return base.cpu()
+    a = apply()
+    for mode in (1, 2, 3):  # as many of them as the size has
+        assert torch.equal(a, _forced(ftk, mode, apply))
+    if pad:
+        assert bool((a[:, 1 << N:] == 7.0).all())
+    assert bool((a[:, :1 << N].abs().sum(1) > 0).all())
+
+
+@pytest.mark.parametrize("N,B,n,tol", [(16, 1, 1, 0.0), (16, 1, 14, 0.0), (16, 8, 9, 0.0), (16, 4, 40, 1e-3), (18, 2, 7, 0.0)])
+def test_two_launch_steps(env, N, B, n, tol):
+    """Green's sequences, the last batch ragged, and the filter runs before them."""
+    ftk, ctx, torch = env
+    print(f"pairs N={N} B={B} n={n} tol={tol}", flush=True)
+    cl = ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[N]))[0]
+
+    def run():
+        h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
+        st = ftk.TypicalStates(h, seed=3, n_vectors=1, betas=[0.0, 1.0], E_b=None, eps=None, L=3, M=4, n_steps=11)
+        sp = ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-3, 3, 30), eta=0.3, n_steps=n, rhs_block=B,
+                          resid_tol=tol, alpha_mask=3)
+        return (*st.scalars(), *sp.raw(), sp.norms())
+    two = run()
+    for x, y in zip(two, _forced(ftk, 3, run)):
+        assert np.array_equal(x, y)
+    assert np.abs(two[-2]).max() > 0
