@@ -202,6 +202,59 @@ struct Arena {
 // asks for another form
 bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
 
+// A few sequences of the larger resident sizes go through the whole chip together, two
+// launches a step, instead of one workgroup each, which leaves most compute units idle.
+// us per step of 1 / 8 / 32 sequences, one workgroup each against together (three bonds
+// per site): 12 sites 13.0 / 13.1 / 13.5, 12.4 / 12.8 / 16.9; 13 sites 41.8 / 41.9 / 42.0,
+// 12.9 / 13.9 / 22.2; 14 sites 49.8 / 49.8 / 49.8, 13.0 / 17.6 / 35.2.
+constexpr int kFewSeqs = kMaxBatch;
+bool few_sequences(const HvOp &op, size_t n_seq)
+{
+    return op.P.n_sites >= kFewMinSites && n_seq <= (size_t)kFewSeqs && lanczos_pairs(op, (int)n_seq);
+}
+struct FewScratch {  // second states and partial sums of those
+    SeqState *st;
+    double *pa, *pb;
+    void parts(Arena &m, size_t dim)
+    {
+        m.part(&st, kFewSeqs);
+        m.part(&pa, 2 * (size_t)kFewSeqs * vec_grid((uint32_t)dim));
+        m.part(&pb, 2 * (size_t)kFewSeqs * vec_grid((uint32_t)dim));
+    }
+};
+// The steps of run (resident.h) that way: rows row0 .. row0 + n_seq - 1, vectors started
+// from start (one after the other) at k0 = 0.  A residual test per step is not done here.
+void run_few(const HvOp &op, const ResidentRun &run, const FewScratch &f, int row0, const double *start,
+             const BatchShifts &shifts, int n_seq, hipStream_t s)
+{
+    const size_t dim = (size_t)1 << op.P.n_sites, vs = 4 * dim;
+    const int nparts = vec_grid((uint32_t)dim);
+    double *W[2] = {run.carry, run.carry + 2 * dim};
+    double *al = run.alpha + (size_t)row0 * run.stride, *be = run.beta + (size_t)row0 * run.stride;
+    SeqState *st[2] = {run.st + row0, f.st};
+    int slot = (run.k1 - run.k0 - 1) & 1;  // the state changes place at every step but the first, ending at run.st
+    if (run.k0 == 0) {
+        launch_start_stacked(n_seq, (uint32_t)dim, start, f.pa, st[slot], shifts, s);
+        HIP_CHECK(hipMemcpy2DAsync(W[1], 8 * vs, start, 16 * dim, 16 * dim, n_seq, hipMemcpyDeviceToDevice, s));
+    } else if (slot) {
+        HIP_CHECK(hipMemcpyAsync(st[1], st[0], sizeof(SeqState) * n_seq, hipMemcpyDeviceToDevice, s));
+    }
+    for (int k = run.k0; k < run.k1; ++k) {
+        const double *cur = W[(k + 1) % 2];
+        double *out = W[k % 2];
+        double *vout = run.vout ? run.vout + (size_t)(k - run.k0) * 2 * dim : nullptr;
+        SeqState *now = st[slot];
+        const FinBeta fb{now, f.pb, nparts, be, k - 1, run.tol, nullptr, nullptr, 0, 0.0, 0.0, run.stride};
+        if (k > run.k0) slot ^= 1;
+        launch_lanczos_pair_a(op, cur, out, out, vout, now, f.pa, k == 0, s, k > run.k0 ? &fb : nullptr, st[slot], n_seq,
+                              vs, run.vstride);
+        const FinAlpha fa{f.pa, nparts, al, run.stride, k};
+        launch_lanczos_b((uint32_t)dim, cur, out, st[slot], f.pb, s, n_seq, vs, &fa);
+    }
+    launch_finalize_beta(st[slot], f.pb, nparts, be, run.k1 - 1, run.tol, nullptr, nullptr, 0, 0.0, s, 0.0, n_seq,
+                         run.stride);
+}
+
 }  // namespace
 
 struct ftk_hamiltonian {
@@ -1005,6 +1058,9 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             m.part(&coef, group * 2 * st->L * n);
             m.part(&al_d, group * n);
             m.part(&be_d, group * n);
+            FewScratch fs;
+            const bool few = few_sequences(h->op, group);
+            if (few) fs.parts(m, dim);
             m.allocate(ctx);
             std::vector<ResidentSeq> hseq(group);
             std::vector<SeqState> hstate(group);
@@ -1022,6 +1078,14 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             run.stride = n;
             run.tol = 1e-12 * h->table.norm_bound;
             run.carry = carry;
+            auto steps_of = [&](size_t cnt) {
+                ctx->timed("filter_run", true, [&] {
+                    if (few)
+                        run_few(h->op, run, fs, 0, phib, BatchShifts{}, (int)cnt, s);
+                    else
+                        launch_resident(h->op, run, (int)cnt, s);
+                });
+            };
             int have = -1;  // the vector in phi0
             for (size_t g0 = 0; g0 < pairs; g0 += group) {
                 const size_t cnt = std::min(group, pairs - g0);
@@ -1034,7 +1098,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                 run.k0 = 0;
                 run.k1 = n;
                 run.vout = nullptr;
-                ctx->timed("filter_run", true, [&] { launch_resident(h->op, run, (int)cnt, s); });
+                steps_of(cnt);
                 HIP_CHECK(hipMemcpyAsync(hstate.data(), state, cnt * sizeof(SeqState), hipMemcpyDeviceToHost, s));
                 HIP_CHECK(hipMemcpyAsync(hal.data(), al_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
                 HIP_CHECK(hipMemcpyAsync(hbe.data(), be_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
@@ -1056,7 +1120,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                 for (int k0 = 0; k0 < most; k0 += nb) {
                     run.k0 = k0;
                     run.k1 = std::min(most, k0 + nb);
-                    ctx->timed("filter_run", true, [&] { launch_resident(h->op, run, (int)cnt, s); });
+                    steps_of(cnt);
                     for (size_t i = 0; i < cnt; ++i)
                         if (steps[i] > k0)
                             launch_accumulate(dim, vbuf + i * nb * cplx, std::min(nb, steps[i] - k0),
@@ -1696,7 +1760,8 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     const size_t dim = h->dim, rows = work.size();
     if (rows == 0) return empty_green(nseq, n, nw);
     const bool stop = rtol > 0.0;
-    const bool carried = stop || h->n_sites >= kResidentPlanes;
+    const bool few = !stop && few_sequences(h->op, rows);
+    const bool carried = few || stop || h->n_sites >= kResidentPlanes;
     const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
     const size_t slab = std::min(rows, std::max<size_t>(1, ctx->spare_bytes / per));
 
@@ -1719,6 +1784,8 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     m.part(&chi, slab * dim * 2);
     m.part(&carry, carried ? slab * dim * 4 : 0);
     m.part(&sh, stop ? slab * nw : 0);
+    FewScratch fs;
+    if (few) fs.parts(m, dim);
     m.allocate(ctx);
 
     std::vector<ResidentSeq> hseq(rows);
@@ -1749,11 +1816,16 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
         run.carry = carried ? carry : nullptr;
         ShiftRun shifts{st + r0, al + r0 * n, be + r0 * n, n, om, nw, eta, g + r0 * 2 * nw};
         launch_start_vectors(h->n_sites, ops.sq ? kLoadSpin : kLoadPair, run, cnt, s);
+        BatchShifts bs{};
+        for (int r = 0; few && r < cnt; ++r) bs.re[r] = work[r0 + r].Em;
         ctx->timed("lanczos_block", true, [&] {
             for (int k = 0; k < n; k = run.k1) {
                 run.k0 = k;
                 run.k1 = stop ? std::min(n, k + kResidentCheck) : n;
-                launch_resident(h->op, run, cnt, s);
+                if (few)
+                    run_few(h->op, run, fs, (int)r0, chi, bs, cnt, s);
+                else
+                    launch_resident(h->op, run, cnt, s);
                 if (stop) launch_shifts_until(shifts, run.k0, run.k1, rtol, sh, cnt, s);
             }
             if (!stop) launch_shifts(shifts, cnt, s);

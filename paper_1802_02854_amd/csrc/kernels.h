@@ -180,14 +180,15 @@ struct FinAlpha {
 };
 // Step k in two launches, for small stacks whose H v runs one element per thread:
 //   launch_lanczos_pair_a: u_k, and before it beta of step k-1 from fb (every workgroup
-//       reduces its partials; the state goes from st to st_out);
+//       reduces its partials; the state goes from st to st_out); vout rows vout_stride
+//       doubles apart (0: vs);
 //   launch_lanczos_b with fa: alpha_k from its partials, then w_k.
 // The partials of alpha and of the norm are in two buffers: a launch reads one and
 // writes the other.
 bool lanczos_pairs(const HvOp &op, int B);
 void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
                            SeqState *st, double *partials, int first_step, hipStream_t s, const FinBeta *fb,
-                           SeqState *st_out, int B = 1, size_t vs = 0);
+                           SeqState *st_out, int B = 1, size_t vs = 0, size_t vout_stride = 0);
 bool alpha_in_fused_pass();  // the fused first pass finalises the previous alpha
 // true when launch_lanczos_a_rest can run the beta finalisation of step k-1 as one
 // more workgroup column of its first (middle) pass: plans of three or more passes;

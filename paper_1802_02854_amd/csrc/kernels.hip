@@ -928,6 +928,7 @@ struct EpiLanczosADev {
     const double2 *Wprev;
     double2 *U;
     double2 *vout;
+    size_t vo;  // entries between sequences' vout (0: as the other vectors)
     double *partials;
     const SeqState *st;
     int first;
@@ -942,7 +943,7 @@ struct EpiLanczosADev {
     {
         Wprev += r * vs;
         U += r * vs;
-        if (vout) vout += r * vs;
+        if (vout) vout += r * (vo ? vo : vs);
         st += r;
         if (st_out) st_out += r;
         partials += (size_t)r * pstride;
@@ -1026,6 +1027,7 @@ void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, d
     e.Wprev = (const double2 *)Wprev;
     e.U = (double2 *)U;
     e.vout = (double2 *)vout;
+    e.vo = 0;
     e.partials = partials;
     e.st = st;
     e.first = first_step;
@@ -1040,12 +1042,13 @@ void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, d
 // u = H v_k - beta_k v_{k-1} for the two-launch form
 void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U, double *vout,
                            SeqState *st, double *partials, int first_step, hipStream_t s, const FinBeta *fb,
-                           SeqState *st_out, int B, size_t vs)
+                           SeqState *st_out, int B, size_t vs, size_t vout_stride)
 {
     EpiLanczosADev e;
     e.Wprev = (const double2 *)Wprev;
     e.U = (double2 *)U;
     e.vout = (double2 *)vout;
+    e.vo = vout_stride / 2;
     e.partials = partials;
     e.st = st;
     e.first = first_step;
@@ -1098,6 +1101,7 @@ void launch_lanczos_a_rest(const HvOp &op, const double *Wcur, const double *Wpr
     e.Wprev = (const double2 *)Wprev;
     e.U = (double2 *)U;
     e.vout = (double2 *)vout;
+    e.vo = 0;
     e.partials = partials;
     e.st = st;
     e.first = 0;

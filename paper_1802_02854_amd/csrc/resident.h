@@ -10,6 +10,7 @@ namespace ftk {
 constexpr int kResidentMinSites = 6;
 constexpr int kResidentMaxSites = 14;
 constexpr int kResidentPlanes = 13;  // from here on a plane at a time, with a carry buffer
+constexpr int kFewMinSites = 13;    // from here on a few sequences run in lockstep instead
 // whether sequences of op run resident (by size, unless a form of H v is forced)
 bool resident(const HvOp &op);
 

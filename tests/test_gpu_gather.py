@@ -65,3 +65,33 @@ def test_two_launch_steps(env, N, B, n, tol):
     for x, y in zip(two, _forced(ftk, 3, run)):
         assert np.array_equal(x, y)
     assert np.abs(two[-2]).max() > 0
+
+
+@pytest.mark.parametrize("N", [13, 14])
+def test_few_and_many_sequences(env, N):
+    """More sequences than run in lockstep (one workgroup each) and few, each row the same."""
+    ftk, ctx, torch = env
+    print(f"few N={N}", flush=True)
+    ij = sorted({(min(i, (i + d) % N), max(i, (i + d) % N)) for d in (1, 2, 3) for i in range(N)})
+    cl = ftk.Cluster(N, np.array([b[0] for b in ij], np.int32), np.array([b[1] for b in ij], np.int32),
+                     (np.arange(len(ij)) % 3).astype(np.int8), np.arange(2.0 * N).reshape(N, 2) ** 0.5)
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.07)
+    st = {}
+    for nv in (17, 2):  # 34 filter sequences, 4
+        st[nv] = ftk.TypicalStates(h, seed=4, n_vectors=nv, betas=[0.0, 0.8], E_b=None, eps=None, L=9, M=4, n_steps=8,
+                                   block_steps=3)
+    for s in range(2):
+        for a in range(2):
+            for x, y in zip(st[17].lanczos(s, a), st[2].lanczos(s, a)):
+                assert np.array_equal(x, y)
+            for m in (0, 4, 8):
+                assert np.array_equal(st[17].shell(s, a, m).cpu().numpy(), st[2].shell(s, a, m).cpu().numpy())
+    kw = dict(q_xy=[(0.3, 0.1)], omega=np.linspace(-3, 3, 40), eta=0.2, n_steps=21, rhs_block=1)
+    many = ftk.Spectrum(h, st[2], **kw)  # 2 x 2 x 9 x 3 = 108
+    few = ftk.Spectrum(h, st[2], shells=(3, 2), **kw)  # 24
+    for s in range(2):
+        for a in range(2):
+            for al in range(3):
+                for x, y in zip(many.lanczos(s, a, 3, al, 0), few.lanczos(s, a, 3, al, 0)):
+                    assert np.array_equal(x, y)
+    assert np.array_equal(many.raw()[0][:, :, 3], few.raw()[0][:, :, 3]) and np.abs(few.raw()[0]).max() > 0
