@@ -261,10 +261,15 @@ struct ftk_hamiltonian {
     ftk_ctx *ctx = nullptr;
     BondTable table;
     HvOp op;        // bond table, multi-pass plan and its scratch vector
-    DevBuf scratch;
+    DevBuf scratch, dev;  // dev: op.dev
     std::vector<double> site_xy;
     int n_sites = 0;
     uint32_t dim = 0;
+    ~ftk_hamiltonian()
+    {
+        // queued launches read dev; hipFree waits for them, a caller's free need not
+        if (ctx && ctx->free_fn) (void)hipStreamSynchronize(ctx->stream);
+    }
 };
 
 namespace {
@@ -631,6 +636,13 @@ ftk_status ftk_build_hamiltonian(ftk_ctx *ctx, const ftk_cluster *c, double K, d
             h->scratch = DevBuf(ctx, sizeof(double) * 2 * (size_t)h->dim);
             h->op.scratch = h->scratch.d();
         }
+        auto image = std::make_unique<HvDev>();
+        const size_t used = make_hv_dev(h->op.P, h->op.plan, *image);
+        HIP_CHECK(hipSetDevice(ctx->device));
+        h->dev = DevBuf(ctx, used);
+        HIP_CHECK(hipMemcpyAsync(h->dev.p, image.get(), used, hipMemcpyHostToDevice, ctx->stream));
+        HIP_CHECK(hipStreamSynchronize(ctx->stream));
+        h->op.dev = (const HvDev *)h->dev.p;
         h->site_xy.assign(c->site_xy, c->site_xy + 2 * c->n_sites);
         *out = h.release();
     });
@@ -1358,7 +1370,7 @@ struct BatchRunner {
         // per-step events only outside graph capture (a captured graph is timed as a whole)
         ctx->timed("lanczos_step", !capturing && (k & 7) == 1, [&] {
             if (B > 1 && !stacked) {
-                launch_lanczos_a_batch(B, op.P, cur, prv, out, q, partials.d(), k == 0, s);
+                launch_lanczos_a_batch(B, op, cur, prv, out, q, partials.d(), k == 0, s);
                 launch_finalize_alpha_batch(B, q, partials.d(), nparts_a, al.d(), n, k, s);
                 launch_lanczos_b_batch(B, dim, cur, out, q, partials.d(), s);
                 launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nsh, eta,

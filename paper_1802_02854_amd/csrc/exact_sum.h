@@ -77,6 +77,13 @@ __device__ __forceinline__ void lane_sum(double &hi, double &lo)
     }
 }
 
+// The launch-invariant data behind p, read through the scalar cache.
+template <class T>
+__device__ __forceinline__ const T *constant(const T *p)
+{
+    return (const T *)(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
 // Barrier over LDS only: global stores (the recorded coefficients) stay in flight.
 __device__ __forceinline__ void lds_barrier()
 {

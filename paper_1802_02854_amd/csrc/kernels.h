@@ -10,15 +10,16 @@
 namespace ftk {
 
 // Bond table as passed to every H-applying kernel (by value, ~1 KB).
+constexpr int kBondSlots = 48;  // kMaxBonds in whole groups of 8
 struct HvParams {
     int n_sites;
     int n_bonds;
-    uint32_t mask[kMaxBonds];  // 2^i | 2^j
+    uint32_t mask[kBondSlots]; // 2^i | 2^j; 0 past the last bond
     uint8_t bi[kMaxBonds];
     uint8_t bj[kMaxBonds];
     uint8_t isz[kMaxBonds];    // 1 for z bonds
-    double ap[kMaxBonds];      // flip amplitude, parallel spins
-    double aa[kMaxBonds];      // flip amplitude, antiparallel spins
+    double ap[kBondSlots];     // flip amplitude, parallel spins
+    double aa[kBondSlots];     // flip amplitude, antiparallel spins
     uint32_t code[kMaxBonds];  // mask | bond type << 30
     double ap3[3], aa3[3];     // the amplitudes by bond type
     double jq, kq;             // J/4, K/4
@@ -54,7 +55,8 @@ struct ShiftState {
 constexpr int kR = 8;               // elements per thread in the blocked H v
 constexpr int kBlock = 256;         // threads per block of the vector kernels
 constexpr int kMaxRows = 32768;     // rows of one launch (grid y)
-constexpr int kGatherSites = 18;    // largest N that single vectors run one element per thread
+constexpr int kGatherSites = 18;    // largest N whose Lanczos steps run one element per thread
+constexpr int kApplySites = 20;     // and whose plain products and Taylor terms do
 constexpr int kPairBits = 19;       // largest log2(sequences * 2^N) of the two-launch Lanczos step
 constexpr int kMaxGrid = 4096;      // blocks of the grid-stride vector kernels
 constexpr int kChunk = 512;         // elements per wave in the blocked H v (64 lanes x 8)
@@ -72,6 +74,8 @@ constexpr int kPassBits = 12;
 constexpr int kPassTile = 1 << kPassBits;  // 4096 elements, 64 KiB of LDS
 constexpr int kPassThreads = 512;          // 8 waves x 64 lanes x kR elements
 constexpr int kMaxPasses = 6;
+constexpr int kTileBits = 9;               // two of them hold a tile's number
+static_assert(kMaxSites <= kPassBits + 2 * kTileBits, "tile numbers");
 constexpr int kPassMinSites = 16;          // smallest N given the scratch vector of the multi-pass form
 struct PassGeom {
     int b0, b1;                         // the segment: bonds [b0, b1)
@@ -80,7 +84,6 @@ struct PassGeom {
     uint8_t esite[3];                   // sites of tile bits 6..8 (register element e)
     uint8_t hsite[kMaxSites];           // sites of the tile-index bits
     uint32_t code[kMaxBonds];           // of bond b0 + i: its flip mask in tile bits | bond type << 30
-    uint8_t rev;                        // tiles in descending order (set per launch)
 };
 struct HvPlan {
     int n_passes = 0;  // 0: no multi-pass form (N <= kPassBits or too many segments)
@@ -89,10 +92,40 @@ struct HvPlan {
 };
 HvPlan make_hv_plan(const BondTable &t);
 
+// A part of a state index x and the bond parities of that part.
+struct IndexPart {
+    uint64_t par;
+    uint32_t x, pad;
+};
+// A pass as its kernels read it.
+struct PassDev {
+    int b0, b1;
+    uint32_t ebit[kR];           // as in PassGeom, and the parities of its three bits
+    uint64_t epar[3];
+    uint32_t code[kBondSlots];
+    IndexPart thread[kPassThreads];
+    // the tile's part, from the low and the high 9 bits of its number
+    IndexPart tile_lo[1 << kTileBits], tile_hi[1 << kTileBits];
+};
+// What kernels read of an operator, laid out once in device memory.  As kernel
+// arguments its 2.3 KB were written by the host at every launch and came cold to every
+// workgroup, which then formed its threads' and tiles' index parts a site at a time (us
+// per Lanczos step so / from here: 14 sites, one sequence 13.8 / 12.1; 16 sites, stack of
+// 16, 39.8 / 36.3; 18 sites, stack of 4, 41.4 / 36.7; 20 sites, one 52.0 / 46.6, stack of
+// 16 494 / 471; an apply of 24 sites 358 / 346).  The resident kernels read P once for a
+// whole sequence and take it as an argument (12 sites 13.0, from here 13.2).
+struct HvDev {
+    HvParams P;
+    PassDev pass[kMaxPasses];  // the plan's n_passes of them
+};
+// the device image of an operator: bytes of it that are used, written to the host copy d
+size_t make_hv_dev(const HvParams &P, const HvPlan &plan, HvDev &d);
+
 // Everything an H-applying launch needs: bond table, pass plan, scratch vector.
 struct HvOp {
     HvParams P;
     HvPlan plan;
+    const HvDev *dev = nullptr;  // device copy of P and the plan's passes
     double *scratch = nullptr;  // 2^N complex; needed by the multi-pass form
     int pass_grid = 0;          // persistent workgroups of a reducing multi-pass launch
                                 // (0: set_pass_grid's value, else two per compute unit)
@@ -287,7 +320,7 @@ void launch_start_batch(int B, uint32_t dim, const double *chi, double *partials
 // start of a stack of B sequences whose vectors are 2*dim doubles apart
 void launch_start_stacked(int B, uint32_t dim, const double *chi, double *partials, SeqState *st,
                           const BatchShifts &shift_re, hipStream_t s);
-void launch_lanczos_a_batch(int B, const HvParams &P, const double *Wcur, const double *Wprev, double *U,
+void launch_lanczos_a_batch(int B, const HvOp &op, const double *Wcur, const double *Wprev, double *U,
                             SeqState *st, double *partials, int first, hipStream_t s);
 void launch_finalize_alpha_batch(int B, SeqState *st, const double *partials, int nparts, double *alpha_out,
                                  int n_max, int k, hipStream_t s);

@@ -136,6 +136,30 @@ HvPlan make_hv_plan(const BondTable &t)
     return best;
 }
 
+size_t make_hv_dev(const HvParams &P, const HvPlan &plan, HvDev &d)
+{
+    d.P = P;
+    for (int p = 0; p < plan.n_passes; ++p) {
+        const PassGeom &g = plan.pass[p];
+        PassDev &q = d.pass[p];
+        std::memset(&q, 0, sizeof(q));
+        q.b0 = g.b0;
+        q.b1 = g.b1;
+        std::copy(g.ebit, g.ebit + kR, q.ebit);
+        for (int j = 0; j < 3; ++j) q.epar[j] = P.smask[g.esite[j]];
+        std::copy(g.code, g.code + (g.b1 - g.b0), q.code);
+        auto part = [&](IndexPart &t, const uint8_t *site, int bits, uint32_t i) {
+            for (int j = 0; j < bits; ++j)
+                if (i >> j & 1u) t.x |= 1u << site[j], t.par ^= P.smask[site[j]];
+        };
+        for (uint32_t t = 0; t < kPassThreads; ++t) part(q.thread[t], g.ysite, 9, t);
+        const int nh = P.n_sites - kPassBits, lo = nh < kTileBits ? nh : kTileBits;
+        for (uint32_t t = 0; t < 1u << lo; ++t) part(q.tile_lo[t], g.hsite, lo, t);
+        for (uint32_t t = 0; t < 1u << (nh - lo); ++t) part(q.tile_hi[t], g.hsite + lo, nh - lo, t);
+    }
+    return offsetof(HvDev, pass) + sizeof(PassDev) * (size_t)plan.n_passes;
+}
+
 int vec_grid(uint32_t dim)
 {
     uint32_t g = (dim + kBlock - 1) / kBlock;
@@ -236,6 +260,14 @@ int hv_mode(const HvOp &op)
     return best;
 }
 
+// Without reductions and a first half step to fuse with, one element per thread is ahead
+// two sites further: 20 sites 24 us, multi-pass 36 (42 with natural labels); a Lanczos
+// step 66, multi-pass 50; 24 sites 880, multi-pass 360.
+static int product_mode(const HvOp &op)
+{
+    return g_hv_mode < 0 && op.P.n_sites <= kApplySites ? 0 : hv_mode(op);
+}
+
 int pass_grid_cap(const HvOp &op)
 {
     if (op.pass_grid > 0) return op.pass_grid;
@@ -318,43 +350,68 @@ __device__ __forceinline__ void st_h(double2 *p, double2 a)
 }
 
 // ---------------------------------------------------------------------------
-constexpr int kGather = 8;  // partner loads in flight per thread
-
-// C bonds from bond b on of one element, their partner loads all in flight at once.
-template <int C>
-__device__ __forceinline__ void hv_bonds(const HvParams &P, int b, uint32_t x, uint64_t par,
-                                         const double2 *__restrict__ v, double &re, double &im)
-{
-    double2 vy[C];
+// The partners of kGather bonds from bond b on, all loads in flight at once (the masks past
+// the last bond are 0: the element itself).
+constexpr int kGather = 8;
+static_assert(kBondSlots % kGather == 0 && kBondSlots >= kMaxBonds, "whole groups of bonds");
+struct Gather {
+    double2 vy[kGather];
+    __device__ __forceinline__ void load(const HvParams &P, int b, uint32_t x, const double2 *__restrict__ v)
+    {
 #pragma unroll
-    for (int i = 0; i < C; ++i) vy[i] = v[FTK_IDX(x ^ P.mask[b + i], 0, 1u << P.n_sites, 1)];
-    const uint32_t anti = (uint32_t)(par >> b);
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-        const double amp = (anti >> i) & 1u ? P.aa[b + i] : P.ap[b + i];
-        re = fma(amp, vy[i].x, re);
-        im = fma(amp, vy[i].y, im);
+        for (int i = 0; i < kGather; ++i) vy[i] = v[FTK_IDX(x ^ P.mask[b + i], 0, 1u << P.n_sites, 1)];
     }
-}
+    template <bool ALL>
+    __device__ __forceinline__ void use(const HvParams &P, int b, uint64_t par, double &re, double &im) const
+    {
+        const uint32_t anti = (uint32_t)(par >> b);
+#pragma unroll
+        for (int i = 0; i < kGather; ++i) {
+            if (!ALL && b + i >= P.n_bonds) break;
+            const double p = P.ap[b + i], q = P.aa[b + i];  // both by scalar loads, not one by a vector load
+            const double amp = (anti >> i) & 1u ? q : p;
+            re = fma(amp, vy[i].x, re);
+            im = fma(amp, vy[i].y, im);
+        }
+    }
+    __device__ __forceinline__ void use(const HvParams &P, int b, uint64_t par, double &re, double &im) const
+    {
+        if (b + kGather <= P.n_bonds)
+            use<true>(P, b, par, re, im);
+        else
+            use<false>(P, b, par, re, im);
+    }
+};
 
 // (H v)[x] by the contract, one element: D from the bond parities, then one fma per
-// bond in list order.
+// bond in list order.  The next group's loads are issued before a group is used; the
+// parities come from the masks, a group of them per scalar load (per site from smask,
+// a load and its wait for each, they took 1.5 us of an apply of 16 sites).
 __device__ __forceinline__ void hv_at(const HvParams &P, uint32_t x, const double2 *__restrict__ v,
                                       double &re, double &im, double2 &vx)
 {
+    const int n = P.n_bonds;
+    Gather a, c;
     vx = v[x];
+    a.load(P, 0, x, v);
     uint64_t par = 0;
-    for (int l = 0; l < P.n_sites; ++l)
-        if ((x >> l) & 1u) par ^= P.smask[l];
-    const int s_all = P.n_bonds - 2 * __popcll(par);
+    for (int b = 0; b < n; b += kGather) {
+        uint32_t anti = 0;
+#pragma unroll
+        for (int i = 0; i < kGather; ++i) anti |= (__popc(x & P.mask[b + i]) & 1u) << i;
+        par |= (uint64_t)anti << b;
+    }
+    const int s_all = n - 2 * __popcll(par);
     const int s_z = __popcll(P.zmask) - 2 * __popcll(par & P.zmask);
     const double D = fma(P.kq, (double)s_z, P.jq * (double)s_all);
     re = D * vx.x;
     im = D * vx.y;
-    int b = 0;
-    for (; b + kGather <= P.n_bonds; b += kGather) hv_bonds<kGather>(P, b, x, par, v, re, im);
-    for (; b + 4 <= P.n_bonds; b += 4) hv_bonds<4>(P, b, x, par, v, re, im);
-    for (; b < P.n_bonds; ++b) hv_bonds<1>(P, b, x, par, v, re, im);
+    for (int b = 0; b < n; b += 2 * kGather) {
+        if (b + kGather < n) c.load(P, b + kGather, x, v);
+        a.use(P, b, par, re, im);
+        if (b + 2 * kGather < n) a.load(P, b + 2 * kGather, x, v);
+        if (b + kGather < n) c.use(P, b + kGather, par, re, im);
+    }
 }
 
 // Blocked form: the 8 elements xb + 64 e (xb has bits 6..8 clear).
@@ -480,17 +537,18 @@ struct EpiTaylor {
     __device__ void finish() {}
 };
 
-// One element per thread, partners from global memory, kGather of them in flight: a
-// small cluster's vector is in the L2s, and what an apply takes is the latency of its
+// One element per thread, partners from global memory, up to 2 kGather of them in flight:
+// a small cluster's vector is in the L2s, and what an apply takes is the latency of its
 // chain of loads, shortest with one element in each of the most threads (the forms with
 // eight elements per thread have 1/8 of the wavefronts and a chain of loads each).  us
-// per apply at 12 / 14 / 16 / 18 / 20 sites: 10.4 / 18.6 / 24.1 / 28.5 / 39.1 tiled, -  / -
-// / 17.0 / 19.4 / 35.8 multi-pass, 5.7 / 5.7 / 5.7 / 10.5 / 34 here (up to 16 sites the
-// host's launch); workgroups of 512 and 1024 or 16 loads in flight are no faster.  From 20
-// sites the caches' bandwidth bounds it (the gathers of 20 sites come at 15 TB/s).
+// per apply at 12 / 14 / 16 / 18 / 20 sites: 10.4 / 18.6 / 24.1 / 28.5 / 39.1 tiled, - /
+// - / 17.0 / 19.4 / 35.8 multi-pass, 5.3 / 5.3 / 5.3 / 7.1 / 24 here (up to 16 sites the
+// host's launch); workgroups of 512 and 1024 or 16 loads in one group are no faster.  From
+// 20 sites the caches' bandwidth bounds it (the gathers of 20 sites come at 21 TB/s).
 template <class Epi>
-__global__ void __launch_bounds__(kBlock) k_hv_simple(HvParams P, const double2 *__restrict__ v, size_t vs, Epi epi)
+__global__ void __launch_bounds__(kBlock) k_hv_simple(const HvDev *__restrict__ dev, const double2 *__restrict__ v, size_t vs, Epi epi)
 {
+    const HvParams &P = constant(dev)->P;
     const uint32_t dim = 1u << P.n_sites;
     // sequence or row blockIdx.y
     v += blockIdx.y * vs;
@@ -513,8 +571,9 @@ __global__ void __launch_bounds__(kBlock) k_hv_simple(HvParams P, const double2 
 
 // 8 elements per thread, partners from global memory
 template <class Epi>
-__global__ void __launch_bounds__(kBlock) k_hv_blocked(HvParams P, const double2 *__restrict__ v, Epi epi)
+__global__ void __launch_bounds__(kBlock) k_hv_blocked(const HvDev *__restrict__ dev, const double2 *__restrict__ v, Epi epi)
 {
+    const HvParams &P = constant(dev)->P;
     const uint32_t dim = 1u << P.n_sites;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t waves = gridDim.x * (kBlock / 64);
@@ -542,8 +601,9 @@ __global__ void __launch_bounds__(kBlock) k_hv_blocked(HvParams P, const double2
 
 // 16 waves per workgroup, the 8192-element tile staged in LDS (128 KiB)
 template <class Epi>
-__global__ void __launch_bounds__(kTileThreads) k_hv_tiled(HvParams P, const double2 *__restrict__ v, Epi epi)
+__global__ void __launch_bounds__(kTileThreads) k_hv_tiled(const HvDev *__restrict__ dev, const double2 *__restrict__ v, Epi epi)
 {
+    const HvParams &P = constant(dev)->P;
     extern __shared__ double2 tile[];
     const uint32_t dim = 1u << P.n_sites;
     const uint32_t ntiles = dim / kTile;
@@ -593,24 +653,21 @@ struct PassThread {
     uint32_t yb;   // tile index of element 0
     uint32_t xy;   // the thread's part of the state index
     uint64_t par;  // bond parities of that part
-    __device__ PassThread(const HvParams &P, const PassGeom &g) : xy(0), par(0)
+    __device__ PassThread(const PassDev &g)
     {
         const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         yb = FTK_IDX(lane | (wave << 9), 7u << kRegShift, kPassTile, 7);
-#pragma unroll
-        for (int j = 0; j < 6; ++j)
-            if ((lane >> j) & 1u) xy |= 1u << g.ysite[j], par ^= P.smask[g.ysite[j]];
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            if ((wave >> j) & 1u) xy |= 1u << g.ysite[6 + j], par ^= P.smask[g.ysite[6 + j]];
+        const IndexPart t = g.thread[threadIdx.x];
+        xy = t.x;
+        par = t.par;
     }
 };
 
 // D(x) = K/4 s_z + J/4 s_all of a thread's elements, s = (bonds) - 2 (antiparallel bonds),
 // counted on the bond-parity vector: tile-index part, thread part, register-element part
-__device__ __forceinline__ void pass_diagonal(const HvParams &P, const PassGeom &g, uint64_t par, double (&D)[kR])
+__device__ __forceinline__ void pass_diagonal(const HvParams &P, const PassDev &g, uint64_t par, double (&D)[kR])
 {
-    const uint64_t pe6 = P.smask[g.esite[0]], pe7 = P.smask[g.esite[1]], pe8 = P.smask[g.esite[2]];
+    const uint64_t pe6 = g.epar[0], pe7 = g.epar[1], pe8 = g.epar[2];
     const int nz = __popcll(P.zmask);
 #pragma unroll
     for (int e = 0; e < kR; ++e) {
@@ -640,9 +697,11 @@ __device__ __forceinline__ void pass_bonds(double (&acc)[2 * kR], const Bonds &b
 // partial sums in `part`; LAST hands the finished (H v)[x] to the epilogue, whose inputs
 // are read while the bonds run; otherwise the partial sums go back to `part`.
 template <class Epi, bool FIRST, bool LAST, bool SH>
-__global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeom g, const double2 *__restrict__ v,
+__global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(const HvDev *__restrict__ dev, int pass, int rev, const double2 *__restrict__ v,
                                                          double2 *part, Epi epi, size_t vs)
 {
+    const HvParams &P = constant(dev)->P;
+    const PassDev &g = constant(dev)->pass[pass];
     extern __shared__ double planes[];
     // the tile workgroups are gx = gridDim.x columns; a middle pass of a Lanczos step
     // may carry one more column that finalises beta of the previous half step
@@ -663,22 +722,17 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeo
     if (!epi.active()) return;
     const int hbits = P.n_sites - kPassBits;
     const uint32_t ntiles = 1u << hbits;
-    const PassThread t(P, g);
+    const PassThread t(g);
     const Bonds bonds(P, g.code, g.b1 - g.b0, t.par >> g.b0);
     const uint32_t tile_at = lds_address(planes);
     double *re = planes + t.yb, *im = re + kPassTile;
     if (LAST) epi.prepare(blockIdx.y);
     bool begun = false;
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gx) {
-        const uint32_t tt = g.rev ? ntiles - 1u - ti : ti;
-        uint32_t xh = 0;
-        uint64_t par = t.par;
-        for (int j = 0; j < hbits; ++j)
-            if ((tt >> j) & 1u) {
-                xh |= 1u << g.hsite[j];
-                if (FIRST) par ^= P.smask[g.hsite[j]];
-            }
-        uint32_t xb = xh | t.xy;
+        const uint32_t tt = rev ? ntiles - 1u - ti : ti;
+        const IndexPart &tl = g.tile_lo[tt & ((1u << kTileBits) - 1u)], &th = g.tile_hi[tt >> kTileBits];
+        const uint64_t par = t.par ^ tl.par ^ th.par;
+        uint32_t xb = tl.x | th.x | t.xy;
         double acc[2 * kR];
         double2 o[kR];
 #pragma unroll
@@ -735,12 +789,14 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(HvParams P, PassGeo
 // with the partial sums of ||w_{k-1}||^2; the tile of w_{k-1} then goes through
 // the first segment of bonds like any first pass.
 template <bool SH>
-__global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(HvParams P, PassGeom g, double2 *__restrict__ W,
+__global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *__restrict__ dev, int pass, int rev, double2 *__restrict__ W,
                                                                   const double2 *__restrict__ Wm2,
                                                                   double2 *__restrict__ part, SeqState *st,
                                                                   double *partials, size_t vs, FinAlpha fa,
                                                                   int use_fa)
 {
+    const HvParams &P = constant(dev)->P;
+    const PassDev &g = constant(dev)->pass[pass];
     extern __shared__ double planes[];
     W += blockIdx.y * vs;
     Wm2 += blockIdx.y * vs;
@@ -757,7 +813,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(HvParams P, P
     if (use_fa && (int)threadIdx.x < fa.nparts) ah = pa[2 * threadIdx.x], al = pa[2 * threadIdx.x + 1];
     const int hbits = P.n_sites - kPassBits;
     const uint32_t ntiles = 1u << hbits;
-    const PassThread t(P, g);
+    const PassThread t(g);
     const Bonds bonds(P, g.code, g.b1 - g.b0, t.par >> g.b0);
     const uint32_t tile_at = lds_address(planes);
     double *re = planes + t.yb, *im = re + kPassTile;
@@ -777,12 +833,10 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(HvParams P, P
     }
     double hi = 0.0, lo = 0.0;
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gridDim.x) {
-        const uint32_t tt = g.rev ? ntiles - 1u - ti : ti;
-        uint32_t xh = 0;
-        uint64_t par = t.par;
-        for (int j = 0; j < hbits; ++j)
-            if ((tt >> j) & 1u) xh |= 1u << g.hsite[j], par ^= P.smask[g.hsite[j]];
-        uint32_t xb = xh | t.xy;
+        const uint32_t tt = rev ? ntiles - 1u - ti : ti;
+        const IndexPart &tl = g.tile_lo[tt & ((1u << kTileBits) - 1u)], &th = g.tile_hi[tt >> kTileBits];
+        const uint64_t par = t.par ^ tl.par ^ th.par;
+        uint32_t xb = tl.x | th.x | t.xy;
         // w_{k-1} to the tile (W, Wm2 and part are distinct buffers).  No global store
         // among these loads: on gfx950 loads and stores share one counter, so a store
         // issued between two elements' loads would make the second element wait for it.
@@ -840,8 +894,7 @@ static void launch_passes_h(const HvOp &op, int p0, const double *v, Epi epi, hi
     double2 *part = (double2 *)(scratch ? scratch : op.scratch);
     const size_t vs2 = vs / 2;  // in complex entries
     for (int p = p0; p < np; ++p) {
-        PassGeom g = op.plan.pass[p];
-        g.rev = SH && p == 0;
+        const int rev = SH && p == 0;
         const bool first = p == 0, last = p == np - 1;
         dim3 grid = (last && Epi::kReduces) || !g_full_grid ? grid_red : grid_full;
         Epi ep = epi;
@@ -851,16 +904,16 @@ static void launch_passes_h(const HvOp &op, int p0, const double *v, Epi epi, hi
             if (ep.fin == 1) grid.x += 1;
         }
         if (first && last)
-            hipLaunchKernelGGL((k_hv_pass<Epi, true, true, SH>), grid, dim3(kPassThreads), lds, s, op.P, g,
+            hipLaunchKernelGGL((k_hv_pass<Epi, true, true, SH>), grid, dim3(kPassThreads), lds, s, op.dev, p, rev,
                                (const double2 *)v, part, ep, vs2);
         else if (first)
-            hipLaunchKernelGGL((k_hv_pass<Epi, true, false, SH>), grid, dim3(kPassThreads), lds, s, op.P, g,
+            hipLaunchKernelGGL((k_hv_pass<Epi, true, false, SH>), grid, dim3(kPassThreads), lds, s, op.dev, p, rev,
                                (const double2 *)v, part, ep, vs2);
         else if (last)
-            hipLaunchKernelGGL((k_hv_pass<Epi, false, true, SH>), grid, dim3(kPassThreads), lds, s, op.P, g,
+            hipLaunchKernelGGL((k_hv_pass<Epi, false, true, SH>), grid, dim3(kPassThreads), lds, s, op.dev, p, rev,
                                (const double2 *)v, part, ep, vs2);
         else
-            hipLaunchKernelGGL((k_hv_pass<Epi, false, false, SH>), grid, dim3(kPassThreads), lds, s, op.P, g,
+            hipLaunchKernelGGL((k_hv_pass<Epi, false, false, SH>), grid, dim3(kPassThreads), lds, s, op.dev, p, rev,
                                (const double2 *)v, part, ep, vs2);
     }
 }
@@ -878,21 +931,21 @@ static void launch_passes(const HvOp &op, int p0, const double *v, Epi epi, hipS
 template <class Epi>
 void launch_hv(const HvOp &op, const double *v, Epi epi, hipStream_t s)
 {
-    const HvParams &P = op.P;
     const int grid = hv_grid(op);
-    switch (hv_mode(op)) {
+    switch (Epi::kReduces ? hv_mode(op) : product_mode(op)) {
     case 3:
         launch_passes(op, 0, v, epi, s);
         break;
     case 2:
-        hipLaunchKernelGGL(k_hv_tiled<Epi>, dim3(grid), dim3(kTileThreads), kTile * sizeof(double2), s, P,
+        hipLaunchKernelGGL(k_hv_tiled<Epi>, dim3(grid), dim3(kTileThreads), kTile * sizeof(double2), s, op.dev,
                            (const double2 *)v, epi);
         break;
     case 1:
-        hipLaunchKernelGGL(k_hv_blocked<Epi>, dim3(grid), dim3(kBlock), 0, s, P, (const double2 *)v, epi);
+        hipLaunchKernelGGL(k_hv_blocked<Epi>, dim3(grid), dim3(kBlock), 0, s, op.dev, (const double2 *)v, epi);
         break;
     default:
-        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(grid), dim3(kBlock), 0, s, P, (const double2 *)v, (size_t)0, epi);
+        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(vec_grid(1u << op.P.n_sites)), dim3(kBlock), 0, s, op.dev,
+                           (const double2 *)v, (size_t)0, epi);
     }
 }
 
@@ -900,10 +953,10 @@ void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s, i
 {
     EpiApply e;
     e.w = (double2 *)w;
-    if (hv_mode(op) == 0) {  // all rows in one launch
+    if (product_mode(op) == 0) {  // all rows in one launch
         for (int r = 0; r < n_rhs; r += kMaxRows) {
-            hipLaunchKernelGGL(k_hv_simple<EpiApply>, dim3(hv_grid(op), std::min(kMaxRows, n_rhs - r)), dim3(kBlock), 0,
-                               s, op.P, (const double2 *)(v + r * stride), stride / 2, e);
+            hipLaunchKernelGGL(k_hv_simple<EpiApply>, dim3(vec_grid(1u << op.P.n_sites), std::min(kMaxRows, n_rhs - r)),
+                               dim3(kBlock), 0, s, op.dev, (const double2 *)(v + r * stride), stride / 2, e);
             e.w += kMaxRows * (stride / 2);
         }
         return;
@@ -1055,7 +1108,7 @@ void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wpr
     e.fin = fb ? 2 : 0;
     e.st_out = st_out;
     if (fb) e.fb = *fb;
-    hipLaunchKernelGGL(k_hv_simple<EpiLanczosADev>, dim3(hv_grid(op), B), dim3(kBlock), 0, s, op.P,
+    hipLaunchKernelGGL(k_hv_simple<EpiLanczosADev>, dim3(hv_grid(op), B), dim3(kBlock), 0, s, op.dev,
                        (const double2 *)Wcur, vs / 2, e);
 }
 
@@ -1076,15 +1129,13 @@ void launch_lanczos_fused_first(const HvOp &op, double *W, const double *Wm2, Se
 {
     double *part = sk.scratch ? sk.scratch : op.scratch;
     const FinAlpha f = fa ? *fa : FinAlpha{nullptr, 0, nullptr, 0, 0};
-    PassGeom g = op.plan.pass[0];
     const bool sh = stream_hints(op, sk.B);
-    g.rev = sh;
     const dim3 grid(hv_grid(op, sk.B), sk.B);
     if (sh)
-        hipLaunchKernelGGL(k_hv_pass_fused<true>, grid, dim3(kPassThreads), kPassTile * sizeof(double2), s, op.P, g,
+        hipLaunchKernelGGL(k_hv_pass_fused<true>, grid, dim3(kPassThreads), kPassTile * sizeof(double2), s, op.dev, 0, 1,
                            (double2 *)W, (const double2 *)Wm2, (double2 *)part, st, partials, sk.vs / 2, f, fa ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_hv_pass_fused<false>, grid, dim3(kPassThreads), kPassTile * sizeof(double2), s, op.P, g,
+        hipLaunchKernelGGL(k_hv_pass_fused<false>, grid, dim3(kPassThreads), kPassTile * sizeof(double2), s, op.dev, 0, 0,
                            (double2 *)W, (const double2 *)Wm2, (double2 *)part, st, partials, sk.vs / 2, f, fa ? 1 : 0);
 }
 
@@ -1613,8 +1664,9 @@ struct EpiLanczosABatch {
 };
 
 template <int B, class Epi>
-__global__ void __launch_bounds__(kBlock) k_hv_batch(HvParams P, const double2 *__restrict__ v, Epi epi)
+__global__ void __launch_bounds__(kBlock) k_hv_batch(const HvDev *__restrict__ dev, const double2 *__restrict__ v, Epi epi)
 {
+    const HvParams &P = constant(dev)->P;
     using G = BatchGeom<B>;
     const uint32_t dim = 1u << P.n_sites;
     const uint32_t lane = threadIdx.x & 63;
@@ -1672,7 +1724,7 @@ int vec_batch_grid(uint32_t dim, int B)
 }
 
 template <int B>
-static void launch_lanczos_a_batch_t(const HvParams &P, const double *Wcur, const double *Wprev, double *U,
+static void launch_lanczos_a_batch_t(const HvOp &op, const double *Wcur, const double *Wprev, double *U,
                                      SeqState *st, double *partials, int first, hipStream_t s)
 {
     EpiLanczosABatch<B> e;
@@ -1681,19 +1733,19 @@ static void launch_lanczos_a_batch_t(const HvParams &P, const double *Wcur, cons
     e.partials = partials;
     e.st = st;
     e.first = first;
-    const uint32_t dim = 1u << P.n_sites;
-    hipLaunchKernelGGL((k_hv_batch<B, EpiLanczosABatch<B>>), dim3(hv_batch_grid(dim, B)), dim3(kBlock), 0, s, P,
+    const uint32_t dim = 1u << op.P.n_sites;
+    hipLaunchKernelGGL((k_hv_batch<B, EpiLanczosABatch<B>>), dim3(hv_batch_grid(dim, B)), dim3(kBlock), 0, s, op.dev,
                        (const double2 *)Wcur, e);
 }
 
-void launch_lanczos_a_batch(int B, const HvParams &P, const double *Wcur, const double *Wprev, double *U,
+void launch_lanczos_a_batch(int B, const HvOp &op, const double *Wcur, const double *Wprev, double *U,
                             SeqState *st, double *partials, int first, hipStream_t s)
 {
     switch (B) {
-    case 2: launch_lanczos_a_batch_t<2>(P, Wcur, Wprev, U, st, partials, first, s); break;
-    case 4: launch_lanczos_a_batch_t<4>(P, Wcur, Wprev, U, st, partials, first, s); break;
-    case 8: launch_lanczos_a_batch_t<8>(P, Wcur, Wprev, U, st, partials, first, s); break;
-    case 16: launch_lanczos_a_batch_t<16>(P, Wcur, Wprev, U, st, partials, first, s); break;
+    case 2: launch_lanczos_a_batch_t<2>(op, Wcur, Wprev, U, st, partials, first, s); break;
+    case 4: launch_lanczos_a_batch_t<4>(op, Wcur, Wprev, U, st, partials, first, s); break;
+    case 8: launch_lanczos_a_batch_t<8>(op, Wcur, Wprev, U, st, partials, first, s); break;
+    case 16: launch_lanczos_a_batch_t<16>(op, Wcur, Wprev, U, st, partials, first, s); break;
     default: break;
     }
 }
