@@ -358,6 +358,7 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * vectors of such a launch take up to 256 MiB of device memory.  From 16 sites
  * on, batches whose vectors (4 per sequence) come to at most 256 MiB run in two
  * chains on two streams, with the buffers of both (not while kernel timing is on).
+ * Shifted COCG runs as many sequences in lockstep as fit in 256 MiB, up to 32.
  * resid_tol > 0 truncates each sequence at the first step k <= n_steps after
  * which the largest Galerkin residual over the shifts, per unit right-hand side
  * (|p_k| beta_{k+1} / |d_k|), is <= resid_tol (Sec. V, truncation of the CG

@@ -1944,7 +1944,7 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     return out;
 }
 
-// Shifted COCG sequences, one at a time: load(chi, lam, item) writes the right-hand
+// Shifted COCG sequences in lockstep batches: load(chi, lam, item) writes the right-hand
 // side chi and, when it returns true, a projection vector lam (else lam = chi); the
 // n-step complex-symmetric Lanczos loop with the per-shift recurrences, then
 // g = <lam|x(z)>.
@@ -1970,34 +1970,88 @@ CocgOut run_cocg(const ftk_hamiltonian *h, int n, const double *omega, int nw, d
     out.c.assign((size_t)nseq * (n + 1) * 2, 0.0);
     out.states.assign(nseq, CocgState{});
     if (work.empty()) return out;
-    DevBuf chi(ctx, vb), lamb(ctx, vb), W0(ctx, vb), W1(ctx, vb), Hw(ctx, vb), st(ctx, sizeof(CocgState)),
-        sh(ctx, sizeof(CocgShift) * (size_t)nw), om(ctx, sizeof(double) * nw),
-        partials(ctx, sizeof(double) * 10 * (size_t)kMaxGrid), ad(ctx, sizeof(double) * 2 * (size_t)n),
-        bd(ctx, sizeof(double) * 2 * (size_t)n), cd(ctx, sizeof(double) * 2 * (size_t)(n + 1)),
-        gd(ctx, sizeof(double) * 2 * (size_t)nw);
-    HIP_CHECK(hipMemcpyAsync(om.p, omega, sizeof(double) * nw, hipMemcpyHostToDevice, s));
-    double *W[2] = {W0.d(), W1.d()};
-    for (const GreenItem &q : work) {
-        const double *lam = load(chi.d(), lamb.d(), q) ? lamb.d() : chi.d();
-        HIP_CHECK(hipMemsetAsync(ad.p, 0, ad.n, s));
-        HIP_CHECK(hipMemsetAsync(bd.p, 0, bd.n, s));
-        HIP_CHECK(hipMemsetAsync(cd.p, 0, cd.n, s));
-        launch_cocg_start(dim, chi.d(), lam, partials.d(), (CocgState *)st.p, (CocgShift *)sh.p, nw, q.Em, cd.d(), s);
-        for (int k = 0; k < n; ++k) {
-            const double *cur = k == 0 ? chi.d() : W[(k - 1) % 2];
-            const double *prv = k == 1 ? chi.d() : W[k % 2];
-            launch_cocg_step(h->op, lam, cur, prv, W[k % 2], Hw.d(), partials.d(), (CocgState *)st.p,
-                             (CocgShift *)sh.p, om.d(), nw, eta, k, tol, rtol, seed_tol, ad.d(), bd.d(), cd.d(), s);
+    // As many sequences in lockstep as the call may take memory for, at least one: a step
+    // of one is bound by launches and by the scalar kernel between the vector halves
+    // (18 sites, six sequences of 150 steps of 500 shifts: 57.0 ms in turn, five kernels a
+    // step, 12.4 together in three)
+    const bool hw = cocg_work_vectors(h->op);
+    size_t most = std::min(work.size(), std::max<size_t>(1, ctx->spare_bytes / (vb * (hw ? 5 : 4))));
+    most = std::min<size_t>(most, kMaxBatch);
+    Arena m;
+    CocgBatch q{};
+    double *chi, *lamb, *W[2], *om, *gd;
+    auto buffers = [&](size_t B) {
+        const size_t cplx = 2 * (size_t)dim;
+        m = Arena();
+        m.part(&chi, B * cplx);
+        m.part(&lamb, B * cplx);
+        m.part(&W[0], B * cplx);
+        m.part(&W[1], B * cplx);
+        m.part(&q.Hw, hw ? B * cplx : 0);
+        m.part(&q.pa, B * 10 * vec_grid(dim));
+        m.part(&q.pb, B * 10 * vec_grid(dim));
+        m.part(&q.st, B);
+        m.part(&q.sh, B * nw);
+        m.part(&om, nw);
+        m.part(&q.a, B * 2 * n);
+        m.part(&q.b, B * 2 * n);
+        m.part(&q.c, B * 2 * (n + 1));
+        m.part(&gd, B * 2 * nw);
+        m.allocate(ctx);
+    };
+    try {
+        buffers(most);
+    } catch (const Error &e) {
+        if (e.status != FTK_ENOMEM || most == 1) throw;
+        buffers(most = 1);
+    }
+    HIP_CHECK(hipMemcpyAsync(om, omega, sizeof(double) * nw, hipMemcpyHostToDevice, s));
+    q.n = n;
+    q.omega = om;
+    q.n_omega = nw;
+    q.eta = eta;
+    q.tol = tol;
+    q.rtol = rtol;
+    q.seed_tol = seed_tol;
+    std::vector<double> hg(most * nw * 2), ha(most * n * 2), hb(most * n * 2), hc(most * (n + 1) * 2);
+    std::vector<CocgState> hs(most);
+    for (size_t w0 = 0; w0 < work.size(); w0 += most) {
+        const size_t cnt = std::min(most, work.size() - w0);
+        BatchShifts bs{};
+        q.B = (int)cnt;
+        q.lam = chi;
+        for (size_t r = 0; r < cnt; ++r) {
+            bs.re[r] = work[w0 + r].Em;
+            if (load(chi + r * 2 * dim, lamb + r * 2 * dim, work[w0 + r])) q.lam = lamb;  // all of them or none
         }
-        launch_cocg_finish((const CocgState *)st.p, (const CocgShift *)sh.p, nw, gd.d(), s);
-        const size_t i = (size_t)q.index;
-        HIP_CHECK(hipMemcpyAsync(out.g.data() + i * nw * 2, gd.p, gd.n, hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipMemcpyAsync(out.a.data() + i * n * 2, ad.p, ad.n, hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipMemcpyAsync(out.b.data() + i * n * 2, bd.p, bd.n, hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipMemcpyAsync(out.c.data() + i * (n + 1) * 2, cd.p, cd.n, hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipMemcpyAsync(&out.states[i], st.p, sizeof(CocgState), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipMemsetAsync(q.a, 0, sizeof(double) * cnt * 2 * n, s));
+        HIP_CHECK(hipMemsetAsync(q.b, 0, sizeof(double) * cnt * 2 * n, s));
+        HIP_CHECK(hipMemsetAsync(q.c, 0, sizeof(double) * cnt * 2 * (n + 1), s));
+        launch_cocg_start(dim, chi, q, bs, s);
+        for (int k = 0; k < n; ++k) {
+            const double *cur = k == 0 ? chi : W[(k - 1) % 2];
+            const double *prv = k == 1 ? chi : W[k % 2];
+            launch_cocg_step(h->op, q, cur, prv, W[k % 2], k, s);
+        }
+        launch_cocg_finish(q, gd, s);
+        auto down = [&](void *dst, const void *src, size_t bytes) {
+            HIP_CHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+        };
+        down(hg.data(), gd, sizeof(double) * cnt * nw * 2);
+        down(ha.data(), q.a, sizeof(double) * cnt * n * 2);
+        down(hb.data(), q.b, sizeof(double) * cnt * n * 2);
+        down(hc.data(), q.c, sizeof(double) * cnt * (n + 1) * 2);
+        down(hs.data(), q.st, sizeof(CocgState) * cnt);
         HIP_CHECK(hipStreamSynchronize(s));
-        if (out.states[i].numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in shifted COCG coefficients");
+        for (size_t r = 0; r < cnt; ++r) {
+            const size_t i = (size_t)work[w0 + r].index;
+            std::copy_n(hg.begin() + r * nw * 2, (size_t)nw * 2, out.g.begin() + i * nw * 2);
+            std::copy_n(ha.begin() + r * n * 2, (size_t)n * 2, out.a.begin() + i * n * 2);
+            std::copy_n(hb.begin() + r * n * 2, (size_t)n * 2, out.b.begin() + i * n * 2);
+            std::copy_n(hc.begin() + r * (n + 1) * 2, (size_t)(n + 1) * 2, out.c.begin() + i * (n + 1) * 2);
+            out.states[i] = hs[r];
+            if (hs[r].numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in shifted COCG coefficients");
+        }
     }
     HIP_CHECK(hipGetLastError());
     return out;

@@ -5,12 +5,13 @@
 
 #include <cstdint>
 
+#include "exact_sum.h"
 #include "kernels.h"
 
 namespace ftk {
 
 // Shifted COCG with seed switching (complex-symmetric Lanczos basis + per-shift
-// scalar recurrences; kernels.hip).  One sequence per run.
+// scalar recurrences; cocg.hip), per sequence.
 struct CocgState {
     double invr, invi;  // inv_k = 1/b_k (1/delta_0 at k = 0)
     double ipr, ipi;    // inv_{k-1}
@@ -36,17 +37,85 @@ struct CocgShift {
     double gr, gi;    // <chi|x_k> of the shift
     double res;       // residual 2-norm after the shift's last update (+inf before the first)
 };
-// state from the right-hand side chi and the projection vector lam (= chi for a
-// spectrum); c_out[0..1] = c_0
-void launch_cocg_start(uint32_t dim, const double *chi, const double *lam, double *partials, CocgState *st,
-                       CocgShift *sh, int n_omega, double shift_re, double *c_out, hipStream_t s);
+// A batch of B sequences run in lockstep: sequence r's vectors lie 2 * 2^N doubles after
+// sequence r - 1's, its state, shifts and recorded scalars one row further.
+struct CocgBatch {
+    int B, n;                 // sequences; steps (rows of a and b: n entries, of c: n + 1)
+    const double *lam;        // the projection vectors (chi for a spectrum)
+    double *Hw;               // work vectors, needed by cocg_work_vectors(op)
+    double *pa, *pb;          // partial sums, B * 10 * vec_grid doubles each
+    CocgState *st;
+    CocgShift *sh;
+    const double *omega;
+    int n_omega;
+    double eta, tol, rtol, seed_tol;
+    double *a, *b, *c;        // a_k, b_{k+1}, c_{k+1} (c_0 at the start), complex
+};
+// H v one element per thread takes the first half step as its epilogue; the other forms
+// leave H w in work vectors.
+bool cocg_work_vectors(const HvOp &op);
+// the first half step in that epilogue (kernels.hip): u over U, partial sums to pa
+void launch_hv_cocg(const HvOp &op, const double *Wcur, const double *Wprev, double *U, const CocgState *st,
+                    double *pa, int first, int B, hipStream_t s);
+// states from the right-hand sides chi and E_m
+void launch_cocg_start(uint32_t dim, const double *chi, const CocgBatch &q, const BatchShifts &shift_re, hipStream_t s);
 // step k: Wcur = w_{k-1} (chi at k = 0), Wprev = w_{k-2} (chi at k = 1, unused at
-// k = 0); U (may be Wprev) receives w_k; Hw is a work vector; a_out[2k], b_out[2k] =
-// a_k, b_{k+1}, c_out[2k+2] = c_{k+1}; partials holds 10 vec_grid doubles
-void launch_cocg_step(const HvOp &op, const double *lam, const double *Wcur, const double *Wprev, double *U,
-                      double *Hw, double *partials, CocgState *st, CocgShift *sh, const double *omega, int n_omega,
-                      double eta, int k, double tol, double rtol, double seed_tol, double *a_out, double *b_out,
-                      double *c_out, hipStream_t s);
-void launch_cocg_finish(const CocgState *st, const CocgShift *sh, int n_omega, double *g, hipStream_t s);
+// k = 0); U (may be Wprev) receives w_k
+void launch_cocg_step(const HvOp &op, const CocgBatch &q, const double *Wcur, const double *Wprev, double *U, int k,
+                      hipStream_t s);
+// g [B][n_omega]
+void launch_cocg_finish(const CocgBatch &q, double *g, hipStream_t s);
+
+#if defined(__HIPCC__)
+// complex products of the vector updates: (fma(ar, br, -(ai bi)), fma(ar, bi, ai br))
+__device__ __forceinline__ void cmul_v(double ar, double ai, double br, double bi, double &r, double &i)
+{
+    r = fma(ar, br, -(ai * bi));
+    i = fma(ar, bi, ai * br);
+}
+
+// up to 5 exact sums per block, (hi, lo) pairs in partials[(block * 5 + j) * 2]
+template <int NS>
+__device__ __forceinline__ void write_partials5(double *partials, double (&hi)[NS], double (&lo)[NS])
+{
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        block_pair<kBlock>(hi[j], lo[j]);
+        if (threadIdx.x == 0) {
+            partials[(blockIdx.x * 5 + j) * 2] = hi[j];
+            partials[(blockIdx.x * 5 + j) * 2 + 1] = lo[j];
+        }
+        __syncthreads();
+    }
+}
+
+// u = (H w_{k-1}) inv_k + c1 w_{k-2}, one element; its part of the sums of w_{k-1}^T u
+struct CocgA {
+    double ir, ii, c1r, c1i;
+    double hi[2] = {0, 0}, lo[2] = {0, 0};
+    __device__ __forceinline__ void init(const CocgState *st)
+    {
+        ir = st->invr, ii = st->invi;
+        cmul_v(st->bkr, st->bki, st->ipr, st->ipi, c1r, c1i);
+        c1r = -c1r;
+        c1i = -c1i;
+    }
+    __device__ __forceinline__ double2 operator()(double hr, double him, const double2 &wc, const double2 &wp, int first)
+    {
+        double tr, ti;
+        cmul_v(hr, him, ir, ii, tr, ti);
+        double ur = tr, ui = ti;
+        if (!first) {
+            ur = fma(c1r, wp.x, fma(-c1i, wp.y, tr));
+            ui = fma(c1r, wp.y, fma(c1i, wp.x, ti));
+        }
+        pair_prod(hi[0], lo[0], wc.x, ur);
+        pair_prod(hi[0], lo[0], -wc.y, ui);
+        pair_prod(hi[1], lo[1], wc.x, ui);
+        pair_prod(hi[1], lo[1], wc.y, ur);
+        return make_double2(ur, ui);
+    }
+};
+#endif
 
 }  // namespace ftk

@@ -29,12 +29,6 @@ namespace ftk {
 // (past convergence pi_j only grows, towards overflow once the Krylov space is
 // exhausted); the run ends once every shift is converged.
 
-// complex products of the vector updates: (fma(ar, br, -(ai bi)), fma(ar, bi, ai br))
-__device__ __forceinline__ void cmul_v(double ar, double ai, double br, double bi, double &r, double &i)
-{
-    r = fma(ar, br, -(ai * bi));
-    i = fma(ar, bi, ai * br);
-}
 // scalar complex arithmetic of the recurrences: plain products, Smith's division
 // (R. L. Smith, CACM 5, 435, 1962)
 __device__ __forceinline__ void cmul_s(double ar, double ai, double br, double bi, double &r, double &i)
@@ -86,21 +80,6 @@ __device__ __forceinline__ void csqrt_s(double x, double y, double &r, double &i
     }
 }
 
-// up to 5 exact sums per block, (hi, lo) pairs in partials[(block * 5 + j) * 2]
-template <int NS>
-__device__ __forceinline__ void write_partials5(double *partials, double (&hi)[NS], double (&lo)[NS])
-{
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        block_pair<kBlock>(hi[j], lo[j]);
-        if (threadIdx.x == 0) {
-            partials[(blockIdx.x * 5 + j) * 2] = hi[j];
-            partials[(blockIdx.x * 5 + j) * 2 + 1] = lo[j];
-        }
-        __syncthreads();
-    }
-}
-
 // sums over w of: Re w^T w = sum (w_r^2 - w_i^2), sum w_r w_i, <lam|w> (re, im), ||w||^2
 __device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &l, double (&hi)[5], double (&lo)[5])
 {
@@ -115,9 +94,13 @@ __device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &
     pair_prod(hi[4], lo[4], w.y, w.y);
 }
 
+// Sequence blockIdx.y of the batch in all of these.
 __global__ void __launch_bounds__(kBlock) k_cocg_start_sums(uint32_t dim, const double2 *__restrict__ w,
                                                             const double2 *__restrict__ lam, double *partials)
 {
+    w += (size_t)blockIdx.y * dim;
+    lam += (size_t)blockIdx.y * dim;
+    partials += (size_t)blockIdx.y * 10 * gridDim.x;
     double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 v = w[x];
@@ -127,47 +110,77 @@ __global__ void __launch_bounds__(kBlock) k_cocg_start_sums(uint32_t dim, const 
     write_partials5<5>(partials, hi, lo);
 }
 
-// u = (H w_{k-1}) inv_k + c1 w_{k-2} into U (U may be Wprev: each element is read
-// before it is written); partial sums of w_{k-1}^T u
+// u over U (U may be Wprev: each element is read before it is written) from H w_{k-1}
 __global__ void __launch_bounds__(kBlock) k_cocg_a(uint32_t dim, const double2 *__restrict__ Hw,
                                                    const double2 *__restrict__ Wcur, const double2 *Wprev,
                                                    double2 *U, const CocgState *st, double *partials, int first)
 {
+    Hw += (size_t)blockIdx.y * dim;
+    Wcur += (size_t)blockIdx.y * dim;
+    Wprev += (size_t)blockIdx.y * dim;
+    U += (size_t)blockIdx.y * dim;
+    st += blockIdx.y;
+    partials += (size_t)blockIdx.y * 10 * gridDim.x;
     if (st->done) return;
-    const double ir = st->invr, ii = st->invi;
-    double c1r, c1i;
-    cmul_v(st->bkr, st->bki, st->ipr, st->ipi, c1r, c1i);
-    c1r = -c1r;
-    c1i = -c1i;
-    double hi[2] = {0, 0}, lo[2] = {0, 0};
+    CocgA a;
+    a.init(st);
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 h = Hw[x];
-        const double2 wc = Wcur[x];
-        double tr, ti;
-        cmul_v(h.x, h.y, ir, ii, tr, ti);
-        double ur = tr, ui = ti;
-        if (!first) {
-            const double2 wp = Wprev[x];
-            ur = fma(c1r, wp.x, fma(-c1i, wp.y, tr));
-            ui = fma(c1r, wp.y, fma(c1i, wp.x, ti));
-        }
-        U[x] = make_double2(ur, ui);
-        pair_prod(hi[0], lo[0], wc.x, ur);
-        pair_prod(hi[0], lo[0], -wc.y, ui);
-        pair_prod(hi[1], lo[1], wc.x, ui);
-        pair_prod(hi[1], lo[1], wc.y, ur);
+        U[x] = a(h.x, h.y, Wcur[x], first ? make_double2(0.0, 0.0) : Wprev[x], first);
     }
-    write_partials5<2>(partials, hi, lo);
+    write_partials5<2>(partials, a.hi, a.lo);
 }
 
+// NS rounded sums of the 5-sum partials in every thread of a block
+template <int BLOCK, int NS>
+__device__ __forceinline__ void reduce_sums5(const double *partials, int nparts, double (&s)[NS])
+{
+    double hi[NS], lo[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) hi[j] = lo[j] = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += BLOCK) {
+#pragma unroll
+        for (int j = 0; j < NS; ++j) pair_add(hi[j], lo[j], partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
+    }
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        block_pair<BLOCK>(hi[j], lo[j]);
+        __syncthreads();
+        s[j] = hi[j] + lo[j];
+    }
+}
+
+// a_k from the sums of the first half, in every workgroup (workgroup 0 records it), then
 // w_k = u + c2 w_{k-1} over U (in place); partial sums of w_k^T w_k, <lam|w_k>, ||w_k||^2
 __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__restrict__ U,
                                                    const double2 *__restrict__ Wcur,
-                                                   const double2 *__restrict__ lam, const CocgState *st,
-                                                   double *partials)
+                                                   const double2 *__restrict__ lam, CocgState *st, const double *pa,
+                                                   int nparts, double *partials, double *a_out, int k, int n)
 {
+    U += (size_t)blockIdx.y * dim;
+    Wcur += (size_t)blockIdx.y * dim;
+    lam += (size_t)blockIdx.y * dim;
+    st += blockIdx.y;
+    pa += (size_t)blockIdx.y * 10 * nparts;
+    partials += (size_t)blockIdx.y * 10 * gridDim.x;
+    a_out += (size_t)blockIdx.y * 2 * n;
     if (st->done) return;
-    const double c2r = st->c2r, c2i = st->c2i;
+    double s[2];
+    reduce_sums5<kBlock, 2>(pa, nparts, s);
+    double ar, ai, c2r, c2i;
+    cmul_v(st->invr, st->invi, s[0], s[1], ar, ai);
+    cmul_v(ar, ai, st->invr, st->invi, c2r, c2i);
+    c2r = -c2r;
+    c2i = -c2i;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->akr = ar;
+        st->aki = ai;
+        st->c2r = c2r;
+        st->c2i = c2i;
+        a_out[2 * k] = ar;
+        a_out[2 * k + 1] = ai;
+        if (!(isfinite(ar) && isfinite(ai))) st->numeric_error = 1;
+    }
     double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = U[x];
@@ -182,27 +195,15 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
     write_partials5<5>(partials, hi, lo);
 }
 
-// rounded sum j of the 5-sum partials (thread 0)
-__device__ __forceinline__ double reduce_sum5(const double *partials, int nparts, int j)
+__global__ void __launch_bounds__(kBlock) k_cocg_fin_start(CocgBatch Q, int nparts, BatchShifts shifts)
 {
-    double hi = 0.0, lo = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += kBlock)
-        pair_add(hi, lo, partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
-    block_pair<kBlock>(hi, lo);
-    __syncthreads();
-    return hi + lo;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cocg_fin_start(CocgState *st, CocgShift *sh, int n_omega,
-                                                           const double *partials, int nparts, double shift_re,
-                                                           double *c_out)
-{
-    __shared__ double s[5];
-    for (int j = 0; j < 5; ++j) {
-        const double v = reduce_sum5(partials, nparts, j);
-        if (threadIdx.x == 0) s[j] = v;
-    }
-    __syncthreads();
+    CocgState *st = Q.st + blockIdx.x;
+    const int n_omega = Q.n_omega;
+    CocgShift *sh = Q.sh + (size_t)blockIdx.x * n_omega;
+    double *c_out = Q.c + (size_t)blockIdx.x * 2 * (Q.n + 1);
+    const double shift_re = shifts.re[blockIdx.x];
+    double s[5];
+    reduce_sums5<kBlock, 5>(Q.pb + (size_t)blockIdx.x * 10 * nparts, nparts, s);
     for (int j = threadIdx.x; j < n_omega; j += kBlock)
         sh[j] = CocgShift{1.0, 0.0, 1.0, 0.0, 0.0, 0.0, 0.0, 0.0, HUGE_VAL};
     if (threadIdx.x == 0) {
@@ -240,42 +241,22 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_start(CocgState *st, CocgSh
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_cocg_fin_a(CocgState *st, const double *partials, int nparts,
-                                                       double *a_out, int k)
-{
-    if (st->done) return;
-    const double s0 = reduce_sum5(partials, nparts, 0);
-    const double s1 = reduce_sum5(partials, nparts, 1);
-    if (threadIdx.x == 0) {
-        double ar, ai;
-        cmul_v(st->invr, st->invi, s0, s1, ar, ai);
-        st->akr = ar;
-        st->aki = ai;
-        double c2r, c2i;
-        cmul_v(ar, ai, st->invr, st->invi, c2r, c2i);
-        st->c2r = -c2r;
-        st->c2i = -c2i;
-        a_out[2 * k] = ar;
-        a_out[2 * k + 1] = ai;
-        if (!(isfinite(ar) && isfinite(ai))) st->numeric_error = 1;
-    }
-}
-
 // one step k of every shift's recurrence, the seed switch, the next basis scalars
-__global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift *sh, const double *omega,
-                                                       int n_omega, double eta, const double *partials, int nparts,
-                                                       int k, double tol, double rtol, double seed_tol,
-                                                       double *b_out, double *c_out)
+// (the shifts' chains of divisions bound it: one shift per thread up to 512 of them)
+constexpr int kFinThreads = 512;
+__global__ void __launch_bounds__(kFinThreads) k_cocg_fin_b(CocgBatch Q, int nparts, int k)
 {
+    CocgState *st = Q.st + blockIdx.x;
     if (st->done) return;
-    __shared__ double s[5];
-    __shared__ double q_sc[16];
+    const int n_omega = Q.n_omega;
+    CocgShift *sh = Q.sh + (size_t)blockIdx.x * n_omega;
+    double *b_out = Q.b + (size_t)blockIdx.x * 2 * Q.n, *c_out = Q.c + (size_t)blockIdx.x * 2 * (Q.n + 1);
+    const double *omega = Q.omega;
+    const double eta = Q.eta, tol = Q.tol, rtol = Q.rtol, seed_tol = Q.seed_tol;
+    __shared__ double q_sc[4];
     __shared__ int s_switch;
-    for (int j = 0; j < 5; ++j) {
-        const double v = reduce_sum5(partials, nparts, j);
-        if (threadIdx.x == 0) s[j] = v;
-    }
-    __syncthreads();
+    double s[5];
+    reduce_sums5<kFinThreads, 5>(Q.pb + (size_t)blockIdx.x * 10 * nparts, nparts, s);
     const CocgState q = *st;
     const double wwr = s[0], wwi = 2.0 * s[1], nrm2 = s[4];
     double bnr, bni;
@@ -311,7 +292,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift 
     double rmax = -1.0;
     int imax = 0;
     double rseed = 0.0;
-    for (int j = threadIdx.x; j < n_omega; j += kBlock) {
+    for (int j = threadIdx.x; j < n_omega; j += kFinThreads) {
         CocgShift p = sh[j];
         if (j != sd && p.res <= thr) {  // converged: keeps its values
             if (p.res > rmax) {
@@ -355,9 +336,9 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift 
         if (j == sd) rseed = res;
     }
     // block argmax (first index on ties) and the seed's residual
-    __shared__ double r_sh[kBlock / 64];
-    __shared__ int i_sh[kBlock / 64];
-    __shared__ double rs_sh[kBlock / 64];
+    __shared__ double r_sh[kFinThreads / 64];
+    __shared__ int i_sh[kFinThreads / 64];
+    __shared__ double rs_sh[kFinThreads / 64];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         const double orr = __shfl_xor(rmax, off, 64);
@@ -376,7 +357,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift 
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) {
+        for (int w = 1; w < kFinThreads / 64; ++w) {
             if (r_sh[w] > r_sh[0] || (r_sh[w] == r_sh[0] && i_sh[w] < i_sh[0])) {
                 r_sh[0] = r_sh[w];
                 i_sh[0] = i_sh[w];
@@ -439,7 +420,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift 
     __syncthreads();
     if (s_switch >= 0) {
         const double o_r = q_sc[0], o_i = q_sc[1], n_r = q_sc[2], n_i = q_sc[3];
-        for (int j = threadIdx.x; j < n_omega; j += kBlock) {
+        for (int j = threadIdx.x; j < n_omega; j += kFinThreads) {
             CocgShift p = sh[j];
             if (!(p.res > thr)) continue;  // converged shifts are not rebased
             cdiv_s(p.por, p.poi, o_r, o_i, p.por, p.poi);
@@ -451,42 +432,51 @@ __global__ void __launch_bounds__(kBlock) k_cocg_fin_b(CocgState *st, CocgShift 
 
 __global__ void k_cocg_finish(const CocgState *st, const CocgShift *sh, int n_omega, double2 *g)
 {
+    st += blockIdx.y;
+    sh += (size_t)blockIdx.y * n_omega;
+    g += (size_t)blockIdx.y * n_omega;
     const bool any = st->steps > 0;
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n_omega; j += gridDim.x * blockDim.x)
         g[j] = any ? make_double2(sh[j].gr, sh[j].gi) : make_double2(0.0, 0.0);
 }
 
-void launch_cocg_start(uint32_t dim, const double *chi, const double *lam, double *partials, CocgState *st,
-                       CocgShift *sh, int n_omega, double shift_re, double *c_out, hipStream_t s)
+// The grid of the vector halves: at most 256 workgroups a sequence, whose five sums the
+// next kernel then reads in one load per thread.
+static int cocg_grid(uint32_t dim) { return vec_grid(dim) < 256 ? vec_grid(dim) : 256; }
+
+void launch_cocg_start(uint32_t dim, const double *chi, const CocgBatch &q, const BatchShifts &shift_re, hipStream_t s)
 {
-    const int grid = vec_grid(dim);
-    hipLaunchKernelGGL(k_cocg_start_sums, dim3(grid), dim3(kBlock), 0, s, dim, (const double2 *)chi,
-                       (const double2 *)lam, partials);
-    hipLaunchKernelGGL(k_cocg_fin_start, dim3(1), dim3(kBlock), 0, s, st, sh, n_omega, partials, grid, shift_re,
-                       c_out);
+    const int grid = cocg_grid(dim);
+    hipLaunchKernelGGL(k_cocg_start_sums, dim3(grid, q.B), dim3(kBlock), 0, s, dim, (const double2 *)chi,
+                       (const double2 *)q.lam, q.pb);
+    hipLaunchKernelGGL(k_cocg_fin_start, dim3(q.B), dim3(kBlock), 0, s, q, grid, shift_re);
 }
 
-void launch_cocg_step(const HvOp &op, const double *lam, const double *Wcur, const double *Wprev, double *U,
-                      double *Hw, double *partials, CocgState *st, CocgShift *sh, const double *omega, int n_omega,
-                      double eta, int k, double tol, double rtol, double seed_tol, double *a_out, double *b_out,
-                      double *c_out, hipStream_t s)
+void launch_cocg_step(const HvOp &op, const CocgBatch &q, const double *Wcur, const double *Wprev, double *U, int k,
+                      hipStream_t s)
 {
     const uint32_t dim = 1u << op.P.n_sites;
-    const int grid = vec_grid(dim);
-    launch_apply_h(op, Wcur, Hw, s);
-    hipLaunchKernelGGL(k_cocg_a, dim3(grid), dim3(kBlock), 0, s, dim, (const double2 *)Hw, (const double2 *)Wcur,
-                       (const double2 *)Wprev, (double2 *)U, (const CocgState *)st, partials, k == 0 ? 1 : 0);
-    hipLaunchKernelGGL(k_cocg_fin_a, dim3(1), dim3(kBlock), 0, s, st, partials, grid, a_out, k);
-    hipLaunchKernelGGL(k_cocg_b, dim3(grid), dim3(kBlock), 0, s, dim, (double2 *)U, (const double2 *)Wcur,
-                       (const double2 *)lam, (const CocgState *)st, partials);
-    hipLaunchKernelGGL(k_cocg_fin_b, dim3(1), dim3(kBlock), 0, s, st, sh, omega, n_omega, eta, partials, grid, k, tol,
-                       rtol, seed_tol, b_out, c_out);
+    int parts = vec_grid(dim);
+    const int grid = cocg_grid(dim);
+    if (cocg_work_vectors(op)) {
+        parts = grid;
+        launch_apply_h(op, Wcur, q.Hw, s, q.B, 2 * (size_t)dim);
+        hipLaunchKernelGGL(k_cocg_a, dim3(grid, q.B), dim3(kBlock), 0, s, dim, (const double2 *)q.Hw,
+                           (const double2 *)Wcur, (const double2 *)Wprev, (double2 *)U, (const CocgState *)q.st, q.pa,
+                           k == 0 ? 1 : 0);
+    } else {
+        launch_hv_cocg(op, Wcur, Wprev, U, q.st, q.pa, k == 0 ? 1 : 0, q.B, s);
+    }
+    hipLaunchKernelGGL(k_cocg_b, dim3(grid, q.B), dim3(kBlock), 0, s, dim, (double2 *)U, (const double2 *)Wcur,
+                       (const double2 *)q.lam, q.st, (const double *)q.pa, parts, q.pb, q.a, k, q.n);
+    hipLaunchKernelGGL(k_cocg_fin_b, dim3(q.B), dim3(kFinThreads), 0, s, q, grid, k);
 }
 
-void launch_cocg_finish(const CocgState *st, const CocgShift *sh, int n_omega, double *g, hipStream_t s)
+void launch_cocg_finish(const CocgBatch &q, double *g, hipStream_t s)
 {
-    const int grid = (n_omega + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_cocg_finish, dim3(grid < 1 ? 1 : grid), dim3(kBlock), 0, s, st, sh, n_omega, (double2 *)g);
+    const int grid = (q.n_omega + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_cocg_finish, dim3(grid < 1 ? 1 : grid, q.B), dim3(kBlock), 0, s, (const CocgState *)q.st,
+                       (const CocgShift *)q.sh, q.n_omega, (double2 *)g);
 }
 
 }  // namespace ftk

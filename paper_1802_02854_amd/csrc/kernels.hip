@@ -25,6 +25,7 @@
 
 #include "bond_ops.h"
 #include "exact_sum.h"
+#include "cocg.h"
 #include "kernels.h"
 #include "shift_update.h"
 
@@ -1119,6 +1120,50 @@ void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wpr
 bool lanczos_pairs(const HvOp &op, int B)
 {
     return g_fuse_fin && hv_mode(op) == 0 && ((size_t)B << op.P.n_sites) <= ((size_t)1 << kPairBits);
+}
+
+// First half of a shifted COCG step (cocg.hip) where H v is one element per thread.
+struct EpiCocg {
+    const double2 *Wprev;
+    double2 *U;
+    double *partials;
+    const CocgState *st;
+    int first;
+    CocgA a;
+    __device__ void select(int r, size_t vs, int pstride)
+    {
+        Wprev += r * vs;
+        U += r * vs;
+        st += r;
+        partials += (size_t)r * 5 * pstride;
+    }
+    __device__ bool active() const { return !st->done; }
+    __device__ void prepare(int) { a.init(st); }
+    template <int BLOCK>
+    __device__ bool begin(int) { return true; }
+    __device__ double2 load(size_t x) const { return first ? make_double2(0.0, 0.0) : Wprev[x]; }
+    __device__ void apply(size_t x, double re, double im, const double2 &wc, const double2 &wp)
+    {
+        U[x] = a(re, im, wc, wp, first);
+    }
+    template <int BLOCK>
+    __device__ void finish() { write_partials5<2>(partials, a.hi, a.lo); }
+};
+
+bool cocg_work_vectors(const HvOp &op) { return product_mode(op) != 0; }
+
+void launch_hv_cocg(const HvOp &op, const double *Wcur, const double *Wprev, double *U, const CocgState *st,
+                    double *pa, int first, int B, hipStream_t s)
+{
+    EpiCocg e;
+    e.Wprev = (const double2 *)Wprev;
+    e.U = (double2 *)U;
+    e.partials = pa;
+    e.st = st;
+    e.first = first;
+    const uint32_t dim = 1u << op.P.n_sites;
+    hipLaunchKernelGGL(k_hv_simple<EpiCocg>, dim3(vec_grid(dim), B), dim3(kBlock), 0, s, op.dev, (const double2 *)Wcur,
+                       (size_t)dim, e);
 }
 
 bool lanczos_fusable(const HvOp &op) { return hv_mode(op) == 3 && op.plan.n_passes >= 2; }

@@ -95,3 +95,37 @@ def test_few_and_many_sequences(env, N):
                 for x, y in zip(many.lanczos(s, a, 3, al, 0), few.lanczos(s, a, 3, al, 0)):
                     assert np.array_equal(x, y)
     assert np.array_equal(many.raw()[0][:, :, 3], few.raw()[0][:, :, 3]) and np.abs(few.raw()[0]).max() > 0
+
+
+@pytest.mark.parametrize("N,L,shells", [(8, 12, (2, 3)), (16, 4, (1, 1))])
+def test_cocg_batches(env, N, L, shells):
+    """Shifted COCG sequences in lockstep, the last batch ragged: the rows of another batching
+    and of the form with work vectors, spectra and operator pairs."""
+    ftk, ctx, torch = env
+    print(f"cocg batches N={N}", flush=True)
+    cl = ftk.honeycomb_cluster(*SUPERCELLS[N])
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
+    st = ftk.TypicalStates(h, seed=6, n_vectors=1, betas=[0.3], E_b=None, eps=None, L=L, M=4, n_steps=10)
+    kw = dict(omega=np.linspace(-2, 2, 600), eta=0.3, n_steps=25, solver="cocg")
+    qs = [(0.0, 0.0), (0.4, 0.2)]
+
+    def spectrum(shells=None):
+        sp = ftk.Spectrum(h, st, q_xy=qs, shells=shells, seed_tol=1e-3, **kw)
+        return sp.raw(), [sp.cocg(0, 0, m, a, q) for m in range(shells[0], sum(shells)) for a in range(3) for q in (0, 1)] \
+            if shells else [sp.cocg(0, 0, m, a, q) for m in range(L) for a in range(3) for q in (0, 1)]
+    op_a = np.stack([ftk.momentum_operator(cl, 0, qs[1])])
+    op_b = np.stack([ftk.momentum_operator(cl, 2, qs[0])])
+
+    def pair():
+        return ftk.PairSpectrum(h, st, op_a=op_a, op_b=op_b, **kw).raw()
+    many, few = spectrum(), spectrum(shells)  # 8 sites: 72 sequences, 18
+    other, pairs = _forced(ftk, 1, spectrum), (pair(), _forced(ftk, 1, pair))
+    for x, y in zip(many[0], other[0]):
+        assert np.array_equal(x, y)
+    for m, o in zip(many[1], other[1]):
+        assert m[3] == o[3] and all(np.array_equal(x, y) for x, y in zip(m[:3], o[:3]))
+    for m, o in zip(many[1][shells[0] * 6:], few[1]):
+        assert m[3] == o[3] and all(np.array_equal(x, y) for x, y in zip(m[:3], o[:3]))
+    for x, y in zip(*pairs):
+        assert np.array_equal(x, y)
+    assert np.abs(many[0][0]).max() > 0 and np.abs(pairs[0][0]).max() > 0
