@@ -978,9 +978,9 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             return log_norm - N * st->betas[a] * plan.ell / 2.0;
         };
         // After pass 1 of (vector sv, anchor a): T_n kept, the automatic window, the steps pass 2
-        // takes, and the shell coefficients [L][steps] into hcoef.  al, be hold q1.steps entries.
+        // takes, per shell into k_m [L] under residual truncation.  al, be hold q1.steps entries.
         auto shell_setup = [&](int sv, int a, const SeqState &q1, std::vector<double> &al, std::vector<double> &be,
-                               double *hcoef) {
+                               int *k_m) {
             const size_t sa = (size_t)sv * st->na + a;
             if (q1.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in filter Lanczos coefficients");
             int steps = q1.steps;
@@ -989,12 +989,10 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                 if (!(std::isfinite(st->eps[a]) && st->eps[a] > 0))
                     fail(FTK_ENUMERIC, "automatic shell window is empty or not finite");
             }
-            std::vector<int> k_m;  // per-shell steps under residual truncation
             if (p->resid_tol > 0) {
                 // each filter operator on its own (Sec. V): shell m takes T_{k_m} for the
                 // first k_m at which all of its M contour shifts have converged
                 std::vector<double> zr(st->M), zi(st->M);
-                k_m.resize(st->L);
                 int kmax = 1;
                 for (int m = 0; m < st->L; ++m) {
                     for (int j = 1; j <= st->M; ++j) {
@@ -1013,20 +1011,43 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             std::copy(be.begin(), be.end(), st->beta.begin() + sa * n);
             st->steps[sa] = steps;
 
-            // shell coefficients c^m (host, Sec. III.B); the device accumulates the
-            // unnormalised residuals w_{k-1} = v_k / inv_k, so fold inv_k into c^m_k
-            shell_coefficients(al.data(), be.data(), steps, q1.norm, st->E_b[a], st->eps[a], st->L, st->M, hcoef,
-                               k_m.empty() ? nullptr : k_m.data());
-            std::vector<double> inv(steps);
-            inv[0] = 1.0 / q1.norm;
-            for (int k = 1; k < steps; ++k) inv[k] = 1.0 / be[k - 1];
-            for (int m = 0; m < st->L; ++m)
-                for (int k = 0; k < steps; ++k) {
-                    double *c = &hcoef[2 * ((size_t)m * steps + k)];
-                    c[0] = c[0] * inv[k];
-                    c[1] = c[1] * inv[k];
-                }
             return steps;
+        };
+        // shell coefficients c^m (Sec. III.B) of cnt sequences from their recorded lists
+        std::vector<double> hcs(2 * (size_t)st->M);
+        for (int j = 1; j <= st->M; ++j) {
+            const double th = 2.0 * M_PI * ((double)j - 0.5) / (double)st->M;
+            hcs[2 * (j - 1)] = std::cos(th);
+            hcs[2 * (j - 1) + 1] = std::sin(th);
+        }
+        struct Filter {
+            Arena m;
+            ShellSeq *seq;
+            int *kn;
+            double *cs, *work, *coef;
+            size_t row;  // coefficients of a sequence
+            int items;
+            std::vector<ShellSeq> hseq;
+            std::vector<int> hkn;
+        };
+        auto filter_for = [&](Filter &f, size_t count) {
+            f.row = 2 * (size_t)n * shell_rows(st->L);
+            const size_t item = 2 * shell_work(st->M, n);  // doubles: two complex lists
+            f.items = (int)std::min(count * st->L, std::max<size_t>(1, (size_t(64) << 20) / (item * sizeof(double))));
+            f.m.part(&f.seq, count);
+            f.m.part(&f.kn, count * st->L);
+            f.m.part(&f.cs, 2 * (size_t)st->M);
+            f.m.part(&f.work, f.items * item);
+            f.m.part(&f.coef, count * f.row);
+            f.m.allocate(ctx);
+            f.hseq.resize(count);
+            f.hkn.resize(count * st->L);
+            HIP_CHECK(hipMemcpyAsync(f.cs, hcs.data(), hcs.size() * sizeof(double), hipMemcpyHostToDevice, s));
+        };
+        auto coefficients = [&](Filter &f, size_t cnt) {
+            HIP_CHECK(hipMemcpyAsync(f.seq, f.hseq.data(), cnt * sizeof(ShellSeq), hipMemcpyHostToDevice, s));
+            HIP_CHECK(hipMemcpyAsync(f.kn, f.hkn.data(), cnt * st->L * sizeof(int), hipMemcpyHostToDevice, s));
+            launch_shell_coefficients(f.seq, (int)cnt, n, st->L, st->M, f.cs, f.work, f.items, s);
         };
         auto check_regenerated = [&](const double *al2, const std::vector<double> &al) {
             if (std::memcmp(al2, al.data(), sizeof(double) * al.size()) != 0)
@@ -1061,13 +1082,14 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             Arena m;
             ResidentSeq *seq;
             SeqState *state;
-            double *phib, *carry, *vbuf, *coef, *al_d, *be_d;
+            double *phib, *carry, *vbuf, *al_d, *be_d;
+            Filter fl;
+            filter_for(fl, group);
             m.part(&seq, group);
             m.part(&state, group);
             m.part(&phib, group * cplx);
             m.part(&carry, group * 2 * cplx);
             m.part(&vbuf, group * nb * cplx);
-            m.part(&coef, group * 2 * st->L * n);
             m.part(&al_d, group * n);
             m.part(&be_d, group * n);
             FewScratch fs;
@@ -1076,7 +1098,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             m.allocate(ctx);
             std::vector<ResidentSeq> hseq(group);
             std::vector<SeqState> hstate(group);
-            std::vector<double> hcoef(group * 2 * st->L * n), hal(group * n), hbe(group * n);
+            std::vector<double> hal(group * n), hbe(group * n);
             std::vector<std::vector<double>> al(group), be(group);
             std::vector<int> steps(group);
             for (size_t i = 0; i < group; ++i)
@@ -1121,12 +1143,14 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     const int sv = (int)((g0 + i) / st->na), a = (int)((g0 + i) % st->na);
                     al[i].assign(hal.begin() + i * n, hal.begin() + i * n + hstate[i].steps);
                     be[i].assign(hbe.begin() + i * n, hbe.begin() + i * n + hstate[i].steps);
-                    steps[i] = shell_setup(sv, a, hstate[i], al[i], be[i], hcoef.data() + i * 2 * st->L * n);
+                    steps[i] = shell_setup(sv, a, hstate[i], al[i], be[i], fl.hkn.data() + i * st->L);
+                    fl.hseq[i] = ShellSeq{al_d + i * n, be_d + i * n, steps[i], hstate[i].norm, st->E_b[a], st->eps[a],
+                                          p->resid_tol > 0 ? fl.kn + i * st->L : nullptr, fl.coef + i * fl.row};
                     most = std::max(most, steps[i]);
                     shells.emplace_back(ctx, vbytes * st->L);
                     HIP_CHECK(hipMemsetAsync(shells[i].p, 0, vbytes * st->L, s));
                 }
-                HIP_CHECK(hipMemcpyAsync(coef, hcoef.data(), sizeof(double) * cnt * 2 * st->L * n, hipMemcpyHostToDevice, s));
+                coefficients(fl, cnt);
                 run.vout = vbuf;
                 run.vstride = nb * cplx;
                 for (int k0 = 0; k0 < most; k0 += nb) {
@@ -1136,7 +1160,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     for (size_t i = 0; i < cnt; ++i)
                         if (steps[i] > k0)
                             launch_accumulate(dim, vbuf + i * nb * cplx, std::min(nb, steps[i] - k0),
-                                              coef + i * 2 * st->L * n, steps[i], k0, shells[i].d(), st->L, s);
+                                              fl.coef + i * fl.row, steps[i], k0, shells[i].d(), st->L, s);
                 }
                 HIP_CHECK(hipMemcpyAsync(hal.data(), al_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
                 for (size_t i = 0; i < cnt; ++i) {
@@ -1147,8 +1171,8 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             }
         } else {
             DevBuf phib(ctx, vbytes), W0(ctx, vbytes), W1(ctx, vbytes), Vbuf(ctx, vbytes * nb);
-            DevBuf coef(ctx, sizeof(double) * 2 * (size_t)st->L * n);
-            std::vector<double> hcoef((size_t)2 * st->L * n);
+            Filter fl;
+            filter_for(fl, 1);
             for (int sv = 0; sv < st->nv; ++sv) {
                 start_vector(sv);
                 for (int a = 0; a < st->na; ++a) {
@@ -1163,15 +1187,16 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     HIP_CHECK(hipMemcpyAsync(al.data(), kr.al(0), sizeof(double) * q1.steps, hipMemcpyDeviceToHost, s));
                     HIP_CHECK(hipMemcpyAsync(be.data(), kr.be(0), sizeof(double) * q1.steps, hipMemcpyDeviceToHost, s));
                     HIP_CHECK(hipStreamSynchronize(s));
-                    const int steps = shell_setup(sv, a, q1, al, be, hcoef.data());
-                    HIP_CHECK(hipMemcpyAsync(coef.p, hcoef.data(), sizeof(double) * 2 * st->L * steps,
-                                             hipMemcpyHostToDevice, s));
+                    const int steps = shell_setup(sv, a, q1, al, be, fl.hkn.data());
+                    fl.hseq[0] = ShellSeq{kr.al(0), kr.be(0), steps, q1.norm, st->E_b[a], st->eps[a],
+                                          p->resid_tol > 0 ? fl.kn : nullptr, fl.coef};
+                    coefficients(fl, 1);
 
                     // pass 2: regenerate v_k and accumulate phi^m = sum_k c^m_k v_k
                     DevBuf shells(ctx, vbytes * st->L);
                     HIP_CHECK(hipMemsetAsync(shells.p, 0, vbytes * st->L, s));
                     auto flush = [&](int k0, int cnt) {
-                        launch_accumulate(dim, Vbuf.d(), cnt, coef.d(), steps, k0, shells.d(), st->L, s);
+                        launch_accumulate(dim, Vbuf.d(), cnt, fl.coef, steps, k0, shells.d(), st->L, s);
                     };
                     kr.run(0, phib.d(), W0.d(), W1.d(), steps, Vbuf.d(), nb, flush);
                     std::vector<double> al2(steps);

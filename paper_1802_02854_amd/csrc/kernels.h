@@ -301,7 +301,25 @@ void launch_copy(uint32_t dim, const double *src, double *dst, hipStream_t s);
 // complex Gaussian draws of (seed, sample)
 void launch_gaussian(uint32_t dim, uint64_t seed, uint64_t sample, double *g, hipStream_t s);
 
-// Phi[m] += sum_{k < nk} c[m][k0 + k] V[k] for m < L (coef: [L][n] complex)
+// Filter coefficients of the shells of several sequences (the arithmetic of
+// shell_coefficients in ftkw_internal.h, step for step, then inv_k folded in: the
+// accumulated vectors are the unnormalised residuals).
+constexpr int kShellTile = 8;
+inline int shell_rows(int L) { return (L + kShellTile - 1) / kShellTile * kShellTile; }
+struct ShellSeq {
+    const double *alpha, *beta;  // device, n entries
+    int n;
+    double norm, E_b, eps;
+    const int *kn;               // device, NULL or per shell the steps its operator takes
+    double *coef;                // [n][shell_rows(L)] complex
+};
+// complex work entries per (sequence, shell)
+inline size_t shell_work(int M, int n) { return 2 * (size_t)M * n; }
+// seq [n_seq] and cs (cos, sin of the M contour angles) on the device; n_max the largest
+// n; work for `items` (sequence, shell) pairs at a time
+void launch_shell_coefficients(const ShellSeq *seq, int n_seq, int n_max, int L, int M, const double *cs, double *work,
+                               int items, hipStream_t s);
+// Phi[m] += sum_{k < nk} c[k0 + k][m] V[k] for m < L (coef: [n][shell_rows(L)] complex)
 void launch_accumulate(uint32_t dim, const double *V, int nk, const double *coef, int n, int k0,
                        double *Phi, int L, hipStream_t s);
 

@@ -1546,6 +1546,90 @@ void launch_gaussian(uint32_t dim, uint64_t seed, uint64_t sample, double *g, hi
 }
 
 // ---------------------------------------------------------------------------
+// Filter coefficients: y = (z - T)^{-1} e_0 for every (shell, contour point), a thread
+// each, by the pivots forwards and the substitution backwards; its M terms of each c_k
+// are then summed in contour order.  On the host this took 15 of 84 ms for 128 shells,
+// 16 points and 500 steps, with the GPU idle; here the two serial chains take
+// 0.27 ms.  Work entries are [step][thread]: ip and f, then the term over ip.
+__global__ void __launch_bounds__(64) k_shell_terms(const ShellSeq *__restrict__ seqs, int i0, int count, int L, int M,
+                                                    const double2 *__restrict__ cs, double2 *__restrict__ ip,
+                                                    double2 *__restrict__ f)
+{
+    const size_t T = (size_t)count * M, t = blockIdx.x * 64 + threadIdx.x;
+    if (t >= T) return;
+    const int item = i0 + (int)(t / M), j = (int)(t % M), m = item % L;
+    const ShellSeq q = seqs[item / L];
+    const double *__restrict__ alpha = q.alpha, *__restrict__ beta = q.beta;
+    const int nm = q.kn ? q.kn[m] : q.n;
+    if (nm < 1) return;
+    const double wr = q.eps * cs[j].x, wi = q.eps * cs[j].y;
+    const double zr = (q.E_b + (double)(2 * m + 1) * q.eps) + wr, zi = wi;
+    double pr = zr - alpha[0], pi = zi;
+    double den = pr * pr + pi * pi;
+    double2 a = make_double2(pr / den, -pi / den), g = make_double2(1.0, 0.0);
+    ip[t] = a;
+    f[t] = g;
+#pragma unroll 4
+    for (int k = 1; k < nm; ++k) {
+        const double b = beta[k - 1];
+        const double lr = b * a.x, li = b * a.y;
+        pr = (zr - alpha[k]) - b * lr;
+        pi = zi - b * li;
+        den = pr * pr + pi * pi;
+        a = make_double2(pr / den, -pi / den);
+        g = make_double2(lr * g.x - li * g.y, lr * g.y + li * g.x);
+        ip[k * T + t] = a;
+        f[k * T + t] = g;
+    }
+    double yr = g.x * a.x - g.y * a.y, yi = g.x * a.y + g.y * a.x;
+    ip[(nm - 1) * T + t] = make_double2(wr * yr - wi * yi, wr * yi + wi * yr);
+#pragma unroll 4
+    for (int k = nm - 2; k >= 0; --k) {
+        const double b = beta[k];
+        const double2 fk = f[k * T + t], pk = ip[k * T + t];
+        const double tr = fk.x + b * yr, ti = fk.y + b * yi;
+        yr = tr * pk.x - ti * pk.y;
+        yi = tr * pk.y + ti * pk.x;
+        ip[k * T + t] = make_double2(wr * yr - wi * yi, wr * yi + wi * yr);
+    }
+}
+
+// c_k of (sequence, shell) i0 + blockIdx.x
+__global__ void __launch_bounds__(kBlock) k_shell_sum(const ShellSeq *__restrict__ seqs, int i0, int count, int L, int M,
+                                                      int rows, const double2 *__restrict__ term)
+{
+    const int item = i0 + (int)blockIdx.x, m = item % L;
+    const ShellSeq q = seqs[item / L];
+    const int nm = q.kn ? q.kn[m] : q.n;
+    const size_t T = (size_t)count * M;
+    const double s = q.norm / (double)M;
+    for (int k = threadIdx.x; k < q.n; k += kBlock) {
+        double re = 0.0, im = 0.0;
+        if (k < nm)
+            for (int j = 0; j < M; ++j) {
+                const double2 v = term[k * T + (size_t)blockIdx.x * M + j];
+                re = re + v.x;
+                im = im + v.y;
+            }
+        const double inv = 1.0 / (k == 0 ? q.norm : q.beta[k - 1]);
+        ((double2 *)q.coef)[(size_t)k * rows + m] = make_double2(re * s * inv, im * s * inv);
+    }
+}
+
+void launch_shell_coefficients(const ShellSeq *seq, int n_seq, int n_max, int L, int M, const double *cs, double *work,
+                               int items, hipStream_t s)
+{
+    double2 *ip = (double2 *)work, *f = ip + (size_t)items * M * n_max;
+    for (int i0 = 0; i0 < n_seq * L; i0 += items) {
+        const int count = n_seq * L - i0 < items ? n_seq * L - i0 : items;
+        hipLaunchKernelGGL(k_shell_terms, dim3((unsigned)(((size_t)count * M + 63) / 64)), dim3(64), 0, s, seq, i0, count,
+                           L, M, (const double2 *)cs, ip, f);
+        hipLaunchKernelGGL(k_shell_sum, dim3(count), dim3(kBlock), 0, s, seq, i0, count, L, M, shell_rows(L),
+                           (const double2 *)ip);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Filter pass 2 (Sec. III.B, Eq. filtered): Phi_m += sum_k d_{m,k} W_k over a
 // buffered block of Lanczos residual vectors, k in increasing order, 8 shells
 // per thread.  Each workgroup takes one group of 8 shells over a strided set of
@@ -1554,12 +1638,75 @@ void launch_gaussian(uint32_t dim, uint64_t seed, uint64_t sample, double *g, hi
 // index: id = xcd + 8 (group + ny q), element block xcd + 8 q), so they read the
 // range's vectors at about the same time and all but the first read come from
 // that XCD's L2 instead of HBM.  A full group of 8 shells has no per-shell test,
-// so the eight scalar coefficient loads of a step are issued together (measured:
-// 42.6 -> 34.5 ms for 64 vectors into 128 shells at 24 sites; staging the vectors
-// in LDS for 16 shell groups per workgroup read each entry from HBM once but took
-// 70 ms: 128 coefficient rows in flight per workgroup overran the scalar cache).
-constexpr int kShellTile = 8;
+// and the eight coefficients of a step lie side by side, two scalar loads (staging the
+// vectors in LDS for 16 shell groups per workgroup read each entry from HBM once but took
+// twice as long: 128 coefficient rows in flight per workgroup overran the scalar cache).
+// Four vectors are read ahead (14 sites, 16 shells, 64 vectors: a chain of 64 loads, 25.6
+// us -> 14.6), and from 18 sites a thread takes two elements per coefficient load (20
+// sites, 128 shells, 64 vectors: 2.39 ms -> 1.69, 40 TFLOP/s; one element 2.09, four 2.22:
+// two wavefronts per SIMD).  Smaller vectors need the workgroups.
+constexpr int kAccAhead = 4;
+constexpr uint32_t kAccWide = 1u << 18;
+constexpr int kAccE = 2;
 
+template <int E, bool FULL>
+__device__ __forceinline__ void accumulate_step(double2 (&acc)[E][kShellTile], const double2 (&v)[E],
+                                                const double2 *__restrict__ cf, int mc)
+{
+    double2 c[kShellTile];
+#pragma unroll
+    for (int mm = 0; mm < kShellTile; ++mm) c[mm] = cf[mm];
+#pragma unroll
+    for (int mm = 0; mm < kShellTile; ++mm) {
+        if (!FULL && mm >= mc) break;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            double re = acc[e][mm].x, im = acc[e][mm].y;
+            re = fma(c[mm].x, v[e].x, re);
+            re = fma(-c[mm].y, v[e].y, re);
+            im = fma(c[mm].x, v[e].y, im);
+            im = fma(c[mm].y, v[e].x, im);
+            acc[e][mm] = make_double2(re, im);
+        }
+    }
+}
+
+template <int E, bool FULL>
+__device__ __forceinline__ void accumulate_rows(uint32_t dim, const double2 *__restrict__ V, int nk,
+                                                const double2 *__restrict__ cf, int rows, double2 *__restrict__ Phi,
+                                                uint32_t x, int mc)
+{
+    double2 acc[E][kShellTile];
+#pragma unroll
+    for (int mm = 0; mm < kShellTile; ++mm)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (FULL || mm < mc) acc[e][mm] = Phi[(size_t)mm * dim + x + e * kBlock];
+    int k = 0;
+    for (; k + kAccAhead <= nk; k += kAccAhead) {
+        double2 v[kAccAhead][E];
+#pragma unroll
+        for (int u = 0; u < kAccAhead; ++u)
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[u][e] = V[(size_t)(k + u) * dim + x + e * kBlock];
+#pragma unroll
+        for (int u = 0; u < kAccAhead; ++u) accumulate_step<E, FULL>(acc, v[u], cf + (size_t)(k + u) * rows, mc);
+    }
+    for (; k < nk; ++k) {
+        double2 v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = V[(size_t)k * dim + x + e * kBlock];
+        accumulate_step<E, FULL>(acc, v, cf + (size_t)k * rows, mc);
+    }
+#pragma unroll
+    for (int mm = 0; mm < kShellTile; ++mm)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (FULL || mm < mc) Phi[(size_t)mm * dim + x + e * kBlock] = acc[e][mm];
+}
+
+// E elements per thread, kBlock apart; dim is a multiple of E kBlock, or E = 1
+template <int E>
 __global__ void __launch_bounds__(kBlock) k_accumulate(uint32_t dim, const double2 *__restrict__ V, int nk,
                                                        const double2 *__restrict__ coef, int n, int k0,
                                                        double2 *__restrict__ Phi, int L, int gx, int ny)
@@ -1568,58 +1715,30 @@ __global__ void __launch_bounds__(kBlock) k_accumulate(uint32_t dim, const doubl
     const int m0 = (int)(r % (uint32_t)ny) * kShellTile;
     const uint32_t xblock = (blockIdx.x & 7u) + 8u * (r / (uint32_t)ny);
     const int mc = L - m0 < kShellTile ? L - m0 : kShellTile;
-    const double2 *cf = coef + k0;
-    for (uint32_t x = xblock * blockDim.x + threadIdx.x; x < dim; x += (uint32_t)gx * blockDim.x) {
-        double2 acc[kShellTile];
-#pragma unroll
-        for (int mm = 0; mm < kShellTile; ++mm)
-            if (mm < mc) acc[mm] = Phi[(size_t)(m0 + mm) * dim + x];
-        if (mc == kShellTile) {
-            for (int k = 0; k < nk; ++k) {
-                const double2 v = V[(size_t)k * dim + x];
-                double2 c[kShellTile];
-#pragma unroll
-                for (int mm = 0; mm < kShellTile; ++mm) c[mm] = cf[FTK_IDX((m0 + mm) * n + k, 0, L * n, 13)];
-#pragma unroll
-                for (int mm = 0; mm < kShellTile; ++mm) {
-                    double re = acc[mm].x, im = acc[mm].y;
-                    re = fma(c[mm].x, v.x, re);
-                    re = fma(-c[mm].y, v.y, re);
-                    im = fma(c[mm].x, v.y, im);
-                    im = fma(c[mm].y, v.x, im);
-                    acc[mm] = make_double2(re, im);
-                }
-            }
-        } else {
-            for (int k = 0; k < nk; ++k) {
-                const double2 v = V[(size_t)k * dim + x];
-#pragma unroll
-                for (int mm = 0; mm < kShellTile; ++mm) {
-                    if (mm < mc) {
-                        const double2 c = cf[FTK_IDX((m0 + mm) * n + k, 0, L * n, 13)];
-                        double re = acc[mm].x, im = acc[mm].y;
-                        re = fma(c.x, v.x, re);
-                        re = fma(-c.y, v.y, re);
-                        im = fma(c.x, v.y, im);
-                        im = fma(c.y, v.x, im);
-                        acc[mm] = make_double2(re, im);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int mm = 0; mm < kShellTile; ++mm)
-            if (mm < mc) Phi[(size_t)(m0 + mm) * dim + x] = acc[mm];
+    const int rows = ny * kShellTile;
+    const double2 *cf = coef + FTK_IDX(k0 * rows + m0, (nk - 1) * rows + kShellTile - 1, n * rows, 13);
+    Phi += (size_t)m0 * dim;
+    for (uint32_t x = xblock * kBlock * E + threadIdx.x; x < dim; x += (uint32_t)gx * kBlock * E) {
+        if (mc == kShellTile)
+            accumulate_rows<E, true>(dim, V, nk, cf, rows, Phi, x, mc);
+        else
+            accumulate_rows<E, false>(dim, V, nk, cf, rows, Phi, x, mc);
     }
 }
 
 void launch_accumulate(uint32_t dim, const double *V, int nk, const double *coef, int n, int k0,
                        double *Phi, int L, hipStream_t s)
 {
-    const int gx = (vec_grid(dim) + 7) / 8 * 8;  // element blocks, a multiple of the 8 XCDs
     const int ny = (L + kShellTile - 1) / kShellTile;
-    hipLaunchKernelGGL(k_accumulate, dim3(gx * ny), dim3(kBlock), 0, s, dim, (const double2 *)V, nk,
-                       (const double2 *)coef, n, k0, (double2 *)Phi, L, gx, ny);
+    auto launch = [&](auto kernel, uint32_t e) {
+        const int gx = (vec_grid(dim / e) + 7) / 8 * 8;  // element blocks, a multiple of the 8 XCDs
+        hipLaunchKernelGGL(kernel, dim3(gx * ny), dim3(kBlock), 0, s, dim, (const double2 *)V, nk,
+                           (const double2 *)coef, n, k0, (double2 *)Phi, L, gx, ny);
+    };
+    if (dim >= kAccWide)
+        launch(k_accumulate<kAccE>, kAccE);
+    else
+        launch(k_accumulate<1>, 1);
 }
 
 

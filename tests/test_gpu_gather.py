@@ -129,3 +129,29 @@ def test_cocg_batches(env, N, L, shells):
     for x, y in zip(*pairs):
         assert np.array_equal(x, y)
     assert np.abs(many[0][0]).max() > 0 and np.abs(pairs[0][0]).max() > 0
+
+
+@pytest.mark.parametrize("N,M,n,L", [(8, 2, 6, 9), (8, 64, 150, 300), (14, 6, 37, 11), (18, 4, 9, 17)])
+def test_shells_do_not_depend_on_their_number(env, N, M, n, L):
+    """Shell coefficients in one go and in slabs of their work space (300 shells of 64 contour
+    points and 150 steps), whole and partial shell groups, both widths of the accumulation;
+    8 sites also against the host's coefficients on the regenerated Krylov basis."""
+    ftk, ctx, torch = env
+    print(f"shells N={N} L={L}", flush=True)
+    cl = ftk.honeycomb_cluster(*SUPERCELLS[N])
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
+    few = 5
+    kw = dict(seed=8, n_vectors=1, betas=[0.2], E_b=-3.0, eps=0.02, M=M, n_steps=n, block_steps=6)
+    a = ftk.TypicalStates(h, L=L, **kw)
+    b = ftk.TypicalStates(h, L=few, **kw)
+    for m in range(few):
+        assert torch.equal(torch.view_as_real(a.shell(0, 0, m)), torch.view_as_real(b.shell(0, 0, m)))
+    al, be = a.lanczos(0, 0)
+    assert np.abs(a.shell(0, 0, L - 1).cpu().numpy()).max() > 0
+    if N == 8:
+        # all shells lie in the Krylov space of the first steps: sum_k c_k <v_j|v_k> = c_j
+        c = ftk.filter_coefficients(al, be, 1.0, -3.0, 0.02, L, M)
+        n2 = np.array([float((a.shell(0, 0, m).abs() ** 2).sum()) for m in range(L)])
+        ratio = n2 / np.maximum((np.abs(np.asarray(c).reshape(L, -1)[:, :len(al)]) ** 2).sum(1), 1e-300)
+        if n < 20:  # before the basis loses orthogonality, eps per step and term
+            assert np.allclose(ratio, ratio[0], rtol=1e-11)
