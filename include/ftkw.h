@@ -98,7 +98,7 @@ ftk_status ftk_ctx_set_timing(ftk_ctx *ctx, int enable);
  *       per thread, 2 = 8 elements per thread with an LDS-staged 8192-element
  *       tile, 3 = multi-pass (the bond list cut into segments, each applied
  *       inside 4096-element LDS tiles of its own site set; N >= 16 with at most
- *       6 segments, else as -1); -1 (default) takes 0 up to N = 18, 3 above when the
+ *       6 segments, else as -1); -1 (default) takes 0 up to N = 20, 3 above when the
  *       bond list needs at most 6 segments, otherwise 2.  A Hamiltonian of N >= 16 sites holds one scratch
  *       vector for the multi-pass form.
  *   "pass_grid": workgroups of each multi-pass launch that reduces partial

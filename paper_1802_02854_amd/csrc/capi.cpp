@@ -228,7 +228,7 @@ void run_few(const HvOp &op, const ResidentRun &run, const FewScratch &f, int ro
              const BatchShifts &shifts, int n_seq, hipStream_t s)
 {
     const size_t dim = (size_t)1 << op.P.n_sites, vs = 4 * dim;
-    const int nparts = vec_grid((uint32_t)dim);
+    const int nparts = pair_grid((uint32_t)dim, n_seq);
     double *W[2] = {run.carry, run.carry + 2 * dim};
     double *al = run.alpha + (size_t)row0 * run.stride, *be = run.beta + (size_t)row0 * run.stride;
     SeqState *st[2] = {run.st + row0, f.st};
@@ -351,7 +351,7 @@ struct Krylov {
             double *vout = Vbuf ? Vbuf + (size_t)(k - k0) * 2 * dim : nullptr;
             ctx->timed("filter_step", (k & 7) == 1, [&] {
                 if (pairs) {
-                    const FinBeta fb{st(i), pb, nparts, be(i), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, 0};
+                    const FinBeta fb{st(i), pb, nparts_hv, be(i), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, 0};
                     SeqState *now = st(i);
                     if (k > 0) slot ^= 1;
                     launch_lanczos_pair_a(h->op, cur, prv, out, vout, now, pa, k == 0, s, k > 0 ? &fb : nullptr, st(i));
@@ -389,7 +389,7 @@ struct Krylov {
             }
         }
         if (pairs) {
-            launch_finalize_beta(st(i), pb, nparts, be(i), n - 1, tol, nullptr, nullptr, 0, 0.0, s);
+            launch_finalize_beta(st(i), pb, nparts_hv, be(i), n - 1, tol, nullptr, nullptr, 0, 0.0, s);
         } else if (fuse) {
             // alpha and the second half of the last step
             if (fa_on) launch_finalize_alpha(st(i), pa, nparts_hv, al(i), n - 1, s);
@@ -1033,7 +1033,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
         auto filter_for = [&](Filter &f, size_t count) {
             f.row = 2 * (size_t)n * shell_rows(st->L);
             const size_t item = 2 * shell_work(st->M, n);  // doubles: two complex lists
-            f.items = (int)std::min(count * st->L, std::max<size_t>(1, (size_t(64) << 20) / (item * sizeof(double))));
+            f.items = (int)std::min(count * st->L, std::max<size_t>(1, ctx->spare_bytes / 4 / (item * sizeof(double))));
             f.m.part(&f.seq, count);
             f.m.part(&f.kn, count * st->L);
             f.m.part(&f.cs, 2 * (size_t)st->M);
@@ -1323,8 +1323,9 @@ struct BatchRunner {
                 double rtol_ = 0.0, int stack = -1, int pass_grid = 0, int hints = -1, bool own_partials = false)
         : h(H), op(with_grid(H->op, pass_grid, hints)), ctx(H->ctx), s(H->ctx->stream), dim(H->dim), B(B_), n(n_), nw(nw_),
           eta(eta_), tol(1e-12 * H->table.norm_bound), rtol(rtol_), stacked(stack_for(H, B_, stack)),
-          nparts_a(B_ == 1 || (stacked && lanczos_pairs(op, B_)) ? hv_grid(op)
-                                                                 : (stacked ? hv_grid(op, B_) : hv_batch_grid(H->dim, B_))),
+          nparts_a(B_ == 1 ? hv_grid(op)
+                           : !stacked ? hv_batch_grid(H->dim, B_)
+                                      : lanczos_pairs(op, B_) ? pair_grid(H->dim, B_) : hv_grid(op, B_)),
           nparts_b(B_ == 1 || stacked ? vec_grid(H->dim) : vec_batch_grid(H->dim, B_)),
           pairs((B_ == 1 || stacked) && lanczos_pairs(op, B_) && !g_plain_loop),
           fuse(!pairs && (stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop))), late(rtol_ == 0.0 && !g_plain_loop),
@@ -1401,7 +1402,7 @@ struct BatchRunner {
                 launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nsh, eta,
                                            s, rtol);
             } else if (pairs) {
-                const FinBeta fb{q, partials_b.d(), nparts_b, be.d(), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, n};
+                const FinBeta fb{q, partials_b.d(), nparts_a, be.d(), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, n};
                 const bool in_a = late && k > 0;
                 if (in_a) slot ^= 1;
                 launch_lanczos_pair_a(op, cur, prv, out, nullptr, q, partials.d(), k == 0, s, in_a ? &fb : nullptr,
@@ -1409,7 +1410,7 @@ struct BatchRunner {
                 const FinAlpha fa{partials.d(), nparts_a, al.d(), n, k};
                 launch_lanczos_b(dim, cur, out, states(), partials_b.d(), s, B, sk.vs, &fa);
                 if (!late)
-                    launch_finalize_beta(q, partials_b.d(), nparts_b, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol,
+                    launch_finalize_beta(q, partials_b.d(), nparts_a, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol,
                                          B, n);
             } else if (fuse && k > 0) {
                 // second half of step k-1 inside the first pass of step k (which also
@@ -1444,7 +1445,7 @@ struct BatchRunner {
     void finish()
     {
         if (pairs && late)
-            launch_finalize_beta(states(), partials_b.d(), nparts_b, be.d(), n - 1, tol, nullptr, nullptr, 0, eta, s,
+            launch_finalize_beta(states(), partials_b.d(), nparts_a, be.d(), n - 1, tol, nullptr, nullptr, 0, eta, s,
                                  0.0, B, n);
         if (!fuse) return;
         if (alpha_in_fused_pass()) launch_finalize_alpha(states(), partials.d(), nparts_a, al.d(), n - 1, s, B, n);
@@ -1679,7 +1680,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
     }
     // the winner's persistent workgroups per reducing multi-pass launch: half and twice
     // the default (results do not depend on it: the partial sums are exact)
-    if ((hv_mode(h->op) == 3 || h->n_sites >= kGatherSites) && lanczos_stackable(h->op) &&
+    if ((hv_mode(h->op) == 3 || h->n_sites >= 18) && lanczos_stackable(h->op) &&
         (best.rhs_block == 1 || best.stacked)) {
         const int cap = pass_grid_cap(h->op);
         for (int pg : {cap / 2, 2 * cap}) {

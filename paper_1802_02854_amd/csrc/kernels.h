@@ -55,9 +55,8 @@ struct ShiftState {
 constexpr int kR = 8;               // elements per thread in the blocked H v
 constexpr int kBlock = 256;         // threads per block of the vector kernels
 constexpr int kMaxRows = 32768;     // rows of one launch (grid y)
-constexpr int kGatherSites = 18;    // largest N whose Lanczos steps run one element per thread
-constexpr int kApplySites = 20;     // and whose plain products and Taylor terms do
-constexpr int kPairBits = 19;       // largest log2(sequences * 2^N) of the two-launch Lanczos step
+constexpr int kGatherSites = 20;    // largest N whose single vectors run one element per thread
+constexpr int kPairBits = 19;       // largest log2(sequences * 2^N) of stacks in the two-launch Lanczos step
 constexpr int kMaxGrid = 4096;      // blocks of the grid-stride vector kernels
 constexpr int kChunk = 512;         // elements per wave in the blocked H v (64 lanes x 8)
 constexpr int kTile = 8192;         // elements per workgroup tile staged in LDS (128 KiB)
@@ -134,6 +133,7 @@ struct HvOp {
 };
 
 int vec_grid(uint32_t dim);          // grid of the streaming kernels
+int pair_grid(uint32_t dim, int B);  // grid of a sequence in the two launches of a step (lanczos_pairs)
 // 0 one element per thread, 1 blocked, 2 blocked + LDS tile, 3 multi-pass
 int hv_mode(const HvOp &op);
 int hv_grid(const HvOp &op);         // grid of the H-applying kernels (= number of partial sums)
@@ -244,7 +244,7 @@ void launch_finalize_alpha(SeqState *st, const double *partials, int nparts, dou
                            int k, hipStream_t s, int B = 1, int astride = 0);
 // second half: w_k = u - alpha_k v_k in place of u; partial sums of ||w_k||^2
 // (vec_grid of them).  B > 1: vectors vs doubles apart, partials 2*vec_grid apart.
-// fa: alpha_k is summed here first.
+// fa: alpha_k is summed here first (pair_grid partial sums then).
 void launch_lanczos_b(uint32_t dim, const double *Wcur, double *U, SeqState *st,
                       double *partials, hipStream_t s, int B = 1, size_t vs = 0, const FinAlpha *fa = nullptr);
 // beta_{k+1}, inv_{k+1}, breakdown test and the multi-shift update of step k.

@@ -161,6 +161,17 @@ size_t make_hv_dev(const HvParams &P, const HvPlan &plan, HvDev &d)
     return offsetof(HvDev, pass) + sizeof(PassDev) * (size_t)plan.n_passes;
 }
 
+// Few enough workgroups that each can sum all partials of the launch before it, enough to
+// fill the chip: 512 in all up to 2^18 elements, 1024 above.  us per step, workgroups in all
+// 256 / 512 / 1024 / 2048: 16 sites, stack of 2, 16.5 / 15.2 / - / -; 18 sites, one, 22.3 /
+// 19.6 / 20.6 / -, stack of 2, 33.5 / 26.4 / 24.9 / 30.1; 16 sites, stack of 8, - / - / 23.8 /
+// 26.7; 20 sites, one, 62.1 / 44.8 / 42.9 / - (4096: 66).
+int pair_grid(uint32_t dim, int B)
+{
+    const int cap = ((size_t)dim * B <= ((size_t)1 << 18) ? 512 : 1024) / B;
+    return std::min(vec_grid(dim), std::max(cap, 1));
+}
+
 int vec_grid(uint32_t dim)
 {
     uint32_t g = (dim + kBlock - 1) / kBlock;
@@ -252,21 +263,13 @@ int hv_mode(const HvOp &op)
     int best = dim >= (uint32_t)kTile ? 2 : (dim >= (uint32_t)kChunk ? 1 : 0);
     if (g_hv_mode == 3) return multi ? 3 : best;
     if (g_hv_mode >= 0) return g_hv_mode <= best ? g_hv_mode : best;
-    // by size: one element per thread while a vector fits in an XCD's L2 (4 MiB, 18 sites;
-    // the measurements are at k_hv_simple), the multi-pass form above (also with 5 passes
-    // it beats the single-kernel tiled form, 11.9 against 16.9 ms at 28 sites, 48.5 against
-    // 81.8 ms at 30)
+    // by size: one element per thread up to 20 sites (us per apply 24, multi-pass 36, 42 with
+    // natural labels; per Lanczos step of one sequence 41.6 and 45.4; 24 sites 880 and 346 an
+    // apply), the multi-pass form above (also with 5 passes it beats the single-kernel tiled
+    // form, 11.9 against 16.9 ms at 28 sites, 48.5 against 81.8 ms at 30)
     if (op.P.n_sites <= kGatherSites) return 0;
     if (multi) return 3;
     return best;
-}
-
-// Without reductions and a first half step to fuse with, one element per thread is ahead
-// two sites further: 20 sites 24 us, multi-pass 36 (42 with natural labels); a Lanczos
-// step 66, multi-pass 50; 24 sites 880, multi-pass 360.
-static int product_mode(const HvOp &op)
-{
-    return g_hv_mode < 0 && op.P.n_sites <= kApplySites ? 0 : hv_mode(op);
 }
 
 int pass_grid_cap(const HvOp &op)
@@ -306,7 +309,7 @@ int hv_grid(const HvOp &op)
         return (int)(g < 1 ? 1 : (g < (uint32_t)kMaxGrid ? g : (uint32_t)kMaxGrid));
     }
     default:
-        return vec_grid(dim);
+        return pair_grid(dim, 1);
     }
 }
 
@@ -933,7 +936,7 @@ template <class Epi>
 void launch_hv(const HvOp &op, const double *v, Epi epi, hipStream_t s)
 {
     const int grid = hv_grid(op);
-    switch (Epi::kReduces ? hv_mode(op) : product_mode(op)) {
+    switch (hv_mode(op)) {
     case 3:
         launch_passes(op, 0, v, epi, s);
         break;
@@ -945,8 +948,8 @@ void launch_hv(const HvOp &op, const double *v, Epi epi, hipStream_t s)
         hipLaunchKernelGGL(k_hv_blocked<Epi>, dim3(grid), dim3(kBlock), 0, s, op.dev, (const double2 *)v, epi);
         break;
     default:
-        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(vec_grid(1u << op.P.n_sites)), dim3(kBlock), 0, s, op.dev,
-                           (const double2 *)v, (size_t)0, epi);
+        hipLaunchKernelGGL(k_hv_simple<Epi>, dim3(Epi::kReduces ? grid : vec_grid(1u << op.P.n_sites)), dim3(kBlock), 0,
+                           s, op.dev, (const double2 *)v, (size_t)0, epi);
     }
 }
 
@@ -954,7 +957,7 @@ void launch_apply_h(const HvOp &op, const double *v, double *w, hipStream_t s, i
 {
     EpiApply e;
     e.w = (double2 *)w;
-    if (product_mode(op) == 0) {  // all rows in one launch
+    if (hv_mode(op) == 0) {  // all rows in one launch
         for (int r = 0; r < n_rhs; r += kMaxRows) {
             hipLaunchKernelGGL(k_hv_simple<EpiApply>, dim3(vec_grid(1u << op.P.n_sites), std::min(kMaxRows, n_rhs - r)),
                                dim3(kBlock), 0, s, op.dev, (const double2 *)(v + r * stride), stride / 2, e);
@@ -1109,17 +1112,18 @@ void launch_lanczos_pair_a(const HvOp &op, const double *Wcur, const double *Wpr
     e.fin = fb ? 2 : 0;
     e.st_out = st_out;
     if (fb) e.fb = *fb;
-    hipLaunchKernelGGL(k_hv_simple<EpiLanczosADev>, dim3(hv_grid(op), B), dim3(kBlock), 0, s, op.dev,
+    hipLaunchKernelGGL(k_hv_simple<EpiLanczosADev>, dim3(pair_grid(1u << op.P.n_sites, B), B), dim3(kBlock), 0, s, op.dev,
                        (const double2 *)Wcur, vs / 2, e);
 }
 
-// us per step and sequence, multi-pass against two launches of one element per thread:
-// 16 sites, 1 sequence: 35 (46 in four launches, tiled) / 13.4, stack of 4: 7.5 / 5.1, of
-// 8: 4.3 / 3.7, of 16: 2.4 / 3.0; 18 sites, 2: 17.9 / 16.7, 4: 10.3 / 13.7.  A larger stack fills
-// the chip with multi-pass tiles, whose bonds read LDS.
+// us per step, multi-pass against two launches of one element per thread: 16 sites, one
+// sequence 35 (46 in four launches, tiled) / 11.8, stack of 4 26.7 / 16.7, of 8 30.1 /
+// 22.6, of 16 35.2 / 37.0; 18 sites, one 36 / 18.9, stack of 2 32.3 / 24.0, of 4 35.9 /
+// 39.3; 20 sites, one 45.4 / 41.6, stack of 2 73.5 / 80.1.  A larger stack fills the chip with
+// multi-pass tiles, whose bonds read LDS.
 bool lanczos_pairs(const HvOp &op, int B)
 {
-    return g_fuse_fin && hv_mode(op) == 0 && ((size_t)B << op.P.n_sites) <= ((size_t)1 << kPairBits);
+    return g_fuse_fin && hv_mode(op) == 0 && (B == 1 || ((size_t)B << op.P.n_sites) <= ((size_t)1 << kPairBits));
 }
 
 // First half of a shifted COCG step (cocg.hip) where H v is one element per thread.
@@ -1150,7 +1154,7 @@ struct EpiCocg {
     __device__ void finish() { write_partials5<2>(partials, a.hi, a.lo); }
 };
 
-bool cocg_work_vectors(const HvOp &op) { return product_mode(op) != 0; }
+bool cocg_work_vectors(const HvOp &op) { return hv_mode(op) != 0; }
 
 void launch_hv_cocg(const HvOp &op, const double *Wcur, const double *Wprev, double *U, const CocgState *st,
                     double *pa, int first, int B, hipStream_t s)
@@ -1327,8 +1331,8 @@ void launch_finalize_alpha(SeqState *st, const double *partials, int nparts, dou
 void launch_lanczos_b(uint32_t dim, const double *Wcur, double *U, SeqState *st,
                       double *partials, hipStream_t s, int B, size_t vs, const FinAlpha *fa)
 {
-    hipLaunchKernelGGL(k_lanczos_b, dim3(vec_grid(dim), B), dim3(kBlock), 0, s, dim, (const double2 *)Wcur,
-                       (double2 *)U, st, partials, vs / 2, fa ? *fa : FinAlpha{nullptr, 0, nullptr, 0, 0}, fa ? 1 : 0);
+    hipLaunchKernelGGL(k_lanczos_b, dim3(fa ? pair_grid(dim, B) : vec_grid(dim), B), dim3(kBlock), 0, s, dim,
+                       (const double2 *)Wcur, (double2 *)U, st, partials, vs / 2, fa ? *fa : FinAlpha{nullptr, 0, nullptr, 0, 0}, fa ? 1 : 0);
 }
 
 void launch_finalize_beta(SeqState *st, const double *partials, int nparts, double *beta_out,
