@@ -356,8 +356,10 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * of 6 to 14 sites run every sequence of the call in one launch, one workgroup
  * each, whatever rhs_block says (unless a tuning key forces another form); the
  * vectors of such a launch take up to 256 MiB of device memory.  From 16 sites
- * on, batches whose vectors (4 per sequence) come to at most 256 MiB run in two
- * chains on two streams, with the buffers of both (not while kernel timing is on).
+ * on, while the vectors of a batch (4 per sequence) come to at most 256 MiB, more
+ * sequences than rhs_block run at a time, in even batches on two streams with up
+ * to 256 MiB of vectors more, but for the block layout, kernel timing and tuning
+ * keys that force a form.
  * Shifted COCG runs as many sequences in lockstep as fit in 256 MiB, up to 32.
  * resid_tol > 0 truncates each sequence at the first step k <= n_steps after
  * which the largest Galerkin residual over the shifts, per unit right-hand side

@@ -67,6 +67,8 @@ void need(bool ok, const char *msg)
 
 }  // namespace
 
+constexpr int kMaxChains = 2;  // batches of Green's sequences in flight, a stream each
+
 // ---------------------------------------------------------------------------
 struct ftk_ctx {
     int device = 0;
@@ -79,8 +81,8 @@ struct ftk_ctx {
     // (the vectors of a launch of resident sequences: one sequence per compute unit at 14
     // sites, more below; a second chain of batches)
     size_t spare_bytes = size_t(256) << 20;
-    hipStream_t second = nullptr;  // of the second chain, made when first needed
-    std::once_flag second_once;
+    hipStream_t chain[kMaxChains - 1] = {};  // of further chains of batches, made when first needed
+    std::once_flag chain_once;
     size_t bytes = 0;
     size_t peak = 0;  // high-water mark of bytes since the last reset
     bool timing = false;
@@ -114,7 +116,8 @@ struct ftk_ctx {
     ~ftk_ctx()
     {
         clear_events();
-        if (second) (void)hipStreamDestroy(second);
+        for (hipStream_t c : chain)
+            if (c) (void)hipStreamDestroy(c);
         if (own_stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -1478,29 +1481,39 @@ struct BatchRunner {
             }
             return;
         }
-        // The first batch is launched step by step: the GPU starts at once and the host
-        // stays ahead of it.  The graph for the following ones is captured while it runs
-        // (16 sites, one batch of 32 sequences of 200 steps: 74 us a step with the capture
-        // first, 67 without; replayed and launched steps take the same time).
-        if (g_use_graphs && runs++ > 0) {
-            if (!exec) {
-                slot = 0;
-                capturing = true;
-                HIP_CHECK(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-                for (int k = 0; k < n; ++k) step(k);
-                finish();
-                HIP_CHECK(hipStreamEndCapture(s, &graph));
-                capturing = false;
-                HIP_CHECK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-                end_slot = slot;
-            }
-            slot = end_slot;
-            // the whole n-step loop of the batch: B sequences x n steps
-            ctx->timed("lanczos_block", true, [&] { HIP_CHECK(hipGraphLaunch(exec, s)); });
-        } else {
+        if (!replays()) {
             for (int k = 0; k < n; ++k) step(k);
             finish();
+            return;
         }
+        if (!exec) {
+            slot = 0;
+            capturing = true;
+            HIP_CHECK(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
+            for (int k = 0; k < n; ++k) step(k);
+            finish();
+            HIP_CHECK(hipStreamEndCapture(s, &graph));
+            capturing = false;
+            HIP_CHECK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+            end_slot = slot;
+        }
+        slot = end_slot;
+        // the whole n-step loop of the batch: B sequences x n steps
+        ctx->timed("lanczos_block", true, [&] { HIP_CHECK(hipGraphLaunch(exec, s)); });
+    }
+    // The first batch is launched step by step: the GPU starts at once and the host stays
+    // ahead of it.  The graph for the following ones is captured while it runs (16 sites,
+    // one batch of 32 sequences of 200 steps: 74 us a step with the capture first, 67
+    // without; replayed and launched steps take the same time).
+    bool replays() { return g_use_graphs && !g_plain_loop && runs++ > 0; }
+    // The first batches of several chains, step by step in turn: launched one after the
+    // other a chain would start when the host is through with the one before.
+    static void run_together(const std::vector<BatchRunner *> &chains)
+    {
+        if (chains.size() == 1) return chains[0]->run();
+        for (int k = 0; k < chains[0]->n; ++k)
+            for (BatchRunner *c : chains) c->step(k);
+        for (BatchRunner *c : chains) c->finish(), c->runs++;
     }
 };
 
@@ -1879,11 +1892,37 @@ void check_green(const GreenOut &out)
         if (q.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in Green's-function Lanczos coefficients");
 }
 
+// How `rows` sequences run: batches of B in `chains` chains, each on its own stream.  A
+// second chain fills the first one's launch gaps and overlaps its loads with the other's
+// bonds (all workgroups of a small launch are in the same phase), and larger stacks share
+// launches, so up to 64 sequences go in flight, those beyond the batch asked for with up
+// to 256 MiB of vectors (the last-level cache's size), in even batches.  us per sequence and step as asked, in chains of
+// what was asked, so: 16 sites, 6 in batches of 1: 12 / 7.6 / 3.9; 24 of 8: 2.8 / 2.6 /
+// 2.4; 72 of 32: 2.1 / 2.2 / 1.85; 110 of 32: 1.9 / 1.8 / 1.6; 18 sites, 4 of 1: 19 / 13.3
+// / 10.6; 24 of 16: 6.4 / 6.6 / 6.3; 20 sites, 4 of 1: 41.6 / 38.9 / 35.4.  Three or four
+// chains are no faster (16 sites, 110 in flight in four: 1.77).
+// The batch asked for runs alone where its vectors are past 256 MiB (20 sites, two chains
+// of 16: 35.4 us per sequence and step against 31.0; 24 sites, of 1: 557 against 510), in
+// the block layout, under kernel timing and wherever a tuning key forces a form.
+void spread_rows(const ftk_hamiltonian *h, size_t rows, int stack, bool streams, int &B, int &chains)
+{
+    ftk_ctx *ctx = h->ctx;
+    const size_t per = 16 * (size_t)h->dim * 4;
+    if (per * B > ctx->spare_bytes || ctx->timing || forced_hv_mode() >= 0 || g_plain_loop ||
+        (stack == 0 && B > 1) || !BatchRunner::stack_for(h, 2, -1))
+        return;
+    const size_t limit = streams ? kMaxChains : 1;
+    const size_t most = std::max<size_t>(B, std::min(limit * kMaxBatch, B + ctx->spare_bytes / per));
+    const size_t rounds = (rows + most - 1) / most, now = (rows + rounds - 1) / rounds;
+    chains = (int)std::min(limit, now);
+    B = (int)((now + chains - 1) / chains);
+}
+
 // Runs the items in batches of B through one graph-captured BatchRunner; load(run, r,
 // item) writes the item's right-hand side into slot r.  Slots of sequences not listed
 // stay zero.  Small clusters run resident instead, from ops.
-// Two chains of batches on two streams, where load_any_stream says that load works
-// on either.
+// Several chains of batches (spread_rows) where load_any_stream says that load works on
+// any stream.
 template <class Load>
 GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const double *omega, int nw, double eta,
                    double rtol, int nseq, const std::vector<GreenItem> &work, const StartOps &ops, bool load_any_stream,
@@ -1906,62 +1945,77 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     m.part(&be, rows * n);
     m.part(&g, rows * nw * 2);
     m.allocate(ctx);
-    const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
-    BatchRunner first(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints);
-    // A second chain of batches on its own stream fills the first one's launch gaps and
-    // overlaps its loads with the other's bonds: all workgroups of a small launch are in
-    // the same phase.  Worth it while both chains' vectors stay near the last-level cache:
-    // us per sequence and step, one chain against two, 16 sites, stacks of 32 (256 MiB for
-    // both): 1.89 / 1.52; 18 sites, 16 (512 MiB): 6.4 / 5.4; 20 sites, 4 (512 MiB): 35.1 /
-    // 29.7; but 20 sites, 16 (2 GiB): 31.0 / 35.4 and 24 sites, 1 (2 GiB): 510 / 557.
-    // Kernel timing wants the launches of one stream.
-    const size_t vectors = sizeof(double) * 2 * (size_t)h->dim * B * 4;
-    bool two = load_any_stream && (first.fuse || first.pairs) && rows > (size_t)B && vectors <= ctx->spare_bytes && !ctx->timing;
-    std::unique_ptr<BatchRunner> other;
-    struct Joined {  // nothing of the second chain runs once its buffers are freed
-        hipStream_t s = nullptr;
+    int chains = 1;
+    const int asked = B;
+    spread_rows(h, rows, stack, load_any_stream, B, chains);
+    std::vector<std::unique_ptr<BatchRunner>> run;
+    auto make = [&] {
+        const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
+        for (int c = 0; c < chains; ++c)
+            run.push_back(std::make_unique<BatchRunner>(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints, c > 0));
+    };
+    try {
+        make();
+    } catch (const Error &e) {
+        if (e.status != FTK_ENOMEM || (chains == 1 && B == asked)) throw;
+        run.clear();
+        chains = 1;  // no room: one batch at a time, as asked
+        B = asked;
+        make();
+    }
+    struct Joined {  // nothing of a further chain runs once its buffers are freed
+        std::vector<hipStream_t> s;
         hipEvent_t e = nullptr;
         ~Joined()
         {
-            if (s) (void)hipStreamSynchronize(s);
+            for (hipStream_t c : s) (void)hipStreamSynchronize(c);
             if (e) (void)hipEventDestroy(e);
         }
     } joined;
-    if (two) {
-        try {
-            other = std::make_unique<BatchRunner>(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints, true);
-        } catch (const Error &e) {
-            if (e.status != FTK_ENOMEM) throw;
-            two = false;  // no room for it: one chain
-        }
-    }
-    if (two) {
-        std::call_once(ctx->second_once, [&] { HIP_CHECK(hipStreamCreate(&ctx->second)); });
-        other->s = joined.s = ctx->second;
+    if (chains > 1) {
+        std::call_once(ctx->chain_once, [&] {
+            for (hipStream_t &c : ctx->chain) HIP_CHECK(hipStreamCreate(&c));
+        });
         // after everything queued so far: the shells, the allocations of this call
         HIP_CHECK(hipEventCreateWithFlags(&joined.e, hipEventDisableTiming));
         HIP_CHECK(hipEventRecord(joined.e, s));
-        HIP_CHECK(hipStreamWaitEvent(joined.s, joined.e, 0));
-    }
-    for (size_t w0 = 0, batch = 0; w0 < rows; w0 += B, ++batch) {
-        BatchRunner &run = two && batch % 2 ? *other : first;
-        const int cnt = (int)std::min<size_t>(B, rows - w0);
-        if (cnt < B) HIP_CHECK(hipMemsetAsync(run.chi.p, 0, run.chi.n, run.s));
-        BatchShifts bs;
-        for (int r = 0; r < kMaxBatch; ++r) bs.re[r] = 0.0;
-        for (int r = 0; r < cnt; ++r) {
-            load(run, r, work[w0 + r]);
-            bs.re[r] = work[w0 + r].Em;
+        for (int c = 1; c < chains; ++c) {
+            run[c]->s = ctx->chain[c - 1];
+            joined.s.push_back(run[c]->s);
+            HIP_CHECK(hipStreamWaitEvent(run[c]->s, joined.e, 0));
         }
-        run.start(bs);
-        run.run();
-        run.read_green(cnt, g + w0 * 2 * nw);
-        HIP_CHECK(hipMemcpyAsync(al + w0 * n, run.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, run.s));
-        HIP_CHECK(hipMemcpyAsync(be + w0 * n, run.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, run.s));
-        HIP_CHECK(hipMemcpyAsync(st + w0, run.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, run.s));
     }
-    if (two) {
-        HIP_CHECK(hipEventRecord(joined.e, joined.s));
+    for (size_t w0 = 0; w0 < rows; w0 += (size_t)B * chains) {
+        std::vector<BatchRunner *> now;
+        for (int c = 0; c < chains && w0 + (size_t)c * B < rows; ++c) {
+            BatchRunner &q = *run[c];
+            const size_t r0 = w0 + (size_t)c * B;
+            const int cnt = (int)std::min<size_t>(B, rows - r0);
+            if (cnt < B) HIP_CHECK(hipMemsetAsync(q.chi.p, 0, q.chi.n, q.s));
+            BatchShifts bs{};
+            for (int r = 0; r < cnt; ++r) {
+                load(q, r, work[r0 + r]);
+                bs.re[r] = work[r0 + r].Em;
+            }
+            q.start(bs);
+            now.push_back(&q);
+        }
+        if (w0 == 0)
+            BatchRunner::run_together(now);
+        else
+            for (BatchRunner *q : now) q->run();
+        for (size_t c = 0; c < now.size(); ++c) {
+            BatchRunner &q = *now[c];
+            const size_t r0 = w0 + c * B;
+            const int cnt = (int)std::min<size_t>(B, rows - r0);
+            q.read_green(cnt, g + r0 * 2 * nw);
+            HIP_CHECK(hipMemcpyAsync(al + r0 * n, q.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
+            HIP_CHECK(hipMemcpyAsync(be + r0 * n, q.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
+            HIP_CHECK(hipMemcpyAsync(st + r0, q.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, q.s));
+        }
+    }
+    for (hipStream_t c : joined.s) {
+        HIP_CHECK(hipEventRecord(joined.e, c));
         HIP_CHECK(hipStreamWaitEvent(s, joined.e, 0));
     }
     HIP_CHECK(hipGetLastError());

@@ -7,10 +7,10 @@ from seeded_inputs import SUPERCELLS
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,B,alloc", [(16, 1, None), (16, 4, "torch"), (18, 16, None), (20, 4, None)])
+@pytest.mark.parametrize("N,B,alloc", [(16, 1, None), (16, 4, "torch"), (16, 32, None), (18, 16, None), (20, 4, None)])
 def test_two_chains_match_one(N, B, alloc):
-    """An odd number of batches, the last one ragged, every batch's graph replayed at most once
-    more than it was launched step by step; kernel timing keeps the batches in one chain."""
+    """One to three rounds of two batches, with ragged last ones, against the batches asked for
+    in one chain, which kernel timing keeps."""
     import torch
 
     import paper_1802_02854_amd as ftk
@@ -18,7 +18,7 @@ def test_two_chains_match_one(N, B, alloc):
     ctx = ftk.Context(0, allocator=alloc)
     cl = ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[N]))[0]
     h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
-    L = {1: 7, 4: 6, 16: 16}[B]
+    L = {1: 7, 4: 6, 16: 16, 32: 23}[B]
     st = ftk.TypicalStates(h, seed=2, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=L, M=4, n_steps=8)
     alpha = 4 if B == 1 else 7
     res = []
