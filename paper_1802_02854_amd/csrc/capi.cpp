@@ -1076,18 +1076,25 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             }
         };
 
-        if (resident_run(h->op)) {
-            // Small clusters: the filter sequences of several (vector, anchor) pairs run
-            // side by side, one workgroup each; pass 2 in blocks of nb steps with the
-            // sequences' vectors carried over.
-            const size_t pairs = (size_t)st->nv * st->na, cplx = 2 * (size_t)dim;
-            const size_t group = std::min(pairs, std::max<size_t>(1, ctx->spare_bytes / (vbytes * (nb + 3))));
-            Arena m;
-            ResidentSeq *seq;
-            SeqState *state;
-            double *phib, *carry, *vbuf, *al_d, *be_d;
-            Filter fl;
-            filter_for(fl, group);
+        // Small clusters, and pairs of larger ones that the two-launch step takes together (16
+        // sites, two pairs: 14.4 us a step, 11.8 for one): the filter sequences of several
+        // (vector, anchor) pairs run side by side; pass 2 in blocks of nb steps with the
+        // sequences' vectors carried over.
+        const size_t pairs = (size_t)st->nv * st->na, cplx = 2 * (size_t)dim;
+        size_t group = std::min(pairs, std::max<size_t>(1, ctx->spare_bytes / (vbytes * (nb + 3))));
+        bool side_by_side = resident_run(h->op);
+        if (!side_by_side && forced_hv_mode() < 0 && !g_plain_loop && !ctx->timing) {
+            while (group > 1 && !few_sequences(h->op, group)) --group;
+            side_by_side = group > 1;
+        }
+        Arena m;
+        ResidentSeq *seq;
+        SeqState *state;
+        double *phib, *carry, *vbuf, *al_d, *be_d;
+        Filter fl;
+        FewScratch fs;
+        const bool few = side_by_side && few_sequences(h->op, group);
+        if (side_by_side) {
             m.part(&seq, group);
             m.part(&state, group);
             m.part(&phib, group * cplx);
@@ -1095,10 +1102,17 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             m.part(&vbuf, group * nb * cplx);
             m.part(&al_d, group * n);
             m.part(&be_d, group * n);
-            FewScratch fs;
-            const bool few = few_sequences(h->op, group);
             if (few) fs.parts(m, dim);
-            m.allocate(ctx);
+            try {
+                m.allocate(ctx);
+            } catch (const Error &e) {
+                if (e.status != FTK_ENOMEM || resident_run(h->op)) throw;
+                side_by_side = false;  // no room: one after the other
+            }
+        }
+        filter_for(fl, side_by_side ? group : 1);
+
+        if (side_by_side) {
             std::vector<ResidentSeq> hseq(group);
             std::vector<SeqState> hstate(group);
             std::vector<double> hal(group * n), hbe(group * n);
@@ -1174,8 +1188,6 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             }
         } else {
             DevBuf phib(ctx, vbytes), W0(ctx, vbytes), W1(ctx, vbytes), Vbuf(ctx, vbytes * nb);
-            Filter fl;
-            filter_for(fl, 1);
             for (int sv = 0; sv < st->nv; ++sv) {
                 start_vector(sv);
                 for (int a = 0; a < st->na; ++a) {

@@ -155,3 +155,23 @@ def test_shells_do_not_depend_on_their_number(env, N, M, n, L):
         ratio = n2 / np.maximum((np.abs(np.asarray(c).reshape(L, -1)[:, :len(al)]) ** 2).sum(1), 1e-300)
         if n < 20:  # before the basis loses orthogonality, eps per step and term
             assert np.allclose(ratio, ratio[0], rtol=1e-11)
+
+
+@pytest.mark.parametrize("nv,betas", [(1, [0.0, 0.7]), (3, [0.4])])
+def test_filter_runs_side_by_side(env, nv, betas):
+    """16 sites: the filter sequences of several (vector, anchor) pairs in lockstep, in groups
+    of two where the memory allowance asks for it, against one after the other."""
+    ftk, ctx, torch = env
+    print(f"side by side nv={nv}", flush=True)
+    h = ftk.Hamiltonian(ctx, ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[16]))[0], -1.0, 0.1)
+
+    def states(nb):
+        st = ftk.TypicalStates(h, seed=9, n_vectors=nv, betas=betas, E_b=None, eps=None, L=7, M=4, n_steps=105,
+                               block_steps=nb, shell_moments=True)
+        sa = [(s, a) for s in range(nv) for a in range(len(betas))]
+        return [*st.scalars(), *st.moments(), *st.window(), *[x for p in sa for x in st.lanczos(*p)],
+                *[st.shell(*p, m).cpu().numpy() for p in sa for m in range(7)]]
+    two = [states(10), states(100)]  # 100: two pairs to a group
+    for one in (two[1], _forced(ftk, 3, lambda: states(10))):
+        for x, y in zip(two[0], one):
+            assert np.array_equal(x, y)
