@@ -1033,16 +1033,20 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             std::vector<ShellSeq> hseq;
             std::vector<int> hkn;
         };
-        auto filter_for = [&](Filter &f, size_t count) {
+        // the work space is the vectors' buffer of pass 2, free until then, where that holds it
+        auto filter_for = [&](Filter &f, size_t count, double *buf, size_t buf_bytes) {
             f.row = 2 * (size_t)n * shell_rows(st->L);
             const size_t item = 2 * shell_work(st->M, n);  // doubles: two complex lists
-            f.items = (int)std::min(count * st->L, std::max<size_t>(1, ctx->spare_bytes / 4 / (item * sizeof(double))));
+            const size_t all = count * st->L, need_bytes = all * item * sizeof(double);
+            const bool own = need_bytes > buf_bytes;
+            f.items = (int)(own ? std::min(all, std::max<size_t>(1, ctx->spare_bytes / 4 / (item * sizeof(double)))) : all);
             f.m.part(&f.seq, count);
             f.m.part(&f.kn, count * st->L);
             f.m.part(&f.cs, 2 * (size_t)st->M);
-            f.m.part(&f.work, f.items * item);
+            f.m.part(&f.work, own ? f.items * item : 0);
             f.m.part(&f.coef, count * f.row);
             f.m.allocate(ctx);
+            if (!own) f.work = buf;
             f.hseq.resize(count);
             f.hkn.resize(count * st->L);
             HIP_CHECK(hipMemcpyAsync(f.cs, hcs.data(), hcs.size() * sizeof(double), hipMemcpyHostToDevice, s));
@@ -1110,9 +1114,8 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                 side_by_side = false;  // no room: one after the other
             }
         }
-        filter_for(fl, side_by_side ? group : 1);
-
         if (side_by_side) {
+            filter_for(fl, group, vbuf, group * nb * vbytes);
             std::vector<ResidentSeq> hseq(group);
             std::vector<SeqState> hstate(group);
             std::vector<double> hal(group * n), hbe(group * n);
@@ -1188,6 +1191,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             }
         } else {
             DevBuf phib(ctx, vbytes), W0(ctx, vbytes), W1(ctx, vbytes), Vbuf(ctx, vbytes * nb);
+            filter_for(fl, 1, Vbuf.d(), vbytes * nb);
             for (int sv = 0; sv < st->nv; ++sv) {
                 start_vector(sv);
                 for (int a = 0; a < st->na; ++a) {

@@ -1647,7 +1647,7 @@ void launch_shell_coefficients(const ShellSeq *seq, int n_seq, int n_max, int L,
 // twice as long: 128 coefficient rows in flight per workgroup overran the scalar cache).
 // Four vectors are read ahead (14 sites, 16 shells, 64 vectors: a chain of 64 loads, 25.6
 // us -> 14.6), and from 18 sites a thread takes two elements per coefficient load (20
-// sites, 128 shells, 64 vectors: 2.39 ms -> 1.69, 40 TFLOP/s; one element 2.09, four 2.22:
+// sites, 128 shells, 64 vectors: 2.39 ms -> 1.56, 43 TFLOP/s; one element 2.09, four 2.22:
 // two wavefronts per SIMD).  Smaller vectors need the workgroups.
 constexpr int kAccAhead = 4;
 constexpr uint32_t kAccWide = 1u << 18;
@@ -1694,7 +1694,11 @@ __device__ __forceinline__ void accumulate_rows(uint32_t dim, const double2 *__r
 #pragma unroll
             for (int e = 0; e < E; ++e) v[u][e] = V[(size_t)(k + u) * dim + x + e * kBlock];
 #pragma unroll
-        for (int u = 0; u < kAccAhead; ++u) accumulate_step<E, FULL>(acc, v[u], cf + (size_t)(k + u) * rows, mc);
+        for (int u = 0; u < kAccAhead; ++u) {
+            accumulate_step<E, FULL>(acc, v[u], cf + (size_t)(k + u) * rows, mc);
+            // one step's coefficients at a time: four steps' do not fit in the scalar registers
+            if (E > 1) __builtin_amdgcn_sched_barrier(0);
+        }
     }
     for (; k < nk; ++k) {
         double2 v[E];
