@@ -208,8 +208,8 @@ bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
 // A few sequences of the larger resident sizes go through the whole chip together, two
 // launches a step, instead of one workgroup each, which leaves most compute units idle.
 // us per step of 1 / 8 / 32 sequences, one workgroup each against together (three bonds
-// per site): 12 sites 13.0 / 13.1 / 13.5, 12.4 / 12.8 / 16.9; 13 sites 41.8 / 41.9 / 42.0,
-// 12.9 / 13.9 / 22.2; 14 sites 49.8 / 49.8 / 49.8, 13.0 / 17.6 / 35.2.
+// per site): 12 sites 13.0 / 13.1 / 13.5, 12.4 / 12.8 / 16.9; 13 sites 41.5 / 41.9 / 42.3,
+// 11.4 / 12.7 / 18.9; 14 sites 49.3 / 49.9 / 50.2, 11.8 / 15.3 / 28.7.
 constexpr int kFewSeqs = kMaxBatch;
 bool few_sequences(const HvOp &op, size_t n_seq)
 {
