@@ -99,8 +99,8 @@ ftk_status ftk_ctx_set_timing(ftk_ctx *ctx, int enable);
  *       tile, 3 = multi-pass (the bond list cut into segments, each applied
  *       inside 4096-element LDS tiles of its own site set; N >= 16 with at most
  *       6 segments, else as -1); -1 (default) takes 0 up to N = 20, 3 above when the
- *       bond list needs at most 6 segments, otherwise 2.  A Hamiltonian of N >= 16 sites holds one scratch
- *       vector for the multi-pass form.
+ *       bond list needs at most 6 segments, otherwise 2.  A Hamiltonian of
+ *       N >= 16 sites holds one scratch vector for the multi-pass form.
  *   "pass_grid": workgroups of each multi-pass launch that reduces partial
  *       sums (the last pass of a Lanczos step and the fused first pass; 0, the
  *       default: two per compute unit, each looping over 4096-element tiles).
@@ -354,9 +354,9 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * takes the value ftk_autotune picks for this Hamiltonian and n_omega.  32 runs
  * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").  Clusters
  * of 6 to 14 sites run every sequence of the call in one launch, one workgroup
- * each, whatever rhs_block says (unless a tuning key forces another form); the
- * vectors of such a launch take up to 256 MiB of device memory.  From 16 sites
- * on, while the vectors of a batch (4 per sequence) come to at most 256 MiB, more
+ * each (up to 32 of 13 or 14 sites in lockstep), whatever rhs_block says (unless a
+ * tuning key forces another form); the vectors of such a launch take up to 256
+ * MiB of device memory.  From 16 sites on, while the vectors of a batch (4 per sequence) come to at most 256 MiB, more
  * sequences than rhs_block run at a time, in even batches on two streams with up
  * to 256 MiB of vectors more, but for the block layout, kernel timing and tuning
  * keys that force a form.
@@ -390,7 +390,7 @@ ftk_status ftk_states_destroy(ftk_states *st);
  *       once every shift is converged (else after n_steps, a breakdown or the
  *       resid_tol truncation).  For a complex chi the finite-n values differ from
  *       Lanczos-Galerkin; both converge to the resolvent.
- *       Sequences run one per launch (rhs_block is not used); max_resid is the
+ *       Sequences run in lockstep (rhs_block is not used); max_resid is the
  *       largest residual 2-norm over the shifts.
  * FTK_EINVAL: eta <= 0, n_omega < 1, n_q < 1, empty alpha_mask, n_steps < 1,
  * resid_tol < 0, a shell range outside [0, L), an unknown solver, seed_tol < 0. */
