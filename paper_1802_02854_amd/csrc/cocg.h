@@ -80,7 +80,7 @@ __device__ __forceinline__ void write_partials5(double *partials, double (&hi)[N
 {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        block_pair<kBlock>(hi[j], lo[j]);
+        block_pair<kBlock, kEnd>(hi[j], lo[j]);
         if (threadIdx.x == 0) {
             partials[(blockIdx.x * 5 + j) * 2] = hi[j];
             partials[(blockIdx.x * 5 + j) * 2 + 1] = lo[j];

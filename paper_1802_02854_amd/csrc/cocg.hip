@@ -144,7 +144,7 @@ __device__ __forceinline__ void reduce_sums5(const double *partials, int nparts,
     }
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        block_pair<BLOCK>(hi[j], lo[j]);
+        block_pair<BLOCK, kLead>(hi[j], lo[j]);
         __syncthreads();
         s[j] = hi[j] + lo[j];
     }

@@ -126,9 +126,13 @@ __device__ __forceinline__ double block_sum(double hi, double lo, double2 *sh)
     return uniform(hi + lo);
 }
 
-// Sum over the workgroup of pairs; the same pair in every thread.  One barrier; the
-// next use needs another before it.
-template <int BLOCK>
+// Sum over the workgroup of pairs; the same pair in every thread.  One barrier, between
+// the waves' writes and the reads: a wave may be past it while another still reads, so two
+// sums with no barrier between them need different memory.  A kernel's leading sums (the
+// partials of the launch before) and the one that ends it each have their own; a second of
+// the same kind needs a barrier before it.
+enum SumSlot { kLead, kEnd };
+template <int BLOCK, SumSlot SLOT>
 __device__ __forceinline__ void block_pair(double &hi, double &lo)
 {
     __shared__ double2 sh[BLOCK / 64];
@@ -149,14 +153,14 @@ __device__ __forceinline__ double reduce_partials(const double *partials, int np
 {
     double hi = 0.0, lo = 0.0;
     for (int i = threadIdx.x; i < nparts; i += BLOCK) pair_add(hi, lo, partials[2 * i], partials[2 * i + 1]);
-    block_pair<BLOCK>(hi, lo);
+    block_pair<BLOCK, kLead>(hi, lo);
     return hi + lo;
 }
 
 template <int BLOCK>
 __device__ __forceinline__ void write_partial(double *partials, double hi, double lo)
 {
-    block_pair<BLOCK>(hi, lo);
+    block_pair<BLOCK, kEnd>(hi, lo);
     if (threadIdx.x == 0) {
         partials[2 * blockIdx.x] = hi;
         partials[2 * blockIdx.x + 1] = lo;

@@ -826,7 +826,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *
         // every workgroup; workgroup 0 records it
         for (int i = threadIdx.x + kPassThreads; i < fa.nparts; i += kPassThreads)
             pair_add(ah, al, pa[2 * i], pa[2 * i + 1]);
-        block_pair<kPassThreads>(ah, al);
+        block_pair<kPassThreads, kLead>(ah, al);
         const double a = uniform(inv * (ah + al));
         if (threadIdx.x == 0 && blockIdx.x == 0) {
             if (!isfinite(a)) st->numeric_error = 1;
@@ -1038,7 +1038,7 @@ struct EpiLanczosADev {
         if (fin != 2) return true;
         const double *pb = fb.partials + (size_t)r * 2 * fb.nparts;
         for (int i = threadIdx.x + BLOCK; i < fb.nparts; i += BLOCK) pair_add(bh, bl, pb[2 * i], pb[2 * i + 1]);
-        block_pair<BLOCK>(bh, bl);
+        block_pair<BLOCK, kLead>(bh, bl);
         const double bn = uniform(sqrt(bh + bl));
         const bool ends = !(bn > fb.tol);  // invariant subspace
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1797,7 +1797,7 @@ __device__ __forceinline__ double reduce_partials_strided(const double *partials
     double hi = 0.0, lo = 0.0;
     for (int i = threadIdx.x; i < nparts; i += blockDim.x)
         pair_add(hi, lo, partials[2 * (i * B + r)], partials[2 * (i * B + r) + 1]);
-    block_pair<kBlock>(hi, lo);
+    block_pair<kBlock, kLead>(hi, lo);
     return hi + lo;
 }
 
