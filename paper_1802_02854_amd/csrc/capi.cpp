@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "batch_rule.h"
 #include "cocg.h"
 #include "ftkw_internal.h"
 #include "kernels.h"
@@ -66,8 +67,6 @@ void need(bool ok, const char *msg)
 }
 
 }  // namespace
-
-constexpr int kMaxChains = 2;  // batches of Green's sequences in flight, a stream each
 
 // ---------------------------------------------------------------------------
 struct ftk_ctx {
@@ -1356,7 +1355,7 @@ struct BatchRunner {
           partials_b(H->ctx, fuse || pairs ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
           part(H->ctx, (stacked || own_partials) && !pairs ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
     {
-        need(B <= 16 || stacked, "more than 16 sequences per launch need the stacked layout");
+        need(stacked || block_batch(B), "the block layout runs 2, 4, 8 or 16 sequences per launch");
         if (stacked || own_partials) {  // else the Hamiltonian's scratch vector
             sk.B = B;
             sk.scratch = part.d();
@@ -1908,30 +1907,11 @@ void check_green(const GreenOut &out)
         if (q.numeric_error) fail(FTK_ENUMERIC, "NaN/Inf in Green's-function Lanczos coefficients");
 }
 
-// How `rows` sequences run: batches of B in `chains` chains, each on its own stream.  A
-// second chain fills the first one's launch gaps and overlaps its loads with the other's
-// bonds (all workgroups of a small launch are in the same phase), and larger stacks share
-// launches, so up to 64 sequences go in flight, those beyond the batch asked for with up
-// to 256 MiB of vectors (the last-level cache's size), in even batches.  us per sequence and step as asked, in chains of
-// what was asked, so: 16 sites, 6 in batches of 1: 12 / 7.6 / 3.9; 24 of 8: 2.8 / 2.6 /
-// 2.4; 72 of 32: 2.1 / 2.2 / 1.85; 110 of 32: 1.9 / 1.8 / 1.6; 18 sites, 4 of 1: 19 / 13.3
-// / 10.6; 24 of 16: 6.4 / 6.6 / 6.3; 20 sites, 4 of 1: 41.6 / 38.9 / 35.4.  Three or four
-// chains are no faster (16 sites, 110 in flight in four: 1.77).
-// The batch asked for runs alone where its vectors are past 256 MiB (20 sites, two chains
-// of 16: 35.4 us per sequence and step against 31.0; 24 sites, of 1: 557 against 510), in
-// the block layout, under kernel timing and wherever a tuning key forces a form.
-void spread_rows(const ftk_hamiltonian *h, size_t rows, int stack, bool streams, int &B, int &chains)
+// Whether a call may run other batches than the one asked for (batch_rule.h): not in the
+// block layout, under kernel timing or where a tuning key forces a form.
+bool may_spread(const ftk_hamiltonian *h)
 {
-    ftk_ctx *ctx = h->ctx;
-    const size_t per = 16 * (size_t)h->dim * 4;
-    if (per * B > ctx->spare_bytes || ctx->timing || forced_hv_mode() >= 0 || g_plain_loop ||
-        (stack == 0 && B > 1) || !BatchRunner::stack_for(h, 2, -1))
-        return;
-    const size_t limit = streams ? kMaxChains : 1;
-    const size_t most = std::max<size_t>(B, std::min(limit * kMaxBatch, B + ctx->spare_bytes / per));
-    const size_t rounds = (rows + most - 1) / most, now = (rows + rounds - 1) / rounds;
-    chains = (int)std::min(limit, now);
-    B = (int)((now + chains - 1) / chains);
+    return !h->ctx->timing && forced_hv_mode() < 0 && !g_plain_loop && BatchRunner::stack_for(h, 2, -1);
 }
 
 // Runs the items in batches of B through one graph-captured BatchRunner; load(run, r,
@@ -1961,24 +1941,26 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     m.part(&be, rows * n);
     m.part(&g, rows * nw * 2);
     m.allocate(ctx);
-    int chains = 1;
-    const int asked = B;
-    spread_rows(h, rows, stack, load_any_stream, B, chains);
+    const Batches asked{B, 1, stack};
+    Batches plan = asked;
+    if (may_spread(h)) plan = spread_rows(rows, asked, 16 * (size_t)h->dim * 4, ctx->spare_bytes, load_any_stream);
     std::vector<std::unique_ptr<BatchRunner>> run;
     auto make = [&] {
-        const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, B, stack);
-        for (int c = 0; c < chains; ++c)
-            run.push_back(std::make_unique<BatchRunner>(h, B, n, omega, nw, eta, rtol, stack, pgrid, phints, c > 0));
+        const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, plan.B, plan.stack);
+        for (int c = 0; c < plan.chains; ++c)
+            run.push_back(std::make_unique<BatchRunner>(h, plan.B, n, omega, nw, eta, rtol, plan.stack, pgrid, phints,
+                                                        c > 0));
     };
     try {
         make();
     } catch (const Error &e) {
-        if (e.status != FTK_ENOMEM || (chains == 1 && B == asked)) throw;
+        if (e.status != FTK_ENOMEM || (plan.chains == 1 && plan.B == asked.B)) throw;
         run.clear();
-        chains = 1;  // no room: one batch at a time, as asked
-        B = asked;
+        plan = asked;  // no room: one batch at a time, as asked
         make();
     }
+    B = plan.B;
+    const int chains = plan.chains;
     struct Joined {  // nothing of a further chain runs once its buffers are freed
         std::vector<hipStream_t> s;
         hipEvent_t e = nullptr;

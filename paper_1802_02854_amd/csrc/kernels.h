@@ -5,6 +5,7 @@
 
 #include <cstdint>
 
+#include "batch_rule.h"
 #include "ftkw_internal.h"
 
 namespace ftk {
@@ -329,7 +330,6 @@ void launch_accumulate(uint32_t dim, const double *V, int nk, const double *coef
 // shift states [B][n_omega].
 int hv_batch_grid(uint32_t dim, int B);
 int vec_batch_grid(uint32_t dim, int B);
-constexpr int kMaxBatch = 32;  // sequences per batch: 16 in block layout, 32 as a stack
 struct BatchShifts {
     double re[kMaxBatch];  // real offset (E_m) of each sequence's shifts
 };

@@ -1758,6 +1758,11 @@ void launch_accumulate(uint32_t dim, const double *V, int nk, const double *coef
 // exactly that of a single sequence (same operations, exact-sum reductions per
 // sequence), so results do not depend on B or on the batch composition.
 
+[[noreturn]] static void no_block_kernel(int B)
+{
+    fail(FTK_EDEVICE, "no block-layout kernel for " + std::to_string(B) + " sequences");
+}
+
 template <int B>
 struct BatchGeom {
     static constexpr int EL = 64 / B;                                  // element lanes per wave
@@ -1918,7 +1923,7 @@ void launch_lanczos_a_batch(int B, const HvOp &op, const double *Wcur, const dou
     case 4: launch_lanczos_a_batch_t<4>(op, Wcur, Wprev, U, st, partials, first, s); break;
     case 8: launch_lanczos_a_batch_t<8>(op, Wcur, Wprev, U, st, partials, first, s); break;
     case 16: launch_lanczos_a_batch_t<16>(op, Wcur, Wprev, U, st, partials, first, s); break;
-    default: break;
+    default: no_block_kernel(B);
     }
 }
 
@@ -1954,7 +1959,7 @@ void launch_lanczos_b_batch(int B, uint32_t dim, const double *Wcur, double *U, 
     case 4: hipLaunchKernelGGL(k_lanczos_b_batch<4>, g, t, 0, s, dim, (const double2 *)Wcur, (double2 *)U, st, partials); break;
     case 8: hipLaunchKernelGGL(k_lanczos_b_batch<8>, g, t, 0, s, dim, (const double2 *)Wcur, (double2 *)U, st, partials); break;
     case 16: hipLaunchKernelGGL(k_lanczos_b_batch<16>, g, t, 0, s, dim, (const double2 *)Wcur, (double2 *)U, st, partials); break;
-    default: break;
+    default: no_block_kernel(B);
     }
 }
 
@@ -2075,7 +2080,7 @@ void launch_start_batch(int B, uint32_t dim, const double *chi, double *partials
     case 4: hipLaunchKernelGGL(k_dot_batch<4>, g, t, 0, s, dim, (const double2 *)chi, partials); break;
     case 8: hipLaunchKernelGGL(k_dot_batch<8>, g, t, 0, s, dim, (const double2 *)chi, partials); break;
     case 16: hipLaunchKernelGGL(k_dot_batch<16>, g, t, 0, s, dim, (const double2 *)chi, partials); break;
-    default: break;
+    default: no_block_kernel(B);
     }
     hipLaunchKernelGGL(k_start_batch, dim3(B), dim3(kBlock), 0, s, st, partials, vec_batch_grid(dim, B), B,
                        shift_re);

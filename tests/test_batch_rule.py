@@ -1,0 +1,62 @@
+"""The rule that sizes the batches of a Green's-function call (csrc/batch_rule.h), on the host.
+
+The header is plain C++; a driver compiled with g++ walks it over sizes, rows, the batches
+asked for and the layouts a tuning record can hold.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_1802_02854_amd", "csrc")
+
+DRIVER = r"""
+#include <cstdio>
+#include "batch_rule.h"
+using namespace ftk;
+
+static int failures = 0;
+#define EXPECT(c) do { if (!(c)) { std::printf("FAIL line %d: %s (N %d rows %zu asked %d stack %d: %d x %d stack %d)\n", \
+    __LINE__, #c, N, rows, B, stack, r.B, r.chains, r.stack); ++failures; } } while (0)
+
+int main()
+{
+    for (int N = 15; N <= 24; ++N)
+        for (size_t spare : {size_t(48) << 20, size_t(256) << 20})
+            for (bool streams : {false, true})
+                for (int B : {1, 2, 4, 8, 16, 32})
+                    for (int stack : {-1, 0, 1})
+                        for (size_t rows = 1; rows <= 300; ++rows) {
+                            if (B == 32 && stack == 0) continue;  // refused before the rule
+                            const size_t per = (size_t)64 << N;
+                            const Batches r = spread_rows(rows, Batches{B, 1, stack}, per, spare, streams);
+                            const bool as_asked = r.B == B && r.chains == 1 && r.stack == stack;
+                            EXPECT(r.B >= 1 && r.B <= kMaxBatch && r.chains >= 1 && r.chains <= (streams ? kMaxChains : 1));
+                            // a batch whose layout was not picked for it is a stack: a size the
+                            // block layout has no kernel for, or a pick for single sequences
+                            EXPECT(as_asked || r.B == 1 || r.stack == 1);
+                            EXPECT(r.stack != 0 || block_batch(r.B));
+                            EXPECT(r.stack != 0 || r.B == 1 || B > 1);
+                            // memory: the batch asked for and at most the allowance beyond it
+                            EXPECT((size_t)r.B * r.chains * per <= (B + 1) * per + spare);
+                            if (per * B > spare) EXPECT(as_asked);
+                            if (failures > 20) return 1;
+                        }
+    std::printf(failures ? "FAILED\n" : "OK\n");
+    return failures ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_batch_has_a_kernel(tmp_path):
+    src = tmp_path / "drv.cpp"
+    src.write_text(DRIVER)
+    exe = tmp_path / "drv"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=undefined", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert out.stdout.strip().endswith("OK")
