@@ -9,6 +9,7 @@ namespace ftk {
 
 constexpr int kMaxChains = 2;  // batches of Green's sequences in flight, a stream each
 constexpr int kMaxBatch = 32;  // sequences per batch: 16 in block layout, 32 as a stack
+constexpr int kMaxRows = 32768;  // rows of one launch (grid y, which ends at 65535)
 
 // batches the block layout has kernels for; 1 is a sequence alone
 inline bool block_batch(int B) { return B == 1 || B == 2 || B == 4 || B == 8 || B == 16; }
@@ -45,6 +46,13 @@ inline Batches spread_rows(size_t rows, Batches asked, size_t per, size_t spare,
     r.B = (int)((now + r.chains - 1) / r.chains);
     if (r.B > 1) r.stack = 1;
     return r;
+}
+
+// Sequences of one resident launch (one workgroup each; their start vectors and shift
+// updates are rows of a grid): what fits in spare bytes at per bytes a sequence.
+inline size_t resident_rows(size_t rows, size_t per, size_t spare)
+{
+    return std::min({rows, std::max<size_t>(1, spare / per), (size_t)kMaxRows});
 }
 
 }  // namespace ftk

@@ -1829,7 +1829,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     const bool few = !stop && few_sequences(h->op, rows);
     const bool carried = few || stop || h->n_sites >= kResidentPlanes;
     const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
-    const size_t slab = std::min(rows, std::max<size_t>(1, ctx->spare_bytes / per));
+    const size_t slab = resident_rows(rows, per, ctx->spare_bytes);
 
     Arena m;
     ResidentSeq *seq;

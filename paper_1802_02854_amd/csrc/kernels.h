@@ -55,7 +55,6 @@ struct ShiftState {
 
 constexpr int kR = 8;               // elements per thread in the blocked H v
 constexpr int kBlock = 256;         // threads per block of the vector kernels
-constexpr int kMaxRows = 32768;     // rows of one launch (grid y)
 constexpr int kGatherSites = 20;    // largest N whose single vectors run one element per thread
 constexpr int kPairBits = 19;       // largest log2(sequences * 2^N) of stacks in the two-launch Lanczos step
 constexpr int kMaxGrid = 4096;      // blocks of the grid-stride vector kernels

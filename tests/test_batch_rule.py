@@ -44,6 +44,13 @@ int main()
                             if (per * B > spare) EXPECT(as_asked);
                             if (failures > 20) return 1;
                         }
+    // rows of a resident launch fit a grid's y extent at every size it runs
+    for (int N = 6; N <= 14; ++N)
+        for (size_t rows : {size_t(1), size_t(65535), size_t(65536), size_t(300000)})
+            for (size_t spare : {size_t(0), size_t(48) << 20, size_t(256) << 20}) {
+                const size_t n = resident_rows(rows, (size_t)16 << N, spare);
+                if (n < 1 || n > rows || n > 65535) std::printf("FAIL N %d rows %zu: %zu\n", N, rows, n), ++failures;
+            }
     std::printf(failures ? "FAILED\n" : "OK\n");
     return failures ? 1 : 0;
 }

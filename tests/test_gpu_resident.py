@@ -111,3 +111,23 @@ def test_resident_filter_runs_match_per_step(env, N, nb):
                     *[st.shell(s, a, m).cpu().numpy() for s in range(2) for a in range(3) for m in (0, 5, 10)]]
         for x, y in zip(*_both(ftk, states)):
             assert np.array_equal(x, y)
+
+
+def test_more_sequences_than_a_grid_has_rows(env):
+    """70656 sequences of 6 sites in one call (a grid's y extent ends at 65535) against the
+    same in three calls."""
+    ftk, ctx, torch = env
+    print("resident rows", flush=True)
+    cl = ftk.honeycomb_cluster((1, 1), (-1, 2))
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.1)
+    st = ftk.TypicalStates(h, seed=6, n_vectors=23, betas=[0.0], E_b=None, eps=None, L=256, M=2, n_steps=6)
+    qs = [(0.0, 0.0), (0.7, -0.4), (1.1, 0.3), (-0.2, 0.9)]
+
+    def spectrum(first, n):
+        sp = ftk.Spectrum(h, st, q_xy=qs, omega=np.array([-0.4, 0.9]), eta=0.2, n_steps=3, rhs_block=1, shells=(first, n))
+        return sp.raw()[0][:, :, first:first + n], sp.work()[1]
+
+    whole, n_seq = spectrum(0, 256)
+    assert n_seq > 65535
+    parts = [spectrum(f, n)[0] for f, n in ((0, 100), (100, 100), (200, 56))]
+    assert np.array_equal(whole, np.concatenate(parts, axis=2)) and np.abs(whole).max() > 0
