@@ -200,6 +200,19 @@ struct Arena {
     }
 };
 
+// f(), which allocates for `count` sequences at a time, again with half of them while
+// there is no room: the most that fits of what a call may take beyond one.
+template <class F>
+void with_room(size_t &count, F &&f)
+{
+    for (;;) try {
+            return f();
+        } catch (const Error &e) {
+            if (e.status != FTK_ENOMEM || count <= 1) throw;
+            count /= 2;
+        }
+}
+
 // Sequences of op run one per workgroup, whole (resident.h), unless a tuning key
 // asks for another form
 bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
@@ -1022,6 +1035,7 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
             hcs[2 * (j - 1)] = std::cos(th);
             hcs[2 * (j - 1) + 1] = std::sin(th);
         }
+        const size_t filter_row = 2 * (size_t)n * shell_rows(st->L);  // doubles of a sequence's coefficients
         struct Filter {
             Arena m;
             ShellSeq *seq;
@@ -1034,17 +1048,22 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
         };
         // the work space is the vectors' buffer of pass 2, free until then, where that holds it
         auto filter_for = [&](Filter &f, size_t count, double *buf, size_t buf_bytes) {
-            f.row = 2 * (size_t)n * shell_rows(st->L);
+            f.row = filter_row;
             const size_t item = 2 * shell_work(st->M, n);  // doubles: two complex lists
-            const size_t all = count * st->L, need_bytes = all * item * sizeof(double);
-            const bool own = need_bytes > buf_bytes;
-            f.items = (int)(own ? std::min(all, std::max<size_t>(1, ctx->spare_bytes / 4 / (item * sizeof(double)))) : all);
-            f.m.part(&f.seq, count);
-            f.m.part(&f.kn, count * st->L);
-            f.m.part(&f.cs, 2 * (size_t)st->M);
-            f.m.part(&f.work, own ? f.items * item : 0);
-            f.m.part(&f.coef, count * f.row);
-            f.m.allocate(ctx);
+            const size_t all = count * st->L, item_bytes = item * sizeof(double), in_buf = buf_bytes / item_bytes;
+            size_t items = all <= in_buf ? all : std::min(all, std::max<size_t>(1, ctx->spare_bytes / 4 / item_bytes));
+            bool own = false;
+            with_room(items, [&] {
+                own = items > in_buf;
+                f.m = Arena();
+                f.m.part(&f.seq, count);
+                f.m.part(&f.kn, count * st->L);
+                f.m.part(&f.cs, 2 * (size_t)st->M);
+                f.m.part(&f.work, own ? items * item : 0);
+                f.m.part(&f.coef, count * f.row);
+                f.m.allocate(ctx);
+            });
+            f.items = (int)items;
             if (!own) f.work = buf;
             f.hseq.resize(count);
             f.hkn.resize(count * st->L);
@@ -1084,7 +1103,8 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
         // (vector, anchor) pairs run side by side; pass 2 in blocks of nb steps with the
         // sequences' vectors carried over.
         const size_t pairs = (size_t)st->nv * st->na, cplx = 2 * (size_t)dim;
-        size_t group = std::min(pairs, std::max<size_t>(1, ctx->spare_bytes / (vbytes * (nb + 3))));
+        const size_t per_pair = vbytes * (nb + 3) + sizeof(double) * (filter_row + 2 * (size_t)n);
+        size_t group = std::min(pairs, std::max<size_t>(1, ctx->spare_bytes / per_pair));
         bool side_by_side = resident_run(h->op);
         if (!side_by_side && forced_hv_mode() < 0 && !g_plain_loop && !ctx->timing) {
             while (group > 1 && !few_sequences(h->op, group)) --group;
@@ -1096,25 +1116,37 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
         double *phib, *carry, *vbuf, *al_d, *be_d;
         Filter fl;
         FewScratch fs;
-        const bool few = side_by_side && few_sequences(h->op, group);
+        bool few = false;
+        std::vector<DevBuf> shells;  // of every pair: before the work space, which takes what they leave
         if (side_by_side) {
-            m.part(&seq, group);
-            m.part(&state, group);
-            m.part(&phib, group * cplx);
-            m.part(&carry, group * 2 * cplx);
-            m.part(&vbuf, group * nb * cplx);
-            m.part(&al_d, group * n);
-            m.part(&be_d, group * n);
-            if (few) fs.parts(m, dim);
             try {
-                m.allocate(ctx);
+                for (size_t i = 0; i < pairs; ++i) {
+                    shells.emplace_back(ctx, vbytes * st->L);
+                    HIP_CHECK(hipMemsetAsync(shells[i].p, 0, vbytes * st->L, s));
+                }
+                with_room(group, [&] {
+                    few = few_sequences(h->op, group);
+                    m = Arena();
+                    m.part(&seq, group);
+                    m.part(&state, group);
+                    m.part(&phib, group * cplx);
+                    m.part(&carry, group * 2 * cplx);
+                    m.part(&vbuf, group * nb * cplx);
+                    m.part(&al_d, group * n);
+                    m.part(&be_d, group * n);
+                    if (few) fs.parts(m, dim);
+                    m.allocate(ctx);
+                    filter_for(fl, group, vbuf, group * nb * vbytes);
+                });
             } catch (const Error &e) {
                 if (e.status != FTK_ENOMEM || resident_run(h->op)) throw;
                 side_by_side = false;  // no room: one after the other
+                shells.clear();
+                m = Arena();
+                fl = Filter();
             }
         }
         if (side_by_side) {
-            filter_for(fl, group, vbuf, group * nb * vbytes);
             std::vector<ResidentSeq> hseq(group);
             std::vector<SeqState> hstate(group);
             std::vector<double> hal(group * n), hbe(group * n);
@@ -1157,7 +1189,6 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                 HIP_CHECK(hipMemcpyAsync(hbe.data(), be_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
                 HIP_CHECK(hipStreamSynchronize(s));
                 int most = 0;
-                std::vector<DevBuf> shells;
                 for (size_t i = 0; i < cnt; ++i) {
                     const int sv = (int)((g0 + i) / st->na), a = (int)((g0 + i) % st->na);
                     al[i].assign(hal.begin() + i * n, hal.begin() + i * n + hstate[i].steps);
@@ -1166,8 +1197,6 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     fl.hseq[i] = ShellSeq{al_d + i * n, be_d + i * n, steps[i], hstate[i].norm, st->E_b[a], st->eps[a],
                                           p->resid_tol > 0 ? fl.kn + i * st->L : nullptr, fl.coef + i * fl.row};
                     most = std::max(most, steps[i]);
-                    shells.emplace_back(ctx, vbytes * st->L);
-                    HIP_CHECK(hipMemsetAsync(shells[i].p, 0, vbytes * st->L, s));
                 }
                 coefficients(fl, cnt);
                 run.vout = vbuf;
@@ -1179,13 +1208,13 @@ ftk_status ftk_typical_states(const ftk_hamiltonian *h, const ftk_ts_params *p, 
                     for (size_t i = 0; i < cnt; ++i)
                         if (steps[i] > k0)
                             launch_accumulate(dim, vbuf + i * nb * cplx, std::min(nb, steps[i] - k0),
-                                              fl.coef + i * fl.row, steps[i], k0, shells[i].d(), st->L, s);
+                                              fl.coef + i * fl.row, steps[i], k0, shells[g0 + i].d(), st->L, s);
                 }
                 HIP_CHECK(hipMemcpyAsync(hal.data(), al_d, sizeof(double) * cnt * n, hipMemcpyDeviceToHost, s));
                 for (size_t i = 0; i < cnt; ++i) {
-                    shell_sums(g0 + i, shells[i], carry);
+                    shell_sums(g0 + i, shells[g0 + i], carry);
                     check_regenerated(hal.data() + i * n, al[i]);
-                    st->phi.push_back(std::move(shells[i]));
+                    st->phi.push_back(std::move(shells[g0 + i]));
                 }
             }
         } else {
@@ -1829,7 +1858,7 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     const bool few = !stop && few_sequences(h->op, rows);
     const bool carried = few || stop || h->n_sites >= kResidentPlanes;
     const size_t per = 16 * dim * (carried ? 3 : 1) + (stop ? sizeof(ShiftState) * (size_t)nw : 0);
-    const size_t slab = resident_rows(rows, per, ctx->spare_bytes);
+    size_t slab = resident_rows(rows, per, ctx->spare_bytes);
 
     Arena m;
     ResidentSeq *seq;
@@ -1838,21 +1867,24 @@ GreenOut run_green_resident(const ftk_hamiltonian *h, int n, const double *omega
     SeqState *st;
     ShiftState *sh;
     double *al, *be, *g, *om, *chi, *carry;
-    m.part(&seq, rows);
-    m.part(&sq, ops.sq ? ops.sq->size() : 0);
-    m.part(&pa, ops.a ? ops.a->size() : 0);
-    m.part(&pb, ops.b ? ops.b->size() : 0);
-    m.part(&om, nw);
-    m.part(&st, rows);
-    m.part(&al, rows * n);
-    m.part(&be, rows * n);
-    m.part(&g, rows * nw * 2);
-    m.part(&chi, slab * dim * 2);
-    m.part(&carry, carried ? slab * dim * 4 : 0);
-    m.part(&sh, stop ? slab * nw : 0);
     FewScratch fs;
-    if (few) fs.parts(m, dim);
-    m.allocate(ctx);
+    with_room(slab, [&] {
+        m = Arena();
+        m.part(&seq, rows);
+        m.part(&sq, ops.sq ? ops.sq->size() : 0);
+        m.part(&pa, ops.a ? ops.a->size() : 0);
+        m.part(&pb, ops.b ? ops.b->size() : 0);
+        m.part(&om, nw);
+        m.part(&st, rows);
+        m.part(&al, rows * n);
+        m.part(&be, rows * n);
+        m.part(&g, rows * nw * 2);
+        m.part(&chi, slab * dim * 2);
+        m.part(&carry, carried ? slab * dim * 4 : 0);
+        m.part(&sh, stop ? slab * nw : 0);
+        if (few) fs.parts(m, dim);
+        m.allocate(ctx);
+    });
 
     std::vector<ResidentSeq> hseq(rows);
     for (size_t i = 0; i < rows; ++i)

@@ -80,3 +80,62 @@ def test_direct_c_call_status(env):
     rc = _lib.lib().ftk_typical_states(h.handle, ctypes.byref(p), ctypes.byref(out))
     assert rc == FTK_ENUMERIC and not out.value
     assert b"norm" in _lib.lib().ftk_last_error()
+
+
+# -------------------------------------------------------------------------
+class _Pool:
+    """A context whose device memory comes from a pool of `limit` bytes (a caller's allocator)."""
+
+    def __init__(self, ftk, torch, limit):
+        from paper_1802_02854_amd import _lib
+        self.lib, self.limit, self.held, self.refused = _lib, limit, {}, 0
+
+        def alloc(n, _user):
+            if sum(t.numel() for t in self.held.values()) + n > self.limit:
+                self.refused += 1
+                return None
+            t = torch.empty(int(n), dtype=torch.uint8, device="cuda")
+            self.held[t.data_ptr()] = t
+            return t.data_ptr()
+
+        def free(p, _user):
+            torch.cuda.synchronize()
+            del self.held[p]
+
+        self._cb = _lib.ALLOC_FN(alloc), _lib.FREE_FN(free)
+        self.handle = ctypes.c_void_p()
+        _lib.call("ftk_ctx_create_with_allocator", 0, None, *self._cb, None, ctypes.byref(self.handle))
+
+    def close(self):
+        self.lib.lib().ftk_ctx_destroy(self.handle)
+
+
+@pytest.mark.parametrize("N,states_mib,spectra_mib", [(8, 6, 2), (12, 24, 12), (14, 56, 32)])
+def test_small_clusters_fit_a_small_pool(env, N, states_mib, spectra_mib):
+    """A pool that holds the results and the vectors of a sequence or two: 12 (vector, anchor)
+    pairs, their spectra (fixed and truncated) and pairs of operators, as from a pool without
+    that limit.  Per vector of 2^N entries: 12 x 8 shells stay, a filter run takes 64 + 8."""
+    ftk, torch, ctx, _ = env
+    print(f"small pool N={N}", flush=True)
+    cl = ftk.honeycomb_cluster(*SUPERCELLS[N])
+    out = []
+    for limit in (states_mib << 20, 1 << 40):
+        pool = _Pool(ftk, torch, limit)
+        h = ftk.Hamiltonian(pool, cl, -1.0, 0.1)
+        st = ftk.TypicalStates(h, seed=3, n_vectors=4, betas=[0.0, 0.5, 1.0], E_b=None, eps=None, L=8, M=16, n_steps=70)
+        if limit < 1 << 40:  # the shells, and room for a few sequences
+            pool.limit = 12 * 8 * (16 << N) + (spectra_mib << 20)
+        res = [*st.scalars()]
+        for tol in (0.0, 1e-2):
+            sp = ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-2, 2, 9), eta=0.3, n_steps=20, rhs_block=1,
+                              resid_tol=tol)
+            res += [*sp.raw(), sp.norms()]
+        ops = [np.stack([ftk.momentum_operator(cl, a, (0.7, -0.4))]) for a in (0, 1)]
+        res += ftk.PairSpectrum(h, st, op_a=ops[0], op_b=ops[1], omega=np.linspace(-2, 2, 5), eta=0.3, n_steps=12,
+                                rhs_block=1).raw()
+        out.append(res)
+        assert (pool.refused > 0) == (limit < 1 << 40)
+        st.close(), h.close(), pool.close()
+        assert not pool.held
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
