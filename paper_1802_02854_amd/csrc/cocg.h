@@ -76,23 +76,33 @@ __device__ __forceinline__ void cmul_v(double ar, double ai, double br, double b
 
 // up to 5 exact sums per block, (hi, lo) pairs in partials[(block * 5 + j) * 2]
 template <int NS>
-__device__ __forceinline__ void write_partials5(double *partials, double (&hi)[NS], double (&lo)[NS])
+__device__ __forceinline__ void write_partials5(double *partials, Sum (&sum)[NS])
 {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        block_pair<kBlock, kEnd>(hi[j], lo[j]);
+        block_total<kBlock, kEnd>(sum[j]);
+        const double l = sum[j].low();
         if (threadIdx.x == 0) {
-            partials[(blockIdx.x * 5 + j) * 2] = hi[j];
-            partials[(blockIdx.x * 5 + j) * 2 + 1] = lo[j];
+            partials[(blockIdx.x * 5 + j) * 2] = sum[j].hi;
+            partials[(blockIdx.x * 5 + j) * 2 + 1] = l;
         }
         __syncthreads();
     }
 }
 
+// running sums normalised every eighth of a thread's turns
+template <int NS>
+__device__ __forceinline__ void normalise_turns(Sum (&sum)[NS], int turn)
+{
+    if ((turn & 7) != 7) return;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) sum[j].normalise();
+}
+
 // u = (H w_{k-1}) inv_k + c1 w_{k-2}, one element; its part of the sums of w_{k-1}^T u
 struct CocgA {
     double ir, ii, c1r, c1i;
-    double hi[2] = {0, 0}, lo[2] = {0, 0};
+    Sum sum[2];
     __device__ __forceinline__ void init(const CocgState *st)
     {
         ir = st->invr, ii = st->invi;
@@ -109,12 +119,13 @@ struct CocgA {
             ur = fma(c1r, wp.x, fma(-c1i, wp.y, tr));
             ui = fma(c1r, wp.y, fma(c1i, wp.x, ti));
         }
-        pair_prod(hi[0], lo[0], wc.x, ur);
-        pair_prod(hi[0], lo[0], -wc.y, ui);
-        pair_prod(hi[1], lo[1], wc.x, ui);
-        pair_prod(hi[1], lo[1], wc.y, ur);
+        sum[0].product(wc.x, ur);
+        sum[0].product(-wc.y, ui);
+        sum[1].product(wc.x, ui);
+        sum[1].product(wc.y, ur);
         return make_double2(ur, ui);
     }
+    __device__ __forceinline__ void settle(int turn) { normalise_turns(sum, turn); }
 };
 #endif
 

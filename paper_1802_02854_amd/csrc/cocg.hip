@@ -81,17 +81,17 @@ __device__ __forceinline__ void csqrt_s(double x, double y, double &r, double &i
 }
 
 // sums over w of: Re w^T w = sum (w_r^2 - w_i^2), sum w_r w_i, <lam|w> (re, im), ||w||^2
-__device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &l, double (&hi)[5], double (&lo)[5])
+__device__ __forceinline__ void cocg_norm_sums(const double2 &w, const double2 &l, Sum (&sum)[5])
 {
-    pair_prod(hi[0], lo[0], w.x, w.x);
-    pair_prod(hi[0], lo[0], -w.y, w.y);
-    pair_prod(hi[1], lo[1], w.x, w.y);
-    pair_prod(hi[2], lo[2], l.x, w.x);
-    pair_prod(hi[2], lo[2], l.y, w.y);
-    pair_prod(hi[3], lo[3], l.x, w.y);
-    pair_prod(hi[3], lo[3], -l.y, w.x);
-    pair_prod(hi[4], lo[4], w.x, w.x);
-    pair_prod(hi[4], lo[4], w.y, w.y);
+    sum[0].product(w.x, w.x);
+    sum[0].product(-w.y, w.y);
+    sum[1].product(w.x, w.y);
+    sum[2].product(l.x, w.x);
+    sum[2].product(l.y, w.y);
+    sum[3].product(l.x, w.y);
+    sum[3].product(-l.y, w.x);
+    sum[4].product(w.x, w.x);
+    sum[4].product(w.y, w.y);
 }
 
 // Sequence blockIdx.y of the batch in all of these.
@@ -101,13 +101,15 @@ __global__ void __launch_bounds__(kBlock) k_cocg_start_sums(uint32_t dim, const 
     w += (size_t)blockIdx.y * dim;
     lam += (size_t)blockIdx.y * dim;
     partials += (size_t)blockIdx.y * 10 * gridDim.x;
-    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
+    Sum sum[5];
+    int turn = 0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 v = w[x];
         const double2 l = lam[x];
-        cocg_norm_sums(v, l, hi, lo);
+        cocg_norm_sums(v, l, sum);
+        normalise_turns(sum, turn++);
     }
-    write_partials5<5>(partials, hi, lo);
+    write_partials5<5>(partials, sum);
 }
 
 // u over U (U may be Wprev: each element is read before it is written) from H w_{k-1}
@@ -124,29 +126,29 @@ __global__ void __launch_bounds__(kBlock) k_cocg_a(uint32_t dim, const double2 *
     if (st->done) return;
     CocgA a;
     a.init(st);
+    int turn = 0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 h = Hw[x];
         U[x] = a(h.x, h.y, Wcur[x], first ? make_double2(0.0, 0.0) : Wprev[x], first);
+        a.settle(turn++);
     }
-    write_partials5<2>(partials, a.hi, a.lo);
+    write_partials5<2>(partials, a.sum);
 }
 
 // NS rounded sums of the 5-sum partials in every thread of a block
 template <int BLOCK, int NS>
 __device__ __forceinline__ void reduce_sums5(const double *partials, int nparts, double (&s)[NS])
 {
-    double hi[NS], lo[NS];
-#pragma unroll
-    for (int j = 0; j < NS; ++j) hi[j] = lo[j] = 0.0;
+    Sum sum[NS];
     for (int i = threadIdx.x; i < nparts; i += BLOCK) {
 #pragma unroll
-        for (int j = 0; j < NS; ++j) pair_add(hi[j], lo[j], partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
+        for (int j = 0; j < NS; ++j) sum[j].pair(partials[(i * 5 + j) * 2], partials[(i * 5 + j) * 2 + 1]);
     }
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-        block_pair<BLOCK, kLead>(hi[j], lo[j]);
+        block_total<BLOCK, kLead>(sum[j]);
         __syncthreads();
-        s[j] = hi[j] + lo[j];
+        s[j] = sum[j].rounded();
     }
 }
 
@@ -181,7 +183,8 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
         a_out[2 * k + 1] = ai;
         if (!(isfinite(ar) && isfinite(ai))) st->numeric_error = 1;
     }
-    double hi[5] = {0, 0, 0, 0, 0}, lo[5] = {0, 0, 0, 0, 0};
+    Sum sum[5];
+    int turn = 0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = U[x];
         const double2 wc = Wcur[x];
@@ -190,9 +193,10 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
         const double wi = fma(c2r, wc.y, fma(c2i, wc.x, u.y));
         const double2 w = make_double2(wr, wi);
         U[x] = w;
-        cocg_norm_sums(w, l, hi, lo);
+        cocg_norm_sums(w, l, sum);
+        normalise_turns(sum, turn++);
     }
-    write_partials5<5>(partials, hi, lo);
+    write_partials5<5>(partials, sum);
 }
 
 __global__ void __launch_bounds__(kBlock) k_cocg_fin_start(CocgBatch Q, int nparts, BatchShifts shifts)

@@ -500,7 +500,8 @@ __device__ __forceinline__ void offdiag_block(const HvParams &P, uint32_t xb, ui
 // A kernel with kR elements per thread first calls load(x_e) for all of them,
 // then apply(..., loaded value): every input an epilogue reads is loaded before
 // any output is stored, which the compiler could not arrange itself because the
-// buffers may alias (the Lanczos output overwrites w_{k-2} in place).
+// buffers may alias (the Lanczos output overwrites w_{k-2} in place).  After a thread's
+// elements of a turn settle() normalises its running sum.
 struct EpiApply {
     static constexpr bool kReduces = false;  // no per-workgroup partial sums
     double2 *w;
@@ -512,6 +513,7 @@ struct EpiApply {
     __device__ bool begin(int) { return true; }
     __device__ double2 load(size_t) const { return make_double2(0.0, 0.0); }
     __device__ void apply(size_t x, double re, double im, const double2 &, const double2 &) { w[x] = make_double2(re, im); }
+    __device__ void settle() {}
     __device__ void operator()(size_t x, double re, double im, const double2 &vx) { apply(x, re, im, vx, load(x)); }
     template <int BLOCK>
     __device__ void finish() {}
@@ -536,6 +538,7 @@ struct EpiTaylor {
         tn[x] = make_double2(nr, ni);
         acc[x] = make_double2(c.x + nr, c.y + ni);
     }
+    __device__ void settle() {}
     __device__ void operator()(size_t x, double re, double im, const double2 &tx) { apply(x, re, im, tx, load(x)); }
     template <int BLOCK>
     __device__ void finish() {}
@@ -569,6 +572,7 @@ __global__ void __launch_bounds__(kBlock) k_hv_simple(const HvDev *__restrict__ 
         }
         if (x0 == blockIdx.x * kBlock && !epi.template begin<kBlock>(blockIdx.y)) return;
         if (x < dim) epi.apply(x, re, im, vx, in);
+        epi.settle();
     }
     epi.template finish<kBlock>();
 }
@@ -599,6 +603,7 @@ __global__ void __launch_bounds__(kBlock) k_hv_blocked(const HvDev *__restrict__
         for (int e = 0; e < kR; ++e) in[e] = epi.load(xb + (e << kRegShift));
 #pragma unroll
         for (int e = 0; e < kR; ++e) epi.apply(xb + (e << kRegShift), re[e], im[e], v[xb + (e << kRegShift)], in[e]);
+        epi.settle();
     }
     epi.template finish<kBlock>();
 }
@@ -645,6 +650,7 @@ __global__ void __launch_bounds__(kTileThreads) k_hv_tiled(const HvDev *__restri
         for (int e = 0; e < kR; ++e) in[e] = epi.load(xb + (e << kRegShift));
 #pragma unroll
         for (int e = 0; e < kR; ++e) epi.apply(xb + (e << kRegShift), re[e], im[e], tile[xw + (e << kRegShift)], in[e]);
+        epi.settle();
     }
     epi.template finish<kTileThreads>();
 }
@@ -778,6 +784,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass(const HvDev *__rest
             for (int e = 0; e < kR; ++e)
                 epi.apply(FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6), acc[e], acc[kR + e],
                           make_double2(re[e << kRegShift], im[e << kRegShift]), in[e]);
+            epi.settle();
         } else {
 #pragma unroll
             for (int e = 0; e < kR; ++e)
@@ -824,10 +831,11 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *
     if (use_fa) {
         // alpha_{k-1} = inv_{k-1} <v_{k-1}|u_{k-1}>, as k_finalize_alpha forms it, in
         // every workgroup; workgroup 0 records it
+        Sum alpha{ah, 0.0, al};
         for (int i = threadIdx.x + kPassThreads; i < fa.nparts; i += kPassThreads)
-            pair_add(ah, al, pa[2 * i], pa[2 * i + 1]);
-        block_pair<kPassThreads, kLead>(ah, al);
-        const double a = uniform(inv * (ah + al));
+            alpha.pair(pa[2 * i], pa[2 * i + 1]);
+        block_total<kPassThreads, kLead>(alpha);
+        const double a = uniform(inv * alpha.rounded());
         if (threadIdx.x == 0 && blockIdx.x == 0) {
             if (!isfinite(a)) st->numeric_error = 1;
             st->alpha_cur = a;
@@ -835,7 +843,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *
         }
         c2 = -(a * inv);
     }
-    double hi = 0.0, lo = 0.0;
+    Sum sum;
     for (uint32_t ti = blockIdx.x; ti < ntiles; ti += gridDim.x) {
         const uint32_t tt = rev ? ntiles - 1u - ti : ti;
         const IndexPart &tl = g.tile_lo[tt & ((1u << kTileBits) - 1u)], &th = g.tile_hi[tt >> kTileBits];
@@ -858,9 +866,10 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *
             const double wi = fma(c2, wp[e].y, u[e].y);
             re[e << kRegShift] = wr;
             im[e << kRegShift] = wi;
-            pair_prod(hi, lo, wr, wr);
-            pair_prod(hi, lo, wi, wi);
+            sum.product(wr, wr);
+            sum.product(wi, wi);
         }
+        sum.normalise();
         // w_{k-1} to global memory and D w, from the thread's own tile entries
         asm volatile("" : "+v"(xb)::"memory");  // addresses formed again where they are used, not kept
         double D[kR];
@@ -879,7 +888,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_hv_pass_fused(const HvDev *
         for (int e = 0; e < kR; ++e)
             part[FTK_IDX(xb | g.ebit[e], 0, 1u << P.n_sites, 6)] = make_double2(acc[e], acc[kR + e]);
     }
-    write_partial<kPassThreads>(partials, hi, lo);
+    write_partial<kPassThreads>(partials, sum);
 }
 
 // passes p0..n_passes-1 of the multi-pass form (the first of them starts from
@@ -993,7 +1002,8 @@ struct EpiLanczosADev {
                  // 2: the last pass does, every workgroup for itself (begin)
     FinBeta fb;
     SeqState *st_out;  // with fin 2: the state after that half step
-    double inv, c1, hi, lo;
+    double inv, c1;
+    Sum sum;
     __device__ void finalize_block(int r) const { finalize_beta_seq<kPassThreads>(fb, r); }
     // sequence r of a stacked batch: vectors vs entries apart, pstride partial doubles apart
     __device__ void select(int r, size_t vs, int pstride)
@@ -1015,7 +1025,7 @@ struct EpiLanczosADev {
     {
         inv = st->inv_cur;
         c1 = (-st->beta_cur) * st->inv_prev;
-        hi = lo = 0.0;
+        sum = Sum();
     }
     // Before the tiles of the last pass, and before the first epilogue.  With fin 2 beta_k
     // of the previous half step is summed from its partials here, in every workgroup of
@@ -1037,9 +1047,10 @@ struct EpiLanczosADev {
     {
         if (fin != 2) return true;
         const double *pb = fb.partials + (size_t)r * 2 * fb.nparts;
-        for (int i = threadIdx.x + BLOCK; i < fb.nparts; i += BLOCK) pair_add(bh, bl, pb[2 * i], pb[2 * i + 1]);
-        block_pair<BLOCK, kLead>(bh, bl);
-        const double bn = uniform(sqrt(bh + bl));
+        Sum norm2{bh, 0.0, bl};
+        for (int i = threadIdx.x + BLOCK; i < fb.nparts; i += BLOCK) norm2.pair(pb[2 * i], pb[2 * i + 1]);
+        block_total<BLOCK, kLead>(norm2);
+        const double bn = uniform(sqrt(norm2.rounded()));
         const bool ends = !(bn > fb.tol);  // invariant subspace
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             fb.beta_out[(size_t)r * fb.bstride + fb.k] = bn;
@@ -1068,12 +1079,13 @@ struct EpiLanczosADev {
         }
         U[x] = make_double2(ur, ui);
         if (vout) vout[x] = wc;
-        pair_prod(hi, lo, wc.x, ur);
-        pair_prod(hi, lo, wc.y, ui);
+        sum.product(wc.x, ur);
+        sum.product(wc.y, ui);
     }
+    __device__ void settle() { sum.normalise(); }
     __device__ void operator()(size_t x, double re, double im, const double2 &wc) { apply(x, re, im, wc, load(x)); }
     template <int BLOCK>
-    __device__ void finish() { write_partial<BLOCK>(partials, hi, lo); }
+    __device__ void finish() { write_partial<BLOCK>(partials, sum); }
 };
 
 void launch_lanczos_a(const HvOp &op, const double *Wcur, const double *Wprev, double *U,
@@ -1134,6 +1146,7 @@ struct EpiCocg {
     const CocgState *st;
     int first;
     CocgA a;
+    int turn = 0;
     __device__ void select(int r, size_t vs, int pstride)
     {
         Wprev += r * vs;
@@ -1150,8 +1163,9 @@ struct EpiCocg {
     {
         U[x] = a(re, im, wc, wp, first);
     }
+    __device__ void settle() { a.settle(turn++); }
     template <int BLOCK>
-    __device__ void finish() { write_partials5<2>(partials, a.hi, a.lo); }
+    __device__ void finish() { write_partials5<2>(partials, a.sum); }
 };
 
 bool cocg_work_vectors(const HvOp &op) { return hv_mode(op) != 0; }
@@ -1234,17 +1248,18 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double
     } else {
         c2 = -(st->alpha_cur * st->inv_cur);
     }
-    double hi = 0.0, lo = 0.0;
+    Sum sum;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 wc = Wcur[x];
         const double2 u = U[x];
         const double wr = fma(c2, wc.x, u.x);
         const double wi = fma(c2, wc.y, u.y);
         U[x] = make_double2(wr, wi);
-        pair_prod(hi, lo, wr, wr);
-        pair_prod(hi, lo, wi, wi);
+        sum.product(wr, wr);
+        sum.product(wi, wi);
+        sum.normalise();
     }
-    write_partial<kBlock>(partials, hi, lo);
+    write_partial<kBlock>(partials, sum);
 }
 
 __global__ void __launch_bounds__(kBlock) k_finalize_alpha(SeqState *st, const double *partials,
@@ -1358,13 +1373,14 @@ __global__ void __launch_bounds__(kBlock) k_dot(uint32_t dim, const double2 *__r
     a += blockIdx.y * vs;
     b += blockIdx.y * vs;
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
-    double hi = 0.0, lo = 0.0;
+    Sum sum;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = a[x], v = b[x];
-        pair_prod(hi, lo, u.x, v.x);
-        pair_prod(hi, lo, u.y, v.y);
+        sum.product(u.x, v.x);
+        sum.product(u.y, v.y);
+        sum.normalise();
     }
-    write_partial<kBlock>(partials, hi, lo);
+    write_partial<kBlock>(partials, sum);
 }
 
 __global__ void __launch_bounds__(kBlock) k_start_sequence(SeqState *st, const double *partials,
@@ -1773,37 +1789,36 @@ struct BatchGeom {
 // per-sequence (hi, lo) sums of a block: lanes with equal lane % B combine, then
 // waves in order; partials[(block * B + r) * 2 + {0, 1}]
 template <int B, int BLOCK>
-__device__ __forceinline__ void write_partial_batch(double *partials, double hi, double lo)
+__device__ __forceinline__ void write_partial_batch(double *partials, Sum s)
 {
     __shared__ double sh[BLOCK / 64][B][2];
+    s.normalise();
 #pragma unroll
-    for (int off = 32; off >= B; off >>= 1) {
-        double oh = __shfl_xor(hi, off, 64);
-        double ol = __shfl_xor(lo, off, 64);
-        pair_add(hi, lo, oh, ol);
-    }
+    for (int off = 32; off >= B; off >>= 1)
+        s.add(__shfl_xor(s.hi, off, 64), __shfl_xor(s.lo, off, 64), __shfl_xor(s.er, off, 64));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const double low = s.low();
     if (lane < B) {
-        sh[wave][lane][0] = hi;
-        sh[wave][lane][1] = lo;
+        sh[wave][lane][0] = s.hi;
+        sh[wave][lane][1] = low;
     }
     __syncthreads();
     if (threadIdx.x < B) {
-        double h = sh[0][threadIdx.x][0], l = sh[0][threadIdx.x][1];
-        for (int w = 1; w < BLOCK / 64; ++w) pair_add(h, l, sh[w][threadIdx.x][0], sh[w][threadIdx.x][1]);
-        partials[2 * (blockIdx.x * B + threadIdx.x)] = h;
+        Sum t;
+        for (int w = 0; w < BLOCK / 64; ++w) t.pair(sh[w][threadIdx.x][0], sh[w][threadIdx.x][1]);
+        const double l = t.low();
+        partials[2 * (blockIdx.x * B + threadIdx.x)] = t.hi;
         partials[2 * (blockIdx.x * B + threadIdx.x) + 1] = l;
     }
 }
 
-// sum over blocks of sequence r's partials (stride B), rounded; thread 0 of a kBlock block
+// sum over blocks of sequence r's partials (stride B), rounded, by a kBlock block
 __device__ __forceinline__ double reduce_partials_strided(const double *partials, int nparts, int B, int r)
 {
-    double hi = 0.0, lo = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x)
-        pair_add(hi, lo, partials[2 * (i * B + r)], partials[2 * (i * B + r) + 1]);
-    block_pair<kBlock, kLead>(hi, lo);
-    return hi + lo;
+    Sum s;
+    for (int i = threadIdx.x; i < nparts; i += blockDim.x) s.pair(partials[2 * (i * B + r)], partials[2 * (i * B + r) + 1]);
+    block_total<kBlock, kLead>(s);
+    return s.rounded();
 }
 
 template <int B>
@@ -1813,7 +1828,8 @@ struct EpiLanczosABatch {
     double *partials;
     const SeqState *st;  // [B]
     int first;
-    double inv, c1, hi, lo;
+    double inv, c1;
+    Sum sum;
     int done;
     __device__ bool active() const { return true; }
     __device__ void init(int r)
@@ -1821,7 +1837,7 @@ struct EpiLanczosABatch {
         inv = st[r].inv_cur;
         c1 = (-st[r].beta_cur) * st[r].inv_prev;
         done = st[r].done;
-        hi = lo = 0.0;
+        sum = Sum();
     }
     __device__ double2 load(size_t idx) const { return (first || done) ? make_double2(0.0, 0.0) : Wprev[idx]; }
     __device__ void apply(size_t idx, double re, double im, const double2 &wc, const double2 &wp)
@@ -1833,11 +1849,12 @@ struct EpiLanczosABatch {
             ui = fma(c1, wp.y, ui);
         }
         U[idx] = make_double2(ur, ui);
-        pair_prod(hi, lo, wc.x, ur);
-        pair_prod(hi, lo, wc.y, ui);
+        sum.product(wc.x, ur);
+        sum.product(wc.y, ui);
     }
+    __device__ void settle() { sum.normalise(); }
     template <int BLOCK>
-    __device__ void finish() { write_partial_batch<B, BLOCK>(partials, hi, lo); }
+    __device__ void finish() { write_partial_batch<B, BLOCK>(partials, sum); }
 };
 
 template <int B, class Epi>
@@ -1882,6 +1899,7 @@ __global__ void __launch_bounds__(kBlock) k_hv_batch(const HvDev *__restrict__ d
             const size_t idx = (size_t)(xb + (e << G::RS)) * B + r;
             epi.apply(idx, re[e], im[e], v[idx], in[e]);
         }
+        epi.settle();
     }
     epi.template finish<kBlock>();
 }
@@ -1935,7 +1953,7 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b_batch(uint32_t dim, const 
     const int r = threadIdx.x % B;  // kBlock and the grid stride are multiples of B
     const int done = st[r].done;
     const double c2 = -(st[r].alpha_cur * st[r].inv_cur);
-    double hi = 0.0, lo = 0.0;
+    Sum sum;
     const size_t n = (size_t)dim * B;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
         if (done) continue;
@@ -1944,10 +1962,11 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b_batch(uint32_t dim, const 
         const double wr = fma(c2, wc.x, u.x);
         const double wi = fma(c2, wc.y, u.y);
         U[idx] = make_double2(wr, wi);
-        pair_prod(hi, lo, wr, wr);
-        pair_prod(hi, lo, wi, wi);
+        sum.product(wr, wr);
+        sum.product(wi, wi);
+        sum.normalise();
     }
-    write_partial_batch<B, kBlock>(partials, hi, lo);
+    write_partial_batch<B, kBlock>(partials, sum);
 }
 
 void launch_lanczos_b_batch(int B, uint32_t dim, const double *Wcur, double *U, SeqState *st, double *partials,
@@ -2038,14 +2057,15 @@ void launch_finalize_beta_batch(int B, SeqState *st, const double *partials, int
 template <int B>
 __global__ void __launch_bounds__(kBlock) k_dot_batch(uint32_t dim, const double2 *__restrict__ a, double *partials)
 {
-    double hi = 0.0, lo = 0.0;
+    Sum sum;
     const size_t n = (size_t)dim * B;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
         const double2 u = a[idx];
-        pair_prod(hi, lo, u.x, u.x);
-        pair_prod(hi, lo, u.y, u.y);
+        sum.product(u.x, u.x);
+        sum.product(u.y, u.y);
+        sum.normalise();
     }
-    write_partial_batch<B, kBlock>(partials, hi, lo);
+    write_partial_batch<B, kBlock>(partials, sum);
 }
 
 __global__ void __launch_bounds__(kBlock) k_start_batch(SeqState *st, const double *partials, int nparts, int B,

@@ -133,17 +133,17 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
     int bad;  // 1 + the first step after which a scalar was not finite (1: the start), 0 none
     if (R.k0 == 0) {
         const double2 *start = R.chi ? (const double2 *)R.chi + (size_t)blockIdx.x * dim : q.phi;
-        double hi = 0.0, lo = 0.0;
+        Sum sum;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const uint32_t x = tid + e * T;
             wc[e] = start[x];
             wp[e] = make_double2(0.0, 0.0);
             put(x, wc[e]);
-            pair_prod(hi, lo, wc[e].x, wc[e].x);
-            pair_prod(hi, lo, wc[e].y, wc[e].y);
+            sum.product(wc[e].x, wc[e].x);
+            sum.product(wc[e].y, wc[e].y);
         }
-        const double s = block_sum<T>(hi, lo, sh_b);
+        const double s = block_sum<T>(sum, sh_b);
         const double nrm = sqrt(s);
         inv = uniform(nrm > 0.0 ? 1.0 / nrm : 0.0);
         inv_prev = 0.0;
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
         }
         // u = (H w_{k-1}) inv + c1 w_{k-2}; alpha_k
         const double c1 = uniform((-bcur) * inv_prev);
-        double hi = 0.0, lo = 0.0;
+        Sum sum;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             double ur = acc[e] * inv, ui = acc[E + e] * inv;
@@ -226,28 +226,28 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
             }
             acc[e] = ur;
             acc[E + e] = ui;
-            pair_prod(hi, lo, wc[e].x, ur);
-            pair_prod(hi, lo, wc[e].y, ui);
+            sum.product(wc[e].x, ur);
+            sum.product(wc[e].y, ui);
         }
         if (vout) {
 #pragma unroll
             for (int e = 0; e < E; ++e) vout[(size_t)(k - R.k0) * dim + tid + e * T] = wc[e];
         }
-        a = uniform(inv * block_sum<T>(hi, lo, sh_a));  // the barrier ends the reads of the tile
+        a = uniform(inv * block_sum<T>(sum, sh_a));  // the barrier ends the reads of the tile
         // w_k = u + c2 w_{k-1}; beta_{k+1}
         const double c2 = uniform(-(a * inv));
-        hi = lo = 0.0;
+        sum = Sum();
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const double wr = fma(c2, wc[e].x, acc[e]);
             const double wi = fma(c2, wc[e].y, acc[E + e]);
             put(tid + e * T, make_double2(wr, wi));
-            pair_prod(hi, lo, wr, wr);
-            pair_prod(hi, lo, wi, wi);
+            sum.product(wr, wr);
+            sum.product(wi, wi);
             wp[e] = wc[e];
             wc[e] = make_double2(wr, wi);
         }
-        const double bn = uniform(sqrt(block_sum<T>(hi, lo, sh_b)));
+        const double bn = uniform(sqrt(block_sum<T>(sum, sh_b)));
         if (tid == 0) {
             alpha[k] = a;
             beta[k] = bn;
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
     int bad;  // 1 + the first step after which a scalar was not finite (1: the start), 0 none
     if (R.k0 == 0) {
         const double2 *start = R.chi ? (const double2 *)R.chi + (size_t)blockIdx.x * dim : q.phi;
-        double hi = 0.0, lo = 0.0;
+        Sum sum;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const uint32_t x = tid + e * T;
@@ -356,11 +356,11 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
             own(e) = c.x;
             buf.set(2 * dim + e * T, c.x);
             buf.set(3 * dim + e * T, c.y);
-            pair_prod(hi, lo, c.x, c.x);
-            pair_prod(hi, lo, c.y, c.y);
+            sum.product(c.x, c.x);
+            sum.product(c.y, c.y);
             if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        const double s = block_sum<T>(hi, lo, sh_b);
+        const double s = block_sum<T>(sum, sh_b);
         const double nrm = sqrt(s);
         inv = uniform(nrm > 0.0 ? 1.0 / nrm : 0.0);
         inv_prev = 0.0;
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
         const uint32_t wcur = ((k + 1) & 1) * 2 * dim;  // w_{k-1}
         const double c1 = uniform((-bcur) * inv_prev);
         double acc[E];
-        double hi = 0.0, lo = 0.0;
+        Sum sum;
         // u = (H w_{k-1}) inv + c1 w_{k-2} of the plane in LDS, into acc; its share of alpha_k
         auto half = [&](uint32_t wp) {
             double prev[E];  // read while the bonds run (step 0 has none and drops what it reads)
@@ -426,12 +426,18 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
                 const double t = acc[e] * inv, u = fma(c1, prev[e], t);
                 acc[e] = first ? t : u;
             }
+            Sum part;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                pair_prod(hi, lo, own(e), acc[e]);
+                part.product(own(e), acc[e]);
                 if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
-            asm volatile("" : "+v"(hi), "+v"(lo));  // added up here: not their 32 factors kept to the end
+            // added up here, to two registers: not their 32 factors kept to the end
+            const double low = part.low();
+            sum.pair(part.hi, low);
+            sum.er = sum.low();
+            sum.lo = 0.0;
+            asm volatile("" : "+v"(sum.hi), "+v"(sum.er));
         };
         double own_re[E], own_im[E];
         half(wnew);
@@ -451,7 +457,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
             own_re[e] = buf.get(wcur + e * T);
             u_re[e] = buf.get(wnew + e * T);
         }
-        a = uniform(inv * block_sum<T>(hi, lo, sh_a));  // nor the imaginary one
+        a = uniform(inv * block_sum<T>(sum, sh_a));  // nor the imaginary one
         if (vout) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -461,7 +467,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
             asm volatile("" ::: "memory");
         }
         const double c2 = uniform(-(a * inv));
-        hi = lo = 0.0;
+        sum = Sum();
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const double ci = own(e);
@@ -470,11 +476,11 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
             own(e) = wr;
             buf.set(wnew + e * T, wr);
             buf.set(wnew + dim + e * T, wi);
-            pair_prod(hi, lo, wr, wr);
-            pair_prod(hi, lo, wi, wi);
+            sum.product(wr, wr);
+            sum.product(wi, wi);
             if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        const double bn = uniform(sqrt(block_sum<T>(hi, lo, sh_b)));
+        const double bn = uniform(sqrt(block_sum<T>(sum, sh_b)));
         if (tid == 0) {
             alpha[k] = a;
             beta[k] = bn;

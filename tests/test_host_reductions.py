@@ -1,8 +1,11 @@
-"""The workgroup reductions of csrc/exact_sum.h on the host: every lane a thread, a
-workgroup's shared memory static, lanes exchanging through their wave's barrier, built
-with g++ under the thread sanitizer.  Two sums of a kernel may follow each other with
-nothing between (a leading reduce_partials, then write_partial), so no wave may reach
-memory that another one still reads.
+"""The exact sums of csrc/exact_sum.h on the host.
+
+Reductions: every lane a thread, a workgroup's shared memory static, lanes exchanging
+through their wave's barrier, built with g++ under the thread sanitizer.  Two sums of a
+kernel may follow each other with nothing between (a leading reduce_partials, then
+write_partial), so no wave may reach memory that another one still reads.
+
+Accuracy: a thread's running sum and the sums of whole waves against double-double.
 """
 import os
 import shutil
@@ -97,7 +100,9 @@ int main()
             // as k_lanczos_b and the last pass of a step do: a leading sum, then the
             // workgroup's own partial sum, nothing between
             seen[t] = reduce_partials<T>(in.data(), nparts);
-            write_partial<T>(out.data(), t + 1.0, 0.0);
+            Sum s;
+            s.product(t + 1.0, 1.0);
+            write_partial<T>(out.data(), s);
         });
     for (auto &t : ts) t.join();
     int bad = out[0] + out[1] != 0.5 * T * (T + 1);
@@ -121,3 +126,112 @@ def test_consecutive_sums_share_no_memory(tmp_path, block):
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert "data race" not in out.stderr, out.stderr[:4000]
     assert out.returncode == 0 and out.stdout.strip() == "OK", out.stdout + out.stderr[:4000]
+
+
+ACCURACY = r"""
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "exact_sum.h"
+thread_local uint3_t threadIdx, blockIdx, gridDim;
+pthread_barrier_t group_bar, wave_bar[16];
+int lanes[1024], lanes2[1024];
+using namespace ftk;
+typedef __float128 Q;
+
+// double-double with the products' errors summed apart, one renormalisation a product
+struct Ref {
+    double hi = 0, lo = 0, err = 0;
+    static double two(double &a, double b)
+    {
+        const double s = a + b, bb = s - a, e = (a - (s - bb)) + (b - bb);
+        a = s;
+        return e;
+    }
+    void fast(double e)
+    {
+        const double s = hi + e;
+        lo = e - (s - hi);
+        hi = s;
+    }
+    void product(double a, double b)
+    {
+        const double p = a * b;
+        err += std::fma(a, b, -p);
+        const double e = two(hi, p) + lo;
+        fast(e);
+    }
+    void end()
+    {
+        const double e = two(hi, err) + lo;
+        fast(e);
+    }
+    void add(const Ref &o)
+    {
+        double e = two(hi, o.hi), t = lo;
+        const double f = two(t, o.lo);
+        fast(e + t);
+        lo += f;
+        fast(lo);
+    }
+};
+
+int main()
+{
+    std::mt19937_64 g(11);
+    std::normal_distribution<double> N01;
+    int bad = 0;
+    const int per[] = {1, 4, 16, 64, 1024, 4096};  // complex elements of a thread
+    for (int n : per) {
+        const int T = n > 64 ? 8 : 64, trials = 60;
+        double worst = 0, worst_ref = 0;
+        for (int trial = 0; trial < trials; ++trial) {
+            std::vector<Sum> s(T);
+            std::vector<Ref> r(T);
+            Q exact = 0, scale = 0;
+            for (int t = 0; t < T; ++t) {
+                for (int i = 0; i < n; ++i) {
+                    const double a = N01(g), b = N01(g), c = trial % 2 ? a : N01(g), d = trial % 2 ? b : N01(g);
+                    s[t].product(a, c);
+                    s[t].product(b, d);
+                    if (i % 8 == 7) s[t].normalise();
+                    r[t].product(a, c);
+                    r[t].product(b, d);
+                    exact += (Q)a * c + (Q)b * d;
+                    scale += (Q)std::fabs(a * c) + (Q)std::fabs(b * d);
+                }
+                s[t].normalise();
+                r[t].end();
+            }
+            for (int m = T / 2; m > 0; m /= 2)
+                for (int t = 0; t < m; ++t) s[t].add(s[t + m].hi, s[t + m].lo, s[t + m].er), r[t].add(r[t + m]);
+            const double l = s[0].low();
+            worst = std::max(worst, std::fabs((double)(((Q)s[0].hi + l - exact) / scale)));
+            worst_ref = std::max(worst_ref, std::fabs((double)(((Q)r[0].hi + r[0].lo - exact) / scale)));
+        }
+        std::printf("%d threads of %d elements: 2^%.1f, double-double 2^%.1f\n", T, n, std::log2(worst), std::log2(worst_ref));
+        bad += !(worst <= 1.5 * worst_ref);
+    }
+    std::printf(bad ? "WRONG\n" : "OK\n");
+    return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_sums_are_as_accurate_as_double_double(tmp_path):
+    """The unrounded sum of a wave's threads with up to 4096 elements each (a thread's share at 30
+    sites), normalised every eight as the pass kernels do, against renormalised double-double: the same
+    rounding of the pair at the end, which alone is up to 2^-106, so no more than half as much again
+    in the worst of 60."""
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text(HIP_STUB)
+    src = tmp_path / "acc.cpp"
+    src.write_text(ACCURACY)
+    exe = tmp_path / "acc"
+    subprocess.run(["g++", "-std=gnu++17", "-O1", "-w", "-ffp-contract=off", "-I", str(tmp_path), "-I", CSRC, str(src), "-o",
+                    str(exe), "-pthread"], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip().endswith("OK"), out.stdout + out.stderr
