@@ -233,16 +233,18 @@ ftk_status ftk_apply_h_noalloc(const ftk_hamiltonian *h, const double *v_dev, do
 
 /* Device bounds checks (a service of the library, not of the method).  The debug
  * build libftkw_check.so (same sources, -DFTK_DEVICE_CHECKS) checks every gather and
- * scatter index of the H v kernels (global vectors and LDS tiles), of the S^alpha_Q
+ * scatter index of the H v kernels and of the resident sequences (global vectors and
+ * LDS tiles), of the S^alpha_Q
  * gathers and of the filter accumulation against its buffer's extent; a violation
  * is counted in a device word and the access is redirected to entry 0, so the
  * kernel ends normally.  This call waits for ctx's stream and returns compiled (1
  * in the debug build, 0 in the release build, whose counters read 0), the number
  * of violations on ctx's device since the last clear, the site code of the first
  * (1 single-element H v, 2/3 blocked/tiled partner in HBM/LDS, 4/5 own elements in
- * HBM/LDS, 6/7 multi-pass element/tile entry, 8 multi-pass LDS partner, 9 staged
- * bond constants, 10/11 batch-layout own/partner, 12 S^alpha_Q, 13 filter
- * coefficients) and its index; clear != 0 resets them.  Any output may be NULL. */
+ * HBM/LDS, 6/7 multi-pass element/tile entry, 8 multi-pass LDS partner,
+ * 10/11 batch-layout own/partner, 12 S^alpha_Q, 13 filter
+ * coefficients, 14 resident sequences' own entries, 15 their LDS partners, 16 their
+ * carried vectors) and its index; clear != 0 resets them.  Any output may be NULL. */
 ftk_status ftk_device_checks(ftk_ctx *ctx, int *compiled, uint32_t *violations, uint32_t *first_site,
                              uint32_t *first_index, int clear);
 /* Debug build only (FTK_EINVAL in the release build): one kernel claims entry 5 of

@@ -26,8 +26,11 @@
 #include "bond_ops.h"
 #include "exact_sum.h"
 #include "cocg.h"
+#include "device_checks.h"
 #include "kernels.h"
+#include "resident.h"
 #include "shift_update.h"
+#include "spin_ops.h"
 
 namespace ftk {
 
@@ -179,28 +182,7 @@ int vec_grid(uint32_t dim)
 }
 
 // ---------------------------------------------------------------------------
-// Device bounds checks of the debug build (-DFTK_DEVICE_CHECKS, libftkw_check.so):
-// FTK_IDX(i, top, lim, site) states that indices i .. i + top of a buffer with lim
-// entries are read or written.  In the debug build a violation is counted in
-// g_dcheck (count, site of the first, its index) and index 0 is used instead, so
-// the kernel finishes and the host reports it; the release build compiles the
-// check away.  Sites: 1 single-element H v gather, 2/3 blocked and tiled gathers
-// (global, LDS), 4 own elements of the blocked/tiled forms, 5 own LDS entries of
-// the tiled form, 6/7 multi-pass global element and LDS tile entries, 8 multi-pass
-// LDS partners, 9 bond constants staged in LDS, 10/11 batch-layout own elements
-// and partners, 12 S^alpha_Q gathers, 13 filter accumulation.
 #ifdef FTK_DEVICE_CHECKS
-__device__ unsigned int g_dcheck[3];
-__device__ __forceinline__ uint32_t dchk(uint32_t i, uint32_t top, uint32_t lim, uint32_t site)
-{
-    if (i < lim && top < lim - i) return i;
-    if (atomicAdd(&g_dcheck[0], 1u) == 0u) {
-        g_dcheck[1] = site;
-        g_dcheck[2] = i;
-    }
-    return 0u;
-}
-#define FTK_IDX(i, top, lim, site) dchk((uint32_t)(i), (uint32_t)(top), (uint32_t)(lim), (site))
 int device_checks_compiled() { return 1; }
 // one claimed access to entries 5..5 of a 4-entry buffer (site 99): counted, redirected to 0;
 // nothing is read or written at the claimed index
@@ -211,23 +193,15 @@ void device_checks_selftest(uint32_t *out_dev, hipStream_t s)
 }
 void device_checks_read(unsigned int out[3], bool clear)
 {
-    hipError_t e = hipMemcpyFromSymbol(out, HIP_SYMBOL(g_dcheck), 3 * sizeof(unsigned int));
-    if (e == hipSuccess && clear) {
-        const unsigned int z[3] = {0u, 0u, 0u};
-        e = hipMemcpyToSymbol(HIP_SYMBOL(g_dcheck), z, 3 * sizeof(unsigned int));
-    }
-    if (e != hipSuccess) out[0] = out[1] = out[2] = ~0u;
+    out[0] = out[1] = out[2] = 0u;
+    const bool here = dchk_read(out, clear), there = resident_checks_read(out, clear);
+    if (!(here && there)) out[0] = out[1] = out[2] = ~0u;
 }
 #else
-#define FTK_IDX(i, top, lim, site) (i)
 int device_checks_compiled() { return 0; }
 void device_checks_selftest(uint32_t *, hipStream_t) {}
 void device_checks_read(unsigned int out[3], bool) { out[0] = out[1] = out[2] = 0u; }
 #endif
-
-}  // namespace ftk
-#include "spin_ops.h"  // its gathers carry the bounds checks above
-namespace ftk {
 
 static int g_hv_mode = -1;  // -1: chosen by size
 static int g_pass_grid = 0;  // workgroups of a multi-pass launch (0: two per compute unit)

@@ -64,4 +64,7 @@ void launch_shifts(const ShiftRun &run, int n_seq, hipStream_t s);
 // shifts' state between calls; g is written every time.
 void launch_shifts_until(const ShiftRun &run, int k0, int k1, double rtol, ShiftState *sh, int n_seq, hipStream_t s);
 
+// debug build: the bounds checks' counters of these kernels (device_checks.h)
+bool resident_checks_read(unsigned int out[3], bool clear);
+
 }  // namespace ftk

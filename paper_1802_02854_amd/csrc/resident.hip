@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bond_ops.h"
+#include "device_checks.h"
 #include "exact_sum.h"
 #include "resident.h"
 #include "shift_update.h"
@@ -104,7 +105,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
     };
     const uint32_t tile_at = lds_address(tile);
     const ResidentSeq q = R.seq[blockIdx.x];
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = FTK_IDX(threadIdx.x, (E - 1) * T, dim, 14);
     SeqState *st = R.st + q.out;
     double *alpha = R.alpha + (size_t)q.out * R.stride, *beta = R.beta + (size_t)q.out * R.stride;
     const int nb = P.n_bonds;
@@ -180,13 +181,13 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
         if constexpr (kPlanar) {
             for (int b = 0; b < nb; ++b) {
                 const BondAt c = bonds.at(b);
-                const uint32_t t0 = tile_at + (tid ^ (c.m & (T - 1))) * 8;
+                const uint32_t t0 = tile_at + FTK_IDX(tid ^ (c.m & (T - 1)), (E - 1) * T, dim, 15) * 8;
                 bond16<T * 8>(acc, t0, t0 + 8 * dim, c.m >> LOGT, c.even, c.odd);
             }
         } else {
             auto partners = [&](uint32_t m, double2 (&v)[E]) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) v[e] = tile[(tid ^ m) ^ (uint32_t)(e * T)];
+                for (int e = 0; e < E; ++e) v[e] = tile[FTK_IDX((tid ^ m) ^ (uint32_t)(e * T), 0, dim, 15)];
             };
             auto add = [&](const BondAt &c, const double2 (&v)[E]) {
                 const double even = c.even, odd = c.odd;
@@ -278,19 +279,20 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun 
 struct Carried {
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t lane;  // byte offset of entry tid
-    __device__ Carried(double *p, uint32_t entries)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(entries * sizeof(double)), 0x00027000)),
-          lane(threadIdx.x * (uint32_t)sizeof(double))
+    uint32_t entries;
+    __device__ Carried(double *p, uint32_t n)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(n * sizeof(double)), 0x00027000)),
+          lane(threadIdx.x * (uint32_t)sizeof(double)), entries(n)
     {
     }
     __device__ __forceinline__ double get(uint32_t i) const
     {
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane, i * 8, 0));
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane, FTK_IDX(i, blockDim.x - 1, entries, 16) * 8, 0));
     }
     __device__ __forceinline__ void set(uint32_t i, double x) const
     {
         typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, x), rsrc, lane, i * 8, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, x), rsrc, lane, FTK_IDX(i, blockDim.x - 1, entries, 16) * 8, 0);
     }
 };
 
@@ -307,7 +309,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
     __shared__ double plane[dim];
     __shared__ double2 sh_a[T / 64], sh_b[T / 64];
     const ResidentSeq q = R.seq[blockIdx.x];
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = FTK_IDX(threadIdx.x, (E - 1) * T, dim, 14);
     SeqState *st = R.st + q.out;
     double *alpha = R.alpha + (size_t)q.out * R.stride, *beta = R.beta + (size_t)q.out * R.stride;
     const int nb = P.n_bonds;
@@ -405,14 +407,14 @@ __global__ void __launch_bounds__(1 << LOGT) k_resident_planes(HvParams P, Resid
             for (int b = 0; b < nb; ++b) {
                 const BondAt c = bonds.at(b);
                 if constexpr (E == 16) {
-                    const uint32_t t0 = plane_at + (tid ^ (c.m & (T - 1))) * 8;
+                    const uint32_t t0 = plane_at + FTK_IDX(tid ^ (c.m & (T - 1)), (E - 1) * T, dim, 15) * 8;
                     bond16<T * 8>(acc, t0, t0 + 64 * T, c.m >> LOGT, c.even, c.odd);
                     continue;
                 }
                 const double even = c.even, odd = c.odd;
                 const uint32_t sel = odd_elements(c.m >> LOGT);
                 const char *src = (const char *)plane;
-                const uint32_t base = (tid ^ c.m) * (uint32_t)sizeof(double);
+                const uint32_t base = FTK_IDX(tid ^ c.m, 0, dim, 15) * (uint32_t)sizeof(double);
                 double v[E];
 #pragma unroll
                 for (int e = 0; e < E; ++e)
@@ -636,5 +638,9 @@ void launch_shifts_until(const ShiftRun &run, int k0, int k1, double rtol, Shift
     if (n_seq <= 0) return;
     hipLaunchKernelGGL(k_shifts_until, dim3(n_seq), dim3(kUntilThreads), 0, s, run, k0, k1, rtol, sh);
 }
+
+#ifdef FTK_DEVICE_CHECKS
+bool resident_checks_read(unsigned int out[3], bool clear) { return dchk_read(out, clear); }
+#endif
 
 }  // namespace ftk

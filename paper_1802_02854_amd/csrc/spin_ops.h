@@ -5,9 +5,7 @@
 
 #include <cstdint>
 
-#ifndef FTK_IDX
-#define FTK_IDX(i, top, lim, site) (i)
-#endif
+#include "device_checks.h"
 
 namespace ftk {
 
