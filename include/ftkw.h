@@ -70,7 +70,8 @@ ftk_status ftk_ctx_create_with_allocator(int device, void *hip_stream, ftk_alloc
 /* A context serves one thread at a time (its stream, byte counts and timing
  * events are not locked); use one context per thread, as the server does for
  * its workers.  Destroy every handle made on a context (Hamiltonians, states,
- * spectra, pair spectra) before the context itself. */
+ * spectra, pair spectra) before the context itself; one that still holds device memory
+ * keeps the context, and needs its stream and allocator, until it is destroyed. */
 ftk_status ftk_ctx_destroy(ftk_ctx *ctx);
 ftk_status ftk_sync(ftk_ctx *ctx);
 /* Device memory currently held by the library for this context, in bytes. */

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -85,6 +86,11 @@ struct ftk_ctx {
     size_t bytes = 0;
     size_t peak = 0;  // high-water mark of bytes since the last reset
     bool timing = false;
+    std::atomic<int> refs{1};  // the caller's and one per device allocation
+    void unref()
+    {
+        if (--refs == 0) delete this;
+    }
     std::map<std::string, std::vector<std::pair<hipEvent_t, hipEvent_t>>> events;
 
     // brackets the launches made by f with events when timing is on
@@ -144,6 +150,7 @@ struct DevBuf {
                 fail(FTK_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
             }
         }
+        ++c->refs;
         c->bytes += bytes;
         c->peak = std::max(c->peak, c->bytes);
     }
@@ -171,6 +178,7 @@ struct DevBuf {
             else
                 (void)hipFree(p);
             ctx->bytes -= n;
+            ctx->unref();
         }
         p = nullptr;
         n = 0;
@@ -510,7 +518,9 @@ ftk_status ftk_ctx_create_with_allocator(int device, void *hip_stream, ftk_alloc
 
 ftk_status ftk_ctx_destroy(ftk_ctx *ctx)
 {
-    return guard([&] { delete ctx; });
+    return guard([&] {
+        if (ctx) ctx->unref();
+    });
 }
 
 ftk_status ftk_sync(ftk_ctx *ctx)

@@ -139,3 +139,20 @@ def test_small_clusters_fit_a_small_pool(env, N, states_mib, spectra_mib):
         assert not pool.held
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("N", [8, 16])
+def test_handles_outlive_their_context(env, N):
+    """A Hamiltonian and states used and destroyed after their context was."""
+    ftk, torch, _, _ = env
+    print(f"destroy order N={N}", flush=True)
+    ctx = ftk.Context(0)
+    h = ftk.Hamiltonian(ctx, ftk.honeycomb_cluster(*SUPERCELLS[N]), -1.0, 0.1)
+    st = ftk.TypicalStates(h, seed=1, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=4, M=4, n_steps=8)
+    v = ftk.random_vector(ctx, 3, 0, N)
+    w, phi = h.apply(v).cpu(), st.shell(0, 0, 2).cpu()
+    ctx.close()
+    others = [ftk.Context(0) for _ in range(64)]  # its memory, were it free, has other owners now
+    assert torch.equal(h.apply(v).cpu(), w) and torch.equal(st.shell(0, 0, 2).cpu(), phi)
+    st.close(), h.close()
+    del others
