@@ -1558,8 +1558,9 @@ struct BatchRunner {
     // The first batch is launched step by step: the GPU starts at once and the host stays
     // ahead of it.  The graph for the following ones is captured while it runs (16 sites,
     // one batch of 32 sequences of 200 steps: 74 us a step with the capture first, 67
-    // without; replayed and launched steps take the same time).
-    bool replays() { return g_use_graphs && !g_plain_loop && runs++ > 0; }
+    // without; replayed and launched steps take the same time).  Under kernel timing every
+    // batch is replayed and timed as a whole.
+    bool replays() { return g_use_graphs && !g_plain_loop && (runs++ > 0 || ctx->timing); }
     // The first batches of several chains, step by step in turn: launched one after the
     // other a chain would start when the host is through with the one before.
     static void run_together(const std::vector<BatchRunner *> &chains)
@@ -1725,7 +1726,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
         BatchShifts bs;
         for (int r = 0; r < kMaxBatch; ++r) bs.re[r] = 0.0;
         double secs = 1e30;
-        for (int rep = 0; rep < 4; ++rep) {  // the first repetition includes graph capture
+        for (int rep = 0; rep < 4; ++rep) {  // the first launches step by step, the second includes graph capture
             run.start(bs);
             HIP_CHECK(hipStreamSynchronize(s));
             auto t0 = std::chrono::steady_clock::now();

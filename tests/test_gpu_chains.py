@@ -35,3 +35,21 @@ def test_two_chains_match_one(N, B, alloc):
         for x, y in zip(res[0], r):
             assert np.array_equal(x, y)
     assert np.abs(res[0][0]).max() > 0
+
+
+@pytest.mark.parametrize("N,B,rows", [(16, 4, 3), (16, 4, 9), (20, 1, 1), (20, 1, 3)])
+def test_every_batch_is_timed_as_a_whole(N, B, rows):
+    """Kernel timing counts one replayed loop per batch, the first and an only one included, and no
+    single steps."""
+    import paper_1802_02854_amd as ftk
+    print(f"timed batches N={N} B={B} rows={rows}", flush=True)
+    ctx = ftk.Context(0)
+    h = ftk.Hamiltonian(ctx, ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[N]))[0], -1.0, 0.1)
+    st = ftk.TypicalStates(h, seed=2, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=9, M=4, n_steps=8)
+    ctx.set_timing(True)
+    ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-3, 3, 20), eta=0.1, n_steps=9, rhs_block=B, alpha_mask=4,
+                 shells=(0, rows))
+    ctx.set_timing(False)
+    blocks, ms = ctx.kernel_time("lanczos_block")
+    assert blocks == -(-rows // B) and ms > 0
+    assert ctx.kernel_time("lanczos_step") == (0, 0.0)
