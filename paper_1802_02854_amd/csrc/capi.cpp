@@ -2950,13 +2950,20 @@ void seq_chunk(ftk_green_seq *q, int k1)
     ShiftState *sh = (ShiftState *)q->shifts.p;
     const bool fuse = lanczos_fusable(h->op) && !g_plain_loop;
     const bool fa_on = fuse && alpha_in_fused_pass();
-    double *pa = q->partials.d(), *pb = fa_on ? q->partials_b.d() : q->partials.d();
+    const bool pairs = lanczos_pairs(h->op, 1) && !g_plain_loop;
+    double *pa = q->partials.d(), *pb = fa_on || pairs ? q->partials_b.d() : q->partials.d();
     const int k0 = q->k;
     for (int k = k0; k < k1; ++k) {
         const double *cur = k == 0 ? q->chi.d() : W[(k - 1) % 2];
         const double *prv = k == 1 ? q->chi.d() : W[k % 2];
         double *out = W[k % 2];
-        if (fuse && k > k0) {
+        if (pairs) {
+            // two launches and the shift update, which a resumed sequence keeps from step to step
+            launch_lanczos_pair_a(h->op, cur, prv, out, nullptr, st, pa, k == 0, s, nullptr, st);
+            const FinAlpha fa{pa, nparts_hv, q->al.d(), 0, k};
+            launch_lanczos_b(dim, cur, out, st, pb, s, 1, 0, &fa);
+            launch_finalize_beta(st, pb, nparts_hv, q->be.d(), k, tol, sh, q->omega.d(), q->nw, q->eta, s);
+        } else if (fuse && k > k0) {
             const FinAlpha fa{pa, nparts_hv, q->al.d(), 0, k - 1};
             launch_lanczos_fused_first(h->op, W[(k - 1) % 2], prv, st, pb, s, Stack(), fa_on ? &fa : nullptr);
             const FinBeta fb{st, pb, nparts_hv, q->be.d(), k - 1, tol, sh, q->omega.d(), q->nw, q->eta, 0.0, 0};
