@@ -186,24 +186,43 @@ struct DevBuf {
     double *d() const { return (double *)p; }
 };
 
-// Several buffers of one call in one device allocation.
+// Several buffers of one call in one device allocation: from 32 MiB on a buffer of its own
+// costs 0.3 to 0.5 ms of hipMalloc and hipFree (20 sites, 3 sequences in two chains: 2.1 ms a
+// call beside its steps, 1.1 in two).  A buffer each past the last-level cache's size, which
+// is what calls take beyond what they were asked for, and where there is no room for one.
 struct Arena {
+    static constexpr size_t kWhole = size_t(272) << 20;
     std::vector<std::pair<void **, size_t>> parts;
-    DevBuf mem;
+    std::vector<DevBuf> mem;
     template <class T>
     void part(T **p, size_t n)
     {
         parts.push_back({(void **)p, (n * sizeof(T) + 255) / 256 * 256});
     }
-    void allocate(ftk_ctx *ctx)
+    bool whole(ftk_ctx *ctx)
     {
         size_t total = 0;
         for (auto &q : parts) total += q.second;
-        mem = DevBuf(ctx, total);
-        char *at = (char *)mem.p;
+        if (total > kWhole) return false;
+        try {
+            mem.emplace_back(ctx, total);
+        } catch (const Error &e) {
+            if (e.status != FTK_ENOMEM) throw;
+            return false;
+        }
+        char *at = (char *)mem[0].p;
         for (auto &q : parts) {
             *q.first = at;
             at += q.second;
+        }
+        return true;
+    }
+    void allocate(ftk_ctx *ctx)
+    {
+        if (whole(ctx)) return;
+        for (auto &q : parts) {
+            mem.emplace_back(ctx, q.second);
+            *q.first = mem.back().p;
         }
     }
 };
@@ -1354,7 +1373,10 @@ struct BatchRunner {
     bool fuse;   // multi-pass H v: halves of consecutive steps fused
     bool late;  // the multi-shift update once per finished sequence, not every step
     int slot = 0;  // which of the sequences' two states is current
-    DevBuf chi, W0, W1, st, al, be, shifts, omega, partials, partials_b, part;  // partials_b: norms of fused steps
+    Arena m;
+    double *chi, *W0, *W1, *al, *be, *omega, *partials, *partials_b, *part;  // partials_b: norms of fused steps
+    SeqState *st;
+    ShiftState *shifts;
     Stack sk;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1385,22 +1407,29 @@ struct BatchRunner {
                                       : lanczos_pairs(op, B_) ? pair_grid(H->dim, B_) : hv_grid(op, B_)),
           nparts_b(B_ == 1 || stacked ? vec_grid(H->dim) : vec_batch_grid(H->dim, B_)),
           pairs((B_ == 1 || stacked) && lanczos_pairs(op, B_) && !g_plain_loop),
-          fuse(!pairs && (stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop))), late(rtol_ == 0.0 && !g_plain_loop),
-          chi(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), W0(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_),
-          W1(H->ctx, sizeof(double) * 2 * (size_t)H->dim * B_), st(H->ctx, sizeof(SeqState) * 2 * B_),
-          al(H->ctx, sizeof(double) * (size_t)n_ * B_), be(H->ctx, sizeof(double) * (size_t)n_ * B_),
-          shifts(H->ctx, late ? sizeof(double) : sizeof(ShiftState) * (size_t)nw_ * B_), omega(H->ctx, sizeof(double) * nw_),
-          partials(H->ctx, sizeof(double) * 2 * (size_t)kMaxGrid * B_),
-          partials_b(H->ctx, fuse || pairs ? sizeof(double) * 2 * (size_t)kMaxGrid * B_ : sizeof(double)),
-          part(H->ctx, (stacked || own_partials) && !pairs ? sizeof(double) * 2 * (size_t)H->dim * B_ : sizeof(double))
+          fuse(!pairs && (stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop))),
+          late(rtol_ == 0.0 && !g_plain_loop)
     {
         need(stacked || block_batch(B), "the block layout runs 2, 4, 8 or 16 sequences per launch");
+        const size_t vectors = 2 * (size_t)dim * B, sums = 2 * (size_t)kMaxGrid * B;
+        m.part(&chi, vectors);
+        m.part(&W0, vectors);
+        m.part(&W1, vectors);
+        m.part(&part, (stacked || own_partials) && !pairs ? vectors : 0);
+        m.part(&st, 2 * (size_t)B);
+        m.part(&al, (size_t)n * B);
+        m.part(&be, (size_t)n * B);
+        m.part(&shifts, late ? 0 : (size_t)nw * B);
+        m.part(&omega, nw);
+        m.part(&partials, sums);
+        m.part(&partials_b, fuse || pairs ? sums : 0);
+        m.allocate(ctx);
         if (stacked || own_partials) {  // else the Hamiltonian's scratch vector
             sk.B = B;
-            sk.scratch = part.d();
+            sk.scratch = part;
             sk.vs = 2 * (size_t)dim;
         }
-        HIP_CHECK(hipMemcpyAsync(omega.p, omega_host, sizeof(double) * nw, hipMemcpyHostToDevice, s));
+        HIP_CHECK(hipMemcpyAsync(omega, omega_host, sizeof(double) * nw, hipMemcpyHostToDevice, s));
         HIP_CHECK(hipStreamSynchronize(s));
     }
     ~BatchRunner()
@@ -1408,66 +1437,66 @@ struct BatchRunner {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
-    SeqState *states() const { return (SeqState *)st.p + slot * B; }
+    SeqState *states() const { return st + slot * B; }
 
     // right-hand side r = S^alpha_Q phi in the runner's layout
     void load_rhs(const SqParams &P, const double *phi, int r)
     {
         if (stacked)
-            launch_apply_sq(P, phi, chi.d() + (size_t)r * 2 * dim, s);
+            launch_apply_sq(P, phi, chi + (size_t)r * 2 * dim, s);
         else
-            launch_apply_sq(P, phi, chi.d(), s, B, r);
+            launch_apply_sq(P, phi, chi, s, B, r);
     }
 
     // right-hand side r = one of the polarization vectors of (lam, rho)
     void load_polarized(int k, const double *lam, const double *rho, int r)
     {
         if (stacked)
-            launch_polarize(dim, k, lam, rho, chi.d() + (size_t)r * 2 * dim, s);
+            launch_polarize(dim, k, lam, rho, chi + (size_t)r * 2 * dim, s);
         else
-            launch_polarize(dim, k, lam, rho, chi.d(), s, B, r);
+            launch_polarize(dim, k, lam, rho, chi, s, B, r);
     }
 
     void start(const BatchShifts &sh)
     {
         slot = 0;
         if (B == 1) {
-            launch_dot(dim, chi.d(), chi.d(), partials.d(), s);
-            launch_start_sequence(states(), partials.d(), nparts_b, sh.re[0], s);
+            launch_dot(dim, chi, chi, partials, s);
+            launch_start_sequence(states(), partials, nparts_b, sh.re[0], s);
         } else if (stacked) {
-            launch_start_stacked(B, dim, chi.d(), partials.d(), states(), sh, s);
+            launch_start_stacked(B, dim, chi, partials, states(), sh, s);
         } else {
-            launch_start_batch(B, dim, chi.d(), partials.d(), states(), sh, s);
+            launch_start_batch(B, dim, chi, partials, states(), sh, s);
         }
     }
 
     void step(int k)
     {
-        double *W[2] = {W0.d(), W1.d()};
-        const double *cur = k == 0 ? chi.d() : W[(k - 1) % 2];
-        const double *prv = k == 1 ? chi.d() : W[k % 2];
+        double *W[2] = {W0, W1};
+        const double *cur = k == 0 ? chi : W[(k - 1) % 2];
+        const double *prv = k == 1 ? chi : W[k % 2];
         double *out = W[k % 2];
         SeqState *q = states();
-        ShiftState *sh = late ? nullptr : (ShiftState *)shifts.p;
+        ShiftState *sh = late ? nullptr : shifts;
         const int nsh = late ? 0 : nw;
         // per-step events only outside graph capture (a captured graph is timed as a whole)
         ctx->timed("lanczos_step", !capturing && (k & 7) == 1, [&] {
             if (B > 1 && !stacked) {
-                launch_lanczos_a_batch(B, op, cur, prv, out, q, partials.d(), k == 0, s);
-                launch_finalize_alpha_batch(B, q, partials.d(), nparts_a, al.d(), n, k, s);
-                launch_lanczos_b_batch(B, dim, cur, out, q, partials.d(), s);
-                launch_finalize_beta_batch(B, q, partials.d(), nparts_b, be.d(), n, k, tol, sh, omega.d(), nsh, eta,
+                launch_lanczos_a_batch(B, op, cur, prv, out, q, partials, k == 0, s);
+                launch_finalize_alpha_batch(B, q, partials, nparts_a, al, n, k, s);
+                launch_lanczos_b_batch(B, dim, cur, out, q, partials, s);
+                launch_finalize_beta_batch(B, q, partials, nparts_b, be, n, k, tol, sh, omega, nsh, eta,
                                            s, rtol);
             } else if (pairs) {
-                const FinBeta fb{q, partials_b.d(), nparts_a, be.d(), k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, n};
+                const FinBeta fb{q, partials_b, nparts_a, be, k - 1, tol, nullptr, nullptr, 0, 0.0, 0.0, n};
                 const bool in_a = late && k > 0;
                 if (in_a) slot ^= 1;
-                launch_lanczos_pair_a(op, cur, prv, out, nullptr, q, partials.d(), k == 0, s, in_a ? &fb : nullptr,
+                launch_lanczos_pair_a(op, cur, prv, out, nullptr, q, partials, k == 0, s, in_a ? &fb : nullptr,
                                       states(), B, sk.vs);
-                const FinAlpha fa{partials.d(), nparts_a, al.d(), n, k};
-                launch_lanczos_b(dim, cur, out, states(), partials_b.d(), s, B, sk.vs, &fa);
+                const FinAlpha fa{partials, nparts_a, al, n, k};
+                launch_lanczos_b(dim, cur, out, states(), partials_b, s, B, sk.vs, &fa);
                 if (!late)
-                    launch_finalize_beta(q, partials_b.d(), nparts_a, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol,
+                    launch_finalize_beta(q, partials_b, nparts_a, be, k, tol, sh, omega, nsh, eta, s, rtol,
                                          B, n);
             } else if (fuse && k > 0) {
                 // second half of step k-1 inside the first pass of step k (which also
@@ -1475,24 +1504,24 @@ struct BatchRunner {
                 // when there is one, else in the last (without a residual test).  alpha
                 // partials in pa, norm partials in pb.
                 const bool fa_on = alpha_in_fused_pass();
-                double *pa = partials.d(), *pb = fa_on ? partials_b.d() : partials.d();
-                const FinAlpha fa{pa, nparts_a, al.d(), n, k - 1};
+                double *pa = partials, *pb = fa_on ? partials_b : partials;
+                const FinAlpha fa{pa, nparts_a, al, n, k - 1};
                 launch_lanczos_fused_first(op, W[(k - 1) % 2], prv, q, pb, s, sk, fa_on ? &fa : nullptr);
-                const FinBeta fb{q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nsh, eta, rtol, n};
+                const FinBeta fb{q, pb, nparts_a, be, k - 1, tol, sh, omega, nsh, eta, rtol, n};
                 const bool mid = beta_in_middle_pass(op), last = late && beta_in_last_pass(op);
                 if (!mid && !last)
-                    launch_finalize_beta(q, pb, nparts_a, be.d(), k - 1, tol, sh, omega.d(), nsh, eta, s, rtol, B, n);
+                    launch_finalize_beta(q, pb, nparts_a, be, k - 1, tol, sh, omega, nsh, eta, s, rtol, B, n);
                 if (last) slot ^= 1;
                 launch_lanczos_a_rest(op, cur, prv, out, nullptr, q, pa, s, sk, mid || last ? &fb : nullptr,
                                       last ? states() : nullptr);
-                if (!fa_on) launch_finalize_alpha(states(), pa, nparts_a, al.d(), k, s, B, n);
+                if (!fa_on) launch_finalize_alpha(states(), pa, nparts_a, al, k, s, B, n);
             } else {
-                launch_lanczos_a(op, cur, prv, out, nullptr, q, partials.d(), k == 0, s, sk);
+                launch_lanczos_a(op, cur, prv, out, nullptr, q, partials, k == 0, s, sk);
                 if (!(fuse && alpha_in_fused_pass()))
-                    launch_finalize_alpha(q, partials.d(), nparts_a, al.d(), k, s, B, n);
+                    launch_finalize_alpha(q, partials, nparts_a, al, k, s, B, n);
                 if (!fuse) {
-                    launch_lanczos_b(dim, cur, out, q, partials.d(), s);
-                    launch_finalize_beta(q, partials.d(), nparts_b, be.d(), k, tol, sh, omega.d(), nsh, eta, s, rtol);
+                    launch_lanczos_b(dim, cur, out, q, partials, s);
+                    launch_finalize_beta(q, partials, nparts_b, be, k, tol, sh, omega, nsh, eta, s, rtol);
                 }
             }
         });
@@ -1502,24 +1531,24 @@ struct BatchRunner {
     void finish()
     {
         if (pairs && late)
-            launch_finalize_beta(states(), partials_b.d(), nparts_a, be.d(), n - 1, tol, nullptr, nullptr, 0, eta, s,
+            launch_finalize_beta(states(), partials_b, nparts_a, be, n - 1, tol, nullptr, nullptr, 0, eta, s,
                                  0.0, B, n);
         if (!fuse) return;
-        if (alpha_in_fused_pass()) launch_finalize_alpha(states(), partials.d(), nparts_a, al.d(), n - 1, s, B, n);
-        double *W[2] = {W0.d(), W1.d()};
-        const double *cur = n == 1 ? chi.d() : W[(n - 2) % 2];
-        launch_lanczos_b(dim, cur, W[(n - 1) % 2], states(), partials.d(), s, B, sk.vs);
-        launch_finalize_beta(states(), partials.d(), nparts_b, be.d(), n - 1, tol,
-                             late ? nullptr : (ShiftState *)shifts.p, omega.d(), late ? 0 : nw, eta, s, rtol, B, n);
+        if (alpha_in_fused_pass()) launch_finalize_alpha(states(), partials, nparts_a, al, n - 1, s, B, n);
+        double *W[2] = {W0, W1};
+        const double *cur = n == 1 ? chi : W[(n - 2) % 2];
+        launch_lanczos_b(dim, cur, W[(n - 1) % 2], states(), partials, s, B, sk.vs);
+        launch_finalize_beta(states(), partials, nparts_b, be, n - 1, tol,
+                             late ? nullptr : shifts, omega, late ? 0 : nw, eta, s, rtol, B, n);
     }
 
     // g [cnt][n_omega] of the first cnt sequences, after run()
     void read_green(int cnt, double *g)
     {
         if (late)
-            launch_shifts(ShiftRun{states(), al.d(), be.d(), n, omega.d(), nw, eta, g}, cnt, s);
+            launch_shifts(ShiftRun{states(), al, be, n, omega, nw, eta, g}, cnt, s);
         else
-            launch_finish_green(states(), (const ShiftState *)shifts.p, nw, g, s, cnt);
+            launch_finish_green(states(), shifts, nw, g, s, cnt);
     }
 
     void run()
@@ -1529,8 +1558,8 @@ struct BatchRunner {
             double ab[2];
             for (int k = 0; k < n; ++k) {
                 step(k);
-                HIP_CHECK(hipMemcpyAsync(&ab[0], al.d() + k, sizeof(double), hipMemcpyDeviceToHost, s));
-                HIP_CHECK(hipMemcpyAsync(&ab[1], be.d() + k, sizeof(double), hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipMemcpyAsync(&ab[0], al + k, sizeof(double), hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipMemcpyAsync(&ab[1], be + k, sizeof(double), hipMemcpyDeviceToHost, s));
                 HIP_CHECK(hipStreamSynchronize(s));
             }
             return;
@@ -2032,7 +2061,7 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
             BatchRunner &q = *run[c];
             const size_t r0 = w0 + (size_t)c * B;
             const int cnt = (int)std::min<size_t>(B, rows - r0);
-            if (cnt < B) HIP_CHECK(hipMemsetAsync(q.chi.p, 0, q.chi.n, q.s));
+            if (cnt < B) HIP_CHECK(hipMemsetAsync(q.chi, 0, sizeof(double) * 2 * (size_t)h->dim * B, q.s));
             BatchShifts bs{};
             for (int r = 0; r < cnt; ++r) {
                 load(q, r, work[r0 + r]);
@@ -2050,8 +2079,8 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
             const size_t r0 = w0 + c * B;
             const int cnt = (int)std::min<size_t>(B, rows - r0);
             q.read_green(cnt, g + r0 * 2 * nw);
-            HIP_CHECK(hipMemcpyAsync(al + r0 * n, q.al.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
-            HIP_CHECK(hipMemcpyAsync(be + r0 * n, q.be.d(), sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
+            HIP_CHECK(hipMemcpyAsync(al + r0 * n, q.al, sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
+            HIP_CHECK(hipMemcpyAsync(be + r0 * n, q.be, sizeof(double) * n * cnt, hipMemcpyDeviceToDevice, q.s));
             HIP_CHECK(hipMemcpyAsync(st + r0, q.states(), sizeof(SeqState) * cnt, hipMemcpyDeviceToDevice, q.s));
         }
     }

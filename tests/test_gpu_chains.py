@@ -53,3 +53,44 @@ def test_every_batch_is_timed_as_a_whole(N, B, rows):
     blocks, ms = ctx.kernel_time("lanczos_block")
     assert blocks == -(-rows // B) and ms > 0
     assert ctx.kernel_time("lanczos_step") == (0, 0.0)
+
+
+@pytest.mark.parametrize("N,B,rows", [(16, 32, 24), (18, 8, 8), (20, 1, 3)])
+def test_a_call_allocates_a_few_times(N, B, rows):
+    """A call of two chains takes its memory in a few pieces (results, the vectors of each chain): every
+    hipMalloc and hipFree of such buffers costs a good part of a millisecond."""
+    import ctypes
+
+    import torch
+
+    import paper_1802_02854_amd as ftk
+    from paper_1802_02854_amd import _lib
+    print(f"allocations N={N} B={B}", flush=True)
+    held, calls = {}, [0]
+
+    class Counted:
+        def __init__(self):
+            def alloc(n, _user):
+                calls[0] += 1
+                t = torch.empty(int(n), dtype=torch.uint8, device="cuda")
+                held[t.data_ptr()] = t
+                return t.data_ptr()
+
+            def free(p, _user):
+                torch.cuda.synchronize()
+                del held[p]
+
+            self._cb = _lib.ALLOC_FN(alloc), _lib.FREE_FN(free)
+            self.handle = ctypes.c_void_p()
+            _lib.call("ftk_ctx_create_with_allocator", 0, None, *self._cb, None, ctypes.byref(self.handle))
+
+    ctx = Counted()
+    h = ftk.Hamiltonian(ctx, ftk.plan_layout(ftk.honeycomb_cluster(*SUPERCELLS[N]))[0], -1.0, 0.1)
+    st = ftk.TypicalStates(h, seed=2, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=24, M=4, n_steps=8)
+    before = calls[0]
+    ftk.Spectrum(h, st, q_xy=[(0.0, 0.0)], omega=np.linspace(-3, 3, 20), eta=0.1, n_steps=9, rhs_block=B, alpha_mask=4,
+                 shells=(0, rows))
+    assert calls[0] - before <= 4
+    st.close(), h.close()
+    _lib.lib().ftk_ctx_destroy(ctx.handle)
+    assert not held
