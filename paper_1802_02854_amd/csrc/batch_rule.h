@@ -48,6 +48,11 @@ inline Batches spread_rows(size_t rows, Batches asked, size_t per, size_t spare,
     return r;
 }
 
+// The batch whose recorded pass grid and cache hints a run takes: the one asked for, whose
+// stack the batches that run are even parts or multiples of; a record for single
+// sequences holds for those alone (0: none).
+inline int tuned_batch(const Batches &asked, const Batches &run) { return asked.B > 1 || run.B == 1 ? asked.B : 0; }
+
 // Sequences of one resident launch (one workgroup each; their start vectors and shift
 // updates are rows of a grid): what fits in spare bytes at per bytes a sequence.
 inline size_t resident_rows(size_t rows, size_t per, size_t spare)

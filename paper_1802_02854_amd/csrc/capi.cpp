@@ -188,7 +188,7 @@ struct DevBuf {
 
 // Several buffers of one call in one device allocation: from 32 MiB on a buffer of its own
 // costs 0.3 to 0.5 ms of hipMalloc and hipFree (20 sites, 3 sequences in two chains: 2.1 ms a
-// call beside its steps, 1.1 in two).  A buffer each past the last-level cache's size, which
+// call beside its steps, 0.8 in two).  A buffer each past the last-level cache's size, which
 // is what calls take beyond what they were asked for, and where there is no room for one.
 struct Arena {
     static constexpr size_t kWhole = size_t(272) << 20;
@@ -2018,7 +2018,8 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     if (may_spread(h)) plan = spread_rows(rows, asked, 16 * (size_t)h->dim * 4, ctx->spare_bytes, load_any_stream);
     std::vector<std::unique_ptr<BatchRunner>> run;
     auto make = [&] {
-        const auto [pgrid, phints] = tuned_passes(h->ctx->device, h->n_sites, nw, plan.B, plan.stack);
+        const auto [pgrid, phints] =
+            tuned_passes(h->ctx->device, h->n_sites, nw, tuned_batch(asked, plan), asked.stack);
         for (int c = 0; c < plan.chains; ++c)
             run.push_back(std::make_unique<BatchRunner>(h, plan.B, n, omega, nw, eta, rtol, plan.stack, pgrid, phints,
                                                         c > 0));

@@ -39,6 +39,9 @@ int main()
                             EXPECT(as_asked || r.B == 1 || r.stack == 1);
                             EXPECT(r.stack != 0 || block_batch(r.B));
                             EXPECT(r.stack != 0 || r.B == 1 || B > 1);
+                            // what was measured for the batch asked for is not dropped
+                            const int t = tuned_batch(Batches{B, 1, stack}, r);
+                            EXPECT(t == (as_asked || B > 1 || r.B == 1 ? B : 0));
                             // memory: the batch asked for and at most the allowance beyond it
                             EXPECT((size_t)r.B * r.chains * per <= (B + 1) * per + spare);
                             if (per * B > spare) EXPECT(as_asked);
