@@ -2045,7 +2045,8 @@ GreenOut run_green(const ftk_hamiltonian *h, int B, int stack, int n, const doub
     } joined;
     if (chains > 1) {
         std::call_once(ctx->chain_once, [&] {
-            for (hipStream_t &c : ctx->chain) HIP_CHECK(hipStreamCreate(&c));
+            // ordered with the context's stream by events alone, whatever that one waits for
+            for (hipStream_t &c : ctx->chain) HIP_CHECK(hipStreamCreateWithFlags(&c, hipStreamNonBlocking));
         });
         // after everything queued so far: the shells, the allocations of this call
         HIP_CHECK(hipEventCreateWithFlags(&joined.e, hipEventDisableTiming));
