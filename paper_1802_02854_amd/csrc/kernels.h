@@ -18,7 +18,6 @@ struct HvParams {
     uint32_t mask[kBondSlots]; // 2^i | 2^j; 0 past the last bond
     uint8_t bi[kMaxBonds];
     uint8_t bj[kMaxBonds];
-    uint8_t isz[kMaxBonds];    // 1 for z bonds
     double ap[kBondSlots];     // flip amplitude, parallel spins
     double aa[kBondSlots];     // flip amplitude, antiparallel spins
     uint32_t code[kMaxBonds];  // mask | bond type << 30

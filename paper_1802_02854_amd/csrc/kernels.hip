@@ -44,7 +44,6 @@ HvParams make_hv_params(const BondTable &t)
         P.mask[b] = (1u << t.bi[b]) | (1u << t.bj[b]);
         P.bi[b] = (uint8_t)t.bi[b];
         P.bj[b] = (uint8_t)t.bj[b];
-        P.isz[b] = t.gamma[b] == 2 ? 1 : 0;
         P.ap[b] = t.ap[b];
         P.aa[b] = t.aa[b];
         P.code[b] = P.mask[b] | (uint32_t)t.gamma[b] << 30;
@@ -488,7 +487,6 @@ struct EpiApply {
     __device__ double2 load(size_t) const { return make_double2(0.0, 0.0); }
     __device__ void apply(size_t x, double re, double im, const double2 &, const double2 &) { w[x] = make_double2(re, im); }
     __device__ void settle() {}
-    __device__ void operator()(size_t x, double re, double im, const double2 &vx) { apply(x, re, im, vx, load(x)); }
     template <int BLOCK>
     __device__ void finish() {}
 };
@@ -513,7 +511,6 @@ struct EpiTaylor {
         acc[x] = make_double2(c.x + nr, c.y + ni);
     }
     __device__ void settle() {}
-    __device__ void operator()(size_t x, double re, double im, const double2 &tx) { apply(x, re, im, tx, load(x)); }
     template <int BLOCK>
     __device__ void finish() {}
 };
@@ -1057,7 +1054,6 @@ struct EpiLanczosADev {
         sum.product(wc.y, ui);
     }
     __device__ void settle() { sum.normalise(); }
-    __device__ void operator()(size_t x, double re, double im, const double2 &wc) { apply(x, re, im, wc, load(x)); }
     template <int BLOCK>
     __device__ void finish() { write_partial<BLOCK>(partials, sum); }
 };
