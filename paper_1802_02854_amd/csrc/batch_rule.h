@@ -11,8 +11,12 @@ constexpr int kMaxChains = 2;  // batches of Green's sequences in flight, a stre
 constexpr int kMaxBatch = 32;  // sequences per batch: 16 in block layout, 32 as a stack
 constexpr int kMaxRows = 32768;  // rows of one launch (grid y, which ends at 65535)
 
-// batches the block layout has kernels for; 1 is a sequence alone
-inline bool block_batch(int B) { return B == 1 || B == 2 || B == 4 || B == 8 || B == 16; }
+// batches the block layout has kernels for, a wavefront's 512 entries at least; 1 is a
+// sequence alone
+inline bool block_batch(int B, int n_sites)
+{
+    return B == 1 || ((B == 2 || B == 4 || B == 8 || B == 16) && ((size_t)B << n_sites) >= 512);
+}
 
 struct Batches {
     int B;       // sequences of a batch

@@ -1410,7 +1410,7 @@ struct BatchRunner {
           fuse(!pairs && (stacked || (B_ == 1 && lanczos_fusable(op) && !g_plain_loop))),
           late(rtol_ == 0.0 && !g_plain_loop)
     {
-        need(stacked || block_batch(B), "the block layout runs 2, 4, 8 or 16 sequences per launch");
+        need(stacked || block_batch(B, H->n_sites), "the block layout runs 2, 4, 8 or 16 sequences per launch");
         const size_t vectors = 2 * (size_t)dim * B, sums = 2 * (size_t)kMaxGrid * B;
         m.part(&chi, vectors);
         m.part(&W0, vectors);
@@ -1740,7 +1740,7 @@ TuneResult autotune(const ftk_hamiltonian *h, int n_omega)
     // (rhs_block, layout): block layout, and the stacked one where the multi-pass form allows it
     std::vector<std::pair<int, int>> cands{{1, 0}};
     for (int B : {4, 16, 32}) {
-        if (g_stack_mode != 1 && B <= 16) cands.push_back({B, 0});
+        if (g_stack_mode != 1 && block_batch(B, h->n_sites)) cands.push_back({B, 0});
         if (g_stack_mode != 0 && BatchRunner::stack_for(h, B, 1)) cands.push_back({B, 1});
     }
     // Krylov iterations per second of B sequences in layout stk with pass grid pg and
@@ -1838,6 +1838,8 @@ void resolve_layout(const ftk_hamiltonian *h, int rhs_block, int n_omega, int &B
     } else {
         stack = tuned_layout(h->ctx->device, h->n_sites, n_omega, B);
     }
+    if (B <= 16 && !BatchRunner::stack_for(h, B, stack) && !block_batch(B, h->n_sites))
+        B = 1;  // 4 and 5 sites: too few entries for a wavefront of the block layout
     if (B > 16)
         need(BatchRunner::stack_for(h, B, stack < 0 ? -1 : stack),
              "rhs_block 32 runs only as a stack of multi-pass sequences (N >= 16, stack_batch not 0, no plain loop)");

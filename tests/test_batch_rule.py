@@ -37,7 +37,7 @@ int main()
                             // a batch whose layout was not picked for it is a stack: a size the
                             // block layout has no kernel for, or a pick for single sequences
                             EXPECT(as_asked || r.B == 1 || r.stack == 1);
-                            EXPECT(r.stack != 0 || block_batch(r.B));
+                            EXPECT(r.stack != 0 || block_batch(r.B, N));
                             EXPECT(r.stack != 0 || r.B == 1 || B > 1);
                             // what was measured for the batch asked for is not dropped
                             const int t = tuned_batch(Batches{B, 1, stack}, r);
@@ -47,6 +47,11 @@ int main()
                             if (per * B > spare) EXPECT(as_asked);
                             if (failures > 20) return 1;
                         }
+    // the block layout's kernels go 512 entries at a time
+    for (int N = 4; N <= 24; ++N)
+        for (int B : {2, 4, 8, 16})
+            if (block_batch(B, N) != (((long)B << N) % 512 == 0) || block_batch(B + 1, N) || !block_batch(1, N))
+                std::printf("FAIL block N %d B %d\n", N, B), ++failures;
     // rows of a resident launch fit a grid's y extent at every size it runs
     for (int N = 6; N <= 14; ++N)
         for (size_t rows : {size_t(1), size_t(65535), size_t(65536), size_t(300000)})

@@ -131,3 +131,25 @@ def test_more_sequences_than_a_grid_has_rows(env):
     assert n_seq > 65535
     parts = [spectrum(f, n)[0] for f, n in ((0, 100), (100, 100), (200, 56))]
     assert np.array_equal(whole, np.concatenate(parts, axis=2)) and np.abs(whole).max() > 0
+
+
+@pytest.mark.parametrize("N", [4, 5, 6, 7, 8])
+def test_every_rhs_block_of_the_smallest_clusters(env, N):
+    """Batches of 2 to 16 sequences whose entries together are fewer than a wavefront of the block
+    layout takes (4 to 8 sites on the per-step kernels), against one sequence at a time."""
+    ftk, ctx, torch = env
+    print(f"smallest clusters N={N}", flush=True)
+    ij = [(i, i + 1) for i in range(N - 1)]
+    cl = ftk.Cluster(N, np.array([b[0] for b in ij], np.int32), np.array([b[1] for b in ij], np.int32),
+                     (np.arange(N - 1) % 3).astype(np.int8), np.stack([np.arange(N) * 1.0, np.sin(np.arange(N))], axis=1))
+    h = ftk.Hamiltonian(ctx, cl, -1.0, 0.3)
+    st = ftk.TypicalStates(h, seed=2, n_vectors=1, betas=[0.0], E_b=None, eps=None, L=6, M=4, n_steps=6)
+    ftk.set_tuning("hv_variant", 0)
+    try:
+        out = [ftk.Spectrum(h, st, q_xy=[(0.2, 0.1)], omega=np.linspace(-2, 2, 11), eta=0.3, n_steps=5, rhs_block=B).raw()
+               for B in (1, 0, 2, 4, 8, 16)]
+    finally:
+        ftk.set_tuning("hv_variant", -1)
+    assert np.isfinite(out[0][0]).all() and np.abs(out[0][0]).max() > 0
+    for g, r in out[1:]:
+        assert np.array_equal(g, out[0][0]) and np.array_equal(r, out[0][1])
