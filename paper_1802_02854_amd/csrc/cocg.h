@@ -90,11 +90,9 @@ __device__ __forceinline__ void write_partials5(double *partials, Sum (&sum)[NS]
     }
 }
 
-// running sums normalised every eighth of a thread's turns
 template <int NS>
-__device__ __forceinline__ void normalise_turns(Sum (&sum)[NS], int turn)
+__device__ __forceinline__ void normalise(Sum (&sum)[NS])
 {
-    if ((turn & 7) != 7) return;
 #pragma unroll
     for (int j = 0; j < NS; ++j) sum[j].normalise();
 }
@@ -125,7 +123,6 @@ struct CocgA {
         sum[1].product(wc.y, ur);
         return make_double2(ur, ui);
     }
-    __device__ __forceinline__ void settle(int turn) { normalise_turns(sum, turn); }
 };
 #endif
 

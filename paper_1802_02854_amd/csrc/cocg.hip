@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_start_sums(uint32_t dim, const 
         const double2 v = w[x];
         const double2 l = lam[x];
         cocg_norm_sums(v, l, sum);
-        normalise_turns(sum, turn++);
+        if (settles(turn++)) normalise(sum);
     }
     write_partials5<5>(partials, sum);
 }
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_a(uint32_t dim, const double2 *
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 h = Hw[x];
         U[x] = a(h.x, h.y, Wcur[x], first ? make_double2(0.0, 0.0) : Wprev[x], first);
-        a.settle(turn++);
+        if (settles(turn++)) normalise(a.sum);
     }
     write_partials5<2>(partials, a.sum);
 }
@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_b(uint32_t dim, double2 *__rest
         const double2 w = make_double2(wr, wi);
         U[x] = w;
         cocg_norm_sums(w, l, sum);
-        normalise_turns(sum, turn++);
+        if (settles(turn++)) normalise(sum);
     }
     write_partials5<5>(partials, sum);
 }

@@ -18,7 +18,7 @@ namespace ftk {
 // the whole sum against double-double with a normalisation per term and as its tree's additions,
 // on host models of the kernels' shapes over random vectors: 0.4 to 1.0 times (with both errors
 // in one sum, never normalised: 1.2 to 1.5 times at 6 to 20 sites, 5 at 24, 50 at 30; that
-// is faster by 3 % at 8 and 12 sites and by 5 % for COCG's five sums).
+// is faster by 1 to 2 % at 8 and 12 sites and by 3 % for COCG's five sums).
 struct Sum {
     double hi = 0.0, lo = 0.0, er = 0.0;
 
@@ -81,6 +81,10 @@ __device__ __forceinline__ double dpp(double x)
     u.i[1] = __builtin_amdgcn_update_dpp(0, u.i[1], CTRL, 0xf, 0xf, true);
     return u.d;
 }
+
+// A thread that takes an element a turn normalises its sums after every eighth: turn counts
+// them from 0.
+__device__ __forceinline__ bool settles(int turn) { return (turn & 7) == 7; }
 
 // Sum over groups of 2^LEVELS consecutive lanes, the same value in each of
 // them: lane ^ 1, lane ^ 2, then mirrors within 8 and 16 lanes (their groups of 4

@@ -533,6 +533,7 @@ __global__ void __launch_bounds__(kBlock) k_hv_simple(const HvDev *__restrict__ 
     epi.select(blockIdx.y, vs, 2 * gridDim.x);
     if (!epi.active()) return;
     epi.prepare(blockIdx.y);
+    int turn = 0;
     for (uint32_t x0 = blockIdx.x * kBlock; x0 < dim; x0 += gridDim.x * kBlock) {
         const uint32_t x = x0 + threadIdx.x;
         double re, im;
@@ -543,7 +544,7 @@ __global__ void __launch_bounds__(kBlock) k_hv_simple(const HvDev *__restrict__ 
         }
         if (x0 == blockIdx.x * kBlock && !epi.template begin<kBlock>(blockIdx.y)) return;
         if (x < dim) epi.apply(x, re, im, vx, in);
-        epi.settle();
+        if (settles(turn++)) epi.settle();
     }
     epi.template finish<kBlock>();
 }
@@ -1116,7 +1117,6 @@ struct EpiCocg {
     const CocgState *st;
     int first;
     CocgA a;
-    int turn = 0;
     __device__ void select(int r, size_t vs, int pstride)
     {
         Wprev += r * vs;
@@ -1133,7 +1133,7 @@ struct EpiCocg {
     {
         U[x] = a(re, im, wc, wp, first);
     }
-    __device__ void settle() { a.settle(turn++); }
+    __device__ void settle() { normalise(a.sum); }
     template <int BLOCK>
     __device__ void finish() { write_partials5<2>(partials, a.sum); }
 };
@@ -1219,6 +1219,7 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double
         c2 = -(st->alpha_cur * st->inv_cur);
     }
     Sum sum;
+    int turn = 0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 wc = Wcur[x];
         const double2 u = U[x];
@@ -1227,7 +1228,7 @@ __global__ void __launch_bounds__(kBlock) k_lanczos_b(uint32_t dim, const double
         U[x] = make_double2(wr, wi);
         sum.product(wr, wr);
         sum.product(wi, wi);
-        sum.normalise();
+        if (settles(turn++)) sum.normalise();
     }
     write_partial<kBlock>(partials, sum);
 }
@@ -1344,11 +1345,12 @@ __global__ void __launch_bounds__(kBlock) k_dot(uint32_t dim, const double2 *__r
     b += blockIdx.y * vs;
     partials += (size_t)blockIdx.y * 2 * gridDim.x;
     Sum sum;
+    int turn = 0;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += gridDim.x * blockDim.x) {
         const double2 u = a[x], v = b[x];
         sum.product(u.x, v.x);
         sum.product(u.y, v.y);
-        sum.normalise();
+        if (settles(turn++)) sum.normalise();
     }
     write_partial<kBlock>(partials, sum);
 }
