@@ -353,7 +353,8 @@ ftk_status ftk_states_destroy(ftk_states *st);
  * (d_0 = z - alpha_0, p_0 = 1; p_k = p_{k-1} beta_k / d_{k-1},
  *  d_k = z - alpha_k - beta_k^2 / d_{k-1}; G = sum_k p_k^2 / d_k), and the
  * Galerkin residual ||chi|| |p_n| kept per sequence (maximum over shifts).
- * rhs_block (1, 2, 4, 8, 16 or 32) sets how many sequences share one launch; 0
+ * rhs_block (1, 2, 4, 8, 16 or 32) sets how many sequences share one launch (one at a
+ * time at 4 and 5 sites, but for 16 at 5: too few entries for a batch); 0
  * takes the value ftk_autotune picks for this Hamiltonian and n_omega.  32 runs
  * only as a stack of multi-pass sequences (N >= 16, see "stack_batch").  Clusters
  * of 6 to 14 sites run every sequence of the call in one launch, one workgroup

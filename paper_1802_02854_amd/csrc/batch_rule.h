@@ -32,8 +32,9 @@ struct Batches {
 // last-level cache's size), in even batches.  us per sequence and step as asked, in chains of
 // what was asked, so: 16 sites, 6 in batches of 1: 12 / 7.6 / 3.9; 24 of 8: 2.8 / 2.6 /
 // 2.4; 72 of 32: 2.1 / 2.2 / 1.85; 110 of 32: 1.9 / 1.8 / 1.6; 18 sites, 4 of 1: 19 / 13.3
-// / 10.6; 24 of 16: 6.4 / 6.6 / 6.3; 20 sites, 4 of 1: 41.6 / 38.9 / 35.4.  Three or four
-// chains are no faster (16 sites, 110 in flight in four: 1.77).
+// / 10.6; 24 of 16: 6.4 / 6.6 / 6.3; 20 sites, 4 of 1: 41.6 / 38.9 / 35.4; 22 sites, 4 of
+// 1: 137 / 118 as asked and so.  Three or four chains are no faster (16 sites, 110 in flight
+// in four: 1.77).
 // The batch asked for runs alone where its vectors (per bytes a sequence) are past spare
 // (20 sites, two chains of 16: 35.4 us per sequence and step against 31.0; 24 sites, of
 // 1: 557 against 510) and where the block layout was picked for it.  A layout recorded for

@@ -248,7 +248,7 @@ bool resident_run(const HvOp &op) { return resident(op) && !g_plain_loop; }
 // launches a step, instead of one workgroup each, which leaves most compute units idle.
 // us per step of 1 / 8 / 32 sequences, one workgroup each against together (three bonds
 // per site): 12 sites 13.0 / 13.1 / 13.5, 12.4 / 12.8 / 16.9; 13 sites 41.5 / 41.9 / 42.3,
-// 11.4 / 12.7 / 18.9; 14 sites 49.3 / 49.9 / 50.2, 11.8 / 15.3 / 28.7.
+// 11.8 / 12.7 / 19.1; 14 sites 49.3 / 49.9 / 50.2, 12.3 / 15.8 / 28.4.
 constexpr int kFewSeqs = kMaxBatch;
 bool few_sequences(const HvOp &op, size_t n_seq)
 {
@@ -2127,7 +2127,7 @@ CocgOut run_cocg(const ftk_hamiltonian *h, int n, const double *omega, int nw, d
     // As many sequences in lockstep as the call may take memory for, at least one: a step
     // of one is bound by launches and by the scalar kernel between the vector halves
     // (18 sites, six sequences of 150 steps of 500 shifts: 57.0 ms in turn, five kernels a
-    // step, 12.4 together in three)
+    // step, 12.9 together in three)
     const bool hw = cocg_work_vectors(h->op);
     size_t most = std::min(work.size(), std::max<size_t>(1, ctx->spare_bytes / (vb * (hw ? 5 : 4))));
     most = std::min<size_t>(most, kMaxBatch);

@@ -84,8 +84,8 @@ __device__ __forceinline__ uint32_t odd_elements(uint32_t mr)
 // elements) with w_{k-2}; bond constants sit one bond per lane and are read into
 // scalar registers, so the bond loop waits for LDS data only.  fp64 issue bounds the
 // larger sizes, the latency of the two reductions the smaller ones: a step of 48
-// sequences takes 3.6 us at 8 sites, 4.5 at 10 and 9 at 12 (before: 17.5 ms for 192
-// sequences of 64 steps at 8 sites, now 0.33; 28.0 ms for 48 of 300 at 12, now 2.75).
+// sequences takes 2.7 us at 8 sites, 4.0 at 10 and 8.4 at 12 (before: 17.5 ms for 192
+// sequences of 64 steps at 8 sites, now 0.34; 28.0 ms for 48 of 300 at 12, now 2.82).
 template <int LOGT, int E>
 __global__ void __launch_bounds__(1 << LOGT) k_resident(HvParams P, ResidentRun R)
 {
